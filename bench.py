@@ -429,8 +429,9 @@ def main():
     ceil_gbs = min(L, 8) * F * d * es / (e0.elapsed_time(e1) * 1e-3) / 1e9
 
     nch = d * es // 1024
-    occ2 = es == 2 and d * es % 1024 == 0 and (nch == 5 if relu else nch in (4, 8)) and (F + 255) // 256 <= 64
-    n_lanes = 1 if (not use_stack or L < 4) else 3 if (B >= 2 or occ2) else 2      # what the library chooses for sparse stacks
+    # what the library chooses for sparse stacks: batch-1 rows of 2, 5, 8 and 10 KiB run as one launch over all layers (lanes = 1)
+    one_launch = B == 1 and d * es % 1024 == 0 and (nch in (2, 5, 8, 10) or (nch == 4 and (F <= 12288 or L >= 32)))
+    n_lanes = 1 if (not use_stack or L < 4 or one_launch) else 3 if (B >= 2 or nch == 4) else 2
     main_kernel = ("k_ffn_decode_b1 (input rows dense + output rows of kept neurons)" if B == 1 and relu
                    else "k_ffn_decode_b1 (gate rows dense + up/down rows of kept neurons)" if B == 1
                    else "k_bat_gateup + k_bat_down (batched decode, timed as one)")
@@ -479,7 +480,7 @@ def main():
             "call_frac": round(off["bytes_probe"] / (off["call_us"] * 1e-6) / 1e9 / HBM_PEAK_GBS, 4)},
         "regime_indicators_on": _light(on, ms_dense, ideal, B, L) if on else None,
         "regime_negative_coefficients": dict(_light(neg, ms_dense, ideal, B, L), **{"lambda": -0.80, "gamma": -0.12}) if neg else None,
-        "step_path": (f"clada_signals_threshold, then clada_sparse_ffn_stack_decode (lanes on two or three streams) on the "
+        "step_path": (f"clada_signals_threshold, then clada_sparse_ffn_stack_decode (one launch over the layers, or lanes on two or three streams) on the "
                       "L independent layers" if use_stack else "clada_signals_threshold, then L calls of clada_sparse_ffn_decode"),
         "per_layer_calls": per_layer,
         "stack_modes": stack,

@@ -74,9 +74,9 @@ const char *clada_last_error(const clada_ctx *ctx);
  * "decode.wgs_per_cu" (1 or 2 workgroups per compute unit for the generic kernel),
  * "decode.stack" (how the whole-stack calls run: 3 = lanes [default], 2 = chained
  * launches, 1 = one persistent kernel for all layers where the shape has one, 0 = the L
- * per-layer calls; see clada_sparse_ffn_stack_decode), "decode.lane_occ2" (1 = the lanes of
- * batch-1 stacks with rows of 4, 5 or 8 KiB use the kernel instance of which two workgroups
- * fit a compute unit [default], 0 = the instance of the per-layer call),
+ * per-layer calls; see clada_sparse_ffn_stack_decode), "decode.lane_occ2" (1 = where the lanes of
+ * a batch-1 stack have a kernel instance of which two workgroups fit a compute unit, they use
+ * it [default], 0 = the instance of the per-layer call),
  * "decode.batched" (1 = matrix-core kernels for bf16 batches of 2 and more, 16 tokens
  * per pass [default], 0 = the
  * generic kernels), "decode.spin_limit" (how often a balanced batch-1 kernel polls
@@ -272,7 +272,10 @@ clada_status clada_dense_ffn_decode(clada_ctx *ctx, const clada_layer *layer, co
  * future-work paragraphs leave open; this is the second.  Knowing the whole stack, the
  * library can hide what every per-layer call pays: the start-up of a kernel, its ragged
  * end, and the launch of the final reduction.  Option "decode.stack" chooses how:
- *   3 (default)  lanes: the layers go round two or three streams -- hip_stream and streams
+ *   3 (default)  at batch 1, where it is the fastest (rows of 2, 4, 5, 8 and 10 KiB, fp32
+ *                rows of 2 and 8 KiB, by size): one launch over all layers on hip_stream, whose
+ *                workgroups follow each other without a gap, and one reduction launch.
+ *                Otherwise lanes: the layers go round two or three streams -- hip_stream and streams
  *                that the context owns (default priority), forked and joined by events
  *                inside the call.  To the caller the call is ordered on hip_stream like any
  *                other, and a stream capture of hip_stream records all lanes.  The compute

@@ -211,6 +211,7 @@ size_t clada_workspace_bytes(int32_t d, int32_t d_ff, int32_t B, int32_t T, int3
 {
     size_t need = 0, n;
     if (d > 0 && d_ff > 0 && B > 0 && (n = clada_ws_decode(d, d_ff, B)) > need) need = n;
+    if (d > 0 && d_ff > 0 && B > 0 && (n = clada_ws_stack(d)) > need) need = n;
     if (B > 0 && V > 0 && (n = clada_ws_signals(B, V)) > need) need = n;
     if (d > 0 && d_ff > 0 && T > 0 && (n = clada_ws_prefix(d, d_ff, T, true)) > need) need = n;
     if (T > 0 && (n = clada_ws_calibrate()) > need) need = n;

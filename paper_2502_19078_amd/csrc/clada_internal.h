@@ -81,6 +81,12 @@ bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *laye
 // Batch-1 decode over a neuron list with the streaming kernel, when the shape fits it (*ran).
 hipError_t clada_decode_list_b1(clada_ctx *ctx, const clada_layer *layer, const void *x, const int32_t *idx,
                                 const int32_t *n_active, float *partial, int *P_out, hipStream_t stream, bool *ran);
+// Batch-1 layers of a whole-stack call as one launch over (class of neurons, layer); partial outputs go to `partial`.
+#define CLADA_STACK_LAUNCH_LAYERS 48
+size_t clada_ws_stack(int32_t d);
+bool clada_stack_b1_fits(const clada_layer *layer, int32_t L, bool dense);      // shapes it is faster for than lanes
+hipError_t clada_stack_b1(const clada_layer *layers, int32_t L, const void *x, const float *tau, void *y, bool dense,
+                          float *partial, size_t partial_bytes, hipStream_t stream);
 // Fixed-order sum of P partial y's [P][B][d] (fp32) into y (element size es).
 void clada_launch_finalize(int es, const float *partial, int P, int B, int d, char *y, hipStream_t stream,
                            const float *bias = nullptr);
@@ -193,4 +199,14 @@ __device__ __forceinline__ float gelu_tanh_f32(float g)
 
 // sigma of the gated families: SiLU (LLaMA / Mistral) or tanh-form GELU (Gemma)
 __device__ __forceinline__ float gate_sigma_f32(float g, int gelu) { return gelu ? gelu_tanh_f32(g) : silu_f32(g); }
+
+// Activation of the FFN families: sigma(g) (SiLU or tanh-form GELU) for the gated FFN; for the
+// non-gated one max(0, g + bias) (a NaN pre-activation stays NaN).
+template <bool RELU>
+__device__ __forceinline__ float ffn_act(float g, const float *b_in, size_t j, int gelu)
+{
+    if (!RELU) return gate_sigma_f32(g, gelu);
+    if (b_in) g += b_in[j];
+    return g > 0.0f ? g : (g != g ? g : 0.0f);
+}
 #endif

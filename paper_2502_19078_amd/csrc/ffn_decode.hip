@@ -48,17 +48,6 @@ struct DecodeParams {
     int gelu;                   // gated family: sigma = tanh-form GELU instead of SiLU
 };
 
-// Activation of the FFN families: sigma(g) (SiLU or tanh-form GELU) for the gated FFN; for the
-// non-gated one max(0, g + bias) (a NaN pre-activation stays NaN).
-template <bool RELU>
-__device__ __forceinline__ float ffn_act(float g, const float *b_in, size_t j, int gelu)
-{
-    if (!RELU) return gate_sigma_f32(g, gelu);
-    if (b_in) g += b_in[j];
-    return g > 0.0f ? g : (g != g ? g : 0.0f);
-}
-
-
 // ES = element size (2: bf16, 4: fp32); NCH = 16-byte chunks per lane per row;
 // NW = waves per workgroup; GB / UB = rows in flight per wave in the gate /
 // up-down phase.  LIST (with DENSE): the neurons are entries blk, blk+P, ... of a caller-supplied
@@ -1307,27 +1296,21 @@ hipError_t launch_b1(clada_ctx *ctx, const B1Params &p, int P, bool dense, bool 
     return launch_b1_variant<ES, NCH, DCH, false, false, RELU>(ctx, p, P, st);
 }
 
-// The two-per-unit instances (bf16, one round of neurons), sparse or dense; false where the shape has none.
-template <int NCH, int DCH, bool RELU>
-hipError_t launch_b1_occ2_shape(const B1Params &p, int P, bool dense, hipStream_t st)
-{
-    if (dense) hipLaunchKernelGGL((k_ffn_decode_b1<2, NCH, 8, DCH, true, false, RELU, false, false, true>), dim3(P), dim3(512), 0, st, p);
-    else hipLaunchKernelGGL((k_ffn_decode_b1<2, NCH, 8, DCH, false, false, RELU, false, false, true>), dim3(P), dim3(512), 0, st, p);
-    return hipGetLastError();
-}
-
-bool b1_occ2_shape_ok(int es, int nch, bool relu)
+// The two-per-unit instances (bf16, gated, one round of neurons) of the stacks that still run in lanes: 4 KiB rows, and the
+// dense twin with 8 KiB rows; the other widths have none.
+bool b1_occ2_shape_ok(int es, int nch, bool relu, bool dense)
 {
     // (10 KiB rows: the instance needs 128 registers and a few spills, and was measured 6 % slower than the
     // one-per-unit instance in two lanes)
-    return es == 2 && (relu ? nch == 5 : (nch == 4 || nch == 8));
+    return es == 2 && !relu && (nch == 4 || (nch == 8 && dense));
 }
 
-hipError_t launch_b1_occ2(const B1Params &p, int P, int nch, bool relu, bool dense, hipStream_t st)
+hipError_t launch_b1_occ2(const B1Params &p, int P, int nch, bool dense, hipStream_t st)
 {
-    if (relu) return launch_b1_occ2_shape<5, 8, true>(p, P, dense, st);
-    if (nch == 4) return launch_b1_occ2_shape<4, 8, false>(p, P, dense, st);
-    return launch_b1_occ2_shape<8, 8, false>(p, P, dense, st);
+    if (nch == 8) hipLaunchKernelGGL((k_ffn_decode_b1<2, 8, 8, 8, true, false, false, false, false, true>), dim3(P), dim3(512), 0, st, p);
+    else if (dense) hipLaunchKernelGGL((k_ffn_decode_b1<2, 4, 8, 8, true, false, false, false, false, true>), dim3(P), dim3(512), 0, st, p);
+    else hipLaunchKernelGGL((k_ffn_decode_b1<2, 4, 8, 8, false, false, false, false, false, true>), dim3(P), dim3(512), 0, st, p);
+    return hipGetLastError();
 }
 
 // The split-d instantiations by element size, row length and family (exactly the shapes b1_shape_ok admits).
@@ -1748,8 +1731,9 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
         }
         if (persistent) return CLADA_OK;
     }
-    // ---- launches issued by the library itself.  Two things the per-layer calls cannot do:
-    // * lanes (the default): the layers of a stack are independent problems, so they go round two or three
+    // ---- launches issued by the library itself.  Three things the per-layer calls cannot do:
+    // * one launch over all layers (the default where it is the fastest: clada_stack_b1_fits), ffn_stack.hip
+    // * lanes (the default elsewhere): the layers of a stack are independent problems, so they go round two or three
     //   HIP streams (the caller's and the context's own, forked and joined by events, which a stream
     //   capture follows).  A compute unit that has finished its share of layer l takes a workgroup of
     //   layer l+1 at once: the start-up and the ragged end of every kernel are covered by its neighbour
@@ -1765,13 +1749,17 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
     const int smode = ctx->opt_decode_stack;
     const bool own_launches = B == 1 && smode >= 2 && ctx->opt_decode_b1 >= 1 && !n_active && (d * es) % 1024 == 0 &&
                               b1_shape_ok(es, nch, relu) && Pb == COOP_MAX_WGS && F >= Pb && ni_b <= 1024 && L >= 2;
+    if (own_launches && smode == 3 && clada_stack_b1_fits(&layers[0], L, dense)) {
+        CLADA_CHECK_HIP(ctx, clada_stack_b1(layers, L, x, tau, y, dense, reinterpret_cast<float *>(ctx->ws + CLADA_WS_HEADER),
+                                            ctx->ws_bytes - CLADA_WS_HEADER, stream));
+        return CLADA_OK;
+    }
     if (own_launches) {
         static_assert(COOP_MAX_WGS == 256, "the chained reduction is laid out for 256 partial outputs");
-        // Rows of 4, 5 and 8 KiB have an instance of which two workgroups fit a compute unit: with it, workgroups
-        // of different layers share every unit (measured, 7B shape, ms per step of 32 layers at sparsity 0.45 /
-        // dense: two lanes 1.038 / 1.379 with the one-per-unit instance, 1.031 / 1.330 with this one; three lanes
-        // 1.085 / 1.460 and 1.006 / 1.357; four lanes 1.041 / 1.391 with this one)
-        const bool occ2 = b1_occ2_shape_ok(es, nch, relu) && ni_b <= 64 && ctx->opt_decode_lane_occ2 != 0;
+        // With the two-per-unit instance workgroups of different layers share every compute unit (measured, 7B
+        // shape, ms per step of 32 layers at sparsity 0.45 / dense: two lanes 1.038 / 1.379 with the one-per-unit
+        // instance, 1.031 / 1.330 with this one; three lanes 1.085 / 1.460 and 1.006 / 1.357; four lanes 1.041 / 1.391)
+        const bool occ2 = b1_occ2_shape_ok(es, nch, relu, dense) && ni_b <= 64 && ctx->opt_decode_lane_occ2 != 0;
         const int n_lanes = (smode == 3 && L >= 4) ? ((occ2 && !dense) ? 3 : 2) : 1;
         const bool chained = smode == 2;
         unsigned int *epoch = reinterpret_cast<unsigned int *>(ctx->ws + COOP_EPOCH);
@@ -1805,7 +1793,7 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
             b.prev_bias = (sums_prev && relu) ? layers[lp].b_out : nullptr;
             b.epoch_out = epoch;                             // only the balanced instance writes it
             if (n_lanes >= 2 && occ2)
-                CLADA_CHECK_HIP(ctx, launch_b1_occ2(b, Pb, nch, relu, dense, st));
+                CLADA_CHECK_HIP(ctx, launch_b1_occ2(b, Pb, nch, dense, st));
             else
                 CLADA_CHECK_HIP(ctx, launch_b1_shape(ctx, b, Pb, es, nch, relu, dense, &balance, st));
             if (!chained || l + n_lanes >= L) {              // nobody after it in its lane: its own reduction launch

@@ -211,6 +211,42 @@ def test_stack_call_modes_agree_and_replay_from_a_graph(clada):
     assert not ctx.device_fault()
 
 
+# d, F, L, relu, dtype: the launch over all layers (ffn_stack.hip) with every row length it has, both splits (whole slices of
+# eight classes, single classes), one and several rounds of 64 neurons, neuron counts that leave classes of unequal length
+ONE_LAUNCH = [
+    (1024, 4096, 8, True, "bf16"), (1024, 3001, 9, False, "bf16"), (1024, 300, 7, False, "bf16"),
+    (2048, 2300, 6, False, "bf16"), (2048, 16385, 2, False, "bf16"),
+    (2560, 3333, 7, False, "bf16"), (2560, 2600, 5, True, "bf16"),
+    (4096, 2817, 6, False, "bf16"), (4096, 1000, 50, True, "bf16"), (5120, 2222, 6, True, "bf16"), (5120, 2600, 5, False, "bf16"),
+    (512, 1376, 8, False, "f32"), (512, 5000, 3, True, "f32"), (2048, 3000, 6, False, "f32"),
+]
+
+
+@pytest.mark.parametrize("d,F,L,relu,dtype", ONE_LAUNCH)
+def test_one_launch_over_the_layers_is_the_per_layer_calls_bit_for_bit(clada, d, F, L, relu, dtype):
+    """Layers that keep nothing and everything among them, sparse and dense call."""
+    from paper_2502_19078_amd import binding
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(d + F + L)
+    n = lambda *s, std=0.02: torch.randn(s, generator=g, device=DEV) * std
+    relu = relu and dtype == "bf16"                          # (the fp32 non-gated family has no batch-1 kernel)
+    layers = []
+    for _ in range(L):
+        w = [n(F, d).to(dt) for _ in range(2 if relu else 3)]
+        layers.append(clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=n(F), b_out=n(d)) if relu else clada.Layer(*w))
+    x = n(L, d, std=1.0).to(dt)
+    tau = torch.rand(L, generator=g, device=DEV) * 0.5
+    tau[0], tau[L - 1] = 1e9, 0.0
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 1, 0, 0))
+    ctx.set_option("decode.b1", 2)
+    for rep in range(2):
+        y = clada.sparse_ffn_stack_decode(ctx, layers, x, tau)
+        yd = clada.dense_ffn_stack_decode(ctx, layers, x)
+        for l in range(L):
+            assert torch.equal(y[l], clada.sparse_ffn_decode(ctx, layers[l], x[l:l + 1], tau[l:l + 1])[0]), f"layer {l}"
+            assert torch.equal(yd[l], clada.dense_ffn_decode(ctx, layers[l], x[l:l + 1])[0]), f"dense, layer {l}"
+
+
 def _batch_stack(clada, cfg_name, d, F, L, B, seed, shared_frac=0.5):
     cfg = synth.CONFIGS[cfg_name]
     ws = [synth.layer_weights(cfg, seed, l, d=d, d_ff=F) for l in range(L)]
