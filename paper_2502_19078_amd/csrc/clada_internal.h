@@ -81,6 +81,12 @@ bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *laye
 // Batch-1 decode over a neuron list with the streaming kernel, when the shape fits it (*ran).
 hipError_t clada_decode_list_b1(clada_ctx *ctx, const clada_layer *layer, const void *x, const int32_t *idx,
                                 const int32_t *n_active, float *partial, int *P_out, hipStream_t stream, bool *ran);
+// Decode on the vector units, up to eight tokens per pass over the weights, any row length; idx / n_list (device): run over a
+// neuron list (dense must be set); ev: four events around the kernels and the last reduction, or nullptr.
+bool clada_decode_multi_fits(const clada_layer *layer, int32_t B);       // layers it is faster for than the generic kernel
+hipError_t clada_decode_multi(const clada_layer *layer, const void *x, int32_t B, const float *tau, char *y,
+                              unsigned char *keep, float *partial, int P, bool dense, const int32_t *idx,
+                              const int32_t *n_list, hipStream_t stream, hipEvent_t *ev = nullptr);
 // Batch-1 layers of a whole-stack call as one launch over (class of neurons, layer); partial outputs go to `partial`.
 #define CLADA_STACK_LAUNCH_LAYERS 48
 size_t clada_ws_stack(int32_t d);

@@ -1485,6 +1485,16 @@ clada_status run_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
             return CLADA_OK;
         }
     }
+    // ---- several tokens per pass on the vector units: what has no instance above
+    if ((B == 1 ? ctx->opt_decode_b1 >= 1 : ctx->opt_decode_batched) && clada_decode_multi_fits(layer, B)) {
+        CLADA_CHECK_HIP(ctx, clada_decode_multi(layer, x, B, tau, (char *)y, p.keep, p.partial, P, dense, nullptr, nullptr, stream,
+                                                ctx->opt_diag_events ? ctx->ev : nullptr));
+        if (lists) {
+            hipLaunchKernelGGL(k_ffn_lists, dim3(1), dim3(1024), 0, stream, p.keep, B, F, active_idx, n_active, mask_bits);
+            CLADA_CHECK_HIP(ctx, hipGetLastError());
+        }
+        return CLADA_OK;
+    }
     if (ctx->opt_diag_events) CLADA_CHECK_HIP(ctx, hipEventRecord(ctx->ev[0], stream));
 #define CLADA_DECODE_CASE(ES_, NCH_, NW_, GB_, UB_)                                        \
     if (es == ES_ && nch <= NCH_ && e == hipErrorInvalidValue)                             \
@@ -1574,6 +1584,10 @@ clada_status run_list_decode(clada_ctx *ctx, const clada_layer *layer, const voi
             CLADA_CHECK_HIP(ctx, hipGetLastError());
             return CLADA_OK;
         }
+    }
+    if ((B == 1 ? ctx->opt_decode_b1 >= 1 : ctx->opt_decode_batched) && clada_decode_multi_fits(layer, B)) {
+        CLADA_CHECK_HIP(ctx, clada_decode_multi(layer, x, B, nullptr, (char *)y, nullptr, p.partial, P, true, idx, n_active, stream));
+        return CLADA_OK;
     }
     hipError_t e = hipErrorInvalidValue;
 #define CLADA_LIST_CASE(ES_, NCH_, NW_, GB_, UB_)                                          \

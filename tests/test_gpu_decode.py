@@ -321,6 +321,50 @@ def test_limits_of_batch_width_and_neuron_count(clada, cfg_name, d, F, B):
     _check_against_oracle(cfg, w, x, tau, y, idx, cnt, mask, f"{cfg_name} d={d} F={F} B={B}")
 
 
+@pytest.mark.parametrize("cfg_name,d,F,B", [
+    ("c1", 4096, 300, 2),        # fp32 rows above 8 KiB: two column chunks per wave
+    ("c1", 4096, 300, 9),        # two passes (5 + 4)
+    ("c1", 4096, 170, 4),        # fewer neurons than workgroups
+    ("c1", 4096, 700, 1),        # one token
+    ("c1", 2052, 400, 3),        # 16 bytes into the second column chunk of wave 0
+    ("c1", 2048, 500, 8),        # whole passes of eight tokens
+    ("c1", 1000, 700, 4),        # rows that end inside a KiB
+    ("c1", 64, 40000, 3),        # more than 64 neurons per workgroup: rounds
+    ("c2", 3584, 500, 5),        # bf16 widths without a matrix-core instance
+    ("c2", 4360, 400, 5),        # wide bf16 rows: passes of at most four tokens
+    ("c2", 776, 3000, 17),       # three passes, 1.5 KiB rows
+])
+def test_several_tokens_per_pass_on_the_vector_units(clada, cfg_name, d, F, B):
+    """Layers from 8 MB of weights on that no other batched path takes, with thresholds spread over the tokens (one keeps
+    nothing); the dense twin and a list run of the union go through the same kernel."""
+    cfg, w, x = _case(cfg_name, 21, d, F, B)
+    tau = _tau_for(w, x, 0.45) * np.resize(np.array([1.0, 1.8, 1e9, 0.08], np.float32), B)
+    ctx, layer, xd, y, idx, cnt, mask = _run_sparse(clada, cfg, w, x, tau)
+    _check_against_oracle(cfg, w, x, tau, y, idx, cnt, mask, f"{cfg_name} d={d} F={F} B={B}")
+    yd = clada.dense_ffn_decode(ctx, layer, xd)
+    assert_close_y(to_np(yd), oracle.dense_decode(*w, x), TOL_Y[cfg.dtype], "dense twin")
+    n = max(int(cnt[0]), 1)
+    lst = torch.from_numpy(np.arange(0, F, 2, dtype=np.int32)[:n]).to(DEV)
+    full = torch.full((F,), F + 7, dtype=torch.int32, device=DEV)        # entries past the count are not read
+    full[:lst.numel()] = lst
+    ys = clada.static_ffn_decode(ctx, layer, xd, full, torch.tensor([lst.numel()], dtype=torch.int32, device=DEV))
+    keep = np.zeros(F, bool)
+    keep[lst.cpu().numpy()] = True
+    assert_close_y(to_np(ys), oracle.decode_given_mask(*w, x, np.broadcast_to(keep, (B, F))), TOL_Y[cfg.dtype], "list run")
+
+
+def test_infinite_weight_of_a_neuron_a_token_cuts_stays_out_of_its_output(clada):
+    """Token 0 keeps neuron 5, whose output row holds an infinity; token 1 cuts it and stays finite."""
+    cfg, w, x = _case("c1", 22, 2048, 500, 2)
+    w = [a.copy() for a in w]
+    w[2][5, 7] = np.inf
+    w[0][5] = x[0] / np.linalg.norm(x[0])                    # activation of token 0 about ||x||
+    tau = np.array([1.0, 1e3], np.float32)
+    _, _, _, y, _, _, mask = _run_sparse(clada, cfg, w, x, tau)
+    assert mask[0, 5] and not mask[1, 5]
+    assert not np.isfinite(to_np(y)[0, 7]) and np.isfinite(to_np(y)[1]).all()
+
+
 def test_sizes_beyond_the_limits_are_rejected(clada):
     from paper_2502_19078_amd.binding import CladaError
     cfg, w, x = _case("c2", 12, 256, 64, 1)
