@@ -40,7 +40,9 @@ struct clada_ctx {
 
 // The first bytes of the workspace hold self-resetting arrival counters (zeroed
 // once at clada_create); the scratch area proper starts after them.
-#define CLADA_WS_HEADER (416 * 1024)
+#define CALIB_STATE (416 * 1024)          // histograms of the threshold calibration, zero between its calls
+#define CALIB_BYTES (776 * 1024)
+#define CLADA_WS_HEADER (CALIB_STATE + CALIB_BYTES)
 enum { CTR_SIGNALS = 0, CTR_DECODE = 64, CTR_PREFIX = 128, CTR_CALIB = 192 };  // int32 slots
 // Control words of the cooperative decode kernels inside the header (byte offsets).
 #define COOP_MAX_WGS 256

@@ -132,3 +132,47 @@ def test_prefix_stats_full_size_layers_sampled(clada, cfg_name, layer_id):
     y = to_np(st.y)
     for t in toks:
         assert_close_y(y[t:t + 1], oracle.dense_decode(*w, X[t:t + 1]), TOL_Y[cfg.dtype], f"prefill y, token {t}")
+
+
+@pytest.mark.parametrize("n,kind", [
+    (1, "normal"), (3, "normal"), (5, "normal"), (16384 * 4 + 7, "normal"), (3_000_001, "normal"),
+    (13_000_003, "equal"),       # one value: the second pass has to add its 16-bit counts up on the way
+    (700_000, "zeros"),          # half of the pool exactly zero, as a ReLU leaves it
+    (1000, "inf"), (200_000, "tiny"), (70_000, "two"),
+])
+def test_calibrate_is_the_nearest_rank_quantile_bit_for_bit(clada, n, kind):
+    """Against a sort of the same values, ranks at both ends and inside; two calls on one context in a row (the
+    histograms have to be clear again), and replays of a captured call."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    v = torch.randn(n, generator=g, device=DEV).abs()
+    if kind == "equal":
+        v.fill_(0.25)
+    elif kind == "zeros":
+        v = torch.clamp_min(v - 0.67, 0.0)
+    elif kind == "inf":
+        v[::7] = float("inf")
+    elif kind == "tiny":
+        v *= 1e-42                                           # subnormal magnitudes: many ties
+    elif kind == "two":
+        v = torch.where(v > 0.5, torch.tensor(1.0, device=DEV), torch.nextafter(torch.tensor(1.0, device=DEV), torch.tensor(2.0, device=DEV)))
+    ref = v.sort().values
+    ctx = clada.Context(0, clada.workspace_bytes(64, 64, 0, 1, 0))
+    for q in (0.0, 1.0 / 3.0, 0.45, 0.5, 0.9, 0.9999999):
+        k = max(1, int(np.ceil(np.float64(np.float32(q)) * n)))
+        for _ in range(2):
+            got = clada.threshold_calibrate(ctx, v, q)
+            assert torch.equal(got, ref[k - 1:k]), (n, kind, q, float(got), float(ref[k - 1]))
+    out, side = torch.zeros(1, device=DEV), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        clada.graph_begin(ctx)
+        clada.threshold_calibrate(ctx, v, 0.45, out=out)
+        gr = clada.graph_end(ctx)
+        want = ref[max(1, int(np.ceil(np.float64(np.float32(0.45)) * n))) - 1]
+        for _ in range(3):
+            out.zero_()
+            gr.launch()
+            side.synchronize()
+            assert out[0] == want
+            clada.threshold_calibrate(ctx, v, 0.7)
+            side.synchronize()
