@@ -14,7 +14,17 @@ namespace {
 struct CettState {
     unsigned int lo, hi, mid;     // float bit patterns; the probe in flight is `mid`
     float mean_lo, mean_mid;      // mean CETT at lo / at the last probe
+    // the large search (see k_cett_next): what has been measured so far, and the running sum's state
+    int skip;                     // no further dense probe is needed
+    int done;                     // the bisection has ended
+    unsigned int known_lo, known_hi;      // largest feasible / smallest infeasible bit pattern measured
+    float known_mean;             // mean CETT at known_lo
+    int xlo, xhi, x, side;        // their places in the sorted sample, the probe's, which side moved last
+    float glo, ghi;               // mean - bound there (one is halved while the other side keeps moving)
+    unsigned int base;            // the cut sums in buffer `sel` hold the neurons below this bit pattern
+    int sel;
 };
+static_assert(sizeof(CettState) <= 256, "its place in the workspace");
 
 // den[t] = || MLP(x_t) ||_2 from the per-column-tile sums of squares (ascending tile order);
 // thread 0 of block 0 sets up the bracket, or the single probe of an evaluation call.
@@ -63,8 +73,9 @@ k_cett_row_norm(const char *__restrict__ y, int T, int d, float *__restrict__ de
 template <int ES>
 __global__ void __launch_bounds__(256)
 k_cett_mask(const CettState *__restrict__ st, const float *__restrict__ pool, const char *__restrict__ h,
-            char *__restrict__ hcut, int T, int F, int Fp)
+            char *__restrict__ hcut, int T, int F, int Fp, int may_skip)
 {
+    if (may_skip && st->skip) return;
     const float eps = __uint_as_float(st->mid);
     const size_t groups = (size_t)Fp / 8;
     const size_t total = (size_t)T * groups;
@@ -150,6 +161,267 @@ __global__ void k_cett_finish(const CettState *st, float *tau_out, float *mean_o
     }
 }
 
+// ---------------------------------------------------------------------------------------------------------------------
+// The large search.  A dense probe costs a masked projection (80 us for 512 tokens of a 7B layer), and bisecting the bit
+// pattern from 0 .. +inf spends 31 of them, most on thresholds whose answer is known from a neighbour.  Here
+//   (1) some dense probes close a bracket around the answer, at thresholds taken from a sorted sample of the pool: as a
+//       function of the rank the mean is smooth (as one of the threshold it is not: SiLU's minimum piles the magnitudes up),
+//       so that false position with the Illinois rule needs six or seven probes to leave about fifty magnitudes per token;
+//   (2) one more projection leaves the cut sums at the bracket's lower end in fp32;
+//   (3) the same bisection as before then runs; a probe outside the bracket is answered by it, one inside adds the rows of
+//       the neurons between the sums' threshold and the probe to the sums, token by token, and a feasible probe's sums
+//       become the new ones.
+// 512 tokens of 4096 x 11008: 2670 us with 31 dense probes, 1230 us so.  The bracket answers for thresholds outside it as a
+// monotone mean would; inside, every probe is measured.
+constexpr int SAMPLES = 8192;      // sorted sample of the pool; neighbours are 1.3 magnitudes per token apart at 11008 neurons
+constexpr int CLOSE = 40;          // sample places left between the bracket's ends when the dense probes end
+constexpr int DENSE_PROBES = 10;   // launched; those past the end return at once
+
+__device__ __forceinline__ unsigned int sample_hash(unsigned int x)
+{
+    x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
+    return x;
+}
+
+// One workgroup: the sorted bit patterns of SAMPLES pool entries drawn by a fixed hash, and the first probe.
+__global__ void __launch_bounds__(1024)
+k_cett_sample(CettState *st, const float *__restrict__ pool, unsigned long long n, unsigned int *__restrict__ sample, float bound)
+{
+    __shared__ unsigned int s[SAMPLES];
+    const int tid = threadIdx.x;
+    for (int i = tid; i < SAMPLES; i += 1024) {
+        const unsigned long long r = ((unsigned long long)sample_hash(2 * i + 1) << 32) | sample_hash(2 * i + 2);
+        const unsigned int u = __float_as_uint(pool[__umul64hi(r, n)]) & 0x7fffffffu;
+        s[i] = u < 0x7f800000u ? u : 0x7f800000u;
+    }
+    __syncthreads();
+    for (int k = 2; k <= SAMPLES; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int q = tid; q < SAMPLES / 2; q += 1024) {
+                const int i = 2 * q - (q & (j - 1)), l = i + j;
+                const unsigned int a = s[i], b = s[l];
+                if ((a > b) == ((i & k) == 0)) { s[i] = b; s[l] = a; }
+            }
+            __syncthreads();
+        }
+    for (int i = tid; i < SAMPLES; i += 1024) sample[i] = s[i];
+    if (tid == 0) {
+        st->skip = 0; st->done = 0;
+        st->known_lo = 0u; st->known_hi = 0x7f800000u; st->known_mean = 0.0f;
+        st->xlo = -1; st->xhi = SAMPLES; st->side = 0;
+        st->glo = -bound; st->ghi = 1.0f - bound;
+        st->x = SAMPLES / 2;
+        st->mid = s[SAMPLES / 2];
+    }
+}
+
+// Mean CETT of the probe (as in k_cett_update; the sum over the column tiles and over the tokens in the same order).
+__device__ __forceinline__ float mean_cett(const float *__restrict__ rowsq, int n_tn, int T, const float *__restrict__ den, float *s_sum)
+{
+    const int tid = threadIdx.x;
+    float acc = 0.0f;
+    for (int t = tid; t < T; t += 1024) {
+        float s = 0.0f;
+#pragma unroll 8
+        for (int i = 0; i < n_tn; ++i) s += rowsq[(size_t)i * T + t];
+        const float dn = den[t];
+        acc += dn > 0.0f ? sqrtf(s) / dn : 0.0f;
+    }
+    s_sum[tid] = acc;
+    __syncthreads();
+    for (int w = 512; w > 0; w >>= 1) {
+        if (tid < w) s_sum[tid] += s_sum[tid + w];
+        __syncthreads();
+    }
+    return s_sum[0] / (float)T;
+}
+
+// The bisection up to the next threshold that has to be measured.
+__device__ __forceinline__ void bisect_on(CettState &s)
+{
+    while (s.hi - s.lo > 1u) {
+        const unsigned int mid = s.lo + ((s.hi - s.lo) >> 1);
+        if (mid <= s.known_lo) s.lo = mid;
+        else if (mid >= s.known_hi) s.hi = mid;
+        else { s.mid = mid; return; }
+    }
+    s.done = 1;
+    s.mean_lo = s.known_mean;                                // (lo has come to rest on known_lo)
+}
+
+// After a dense probe: the bracket, and the next probe between its ends.
+__global__ void __launch_bounds__(1024)
+k_cett_next(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, const float *__restrict__ den, float bound,
+            const unsigned int *__restrict__ sample)
+{
+    __shared__ float s_sum[1024];
+    if (st->skip) return;
+    const float mean = mean_cett(rowsq, n_tn, T, den, s_sum);
+    if (threadIdx.x != 0) return;
+    CettState s = *st;
+    const bool feasible = mean <= bound;                     // NaN: over the bound
+    if (feasible) { if (s.mid > s.known_lo) { s.known_lo = s.mid; s.known_mean = mean; } }
+    else if (s.mid < s.known_hi) s.known_hi = s.mid;
+    auto take = [&](bool low, float g) {                     // the place x becomes an end of the bracket
+        if (low) { s.xlo = s.x; s.glo = g; if (s.side < 0) s.ghi *= 0.5f; s.side = -1; }
+        else { s.xhi = s.x; s.ghi = g; if (s.side > 0) s.glo *= 0.5f; s.side = 1; }
+    };
+    float g = mean - bound;
+    if (!feasible && !(g > 0.0f)) g = 1.0f;                  // (NaN)
+    take(feasible, g);
+    for (int guard = 0;; ++guard) {
+        if (s.xhi - s.xlo <= CLOSE || guard >= 64) { s.skip = 1; break; }
+        const float pos = (float)s.xlo + (float)(s.xhi - s.xlo) * (-s.glo / (s.ghi - s.glo));
+        // a little past the estimate, towards the end that did not move last: the bracket closes from both sides
+        int x = (int)(s.side > 0 ? pos - 0.4f * CLOSE : pos + 0.4f * CLOSE);
+        x = x > s.xlo ? x : s.xlo + 1;
+        s.x = x < s.xhi ? x : s.xhi - 1;
+        s.mid = sample[s.x];
+        if (s.mid <= s.known_lo) take(true, s.glo);          // equal magnitudes: measured already
+        else if (s.mid >= s.known_hi) take(false, s.ghi);
+        else break;
+    }
+    *st = s;
+}
+
+// The threshold of the cut sums (the bracket's lower end), and the start of the bisection.
+__global__ void k_cett_base(CettState *st, int stage)
+{
+    if (threadIdx.x != 0) return;
+    if (stage == 0) { st->mid = st->known_lo; return; }      // for the masking pass
+    CettState s = *st;
+    s.base = s.known_lo;
+    s.sel = 0;
+    s.lo = 0u;
+    s.hi = 0x7f800000u;
+    bisect_on(s);
+    *st = s;
+}
+
+// Cut sums at the probe, one workgroup per token: the sums at `base` plus h_j W_down[j,:] of the neurons with
+// base <= |a_j| < probe in ascending order, to the other buffer; their sum of squares to rowsq.
+template <int ES, int NV>
+__global__ void __launch_bounds__(256)
+k_cett_between(const CettState *__restrict__ st, const float *__restrict__ pool, const char *__restrict__ h,
+               const char *__restrict__ wd, float *__restrict__ buf0, float *__restrict__ buf1, float *__restrict__ rowsq,
+               int F, int Fp, int d)
+{
+    if (st->done) return;
+    constexpr int VEC = 16 / ES, PER = 16, SEG = 256 * PER;
+    __shared__ int s_cnt[PER * 4], s_j[SEG];
+    __shared__ float s_h[SEG], s_sq[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const size_t t = blockIdx.x;
+    const float lo = __uint_as_float(st->base), hi = __uint_as_float(st->mid);
+    const float *src = (st->sel ? buf1 : buf0) + t * d;
+    float *dst = (st->sel ? buf0 : buf1) + t * d;
+    float acc[NV][VEC];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int col = (v * 256 + tid) * VEC;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[v][e] = col < d ? src[col + e] : 0.0f;
+    }
+    for (int seg = 0; seg < F; seg += SEG) {
+        bool in[PER];
+        int before[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int j = seg + k * 256 + tid;
+            const float a = pool[t * F + (j < F ? j : F - 1)];
+            in[k] = j < F && a >= lo && a < hi;
+            const unsigned long long m = __ballot(in[k]);
+            before[k] = __popcll(m & ((1ull << lane) - 1ull));
+            if (lane == 0) s_cnt[k * 4 + wave] = __popcll(m);
+        }
+        __syncthreads();
+        int total = 0;                                       // 64 counts in ascending order of their neurons
+        {
+            const int c = s_cnt[lane];
+            int inc = c;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int x = __shfl_up(inc, o);
+                if (lane >= o) inc += x;
+            }
+            total = __shfl(inc, 63);
+            const int excl = inc - c;
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const int at = __shfl(excl, k * 4 + wave) + before[k];
+                if (in[k]) {
+                    const int j = seg + k * 256 + tid;
+                    s_j[at] = j;
+                    s_h[at] = ES == 4 ? reinterpret_cast<const float *>(h)[t * Fp + j]
+                                      : __uint_as_float((unsigned int)reinterpret_cast<const unsigned short *>(h)[t * Fp + j] << 16);
+                }
+            }
+        }
+        __syncthreads();
+        for (int e0 = 0; e0 < total; e0 += 4) {
+            u32x4 w[4][NV];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const char *row = wd + (size_t)s_j[min(e0 + q, total - 1)] * d * ES;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const int col = (v * 256 + tid) * VEC;
+                    w[q][v] = *reinterpret_cast<const u32x4 *>(row + (size_t)(col < d ? col : 0) * ES);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (e0 + q < total) {
+                    const float hv = s_h[e0 + q];
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        float f[VEC];
+                        unpack_row16(w[q][v], f);
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) acc[v][e] = fmaf(hv, f[e], acc[v][e]);
+                    }
+                }
+            }
+        }
+    }
+    float sq = 0.0f;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int col = (v * 256 + tid) * VEC;
+        if (col < d) {
+#pragma unroll
+            for (int e = 0; e < VEC; e += 4)
+                *reinterpret_cast<float4 *>(dst + col + e) = make_float4(acc[v][e], acc[v][e + 1], acc[v][e + 2], acc[v][e + 3]);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) sq = fmaf(acc[v][e], acc[v][e], sq);
+        }
+    }
+    sq = wave_sum(sq);
+    if (lane == 0) s_sq[wave] = sq;
+    __syncthreads();
+    if (tid == 0) rowsq[t] = (s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3]);
+}
+
+// After a probe inside the bracket.
+__global__ void __launch_bounds__(1024)
+k_cett_inside(CettState *st, const float *__restrict__ rowsq, int T, const float *__restrict__ den, float bound)
+{
+    __shared__ float s_sum[1024];
+    if (st->done) return;
+    const float mean = mean_cett(rowsq, 1, T, den, s_sum);
+    if (threadIdx.x != 0) return;
+    CettState s = *st;
+    if (mean <= bound) {
+        s.known_lo = s.base = s.mid;
+        s.known_mean = mean;
+        s.sel ^= 1;
+    } else {
+        s.known_hi = s.mid;
+    }
+    bisect_on(s);
+    *st = s;
+}
+
 struct CettWs {
     float *part, *pool, *rowsq_den, *rowsq_num, *den, *splitk;
     char *h, *hcut, *ytmp;
@@ -225,14 +497,62 @@ clada_status probe(clada_ctx *ctx, const clada_layer *layer, int T, const CettWs
     const size_t groups = (size_t)T * (Fp / 8);
     const int grid = (int)((groups + 255) / 256 < 4096 ? (groups + 255) / 256 : 4096);
     if (layer->dtype == CLADA_BF16)
-        hipLaunchKernelGGL(k_cett_mask<2>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp);
+        hipLaunchKernelGGL(k_cett_mask<2>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, 0);
     else
-        hipLaunchKernelGGL(k_cett_mask<4>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp);
+        hipLaunchKernelGGL(k_cett_mask<4>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, 0);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, ctx->opt_prefix_tile, stream));
     hipLaunchKernelGGL(k_cett_update, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound,
                        search, cett_out, mean_out);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
+    return CLADA_OK;
+}
+
+template <int ES>
+void launch_between(const CettWs &w, const clada_layer *layer, int T, int Fp, float *buf1, hipStream_t st)
+{
+    const int d = layer->d, vecs = (d * ES / 16 + 255) / 256;
+    auto kern = vecs <= 1 ? k_cett_between<ES, 1> : vecs == 2 ? k_cett_between<ES, 2> : k_cett_between<ES, 4>;
+    hipLaunchKernelGGL(kern, dim3(T), dim3(256), 0, st, w.state, w.pool, w.h, (const char *)layer->w_down,
+                       reinterpret_cast<float *>(w.ytmp), buf1, w.rowsq_num, layer->d_ff, Fp, d);
+}
+
+// The large search after begin(): ytmp and hcut (free once the dense probes are over) hold the cut sums.
+clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const CettWs &w, float bound, hipStream_t stream)
+{
+    const int d = layer->d, F = layer->d_ff, n_tn = clada_prefix_col_tiles(d);
+    const int Fp = (int)align_up((size_t)F, 64);
+    const size_t groups = (size_t)T * (Fp / 8);
+    const int grid = (int)((groups + 255) / 256 < 4096 ? (groups + 255) / 256 : 4096);
+    unsigned int *sample = reinterpret_cast<unsigned int *>(w.part);         // (the partial aggregates are not used here)
+    auto mask = [&](int may_skip) {
+        if (layer->dtype == CLADA_BF16)
+            hipLaunchKernelGGL(k_cett_mask<2>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, may_skip);
+        else
+            hipLaunchKernelGGL(k_cett_mask<4>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, may_skip);
+        return hipGetLastError();
+    };
+    hipLaunchKernelGGL(k_cett_sample, dim3(1), dim3(1024), 0, stream, w.state, w.pool, (unsigned long long)T * F, sample, bound);
+    CLADA_CHECK_HIP(ctx, hipGetLastError());
+    for (int it = 0; it < DENSE_PROBES; ++it) {
+        CLADA_CHECK_HIP(ctx, mask(1));
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, ctx->opt_prefix_tile, stream, nullptr, &w.state->skip));
+        hipLaunchKernelGGL(k_cett_next, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound, sample);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 0);
+    CLADA_CHECK_HIP(ctx, hipGetLastError());
+    CLADA_CHECK_HIP(ctx, mask(0));
+    CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, w.splitk, ctx->opt_prefix_tile, stream, reinterpret_cast<float *>(w.ytmp)));
+    hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 1);
+    CLADA_CHECK_HIP(ctx, hipGetLastError());
+    for (int it = 0; it < 31; ++it) {
+        if (layer->dtype == CLADA_BF16) launch_between<2>(w, layer, T, Fp, reinterpret_cast<float *>(w.hcut), stream);
+        else launch_between<4>(w, layer, T, Fp, reinterpret_cast<float *>(w.hcut), stream);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+        hipLaunchKernelGGL(k_cett_inside, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, T, w.den, bound);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+    }
     return CLADA_OK;
 }
 
@@ -277,7 +597,15 @@ extern "C" clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_
     const CettWs w = carve(ctx->ws + CLADA_WS_HEADER, layer->d, layer->d_ff, T);
     st = begin(ctx, layer, x_val, T, w, 1, 0.0f, stream);
     if (st != CLADA_OK) return st;
-    for (int it = 0; it < n_probes; ++it) {
+    // The large search pays where a dense probe is many times a pass over the pool, and its bracket is only trusted where
+    // single neurons do not move the mean; fewer probes than the full 31 end somewhere on the way, which only the plain
+    // bisection passes through.
+    const bool large = n_probes == 31 && bound > 0.0f && (size_t)T * layer->d_ff >= (1u << 20) && T >= 64 && layer->d_ff >= layer->d;
+    if (large) {
+        st = search_large(ctx, layer, T, w, bound, stream);
+        if (st != CLADA_OK) return st;
+    }
+    for (int it = 0; it < n_probes && !large; ++it) {
         st = probe(ctx, layer, T, w, bound, 1, nullptr, nullptr, stream);
         if (st != CLADA_OK) return st;
     }

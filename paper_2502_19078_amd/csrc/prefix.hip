@@ -700,6 +700,8 @@ struct DownParams {
     int T, d, F, Fp, n_tm, n_tn;   // Fp = F rounded up to a multiple of BK (row stride of h)
     float *part_out;               // split-K (256 x 256 kernel): fp32 partial outputs [S][T][d] instead of y / rowsq
     int S;                         // number of k ranges the neurons are split into (1 = no split)
+    float *y32;                    // [T][d] the fp32 rows without a bias, or nullptr
+    const int *skip;               // device flag: nothing to do when set (a probe that is not needed), or nullptr
 };
 
 // Row sums of squares of a 128 x 128 output tile held in the accumulators of four waves (2 x 2
@@ -726,10 +728,27 @@ __device__ __forceinline__ void down_rowsq(const f32x16 (&acc)[2][2], const Down
     }
 }
 
+// The fp32 rows of a 128 x 128 tile, without a bias.
+__device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const DownParams &p, int tm, int tn, int wm, int wn, int lane)
+{
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        const int col = tn * BN + wn * 64 + nb * 32 + (lane & 31);
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int t = tm * BM + wm * 64 + mb * 32 + acc_row(r, lane);
+                if (t < p.T && col < p.d) p.y32[(size_t)t * p.d + col] = acc[mb][nb][r];
+            }
+    }
+}
+
 template <int ES>
 __global__ void __launch_bounds__(256)
 k_prefix_down(const DownParams p)
 {
+    if (p.skip && *p.skip) return;
     constexpr int ROW = Tile<ES>::ROW, CH = Tile<ES>::CHUNKS, PT = Tile<ES>::PER_THREAD;
     constexpr int VEC = 16 / ES;
     __shared__ __align__(16) char s_a[BM * ROW];
@@ -801,6 +820,7 @@ k_prefix_down(const DownParams p)
         mma_tile<ES, 1>(s_a + wm * 64 * ROW, sb, acc, lane);
     }
     if (p.rowsq) down_rowsq(acc[0], p, tm, tn, wm, wn, lane, tid, s_rs);
+    if (p.y32) down_store32(acc[0], p, tm, tn, wm, wn, lane);
     if (!p.y) return;
     const int n = lane & 31;
 #pragma unroll
@@ -832,6 +852,7 @@ constexpr int DB_PITCH = BN * 2 + 32;           // W_down tile row pitch: 4 rows
 __global__ void __launch_bounds__(256)
 k_prefix_down_bf16(const DownParams p)
 {
+    if (p.skip && *p.skip) return;
     __shared__ __align__(16) char s_a[BM * DA_PITCH];
     __shared__ __align__(16) char s_b[DBK * DB_PITCH];
     __shared__ float s_rs[2][BM];
@@ -910,6 +931,7 @@ k_prefix_down_bf16(const DownParams p)
         }
     }
     if (p.rowsq) down_rowsq(acc, p, tm, tn, wm, wn, lane, tid, s_rs);
+    if (p.y32) down_store32(acc, p, tm, tn, wm, wn, lane);
     if (!p.y) return;
     const int n = lane & 31;
 #pragma unroll
@@ -944,6 +966,7 @@ constexpr int DW_STAGE = DW_B + 16 * DW_PAIR;       // 34816 bytes
 __global__ void __launch_bounds__(256)
 k_prefix_down_bf16_wide(const DownParams p)
 {
+    if (p.skip && *p.skip) return;
     __shared__ __align__(16) char s_w[4 * DW_STAGE];
 
     const int n_tmw = (p.T + 255) / 256, n_tnw = p.d / 256;
@@ -1132,10 +1155,11 @@ k_prefix_down_bf16_wide(const DownParams p)
     const int n = lane & 31;
     const int t0 = tm * 256 + wm * 128 + 4 * (lane >> 5);
     const int c0 = tn * 256 + wn * 128;                     // one 128-column tile of the row-norm buffer
-    if (p.part_out) {                                       // split-K: fp32 partial sums, reduced by k_prefix_down_combine
+    if (p.part_out || p.y32) {                              // split-K: fp32 partial sums, reduced by k_prefix_down_combine
+        float *rows32 = p.part_out ? p.part_out + (size_t)ks * p.T * p.d : p.y32;
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
-            float *dst = p.part_out + ((size_t)ks * p.T + t0) * p.d + c0 + nb * 32 + n;
+            float *dst = rows32 + (size_t)t0 * p.d + c0 + nb * 32 + n;
 #pragma unroll
             for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
@@ -1144,7 +1168,7 @@ k_prefix_down_bf16_wide(const DownParams p)
                     if (t0 + row < p.T) dst[(size_t)row * p.d] = acc[mb][nb][r];
                 }
         }
-        return;
+        if (p.part_out) return;
     }
     if (p.rowsq) {
 #pragma unroll
@@ -1184,8 +1208,9 @@ k_prefix_down_bf16_wide(const DownParams p)
 // 8 rows x 128 columns: thread = (row tid >> 5, four columns 4 (tid & 31) ..).
 __global__ void __launch_bounds__(256)
 k_prefix_down_combine(const float *__restrict__ part, int S, int T, int d, char *__restrict__ y,
-                      const float *__restrict__ bias, float *__restrict__ rowsq)
+                      const float *__restrict__ bias, float *__restrict__ rowsq, float *__restrict__ y32, const int *__restrict__ skip)
 {
+    if (skip && *skip) return;
     const int t = blockIdx.x * 8 + (threadIdx.x >> 5);
     const int col = blockIdx.y * 128 + 4 * (threadIdx.x & 31);
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1204,6 +1229,7 @@ k_prefix_down_combine(const float *__restrict__ part, int S, int T, int d, char 
         v += __shfl_xor(v, 1);
         if ((threadIdx.x & 31) == 0 && t < T) rowsq[(size_t)blockIdx.y * T + t] = v;
     }
+    if (y32 && t < T) *reinterpret_cast<float4 *>(y32 + (size_t)t * d + col) = s;
     if (y && t < T) {
         if (bias) {
             const float4 b = *reinterpret_cast<const float4 *>(bias + col);
@@ -1348,12 +1374,14 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
 }
 
 // Down projection of h [T][Fp]: y [T][d] in the layer dtype and/or rowsq [col tiles][T], the
-// per-column-tile sums of squares of the fp32 output rows (either may be nullptr).
+// per-column-tile sums of squares of the fp32 output rows, and/or y32 [T][d], those rows without a bias (any may be
+// nullptr).  skip: device flag, nothing is computed when it is set (nullptr: always computed).
 hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq,
-                             float *splitk_ws, int tile_mode, hipStream_t stream)
+                             float *splitk_ws, int tile_mode, hipStream_t stream, float *y32, const int *skip)
 {
     const int d = layer->d, F = layer->d_ff, es = (int)dtype_size(layer->dtype);
     DownParams q;
+    q.y32 = y32; q.skip = skip;
     q.h = h; q.wd = (const char *)layer->w_down; q.y = y; q.rowsq = rowsq;
     q.bias = (layer->kind == CLADA_FFN_RELU && y) ? layer->b_out : nullptr;
     q.T = T; q.d = d; q.F = F; q.Fp = (int)align_up((size_t)F, 64);
@@ -1372,7 +1400,7 @@ hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, cha
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_prefix_down_combine, dim3((T + 7) / 8, d / 128), dim3(256), 0, stream, splitk_ws, S, T, d,
-                           y, q.bias, rowsq);
+                           y, q.bias, rowsq, y32, skip);
     }
     else if (wide_ok && (tile_mode == 2 || n_tmw * n_tnw >= 192)) {
         const int blocks = n_tmw % 8 == 0 ? n_tmw * ((n_tnw + 3) / 4 * 4) : n_tmw * n_tnw;

@@ -194,3 +194,49 @@ def test_cett_search_graph_replay_matches_eager(clada):
         again = clada.threshold_search_cett(ctx, layer, Xd, 0.2)[0]      # eager call between replays
         torch.cuda.synchronize()
         assert torch.equal(again, tau_e)
+
+
+# d, F, T, kind, dtype, weight std: searches large enough (2^20 magnitudes) to close a bracket by sampled thresholds first;
+# rows of one, two and four 16-byte groups per thread, ragged neuron counts and tokens, every family
+LARGE = [
+    (1024, 11008, 96, "silu", "bf16", 0.02), (4096, 5003, 260, "silu", "bf16", 0.02), (2056, 16400, 67, "gelu", "bf16", 0.03),
+    (8192, 8192, 128, "silu", "bf16", 0.005), (1024, 4096, 300, "relu", "bf16", 0.02), (512, 4100, 256, "silu", "f32", 0.04),
+    (4096, 4096, 256, "relu", "f32", 0.02),
+]
+
+
+@pytest.mark.parametrize("d,F,T,kind,dtype,std", LARGE)
+def test_large_search_ends_where_the_plain_bisection_does(clada, d, F, T, kind, dtype, std):
+    """30 probes run the plain bisection and leave two neighbouring floats open, 31 the large search.  Its cut sums are
+    formed in another order (rel. 1e-6 of a norm), which can move the result past the magnitudes that close to the bound."""
+    from paper_2502_19078_amd import binding
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(d + F)
+    n = lambda *s, k=std: torch.randn(s, generator=g, device=DEV) * k
+    w = [n(F, d).to(dt) for _ in range(2 if kind == "relu" else 3)]
+    layer = (clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=n(F), b_out=n(d)) if kind == "relu"
+             else clada.Layer(*w, kind=binding.GEGLU if kind == "gelu" else binding.SWIGLU))
+    x = n(T, d, k=1.0).to(dt)
+    x[5] = x[6]                                              # two tokens with the same magnitudes
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    for bound in (0.02, 0.2, 0.6):
+        t30, m30 = clada.threshold_search_cett(ctx, layer, x, bound, n_probes=30)
+        for _ in range(2):
+            t31, m31 = clada.threshold_search_cett(ctx, layer, x, bound)
+            assert float(t31) == pytest.approx(float(t30), rel=2e-6), bound
+            assert float(m31) == pytest.approx(float(m30), rel=1e-5) and float(m31) <= bound
+            assert float(clada.cett_eval(ctx, layer, x, float(t31))[1]) == pytest.approx(float(m31), rel=2e-6)
+
+
+def test_large_search_without_a_largest_threshold(clada):
+    """A bias that dominates the output: every threshold satisfies the bound, and the largest finite float comes back, as
+    from the plain bisection."""
+    from paper_2502_19078_amd import binding
+    d, F, T = 512, 4096, 257
+    g = torch.Generator(device=DEV).manual_seed(1)
+    w = [(torch.randn((F, d), generator=g, device=DEV) * 0.02).bfloat16() for _ in range(2)]
+    layer = clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=None, b_out=torch.full((d,), 1e4, device=DEV))
+    x = torch.randn((T, d), generator=g, device=DEV).bfloat16()
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    tau, mean = clada.threshold_search_cett(ctx, layer, x, 0.2)
+    assert float(tau) == float(np.finfo(np.float32).max) and 0.0 < float(mean) < 0.2
