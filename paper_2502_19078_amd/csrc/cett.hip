@@ -23,8 +23,9 @@ struct CettState {
     float glo, ghi;               // mean - bound there (one is halved while the other side keeps moving)
     unsigned int base;            // the cut sums in buffer `sel` hold the neurons below this bit pattern
     int sel;
+    int listed;                   // the neurons inside the first bracket are listed (no token had too many)
 };
-static_assert(sizeof(CettState) <= 256, "its place in the workspace");
+static_assert(2 * sizeof(CettState) <= 256, "two of them in their place in the workspace");
 
 // den[t] = || MLP(x_t) ||_2 from the per-column-tile sums of squares (ascending tile order);
 // thread 0 of block 0 sets up the bracket, or the single probe of an evaluation call.
@@ -168,13 +169,13 @@ __global__ void k_cett_finish(const CettState *st, float *tau_out, float *mean_o
 //       function of the rank the mean is smooth (as one of the threshold it is not: SiLU's minimum piles the magnitudes up),
 //       so that false position with the Illinois rule needs six or seven probes to leave about fifty magnitudes per token;
 //   (2) one more projection leaves the cut sums at the bracket's lower end in fp32;
-//   (3) the same bisection as before then runs; a probe outside the bracket is answered by it, one inside adds the rows of
+//   (3) the plain bisection then runs; a probe outside the bracket is answered by it, one inside adds the rows of
 //       the neurons between the sums' threshold and the probe to the sums, token by token, and a feasible probe's sums
 //       become the new ones.
-// 512 tokens of 4096 x 11008: 2670 us with 31 dense probes, 1230 us so.  The bracket answers for thresholds outside it as a
+// 512 tokens of 4096 x 11008: 2670 us with 31 dense probes, 1150 us so.  The bracket answers for thresholds outside it as a
 // monotone mean would; inside, every probe is measured.
-constexpr int SAMPLES = 8192;      // sorted sample of the pool; neighbours are 1.3 magnitudes per token apart at 11008 neurons
-constexpr int CLOSE = 40;          // sample places left between the bracket's ends when the dense probes end
+constexpr int SAMPLES = 4096;      // sorted sample of the pool; neighbours are 2.7 magnitudes per token apart at 11008 neurons
+constexpr int CLOSE = 24;          // sample places left between the bracket's ends when the dense probes end
 constexpr int DENSE_PROBES = 10;   // launched; those past the end return at once
 
 __device__ __forceinline__ unsigned int sample_hash(unsigned int x)
@@ -202,8 +203,11 @@ k_cett_sample(CettState *st, const float *__restrict__ pool, unsigned long long 
                 const unsigned int a = s[i], b = s[l];
                 if ((a > b) == ((i & k) == 0)) { s[i] = b; s[l] = a; }
             }
-            __syncthreads();
+            // up to j = 64 a wave's pairs stay within its own 128 entries, and its LDS accesses are in order
+            if (j > 64 || (j == 1 && k >= 128)) __syncthreads();
+            else asm volatile("" ::: "memory");
         }
+    __syncthreads();
     for (int i = tid; i < SAMPLES; i += 1024) sample[i] = s[i];
     if (tid == 0) {
         st->skip = 0; st->done = 0;
@@ -292,102 +296,178 @@ __global__ void k_cett_base(CettState *st, int stage)
     CettState s = *st;
     s.base = s.known_lo;
     s.sel = 0;
+    s.listed = 1;
     s.lo = 0u;
     s.hi = 0x7f800000u;
     bisect_on(s);
-    *st = s;
+    st[0] = s;
 }
 
-// Cut sums at the probe, one workgroup per token: the sums at `base` plus h_j W_down[j,:] of the neurons with
-// base <= |a_j| < probe in ascending order, to the other buffer; their sum of squares to rowsq.
-template <int ES, int NV>
-__global__ void __launch_bounds__(256)
-k_cett_between(const CettState *__restrict__ st, const float *__restrict__ pool, const char *__restrict__ h,
-               const char *__restrict__ wd, float *__restrict__ buf0, float *__restrict__ buf1, float *__restrict__ rowsq,
-               int F, int Fp, int d)
+// Ascending list of the entries i of [0, n) that want(i) names, by a workgroup of 256 threads, 16 per thread and round of
+// 4096; f(position, i) for each, then done(count) by all threads between barriers.
+template <typename Want, typename Put, typename Done>
+__device__ __forceinline__ void list_ascending(int n, int *s_cnt, Want want, Put put, Done done)
 {
-    if (st->done) return;
-    constexpr int VEC = 16 / ES, PER = 16, SEG = 256 * PER;
-    __shared__ int s_cnt[PER * 4], s_j[SEG];
-    __shared__ float s_h[SEG], s_sq[4];
+    constexpr int PER = 16;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const size_t t = blockIdx.x;
-    const float lo = __uint_as_float(st->base), hi = __uint_as_float(st->mid);
-    const float *src = (st->sel ? buf1 : buf0) + t * d;
-    float *dst = (st->sel ? buf0 : buf1) + t * d;
-    float acc[NV][VEC];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int col = (v * 256 + tid) * VEC;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[v][e] = col < d ? src[col + e] : 0.0f;
-    }
-    for (int seg = 0; seg < F; seg += SEG) {
-        bool in[PER];
+    for (int seg = 0; seg < n; seg += 256 * PER) {
+        unsigned int in = 0u;
         int before[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            const int j = seg + k * 256 + tid;
-            const float a = pool[t * F + (j < F ? j : F - 1)];
-            in[k] = j < F && a >= lo && a < hi;
-            const unsigned long long m = __ballot(in[k]);
-            before[k] = __popcll(m & ((1ull << lane) - 1ull));
-            if (lane == 0) s_cnt[k * 4 + wave] = __popcll(m);
-        }
-        __syncthreads();
-        int total = 0;                                       // 64 counts in ascending order of their neurons
-        {
-            const int c = s_cnt[lane];
-            int inc = c;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int x = __shfl_up(inc, o);
-                if (lane >= o) inc += x;
-            }
-            total = __shfl(inc, 63);
-            const int excl = inc - c;
-#pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                const int at = __shfl(excl, k * 4 + wave) + before[k];
-                if (in[k]) {
-                    const int j = seg + k * 256 + tid;
-                    s_j[at] = j;
-                    s_h[at] = ES == 4 ? reinterpret_cast<const float *>(h)[t * Fp + j]
-                                      : __uint_as_float((unsigned int)reinterpret_cast<const unsigned short *>(h)[t * Fp + j] << 16);
-                }
+            before[k] = 0;
+            if (seg + k * 256 < n) {
+                const int i = seg + k * 256 + tid;
+                const bool w = want(i < n ? i : n - 1) && i < n;
+                const unsigned long long m = __ballot(w);
+                in |= w ? 1u << k : 0u;
+                before[k] = __popcll(m & ((1ull << lane) - 1ull));
+                if (lane == 0) s_cnt[k * 4 + wave] = __popcll(m);
+            } else if (lane == 0) {
+                s_cnt[k * 4 + wave] = 0;
             }
         }
         __syncthreads();
-        for (int e0 = 0; e0 < total; e0 += 4) {
-            u32x4 w[4][NV];
+        const int c = s_cnt[lane];                           // 64 counts in ascending order of their entries
+        int inc = c;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const char *row = wd + (size_t)s_j[min(e0 + q, total - 1)] * d * ES;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(inc, o);
+            if (lane >= o) inc += x;
+        }
+        const int total = __shfl(inc, 63), excl = inc - c;
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const int col = (v * 256 + tid) * VEC;
-                    w[q][v] = *reinterpret_cast<const u32x4 *>(row + (size_t)(col < d ? col : 0) * ES);
-                }
+        for (int k = 0; k < PER; ++k) {
+            const int at = __shfl(excl, k * 4 + wave) + before[k];
+            if ((in >> k) & 1u) put(at, seg + k * 256 + tid);
+        }
+        __syncthreads();
+        done(total);
+    }
+}
+
+// The neurons of every token with known_lo <= |a| < known_hi, the only ones that later probes add: cap of them per token
+// fit; a token with more leaves `listed` at zero, and the probes look through the whole pool.
+__global__ void __launch_bounds__(256)
+k_cett_list(CettState *st, const float *__restrict__ pool, int F, int *__restrict__ list, int cap, int *__restrict__ count)
+{
+    __shared__ int s_cnt[64];
+    const size_t t = blockIdx.x;
+    const float lo = __uint_as_float(st->known_lo), hi = __uint_as_float(st->known_hi);
+    int *mine = list + t * cap;
+    int at = 0;
+    list_ascending(F, s_cnt, [&](int j) { const float a = pool[t * F + j]; return a >= lo && a < hi; },
+                   [&](int i, int j) { if (at + i < cap) mine[at + i] = j; }, [&](int n) { at += n; });
+    if (threadIdx.x == 0) {
+        count[t] = min(at, cap);
+        if (at > cap) st->listed = 0;
+    }
+}
+
+// One probe inside the bracket.  First every workgroup takes in the previous one (the same state and the same norms, so the
+// same result; workgroup 0 leaves it for the next launch), then, a workgroup per token and part of the columns: the cut sums
+// at `base` plus h_j W_down[j,:] of the neurons with base <= |a_j| < probe in ascending order, to the other buffer; their
+// sum of squares to rowsq.
+template <int ES, int NV>
+__global__ void __launch_bounds__(256)
+k_cett_between(CettState *__restrict__ sts, int launch, const float *__restrict__ pool, const char *__restrict__ h,
+               const char *__restrict__ wd, const int *__restrict__ list, int cap, const int *__restrict__ count,
+               float *__restrict__ buf0, float *__restrict__ buf1, const float *__restrict__ rowsq_in, float *__restrict__ rowsq,
+               const float *__restrict__ den, float bound, int T, int F, int Fp, int d)
+{
+    constexpr int VEC = 16 / ES, SEG = 4096;
+    __shared__ int s_cnt[64], s_j[SEG];
+    __shared__ float s_h[SEG], s_sq[256];
+    __shared__ CettState s_st;
+    const int tid = threadIdx.x, parts = gridDim.y, part = blockIdx.y;
+    const CettState *in = sts + (launch & 1);
+    if (!in->done && launch > 0) {
+        float acc = 0.0f;
+        for (int t = tid; t < T; t += 256) {
+            float s = 0.0f;
+            for (int i = 0; i < parts; ++i) s += rowsq_in[(size_t)i * T + t];
+            const float dn = den[t];
+            acc += dn > 0.0f ? sqrtf(s) / dn : 0.0f;
+        }
+        s_sq[tid] = acc;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if (tid < w) s_sq[tid] += s_sq[tid + w];
+            __syncthreads();
+        }
+    }
+    if (tid == 0) {
+        CettState s = *in;
+        if (!s.done && launch > 0) {
+            const float mean = s_sq[0] / (float)T;
+            if (mean <= bound) {
+                s.known_lo = s.base = s.mid;
+                s.known_mean = mean;
+                s.sel ^= 1;
+            } else {
+                s.known_hi = s.mid;                          // NaN: over the bound
             }
+            bisect_on(s);
+        }
+        s_st = s;
+        if (blockIdx.x == 0 && part == 0) sts[(launch + 1) & 1] = s;
+    }
+    __syncthreads();
+    if (s_st.done) return;
+    const size_t t = blockIdx.x;
+    const float lo = __uint_as_float(s_st.base), hi = __uint_as_float(s_st.mid);
+    const bool listed = s_st.listed != 0;
+    const float *src = (s_st.sel ? buf1 : buf0) + t * d;
+    float *dst = (s_st.sel ? buf0 : buf1) + t * d;
+    const int col0 = (part * NV * 256 + tid) * VEC;          // group v of this thread: columns col0 + v 256 VEC ..
+    float acc[NV][VEC];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (e0 + q < total) {
-                    const float hv = s_h[e0 + q];
+    for (int v = 0; v < NV; ++v) {
+        const int col = col0 + v * 256 * VEC;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[v][e] = col < d ? src[col + e] : 0.0f;
+    }
+    const int *mine = list + t * cap;
+    auto neuron = [&](int i) -> int { return listed ? mine[i] : i; };
+    list_ascending(listed ? count[t] : F, s_cnt,
+        [&](int i) { const float a = pool[t * F + neuron(i)]; return a >= lo && a < hi; },
+        [&](int at, int i) {
+            const int j = neuron(i);
+            s_j[at] = j;
+            s_h[at] = ES == 4 ? reinterpret_cast<const float *>(h)[t * Fp + j]
+                              : __uint_as_float((unsigned int)reinterpret_cast<const unsigned short *>(h)[t * Fp + j] << 16);
+        },
+        [&](int total) {
+            for (int e0 = 0; e0 < total; e0 += 4) {
+                u32x4 w[4][NV];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const char *row = wd + (size_t)s_j[min(e0 + q, total - 1)] * d * ES;
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
-                        float f[VEC];
-                        unpack_row16(w[q][v], f);
+                        const int col = col0 + v * 256 * VEC;
+                        w[q][v] = *reinterpret_cast<const u32x4 *>(row + (size_t)(col < d ? col : 0) * ES);
+                    }
+                }
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) acc[v][e] = fmaf(hv, f[e], acc[v][e]);
+                for (int q = 0; q < 4; ++q) {
+                    if (e0 + q < total) {
+                        const float hv = s_h[e0 + q];
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            float f[VEC];
+                            unpack_row16(w[q][v], f);
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) acc[v][e] = fmaf(hv, f[e], acc[v][e]);
+                        }
                     }
                 }
             }
-        }
-    }
+        });
     float sq = 0.0f;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int col = (v * 256 + tid) * VEC;
+        const int col = col0 + v * 256 * VEC;
         if (col < d) {
 #pragma unroll
             for (int e = 0; e < VEC; e += 4)
@@ -397,29 +477,9 @@ k_cett_between(const CettState *__restrict__ st, const float *__restrict__ pool,
         }
     }
     sq = wave_sum(sq);
-    if (lane == 0) s_sq[wave] = sq;
+    if ((tid & 63) == 0) s_sq[tid >> 6] = sq;
     __syncthreads();
-    if (tid == 0) rowsq[t] = (s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3]);
-}
-
-// After a probe inside the bracket.
-__global__ void __launch_bounds__(1024)
-k_cett_inside(CettState *st, const float *__restrict__ rowsq, int T, const float *__restrict__ den, float bound)
-{
-    __shared__ float s_sum[1024];
-    if (st->done) return;
-    const float mean = mean_cett(rowsq, 1, T, den, s_sum);
-    if (threadIdx.x != 0) return;
-    CettState s = *st;
-    if (mean <= bound) {
-        s.known_lo = s.base = s.mid;
-        s.known_mean = mean;
-        s.sel ^= 1;
-    } else {
-        s.known_hi = s.mid;
-    }
-    bisect_on(s);
-    *st = s;
+    if (tid == 0) rowsq[(size_t)part * T + t] = (s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3]);
 }
 
 struct CettWs {
@@ -508,13 +568,26 @@ clada_status probe(clada_ctx *ctx, const clada_layer *layer, int T, const CettWs
     return CLADA_OK;
 }
 
-template <int ES>
-void launch_between(const CettWs &w, const clada_layer *layer, int T, int Fp, float *buf1, hipStream_t st)
+// Columns per thread and workgroups per token of the probes inside the bracket: two workgroups where a row has at least two
+// groups of 256 x 16 bytes (a row in one: 28 us a probe of 512 tokens x 4096 that looks through the pool).
+struct BetweenShape { int nv, parts; };
+BetweenShape between_shape(int d, int es)
 {
-    const int d = layer->d, vecs = (d * ES / 16 + 255) / 256;
-    auto kern = vecs <= 1 ? k_cett_between<ES, 1> : vecs == 2 ? k_cett_between<ES, 2> : k_cett_between<ES, 4>;
-    hipLaunchKernelGGL(kern, dim3(T), dim3(256), 0, st, w.state, w.pool, w.h, (const char *)layer->w_down,
-                       reinterpret_cast<float *>(w.ytmp), buf1, w.rowsq_num, layer->d_ff, Fp, d);
+    const int vecs = (d * es / 16 + 255) / 256;              // 1 .. 4
+    return vecs == 1 ? BetweenShape{1, 1} : vecs == 2 ? BetweenShape{1, 2} : BetweenShape{2, 2};
+}
+
+template <int ES>
+void launch_between(const CettWs &w, const clada_layer *layer, int T, int Fp, int launch, const int *list, int cap, const int *count,
+                    float bound, hipStream_t st)
+{
+    const int d = layer->d;
+    const BetweenShape sh = between_shape(d, ES);
+    auto kern = sh.nv == 1 ? k_cett_between<ES, 1> : k_cett_between<ES, 2>;
+    float *sq[2] = {w.rowsq_num, w.rowsq_den};
+    hipLaunchKernelGGL(kern, dim3(T, sh.parts), dim3(256), 0, st, w.state, launch, w.pool, w.h, (const char *)layer->w_down,
+                       list, cap, count, reinterpret_cast<float *>(w.ytmp), reinterpret_cast<float *>(w.hcut),
+                       sq[launch & 1], sq[(launch + 1) & 1], w.den, bound, T, layer->d_ff, Fp, d);
 }
 
 // The large search after begin(): ytmp and hcut (free once the dense probes are over) hold the cut sums.
@@ -546,11 +619,14 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
     CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, w.splitk, ctx->opt_prefix_tile, stream, reinterpret_cast<float *>(w.ytmp)));
     hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 1);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
-    for (int it = 0; it < 31; ++it) {
-        if (layer->dtype == CLADA_BF16) launch_between<2>(w, layer, T, Fp, reinterpret_cast<float *>(w.hcut), stream);
-        else launch_between<4>(w, layer, T, Fp, reinterpret_cast<float *>(w.hcut), stream);
-        CLADA_CHECK_HIP(ctx, hipGetLastError());
-        hipLaunchKernelGGL(k_cett_inside, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, T, w.den, bound);
+    // behind the second buffer of cut sums there is room for Fp - d neurons per token; the counts go behind the sample
+    int *list = reinterpret_cast<int *>(w.hcut) + (size_t)T * d, *count = reinterpret_cast<int *>(sample + SAMPLES);
+    const int cap = Fp - d;
+    hipLaunchKernelGGL(k_cett_list, dim3(T), dim3(256), 0, stream, w.state, w.pool, F, list, cap, count);
+    CLADA_CHECK_HIP(ctx, hipGetLastError());
+    for (int it = 0; it <= 31; ++it) {                       // (the last one only takes in the 31st probe)
+        if (layer->dtype == CLADA_BF16) launch_between<2>(w, layer, T, Fp, it, list, cap, count, bound, stream);
+        else launch_between<4>(w, layer, T, Fp, it, list, cap, count, bound, stream);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
     }
     return CLADA_OK;
@@ -600,7 +676,8 @@ extern "C" clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_
     // The large search pays where a dense probe is many times a pass over the pool, and its bracket is only trusted where
     // single neurons do not move the mean; fewer probes than the full 31 end somewhere on the way, which only the plain
     // bisection passes through.
-    const bool large = n_probes == 31 && bound > 0.0f && (size_t)T * layer->d_ff >= (1u << 20) && T >= 64 && layer->d_ff >= layer->d;
+    const bool large = n_probes == 31 && bound > 0.0f && (size_t)T * layer->d_ff >= (1u << 20) && T >= 64 && layer->d_ff >= layer->d &&
+                       layer->d_ff >= 512;
     if (large) {
         st = search_large(ctx, layer, T, w, bound, stream);
         if (st != CLADA_OK) return st;
