@@ -127,11 +127,18 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# The raw handle of torch's current stream on a device (0.2 us; torch.cuda.current_stream builds a Stream object, 2.1 us of
+# the 13 us that a single-token call of a small layer spends on the host).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(t: torch.Tensor):
-    return C.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
 
 
 class Context:
@@ -180,16 +187,17 @@ class Layer:
     b_out: torch.Tensor | None = None
 
     def c_struct(self) -> _CLayer:
-        F, d = self.w_gate.shape
-        ws = (self.w_gate, self.w_down) if self.kind == RELU else (self.w_gate, self.w_up, self.w_down)
-        for w in ws:
-            assert w.is_cuda and w.is_contiguous() and tuple(w.shape) == (F, d) and w.dtype == self.w_gate.dtype
-        for b, n in ((self.b_in, F), (self.b_out, d)):
-            assert b is None or (b.is_cuda and b.is_contiguous() and b.dtype == torch.float32 and b.numel() == n)
-        return _CLayer(self.w_gate.data_ptr(), None if self.w_up is None else self.w_up.data_ptr(),
-                       self.w_down.data_ptr(), d, F, _dtype_code(self.w_gate), self.kind,
-                       None if self.b_in is None else self.b_in.data_ptr(),
-                       None if self.b_out is None else self.b_out.data_ptr())
+        wg, wu, wd = self.w_gate, self.w_up, self.w_down
+        shape, dtype = wg.shape, wg.dtype
+        F, d = shape
+        assert wg.is_cuda and wg.is_contiguous()
+        assert wd.is_cuda and wd.is_contiguous() and wd.shape == shape and wd.dtype == dtype
+        if self.kind != RELU:
+            assert wu.is_cuda and wu.is_contiguous() and wu.shape == shape and wu.dtype == dtype
+        b_in, b_out = self.b_in, self.b_out
+        assert b_in is None or (b_in.is_cuda and b_in.is_contiguous() and b_in.dtype == torch.float32 and b_in.numel() == F)
+        assert b_out is None or (b_out.is_cuda and b_out.is_contiguous() and b_out.dtype == torch.float32 and b_out.numel() == d)
+        return _CLayer(wg.data_ptr(), _ptr(wu), wd.data_ptr(), d, F, _dtype_code(wg), self.kind, _ptr(b_in), _ptr(b_out))
 
 
 @dataclass
