@@ -110,7 +110,8 @@ size_t clada_ws_cett(int32_t d, int32_t d_ff, int32_t T);
 int clada_prefix_token_tiles(int T);
 int clada_prefix_col_tiles(int d);
 hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, float *part, float *pool,
-                               char *hbuf, int tile_mode, hipStream_t stream);
+                               char *hbuf, int tile_mode, hipStream_t stream, float *wnorm2 = nullptr, int num_cu = 0,
+                               bool *has_norm2 = nullptr);      // wnorm2: filled where compute units are left over (*has_norm2)
 hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq,
                              float *splitk_ws, int tile_mode, hipStream_t stream, float *y32 = nullptr, const int *skip = nullptr);
 int clada_prefix_down_splits(int d, int F, int T);
