@@ -528,7 +528,7 @@ clada_status begin(clada_ctx *ctx, const clada_layer *layer, const void *x, int 
                    float eps, hipStream_t stream)
 {
     const int n_tn = clada_prefix_col_tiles(layer->d);
-    CLADA_CHECK_HIP(ctx, clada_prefix_gateup(layer, x, T, w.part, w.pool, w.h, ctx->opt_prefix_tile, stream));
+    CLADA_CHECK_HIP(ctx, clada_prefix_gateup(layer, x, T, w.part, w.pool, w.h, ctx->opt_prefix_tile, stream, nullptr, ctx->num_cu));
     const float *rowsq_den = w.rowsq_den;
     if (layer->kind == CLADA_FFN_RELU) {
         // || sum_j a_j W_out[j,:] + b_out ||: through the stored output, which carries the bias

@@ -114,7 +114,7 @@ struct GateUpParams {
     const float *b_in;  // non-gated family: input bias [F] or nullptr
     int relu;           // non-gated family: a = max(0, C_g + b_in), h = a (wu then aliases wg and C_u is ignored)
     int gelu;           // gated family: sigma = tanh-form GELU instead of SiLU
-    // Workgroups behind the GEMM's (the 256-token kernel): they form || W_down[j,:] ||^2 on the compute units that the tiles
+    // Workgroups behind the GEMM's (bf16 kernels): they form || W_down[j,:] ||^2 on the compute units that the tiles
     // leave idle; k_prefix_reduce, which would read W_down for it, then finds it in wnorm2.
     const char *wd;
     float *wnorm2;                 // [F] or nullptr
@@ -123,8 +123,9 @@ struct GateUpParams {
 
 // Epilogue of the gate/up GEMM on the accumulators (shared by the fp32 and bf16 kernels):
 // a = SiLU(C_g), h = a*C_u, per-neuron partial sums over the tile's tokens, |a| pool, h store.
-template <int ES>
-__device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[2][2][2], const GateUpParams &p, int tm, int tn,
+// NB = 1: the non-gated family's kernel without a second operand.
+template <int ES, int NB = 2>
+__device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[NB][2][2], const GateUpParams &p, int tm, int tn,
                                                 int wm, int wn, int lane, int tid, float (&s_stat)[2][4][BN])
 {
     // ------------------------------------------------------------------ epilogue
@@ -140,13 +141,13 @@ __device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[2][2][2], co
             for (int r = 0; r < 16; ++r) {
                 const int t = tm * BM + wm * 64 + mb * 32 + acc_row(r, lane);
                 float a, h;
-                if (p.relu) {
+                if (NB == 1 || p.relu) {
                     const float g = acc[0][mb][nb][r] + ((p.b_in && j < p.F) ? p.b_in[j] : 0.0f);
                     a = g > 0.0f ? g : (g != g ? g : 0.0f);
                     h = a;
                 } else {
                     a = p.gelu ? gelu_prefill(acc[0][mb][nb][r]) : silu_prefill(acc[0][mb][nb][r]);
-                    h = a * acc[1][mb][nb][r];
+                    h = a * acc[NB - 1][mb][nb][r];
                 }
                 if (t < p.T && j < p.F) {
                     const float aa = fabsf(a);
@@ -267,13 +268,53 @@ __device__ __forceinline__ void lds_dma16(const char *gsrc, char *ldst)
                                      (void __attribute__((address_space(3))) *)ldst, 16, 0, 0);
 }
 
+// Sum of squares of a row of W_down, by one wave: 16-byte chunks, lane l takes chunks l, l + 64, .. (eight loads in flight).
+template <int ES>
+__device__ __forceinline__ float row_norm2(const char *row, int d, int lane)
+{
+    constexpr int VEC = 16 / ES;
+    const int nchunk = d * ES / 16;
+    float wn2 = 0.0f;
+    for (int c0 = lane; c0 < nchunk; c0 += 8 * 64) {
+        u32x4 v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            v[i] = c0 + 64 * i < nchunk ? *reinterpret_cast<const u32x4 *>(row + (size_t)(c0 + 64 * i) * 16)
+                                        : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            float w[VEC];
+            unpack_row16(v[i], w);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) wn2 = fmaf(w[e], w[e], wn2);
+        }
+    }
+    return wave_sum(wn2);
+}
+
+// What a workgroup behind the GEMM's does: the norms of every norm_blocks-th group of four rows.
+__device__ __forceinline__ void spare_norms(const GateUpParams &p)
+{
+    const int lane = threadIdx.x & 63;
+    for (int j = 4 * ((int)blockIdx.x - p.gemm_blocks) + (threadIdx.x >> 6); j < p.F; j += 4 * p.norm_blocks) {
+        const float v = row_norm2<2>(p.wd + (size_t)j * p.d * 2, p.d, lane);
+        if (lane == 0) p.wnorm2[j] = v;
+    }
+}
+
+// NB = 2: gate and up operand; NB = 1 (non-gated family): one operand, nothing is computed twice.
+template <int NB>
 __global__ void __launch_bounds__(256)
 k_prefix_gateup_bf16(const GateUpParams p)
 {
-    __shared__ __align__(16) char s_st0[3 * GU_TILE];
-    __shared__ __align__(16) char s_st1[3 * GU_TILE];
-    __shared__ __align__(16) char s_st2[3 * GU_TILE];
+    __shared__ __align__(16) char s_st0[(1 + NB) * GU_TILE];
+    __shared__ __align__(16) char s_st1[(1 + NB) * GU_TILE];
+    __shared__ __align__(16) char s_st2[(1 + NB) * GU_TILE];
     __shared__ float s_stat[2][4][BN];
+    if ((int)blockIdx.x >= p.gemm_blocks) {
+        spare_norms(p);
+        return;
+    }
 
     // Tile order inside an XCD's run: with at least 8 token tiles, blocks of 8 token tiles x 4
     // neuron tiles, so the 32 workgroups that share an L2 at any time re-use each X slice four
@@ -298,9 +339,9 @@ k_prefix_gateup_bf16(const GateUpParams p)
     const int wm = wave & 1, wn = wave >> 1;
     const size_t rowbytes = (size_t)p.d * 2;
 
-    f32x16 acc[2][2][2];
+    f32x16 acc[NB][2][2];
 #pragma unroll
-    for (int w = 0; w < 2; ++w)
+    for (int w = 0; w < NB; ++w)
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -331,7 +372,7 @@ k_prefix_gateup_bf16(const GateUpParams p)
             char *dst = st + (wave + 4 * c4) * 1024;
             lds_dma16(gx[c4] + (size_t)kt * 128, dst);
             lds_dma16(gg[c4] + (size_t)kt * 128, dst + GU_TILE);
-            lds_dma16(gu[c4] + (size_t)kt * 128, dst + 2 * GU_TILE);
+            if constexpr (NB == 2) lds_dma16(gu[c4] + (size_t)kt * 128, dst + 2 * GU_TILE);
         }
     };
     // Fragment reads are issued as inline assembly: for an LDS read the compiler cannot prove
@@ -341,10 +382,32 @@ k_prefix_gateup_bf16(const GateUpParams p)
     const unsigned int a_off = (unsigned int)((wm * 64 + r32) * 128);
     const unsigned int b_off = (unsigned int)(GU_TILE + (wn * 64 + r32) * 128);
     // The reads of k-step ks+1 are in flight while the MFMAs of k-step ks run: LDS returns data in
-    // order, so waiting for lgkmcnt <= 6 means the older set of six has landed.
+    // order, so waiting for lgkmcnt <= 6 (4 with one operand) means the older set has landed.
     auto compute = [&](const char *st) {
         const unsigned int base = (unsigned int)(size_t)(const __attribute__((address_space(3))) char *)st;
-        u32x4 fr[2][6];
+        u32x4 fr[2][2 + 2 * NB];
+#define GU_READ4(S, KS)                                                                                   \
+        {                                                                                                 \
+            const unsigned int pos = (unsigned int)(((2 * (KS) + q) ^ sw) * 16);                          \
+            const unsigned int pa = base + a_off + pos, pb = base + b_off + pos;                          \
+            asm volatile("ds_read_b128 %0, %4\n\t"                                                        \
+                         "ds_read_b128 %1, %4 offset:4096\n\t"                                            \
+                         "ds_read_b128 %2, %5\n\t"                                                        \
+                         "ds_read_b128 %3, %5 offset:4096"                                                \
+                         : "=&v"(fr[S][0]), "=&v"(fr[S][1]), "=&v"(fr[S][2]), "=&v"(fr[S][3])             \
+                         : "v"(pa), "v"(pb));                                                             \
+        }
+#define GU_WAIT4(S, CNT)                                                                                  \
+        asm volatile("s_waitcnt lgkmcnt(" #CNT ")"                                                        \
+                     : "+v"(fr[S][0]), "+v"(fr[S][1]), "+v"(fr[S][2]), "+v"(fr[S][3]));
+#define GU_MMA4(S)                                                                                        \
+        {                                                                                                 \
+            const bf16x8 fa[2] = {__builtin_bit_cast(bf16x8, fr[S][0]), __builtin_bit_cast(bf16x8, fr[S][1])}; \
+            const bf16x8 fb[2] = {__builtin_bit_cast(bf16x8, fr[S][2]), __builtin_bit_cast(bf16x8, fr[S][3])}; \
+            _Pragma("unroll") for (int nb = 0; nb < 2; ++nb)                                              \
+            _Pragma("unroll") for (int mb = 0; mb < 2; ++mb)                                              \
+                acc[0][mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[mb], fb[nb], acc[0][mb][nb], 0, 0, 0); \
+        }
 #define GU_READ6(S, KS)                                                                                   \
         {                                                                                                 \
             const unsigned int pos = (unsigned int)(((2 * (KS) + q) ^ sw) * 16);                          \
@@ -373,6 +436,20 @@ k_prefix_gateup_bf16(const GateUpParams p)
             _Pragma("unroll") for (int mb = 0; mb < 2; ++mb)                                              \
                 acc[w][mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[mb], fb[w][nb], acc[w][mb][nb], 0, 0, 0); \
         }
+        if constexpr (NB == 1) {
+            GU_READ4(0, 0)
+            GU_READ4(1, 1)
+            GU_WAIT4(0, 4)
+            GU_MMA4(0)
+            GU_READ4(0, 2)
+            GU_WAIT4(1, 4)
+            GU_MMA4(1)
+            GU_READ4(1, 3)
+            GU_WAIT4(0, 4)
+            GU_MMA4(0)
+            GU_WAIT4(1, 0)
+            GU_MMA4(1)
+        } else {
         GU_READ6(0, 0)
         GU_READ6(1, 1)
         GU_WAIT(0, 6)
@@ -385,14 +462,18 @@ k_prefix_gateup_bf16(const GateUpParams p)
         GU_MMA(0)
         GU_WAIT(1, 0)
         GU_MMA(1)
+        }
+#undef GU_READ4
+#undef GU_WAIT4
+#undef GU_MMA4
 #undef GU_READ6
 #undef GU_WAIT
 #undef GU_MMA
     };
-    // wait until this wave's transfers of tile k have landed (the 12 of tile k+1 may stay in
+    // wait until this wave's transfers of tile k have landed (the 12, or 8, of tile k+1 may stay in
     // flight), meet the other waves, refill the stage consumed one step ago, multiply
     auto step = [&](int k, const char *cur, char *nxt) {
-        if (k + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0F7C);     // vmcnt(12)
+        if (k + 1 < nk) __builtin_amdgcn_s_waitcnt(NB == 2 ? 0x0F7C : 0x0F78);     // vmcnt(12) / vmcnt(8)
         else            __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
         __builtin_amdgcn_s_barrier();
         if (k + 2 < nk) issue(nxt, k + 2);
@@ -405,7 +486,7 @@ k_prefix_gateup_bf16(const GateUpParams p)
         if (kt + 1 < nk) step(kt + 1, s_st1, s_st0);
         if (kt + 2 < nk) step(kt + 2, s_st2, s_st1);
     }
-    gateup_epilogue<2>(acc, p, tm, tn, wm, wn, lane, tid, s_stat);
+    gateup_epilogue<2, NB>(acc, p, tm, tn, wm, wn, lane, tid, s_stat);
 }
 
 // Epilogue of the 256-token kernel for one wave: 128 tokens (rows tm128*128 ..) x 64 neurons, gate
@@ -497,30 +578,6 @@ __device__ __forceinline__ void wide_epilogue(const f32x16 (&acc)[2][4][2], cons
 constexpr int GW_STAGE = 32 * 1024;    // X 256 x 64 B | gate 128 x 64 B | up 128 x 64 B
 constexpr int GW_G = 16 * 1024, GW_U = 24 * 1024;
 
-// Sum of squares of a row of W_down, by one wave: 16-byte chunks, lane l takes chunks l, l + 64, .. (eight loads in flight).
-template <int ES>
-__device__ __forceinline__ float row_norm2(const char *row, int d, int lane)
-{
-    constexpr int VEC = 16 / ES;
-    const int nchunk = d * ES / 16;
-    float wn2 = 0.0f;
-    for (int c0 = lane; c0 < nchunk; c0 += 8 * 64) {
-        u32x4 v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            v[i] = c0 + 64 * i < nchunk ? *reinterpret_cast<const u32x4 *>(row + (size_t)(c0 + 64 * i) * 16)
-                                        : u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float w[VEC];
-            unpack_row16(v[i], w);
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) wn2 = fmaf(w[e], w[e], wn2);
-        }
-    }
-    return wave_sum(wn2);
-}
-
 // SINGLE: the non-gated family has one input matrix, so the second operand is the next 128 rows of the same
 // matrix and the workgroup tile is 256 tokens x 256 neurons of one GEMM (nothing is computed twice).
 template <bool SINGLE>
@@ -529,11 +586,7 @@ k_prefix_gateup_bf16_wide(const GateUpParams p)
 {
     __shared__ __align__(16) char s_w[4 * GW_STAGE];
     if ((int)blockIdx.x >= p.gemm_blocks) {
-        const int l = threadIdx.x & 63, n_waves = 4 * p.norm_blocks;
-        for (int j = 4 * ((int)blockIdx.x - p.gemm_blocks) + (threadIdx.x >> 6); j < p.F; j += n_waves) {
-            const float v = row_norm2<2>(p.wd + (size_t)j * p.d * 2, p.d, l);
-            if (l == 0) p.wnorm2[j] = v;
-        }
+        spare_norms(p);
         return;
     }
 
@@ -1377,7 +1430,11 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
     // tile_mode: 0 = choose, 1 = 128-token tiles, 2 = 256-token tiles (bf16, d % 64 == 0 only)
     const int n_tmw = (T + 255) / 256;
     const bool wide_ok = es == 2 && d % 64 == 0;
-    const bool wide = wide_ok && (tile_mode == 2 || (tile_mode == 0 && T > 128));     // measured faster from T = 512 down
+    // The 128-token tiles as long as they all run at once, one per compute unit; the 256-token ones beyond, whose single
+    // round is shorter than two of the others (us with statistics, 128- / 256-token tiles: gated, d = 4096: 94 / 108 at 172
+    // tiles, 91 / 106 at 256, 157 / 119 at 258, 167 / 120 at 344, 258 / 248 at 688; non-gated, d = 2560: 50 / 85 at 240,
+    // 79 / 75 at 320, 119 / 79 at 640).
+    const bool wide = wide_ok && (tile_mode == 2 || (tile_mode == 0 && T > 128 && total > (num_cu > 0 ? num_cu : 256)));
     // One workgroup fills a compute unit: with 32 or more units left over (prefixes of some hundred tokens) they take the
     // norms of W_down along, instead of a second pass over it (7B layer, 512 tokens: k_prefix_reduce 16.5 -> 4.5 us).
     if (has_norm2) *has_norm2 = false;
@@ -1397,7 +1454,8 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
         hipLaunchKernelGGL(k_prefix_gateup_bf16_wide<false>, dim3(with_norms((blocks + 7) / 8 * 8)), dim3(256), 0, stream, g);
     }
     else if (es == 4) hipLaunchKernelGGL(k_prefix_gateup<4>, dim3(grid), dim3(256), 0, stream, g);
-    else if (d % 64 == 0) hipLaunchKernelGGL(k_prefix_gateup_bf16, dim3((total_blk + 7) / 8 * 8), dim3(256), 0, stream, g);
+    else if (d % 64 == 0 && relu) hipLaunchKernelGGL(k_prefix_gateup_bf16<1>, dim3(with_norms((total_blk + 7) / 8 * 8)), dim3(256), 0, stream, g);
+    else if (d % 64 == 0) hipLaunchKernelGGL(k_prefix_gateup_bf16<2>, dim3(with_norms((total_blk + 7) / 8 * 8)), dim3(256), 0, stream, g);
     else         hipLaunchKernelGGL(k_prefix_gateup<2>, dim3(grid), dim3(256), 0, stream, g);
     return hipGetLastError();
 }

@@ -176,3 +176,34 @@ def test_calibrate_is_the_nearest_rank_quantile_bit_for_bit(clada, n, kind):
             assert out[0] == want
             clada.threshold_calibrate(ctx, v, 0.7)
             side.synchronize()
+
+
+@pytest.mark.parametrize("d,F,T,relu,tile", [
+    (64, 129, 129, True, 0),     # 128-token tiles of the non-gated family: one operand, a ragged second tile
+    (128, 4000, 300, True, 1), (320, 700, 1030, True, 1),      # 8 and 9 token tiles: both tile orders
+    (64, 128 * 86, 384, False, 0), (64, 128 * 85, 384, False, 0),      # 258 and 255 tiles: either side of one round
+    (128, 300, 70, False, 0),    # spare workgroups many times the tiles
+])
+def test_prefill_tiles_of_short_prefixes_and_norms_on_spare_units(clada, d, F, T, relu, tile):
+    """Every output against a float64 reference; A_j through the norms that idle compute units formed."""
+    from paper_2502_19078_amd import binding
+    g = torch.Generator(device=DEV).manual_seed(d + F + T)
+    n = lambda *s, k: (torch.randn(s, generator=g, device=DEV) * k)
+    w = [n(F, d, k=d ** -0.5).bfloat16() for _ in range(2 if relu else 3)]
+    x = n(T, d, k=1.0).bfloat16()
+    b_in, b_out = n(F, k=0.1), n(d, k=0.1)
+    layer = clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=b_in, b_out=b_out) if relu else clada.Layer(*w)
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    ctx.set_option("prefix.tile", tile)
+    got = clada.prefix_stats(ctx, layer, x)
+    xd, w = x.double().cpu(), [a.double().cpu() for a in w]
+    pre = xd @ w[0].t()
+    a = torch.relu(pre + b_in.double().cpu()) if relu else pre * torch.sigmoid(pre)
+    h = a if relu else a * (xd @ w[1].t())
+    sq = (h * h).sum(0)
+    want = {"sum_abs_act": a.abs().sum(0), "sum_sq_act": (a * a).sum(0), "max_abs_act": a.abs().amax(0), "sum_sq_h": sq,
+            "A": sq.sqrt() * w[-1].norm(dim=1), "abs_act_pool": a.abs()}
+    for k, v in want.items():                                # fp32 accumulation over d and T terms, a hardware exp2 of a few ulp
+        assert _rel(to_np(getattr(got, k)), v.numpy()) < 2e-5, k
+    y = h @ w[-1] + (b_out.double().cpu() if relu else 0.0)
+    assert _rel(to_np(got.y), y.numpy()) < 5e-3              # h and y each rounded once to bf16: 2^-9 of a value
