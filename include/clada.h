@@ -251,9 +251,9 @@ clada_status clada_cognitive_signals_static(clada_ctx *ctx, const void *logits, 
  * The result is bit-reproducible from run to run (fixed summation order).
  * Paths: B = 1 with rows of whole KiB runs the row-streaming kernel (vector ALUs); bf16
  * batches of 2 and more run on the matrix cores, 16 tokens per pass, every weight row read
- * once per pass.  Everything else -- fp32 batches in particular -- runs a generic kernel
- * that works through the tokens one by one and reads the kept rows once PER TOKEN: correct
- * and tested, but its HBM traffic grows with B (a limit of this library, not of the method). */
+ * once per pass.  Other batches (fp32, other widths) of layers from 8 MB on, and fp32 rows above
+ * 8 KiB at B = 1, run a vector kernel that reads every row once per pass of up to eight tokens;
+ * the rest runs a generic kernel that works through the tokens one by one. */
 clada_status clada_sparse_ffn_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
                                      int32_t B, const float *tau_final, void *y,
                                      int32_t *active_idx, int32_t *n_active,
@@ -296,8 +296,10 @@ clada_status clada_dense_ffn_decode(clada_ctx *ctx, const clada_layer *layer, co
  * (modes 0 - 2: the context's "decode.b1"; mode 3: as with "decode.b1" = 2): the same
  * kernels' order of summation.  For B = 1, modes 2 and 3 need the batch-1 kernel's shapes
  * (rows of whole KiB), 256 compute units or more and n_active = NULL.  For B >= 2 there is
- * mode 3 only: the units (layer, pass of up to 16 tokens) of the matrix-core path go round
- * three lanes, where that path applies (bf16, its widths) and n_active = NULL.  Every mode
+ * mode 3 only, where the matrix-core path applies (bf16, its widths) and n_active = NULL: its
+ * kernels run over all units (layer, pass of up to 16 tokens) in one launch each, as many
+ * layers at a time as the workspace holds, or (large rows of 10 KiB) the units go round three
+ * lanes.  Every mode
  * falls back to mode 0 where it does not apply.  The remarks on clada_device_fault apply to modes 0 - 2
  * (balanced kernels wait, bounded, for their own workgroups).  A context serves one call
  * at a time, on whatever stream.  The first call in mode 3 creates the context's lane streams

@@ -77,6 +77,8 @@ clada_status clada_decode_batched(clada_ctx *ctx, const clada_layer *layer, cons
                                   const float *tau, void *y, unsigned char *keep, float *partial,
                                   char *scratch, bool dense, hipStream_t stream, bool *ran,
                                   const int32_t *list = nullptr, const int32_t *list_n = nullptr);
+clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int32_t L, const void *x, int32_t B,
+                                 const float *tau, void *y, bool dense, char *scratch, size_t bytes, hipStream_t stream, bool *ran);
 size_t clada_ws_decode_batched(int32_t d_ff);
 size_t clada_ws_decode_batched_partial(int32_t d);
 bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *layer, int32_t B);

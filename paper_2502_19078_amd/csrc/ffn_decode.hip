@@ -1819,10 +1819,17 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
         CLADA_CHECK_HIP(ctx, lanes_join(ctx, n_lanes, stream));
         return CLADA_OK;
     }
-    // ---- batches on the matrix-core path: the units (layer, pass of up to 16 tokens) go round three lanes, each
-    // with its own partial outputs and scratch.  The path's three launches per unit and its thin ends weigh
-    // more than at batch 1 (c3 layer shape, B = 8: 69.5 -> 60.2 -> 58.5 us per layer with one, two, three lanes).
+    // ---- batches on the matrix-core path: one launch per kernel over all units (layer, pass of up to 16 tokens), or,
+    // where clada_stack_batched leaves them, the units go round three lanes, each with its own partial outputs and
+    // scratch.  The path's three launches per unit and its thin ends weigh more than at batch 1 (c3 layer shape, B = 8: 69.5 -> 60.2 -> 58.5 us per layer with one, two, three lanes).
     const int n_groups = (B + 15) / 16, per_group = (B + n_groups - 1) / n_groups;
+    if (B >= 2 && smode == 3 && !n_active && ctx->opt_decode_batched) {
+        bool ran = false;
+        const clada_status st = clada_stack_batched(ctx, layers, L, x, B, tau, y, dense, ctx->ws + CLADA_WS_HEADER,
+                                                    ctx->ws_bytes - CLADA_WS_HEADER, stream, &ran);
+        if (st != CLADA_OK) return st;
+        if (ran) return CLADA_OK;
+    }
     if (B >= 2 && smode == 3 && !n_active && ctx->opt_decode_batched && L * n_groups >= 3 &&
         clada_decode_batched_eligible(ctx, &layers[0], per_group) &&
         clada_decode_batched_eligible(ctx, &layers[0], B - (n_groups - 1) * per_group)) {

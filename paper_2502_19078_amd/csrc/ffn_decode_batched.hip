@@ -51,7 +51,35 @@ struct BatParams {
     const float *b_in;          // non-gated family: input bias [F] or nullptr
     const int *list, *list_n;   // prefix-static run (with DENSE): the neurons are the list_n[0] entries of list
                                 // (device), every one kept by every token; nullptr: all F neurons
+    int row0, rows;             // this unit's first row of the launch's tokens, and their number (stride of the partials)
 };
+
+// One launch runs n units (blockIdx.y): unit u = layer u / n_pass, pass u % n_pass of its tokens.  A call of one layer is a
+// launch of one unit; the whole-stack call runs as many layers per launch as the workspace has room for.
+constexpr int BAT_LAYERS = 48;
+struct BatArgs {
+    BatParams p;                // of unit 0; B: the tokens of a layer
+    int n_pass, per_pass;
+    const char *wg[BAT_LAYERS], *wu[BAT_LAYERS], *wd[BAT_LAYERS];
+    const float *b_in[BAT_LAYERS];
+};
+// (read through the kernel-argument segment: scalar loads at the unit's index)
+__device__ __forceinline__ BatParams bat_unit(const __attribute__((address_space(4))) BatArgs *a, int unit)
+{
+    BatParams p;
+    __builtin_memcpy(&p, &a->p, sizeof(p));
+    const int n_pass = a->n_pass, layer = unit / n_pass, t0 = (unit - layer * n_pass) * a->per_pass;
+    p.row0 = layer * p.B + t0;
+    p.wg = a->wg[layer]; p.wu = a->wu[layer]; p.wd = a->wd[layer];
+    p.b_in = a->b_in[layer];
+    p.x += (size_t)p.row0 * p.d * 2;
+    if (p.tau) p.tau += p.row0;
+    p.hbuf += (size_t)unit * p.F * 16;
+    p.ulist += (size_t)unit * p.F;
+    p.ucnt += (size_t)unit * COOP_MAX_WGS;
+    p.B = min(a->per_pass, p.B - t0);
+    return p;
+}
 
 __device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, const f32x4 c)
 {
@@ -74,8 +102,9 @@ constexpr int MAX_TILES = 4;    // 16-neuron tiles per workgroup in kernel A (on
 // 10 and 16 KiB rows ~25 registers and pushed them into scratch (52 -> 68 us at the 13B shape).
 template <int KSTEPS, int NW, bool DENSE, bool LIST = false, bool RELU = false>
 __global__ void __launch_bounds__(NW * 64)
-k_bat_gateup(const BatParams p)
+k_bat_gateup(const BatArgs)
 {
+    const BatParams p = bat_unit((const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.y);
     static_assert(!LIST || DENSE, "a list run keeps every listed neuron");
     static_assert(NW >= 4 && NW <= 8, "the tile reductions run on waves 0..3");
     __shared__ float s_part[2][NW][256];
@@ -323,8 +352,9 @@ constexpr int DN_MAX_ROWS = 2048;               // union neurons per row group
 constexpr int DN_MAX_WGS = 64;                  // gate/up workgroups per row group
 
 __global__ void __launch_bounds__(512, 4)
-k_bat_down(const BatParams p)
+k_bat_down(const BatArgs)
 {
+    const BatParams p = bat_unit((const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.y);
     extern __shared__ __align__(16) unsigned char smem_dn[];
     unsigned char *s_tile = smem_dn;                                    // [8][DN_TILE_BYTES], later the fold buffers
     int *s_rows = reinterpret_cast<int *>(smem_dn + 8 * DN_TILE_BYTES); // [DN_MAX_ROWS]
@@ -487,8 +517,56 @@ k_bat_down(const BatParams p)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = 4 * q + r, col = col0 + sub * DN_SUB + t * 16 + n;
-                if (m < B && col < d) p.partial[((size_t)rg * B + m) * d + col] = acc[t][r];
+                if (m < B && col < d) p.partial[((size_t)rg * p.rows + p.row0 + m) * d + col] = acc[t][r];
             }
+    }
+}
+
+// The final reduction of several layers of the non-gated family, whose output biases differ: y rows [n][B][d] from partials
+// [RG][n B][d], in k_ffn_finalize's order (slice q adds the partials q, q + 32, .., then the 32 slices by the fixed tree).
+struct BatBiasArgs {
+    const float *partial;
+    char *y;
+    const float *b_out[BAT_LAYERS];
+    int RG, B, d;
+};
+__global__ void __launch_bounds__(256)
+k_bat_finalize_bias(const BatBiasArgs a)
+{
+    constexpr int CG = 8, SL = 32;
+    __shared__ float4 s_sum[SL][CG];
+    const int cg = threadIdx.x % CG, sl = threadIdx.x / CG;
+    const int col = blockIdx.x * (4 * CG) + cg * 4, row = blockIdx.y;
+    const size_t pstride = (size_t)gridDim.y * a.d;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (col < a.d) {
+        const float *base = a.partial + (size_t)row * a.d + col;
+        for (int q = sl; q < a.RG; q += SL) {
+            const float4 v = *reinterpret_cast<const float4 *>(base + (size_t)q * pstride);
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
+    }
+    s_sum[sl][cg] = s;
+    __syncthreads();
+#pragma unroll
+    for (int h = SL / 2; h >= 1; h >>= 1) {
+        if (sl < h) {
+            const float4 v = s_sum[sl + h][cg];
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+            s_sum[sl][cg] = s;
+        }
+        __syncthreads();
+    }
+    if (sl == 0 && col < a.d) {
+        const float *bias = a.b_out[row / a.B];
+        if (bias) {
+            const float4 bv = *reinterpret_cast<const float4 *>(bias + col);
+            s.x += bv.x; s.y += bv.y; s.z += bv.z; s.w += bv.w;
+        }
+        uint2 o;
+        o.x = f32_to_bf16_bits(s.x) | (f32_to_bf16_bits(s.y) << 16);
+        o.y = f32_to_bf16_bits(s.z) | (f32_to_bf16_bits(s.w) << 16);
+        *reinterpret_cast<uint2 *>(a.y + ((size_t)row * a.d + col) * 2) = o;
     }
 }
 
@@ -543,36 +621,17 @@ size_t clada_ws_decode_batched_partial(int32_t d)
     return align_up(sizeof(float) * 64 * 16 * (size_t)d, 256);
 }
 
-// Runs the batched MFMA path when the shape is eligible (*ran; an ineligible shape launches nothing and the
-// caller uses the generic kernels).
-clada_status clada_decode_batched(clada_ctx *ctx, const clada_layer *layer, const void *x, int32_t B,
-                                  const float *tau, void *y, unsigned char *keep, float *partial,
-                                  char *scratch, bool dense, hipStream_t stream, bool *ran,
-                                  const int32_t *list, const int32_t *list_n)
+// Launches the two kernels for the units of n layers (nl * n_pass of them).
+static clada_status bat_launch(clada_ctx *ctx, BatArgs &a, int n_layers, bool relu, bool dense, hipStream_t stream)
 {
-    *ran = false;
-    const int d = layer->d, F = layer->d_ff;
-    int P, CG, RG;
-    if (!bat_plan(ctx, layer, B, &P, &CG, &RG)) return CLADA_OK;
-
-    BatParams p;
-    p.wg = (const char *)layer->w_gate; p.wu = (const char *)layer->w_up; p.wd = (const char *)layer->w_down;
-    p.x = (const char *)x; p.tau = tau;
-    p.hbuf = reinterpret_cast<float *>(scratch);
-    p.ulist = reinterpret_cast<int *>(scratch + align_up(sizeof(float) * 16 * (size_t)F, 256));
-    p.ucnt = reinterpret_cast<int *>(scratch + align_up(sizeof(float) * 16 * (size_t)F, 256) + align_up(sizeof(int) * (size_t)F, 256));
-    p.keep = keep; p.partial = partial;
-    p.d = d; p.F = F; p.B = B; p.P = P; p.RG = RG; p.CG = CG;
-    p.gelu = layer->kind == CLADA_FFN_GEGLU ? 1 : 0;
-    const bool relu = layer->kind == CLADA_FFN_RELU;
-    p.b_in = layer->b_in;
-    p.list = list; p.list_n = list_n;
-
+    const int d = a.p.d, P = a.p.P;
+    const bool list = a.p.list != nullptr;
+    const dim3 grid(P, n_layers * a.n_pass);
 #define CLADA_BAT_LAUNCH(KS, NW, RELU)                                                                                    \
     {                                                                                                                      \
-        if (list)       hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, true, RELU>), dim3(P), dim3(NW * 64), 0, stream, p);   \
-        else if (dense) hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, false, RELU>), dim3(P), dim3(NW * 64), 0, stream, p);  \
-        else            hipLaunchKernelGGL((k_bat_gateup<KS, NW, false, false, RELU>), dim3(P), dim3(NW * 64), 0, stream, p); \
+        if (list)       hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, true, RELU>), grid, dim3(NW * 64), 0, stream, a);   \
+        else if (dense) hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, false, RELU>), grid, dim3(NW * 64), 0, stream, a);  \
+        else            hipLaunchKernelGGL((k_bat_gateup<KS, NW, false, false, RELU>), grid, dim3(NW * 64), 0, stream, a); \
     }
 #define CLADA_BAT_CASE(D, KS, NW)                                                                            \
     if (d == D) {                                                                                             \
@@ -591,8 +650,103 @@ clada_status clada_decode_batched(clada_ctx *ctx, const clada_layer *layer, cons
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_relaxed);
     }
-    hipLaunchKernelGGL(k_bat_down, dim3(CG * RG), dim3(512), lds, stream, p);
+    hipLaunchKernelGGL(k_bat_down, dim3(a.p.CG * a.p.RG, n_layers * a.n_pass), dim3(512), lds, stream, a);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
+    return CLADA_OK;
+}
+
+// The layers of a whole-stack call, as many per launch as `bytes` of scratch hold (*ran: the shape fits and did).  Three
+// launches cover them all: against three lanes of three launches per layer and pass (us per step) 180 / 307 for 24 layers of
+// 1024 x 4096 at two tokens, 395 / 466 for 18 of 2048 x 8192 at 16, 243 / 277 for 5 of 4096 x 11008 at 4, 1904 / 1928 for 32
+// of 4096 x 14336 at 8, 2152 / 2315 and 1295 / 1350 for 40 and 20 of 5120 x 13824 at two and six, 908 / 990 for 20 of
+// 5120 x 8192 at 16.  The lanes stay ahead (2903 / 2873) for 40 of 5120 x 13824 at 16: the gate/up
+// workgroups of gated 10 KiB rows have five waves, not eight, and a second unit's kernels fill the gaps of a full pass.
+clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int32_t L, const void *x, int32_t B,
+                                 const float *tau, void *y, bool dense, char *scratch, size_t bytes, hipStream_t stream, bool *ran)
+{
+    *ran = false;
+    const int d = layers[0].d, F = layers[0].d_ff;
+    const int n_pass = (B + 15) / 16, per = (B + n_pass - 1) / n_pass;
+    if (L < 2 || (d == 5120 && F > 8192 && per > 8 && layers[0].kind != CLADA_FFN_RELU)) return CLADA_OK;
+    int P, CG, RG;
+    if (!bat_plan(ctx, &layers[0], B - (n_pass - 1) * per, &P, &CG, &RG) || !bat_plan(ctx, &layers[0], per, &P, &CG, &RG)) return CLADA_OK;
+    const size_t part = sizeof(float) * (size_t)RG * B * d;
+    const size_t per_layer = part + n_pass * (sizeof(float) * 16 * (size_t)F + sizeof(int) * ((size_t)F + COOP_MAX_WGS));
+    int nl = bytes < 768 ? 0 : (int)((bytes - 768) / per_layer < (size_t)L ? (bytes - 768) / per_layer : (size_t)L);
+    if (nl > BAT_LAYERS) nl = BAT_LAYERS;
+    if (nl < 2) return CLADA_OK;
+    const int n_launch = (L + nl - 1) / nl;
+    nl = (L + n_launch - 1) / n_launch;
+    const bool relu = layers[0].kind == CLADA_FFN_RELU;
+    char *hb = scratch + align_up(part * nl, 256);
+    char *ul = hb + align_up(sizeof(float) * 16 * (size_t)F * n_pass * nl, 256);
+    char *uc = ul + align_up(sizeof(int) * (size_t)F * n_pass * nl, 256);
+    for (int l0 = 0; l0 < L; l0 += nl) {
+        const int n = L - l0 < nl ? L - l0 : nl;
+        const size_t row = (size_t)l0 * B;
+        BatArgs a;
+        memset(&a, 0, sizeof(a));
+        BatParams &p = a.p;
+        p.x = (const char *)x + row * d * 2; p.tau = tau ? tau + row : nullptr;
+        p.hbuf = reinterpret_cast<float *>(hb); p.ulist = reinterpret_cast<int *>(ul); p.ucnt = reinterpret_cast<int *>(uc);
+        p.partial = reinterpret_cast<float *>(scratch);
+        p.d = d; p.F = F; p.B = B; p.P = P; p.RG = RG; p.CG = CG; p.rows = n * B;
+        p.gelu = layers[0].kind == CLADA_FFN_GEGLU ? 1 : 0;
+        a.n_pass = n_pass; a.per_pass = per;
+        bool bias = false;
+        for (int l = 0; l < n; ++l) {
+            const clada_layer &s = layers[l0 + l];
+            a.wg[l] = (const char *)s.w_gate; a.wu[l] = (const char *)s.w_up; a.wd[l] = (const char *)s.w_down;
+            a.b_in[l] = s.b_in;
+            bias = bias || (relu && s.b_out);
+        }
+        const clada_status st = bat_launch(ctx, a, n, relu, dense, stream);
+        if (st != CLADA_OK) return st;
+        char *y0 = (char *)y + row * d * 2;
+        if (!bias) {
+            clada_launch_finalize(2, p.partial, RG, n * B, d, y0, stream);
+        } else {
+            BatBiasArgs f;
+            memset(&f, 0, sizeof(f));
+            f.partial = p.partial; f.y = y0; f.RG = RG; f.B = B; f.d = d;
+            for (int l = 0; l < n; ++l) f.b_out[l] = layers[l0 + l].b_out;
+            hipLaunchKernelGGL(k_bat_finalize_bias, dim3((d + 31) / 32, n * B), dim3(256), 0, stream, f);
+        }
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+    }
+    *ran = true;
+    return CLADA_OK;
+}
+
+// Runs the batched MFMA path when the shape is eligible (*ran; an ineligible shape launches nothing and the
+// caller uses the generic kernels).
+clada_status clada_decode_batched(clada_ctx *ctx, const clada_layer *layer, const void *x, int32_t B,
+                                  const float *tau, void *y, unsigned char *keep, float *partial,
+                                  char *scratch, bool dense, hipStream_t stream, bool *ran,
+                                  const int32_t *list, const int32_t *list_n)
+{
+    *ran = false;
+    const int d = layer->d, F = layer->d_ff;
+    int P, CG, RG;
+    if (!bat_plan(ctx, layer, B, &P, &CG, &RG)) return CLADA_OK;
+
+    BatArgs a;
+    memset(&a, 0, sizeof(a));
+    BatParams &p = a.p;
+    a.n_pass = 1; a.per_pass = B;
+    a.wg[0] = (const char *)layer->w_gate; a.wu[0] = (const char *)layer->w_up; a.wd[0] = (const char *)layer->w_down;
+    a.b_in[0] = layer->b_in;
+    p.x = (const char *)x; p.tau = tau;
+    p.hbuf = reinterpret_cast<float *>(scratch);
+    p.ulist = reinterpret_cast<int *>(scratch + align_up(sizeof(float) * 16 * (size_t)F, 256));
+    p.ucnt = reinterpret_cast<int *>(scratch + align_up(sizeof(float) * 16 * (size_t)F, 256) + align_up(sizeof(int) * (size_t)F, 256));
+    p.keep = keep; p.partial = partial;
+    p.d = d; p.F = F; p.B = B; p.P = P; p.RG = RG; p.CG = CG; p.rows = B;
+    p.gelu = layer->kind == CLADA_FFN_GEGLU ? 1 : 0;
+    const bool relu = layer->kind == CLADA_FFN_RELU;
+    p.list = list; p.list_n = list_n;
+    const clada_status st = bat_launch(ctx, a, 1, relu, dense, stream);
+    if (st != CLADA_OK) return st;
     clada_launch_finalize(2, partial, RG, B, d, (char *)y, stream, relu ? layer->b_out : nullptr);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     *ran = true;

@@ -303,6 +303,32 @@ def test_batched_stack_call_is_the_per_layer_calls_bit_for_bit(clada, cfg_name, 
     assert_close_y(to_np(y[l]), want, TOL_Y[cfg.dtype], f"layer {l} vs oracle on the device's masks")
 
 
+@pytest.mark.parametrize("d,F,L,B,relu", [
+    (1024, 700, 5, 9, True), (1024, 700, 3, 17, True),                # biases of their own per layer, one and two passes
+    (2048, 1100, 50, 2, False),                                     # more layers than one launch takes
+    (4096, 900, 7, 33, False),                                      # three passes per layer
+    (1024, 20000, 60, 2, False),                                    # several launches by the room in the workspace too
+])
+def test_batched_launches_over_all_units_are_the_per_layer_calls_bit_for_bit(clada, d, F, L, B, relu):
+    from paper_2502_19078_amd import binding
+    g = torch.Generator(device=DEV).manual_seed(d + F + L + B)
+    n = lambda *s, std=0.02: torch.randn(s, generator=g, device=DEV) * std
+    layers = []
+    for _ in range(L):
+        w = [n(F, d).bfloat16() for _ in range(2 if relu else 3)]
+        layers.append(clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=n(F), b_out=n(d)) if relu else clada.Layer(*w))
+    x = n(L, B, d, std=1.0).bfloat16()
+    tau = torch.rand(L, B, generator=g, device=DEV) * 0.5
+    tau[0], tau[L - 1, 0] = 1e9, 0.0                         # a layer that keeps nothing, a token that keeps everything
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, B, 0, 0))
+    for rep in range(2):
+        y = clada.sparse_ffn_stack_decode(ctx, layers, x, tau)
+        yd = clada.dense_ffn_stack_decode(ctx, layers, x)
+        for l in range(L):
+            assert torch.equal(y[l], clada.sparse_ffn_decode(ctx, layers[l], x[l], tau[l])), f"layer {l}"
+            assert torch.equal(yd[l], clada.dense_ffn_decode(ctx, layers[l], x[l])), f"dense, layer {l}"
+
+
 def test_batched_stack_call_replays_from_a_graph(clada):
     cfg, ws, layers, x = _batch_stack(clada, "c3", 4096, 2048, 6, 8, seed=32)
     ctx = clada.Context(0, clada.workspace_bytes(4096, 2048, 8, 0, 0))
