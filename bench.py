@@ -401,8 +401,8 @@ def main():
             stack[mode_name] = m
         ctx.set_option("decode.stack", 3)
         stack["what"] = ("modes of clada_sparse_ffn_stack_decode (option decode.stack).  lanes (default; value and "
-                         "ms_per_step of this line): the layers go round two or three streams, so that the compute units "
-                         "one layer has released run the next already.  chained_launches: one stream, the kernel of "
+                         "ms_per_step of this line): one launch over all layers, or the layers go round two or three streams, "
+                         "so that the compute units one layer has released run the next already.  chained_launches: one stream, the kernel of "
                          "layer l also sums the partial outputs of layer l-1.  persistent_kernel: one launch walks "
                          "the L layers; slower for sparse stacks, kept for the record")
     run_dense = make_runner(True, tau_s, tau_H, lam, gam)
@@ -431,6 +431,8 @@ def main():
     nch = d * es // 1024
     # what the library chooses for sparse stacks: batch-1 rows of 2, 5, 8 and 10 KiB run as one launch over all layers (lanes = 1)
     one_launch = B == 1 and d * es % 1024 == 0 and (nch in (2, 5, 8, 10) or (nch == 4 and (F <= 12288 or L >= 32)))
+    # (as do batches, save gated 10 KiB rows of more than eight tokens per pass)
+    one_launch = one_launch or (B >= 2 and not (nch == 10 and F > 8192 and -(-B // -(-B // 16)) > 8 and not relu))
     n_lanes = 1 if (not use_stack or L < 4 or one_launch) else 3 if (B >= 2 or nch == 4) else 2
     main_kernel = ("k_ffn_decode_b1 (input rows dense + output rows of kept neurons)" if B == 1 and relu
                    else "k_ffn_decode_b1 (gate rows dense + up/down rows of kept neurons)" if B == 1
@@ -504,12 +506,10 @@ def main():
                      "us_per_layer_in_step": round(step_us_per_layer, 2),
                      "note": ("achieved/frac: the kernel of a per-layer call with the chip to itself, timed by kernel-own HIP "
                               "events on the timed steps' inputs (rocprofv3 row of the balanced instance at B = 1).  The "
-                              "launches of the timed step run in lanes and overlap, so the duration of a single one of them "
-                              "(rocprofv3 rows of the lane instance) is not the time it costs: in_step divides the same bytes "
-                              "by the interval at which launches complete, step time / L"),
-                     # the timed step itself: in lanes several launches share the chip at any time, so the
-                     # duration of one launch says little; what counts is the rate at which launches complete
-                     # (step time / L, the signals launch included)
+                              "layers of the timed step overlap (one launch over all of them, or lanes): in_step divides the "
+                              "same bytes by the interval at which layers complete, step time / L"),
+                     # the timed step itself: several layers share the chip at any time; what counts is the rate at
+                     # which they complete (step time / L, the signals launch included)
                      "in_step": {"lanes": n_lanes,
                                  "us_per_launch_completed": round(step_us_per_layer, 2),
                                  "achieved": round(bytes_layer / (step_us_per_layer * 1e-6) / 1e9, 1),

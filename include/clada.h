@@ -72,7 +72,7 @@ const char *clada_last_error(const clada_ctx *ctx);
  * the launch allows it, 0 = the generic kernels), "decode.own_first" (1..14, neurons a
  * workgroup keeps for itself before the balanced hand-over; 0 = default),
  * "decode.wgs_per_cu" (1 or 2 workgroups per compute unit for the generic kernel),
- * "decode.stack" (how the whole-stack calls run: 3 = lanes [default], 2 = chained
+ * "decode.stack" (how the whole-stack calls run: 3 = one launch over the layers or lanes [default], 2 = chained
  * launches, 1 = one persistent kernel for all layers where the shape has one, 0 = the L
  * per-layer calls; see clada_sparse_ffn_stack_decode), "decode.lane_occ2" (1 = where the lanes of
  * a batch-1 stack have a kernel instance of which two workgroups fit a compute unit, they use
@@ -280,8 +280,8 @@ clada_status clada_dense_ffn_decode(clada_ctx *ctx, const clada_layer *layer, co
  *                inside the call.  To the caller the call is ordered on hip_stream like any
  *                other, and a stream capture of hip_stream records all lanes.  The compute
  *                units that layer l has released run layer l+1 already; where the kernel
- *                has an instance of which two workgroups fit a compute unit (rows of 4, 5
- *                and 8 KiB), workgroups of different layers share every unit.  The lanes use
+ *                has an instance of which two workgroups fit a compute unit (rows of 4 KiB,
+ *                dense stacks with 8 KiB), workgroups of different layers share every unit.  The lanes use
  *                the kernels without cross-workgroup balancing (kernels that wait for
  *                their own workgroups must not share the chip).
  *   2            chained launches on hip_stream: the kernel of layer l also sums the
@@ -298,9 +298,8 @@ clada_status clada_dense_ffn_decode(clada_ctx *ctx, const clada_layer *layer, co
  * (rows of whole KiB), 256 compute units or more and n_active = NULL.  For B >= 2 there is
  * mode 3 only, where the matrix-core path applies (bf16, its widths) and n_active = NULL: its
  * kernels run over all units (layer, pass of up to 16 tokens) in one launch each, as many
- * layers at a time as the workspace holds, or (large rows of 10 KiB) the units go round three
- * lanes.  Every mode
- * falls back to mode 0 where it does not apply.  The remarks on clada_device_fault apply to modes 0 - 2
+ * layers at a time as the workspace holds, or (gated layers of 10 KiB rows, more than eight
+ * tokens per pass) the units go round three lanes.  Every mode falls back to mode 0 where it does not apply.  The remarks on clada_device_fault apply to modes 0 - 2
  * (balanced kernels wait, bounded, for their own workgroups).  A context serves one call
  * at a time, on whatever stream.  The first call in mode 3 creates the context's lane streams
  * and events: make it before hip_stream is captured.  clada_dense_ffn_stack_decode is the

@@ -54,7 +54,7 @@ struct BatParams {
     int row0, rows;             // this unit's first row of the launch's tokens, and their number (stride of the partials)
 };
 
-// One launch runs n units (blockIdx.y): unit u = layer u / n_pass, pass u % n_pass of its tokens.  A call of one layer is a
+// One launch runs n units: pass blockIdx.y of the tokens of layer blockIdx.z.  A call of one layer is a
 // launch of one unit; the whole-stack call runs as many layers per launch as the workspace has room for.
 constexpr int BAT_LAYERS = 48;
 struct BatArgs {
@@ -64,11 +64,11 @@ struct BatArgs {
     const float *b_in[BAT_LAYERS];
 };
 // (read through the kernel-argument segment: scalar loads at the unit's index)
-__device__ __forceinline__ BatParams bat_unit(const __attribute__((address_space(4))) BatArgs *a, int unit)
+__device__ __forceinline__ BatParams bat_unit(const __attribute__((address_space(4))) BatArgs *a)
 {
     BatParams p;
     __builtin_memcpy(&p, &a->p, sizeof(p));
-    const int n_pass = a->n_pass, layer = unit / n_pass, t0 = (unit - layer * n_pass) * a->per_pass;
+    const int layer = blockIdx.z, unit = layer * gridDim.y + blockIdx.y, t0 = blockIdx.y * a->per_pass;
     p.row0 = layer * p.B + t0;
     p.wg = a->wg[layer]; p.wu = a->wu[layer]; p.wd = a->wd[layer];
     p.b_in = a->b_in[layer];
@@ -104,7 +104,7 @@ template <int KSTEPS, int NW, bool DENSE, bool LIST = false, bool RELU = false>
 __global__ void __launch_bounds__(NW * 64)
 k_bat_gateup(const BatArgs)
 {
-    const BatParams p = bat_unit((const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.y);
+    const BatParams p = bat_unit((const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr());
     static_assert(!LIST || DENSE, "a list run keeps every listed neuron");
     static_assert(NW >= 4 && NW <= 8, "the tile reductions run on waves 0..3");
     __shared__ float s_part[2][NW][256];
@@ -354,7 +354,7 @@ constexpr int DN_MAX_WGS = 64;                  // gate/up workgroups per row gr
 __global__ void __launch_bounds__(512, 4)
 k_bat_down(const BatArgs)
 {
-    const BatParams p = bat_unit((const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.y);
+    const BatParams p = bat_unit((const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr());
     extern __shared__ __align__(16) unsigned char smem_dn[];
     unsigned char *s_tile = smem_dn;                                    // [8][DN_TILE_BYTES], later the fold buffers
     int *s_rows = reinterpret_cast<int *>(smem_dn + 8 * DN_TILE_BYTES); // [DN_MAX_ROWS]
@@ -621,12 +621,12 @@ size_t clada_ws_decode_batched_partial(int32_t d)
     return align_up(sizeof(float) * 64 * 16 * (size_t)d, 256);
 }
 
-// Launches the two kernels for the units of n layers (nl * n_pass of them).
+// Launches the two kernels for the units of n_layers layers.
 static clada_status bat_launch(clada_ctx *ctx, BatArgs &a, int n_layers, bool relu, bool dense, hipStream_t stream)
 {
     const int d = a.p.d, P = a.p.P;
     const bool list = a.p.list != nullptr;
-    const dim3 grid(P, n_layers * a.n_pass);
+    const dim3 grid(P, a.n_pass, n_layers);
 #define CLADA_BAT_LAUNCH(KS, NW, RELU)                                                                                    \
     {                                                                                                                      \
         if (list)       hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, true, RELU>), grid, dim3(NW * 64), 0, stream, a);   \
@@ -650,7 +650,7 @@ static clada_status bat_launch(clada_ctx *ctx, BatArgs &a, int n_layers, bool re
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_relaxed);
     }
-    hipLaunchKernelGGL(k_bat_down, dim3(a.p.CG * a.p.RG, n_layers * a.n_pass), dim3(512), lds, stream, a);
+    hipLaunchKernelGGL(k_bat_down, dim3(a.p.CG * a.p.RG, a.n_pass, n_layers), dim3(512), lds, stream, a);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     return CLADA_OK;
 }

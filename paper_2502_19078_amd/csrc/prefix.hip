@@ -834,11 +834,13 @@ __device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const Do
     }
 }
 
-template <int ES>
+// PROBE (the three down kernels): the error-bounded search's form, with y32 and skip.  The others are built without: the
+// extra store loop alone raised k_prefix_down_bf16's registers (330 -> 401 us at 2368 x 4096 x 9728).
+template <int ES, bool PROBE>
 __global__ void __launch_bounds__(256)
 k_prefix_down(const DownParams p)
 {
-    if (p.skip && *p.skip) return;
+    if (PROBE && p.skip && *p.skip) return;
     constexpr int ROW = Tile<ES>::ROW, CH = Tile<ES>::CHUNKS, PT = Tile<ES>::PER_THREAD;
     constexpr int VEC = 16 / ES;
     __shared__ __align__(16) char s_a[BM * ROW];
@@ -910,7 +912,7 @@ k_prefix_down(const DownParams p)
         mma_tile<ES, 1>(s_a + wm * 64 * ROW, sb, acc, lane);
     }
     if (p.rowsq) down_rowsq(acc[0], p, tm, tn, wm, wn, lane, tid, s_rs);
-    if (p.y32) down_store32(acc[0], p, tm, tn, wm, wn, lane);
+    if (PROBE && p.y32) down_store32(acc[0], p, tm, tn, wm, wn, lane);
     if (!p.y) return;
     const int n = lane & 31;
 #pragma unroll
@@ -939,10 +941,11 @@ constexpr int DBK = 64;
 constexpr int DA_PITCH = DBK * 2 + 16;          // h tile row pitch (bytes)
 constexpr int DB_PITCH = BN * 2 + 32;           // W_down tile row pitch: 4 rows of a transpose read hit distinct banks
 
-__global__ void __launch_bounds__(256)
+template <bool PROBE>
+__global__ void __launch_bounds__(256, 3)
 k_prefix_down_bf16(const DownParams p)
 {
-    if (p.skip && *p.skip) return;
+    if (PROBE && p.skip && *p.skip) return;
     __shared__ __align__(16) char s_a[BM * DA_PITCH];
     __shared__ __align__(16) char s_b[DBK * DB_PITCH];
     __shared__ float s_rs[2][BM];
@@ -1021,7 +1024,7 @@ k_prefix_down_bf16(const DownParams p)
         }
     }
     if (p.rowsq) down_rowsq(acc, p, tm, tn, wm, wn, lane, tid, s_rs);
-    if (p.y32) down_store32(acc, p, tm, tn, wm, wn, lane);
+    if (PROBE && p.y32) down_store32(acc, p, tm, tn, wm, wn, lane);
     if (!p.y) return;
     const int n = lane & 31;
 #pragma unroll
@@ -1053,10 +1056,11 @@ constexpr int DW_PAIR = 1024 + 128;                 // two W_down rows + padding
 constexpr int DW_B = 16 * 1024;                     // offset of the W_down tile in a stage
 constexpr int DW_STAGE = DW_B + 16 * DW_PAIR;       // 34816 bytes
 
+template <bool PROBE>
 __global__ void __launch_bounds__(256)
 k_prefix_down_bf16_wide(const DownParams p)
 {
-    if (p.skip && *p.skip) return;
+    if (PROBE && p.skip && *p.skip) return;
     __shared__ __align__(16) char s_w[4 * DW_STAGE];
 
     const int n_tmw = (p.T + 255) / 256, n_tnw = p.d / 256;
@@ -1245,8 +1249,8 @@ k_prefix_down_bf16_wide(const DownParams p)
     const int n = lane & 31;
     const int t0 = tm * 256 + wm * 128 + 4 * (lane >> 5);
     const int c0 = tn * 256 + wn * 128;                     // one 128-column tile of the row-norm buffer
-    if (p.part_out || p.y32) {                              // split-K: fp32 partial sums, reduced by k_prefix_down_combine
-        float *rows32 = p.part_out ? p.part_out + (size_t)ks * p.T * p.d : p.y32;
+    if (p.part_out || (PROBE && p.y32)) {                              // split-K: fp32 partial sums, reduced by k_prefix_down_combine
+        float *rows32 = !PROBE || p.part_out ? p.part_out + (size_t)ks * p.T * p.d : p.y32;
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
             float *dst = rows32 + (size_t)t0 * p.d + c0 + nb * 32 + n;
@@ -1258,7 +1262,7 @@ k_prefix_down_bf16_wide(const DownParams p)
                     if (t0 + row < p.T) dst[(size_t)row * p.d] = acc[mb][nb][r];
                 }
         }
-        if (p.part_out) return;
+        if (!PROBE || p.part_out) return;
     }
     if (p.rowsq) {
 #pragma unroll
@@ -1480,10 +1484,12 @@ hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, cha
     const int n_tmw = (T + 255) / 256, n_tnw = d / 256;
     const bool wide_ok = es == 2 && d % 256 == 0 && F % 32 == 0 && tile_mode != 1;
     const int S = wide_ok && splitk_ws ? clada_prefix_down_splits(d, F, T) : 1;
+    const bool probe = y32 || skip;
+    const auto wide = probe ? k_prefix_down_bf16_wide<true> : k_prefix_down_bf16_wide<false>;
     q.part_out = nullptr; q.S = 1;
     if (wide_ok && S > 1) {
         q.part_out = splitk_ws; q.S = S;
-        hipLaunchKernelGGL(k_prefix_down_bf16_wide, dim3((n_tmw * n_tnw * S + 7) / 8 * 8), dim3(256), 0, stream, q);
+        hipLaunchKernelGGL(wide, dim3((n_tmw * n_tnw * S + 7) / 8 * 8), dim3(256), 0, stream, q);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_prefix_down_combine, dim3((T + 7) / 8, d / 128), dim3(256), 0, stream, splitk_ws, S, T, d,
@@ -1491,10 +1497,10 @@ hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, cha
     }
     else if (wide_ok && (tile_mode == 2 || n_tmw * n_tnw >= 192)) {
         const int blocks = n_tmw % 8 == 0 ? n_tmw * ((n_tnw + 3) / 4 * 4) : n_tmw * n_tnw;
-        hipLaunchKernelGGL(k_prefix_down_bf16_wide, dim3((blocks + 7) / 8 * 8), dim3(256), 0, stream, q);
+        hipLaunchKernelGGL(wide, dim3((blocks + 7) / 8 * 8), dim3(256), 0, stream, q);
     }
-    else if (es == 4) hipLaunchKernelGGL(k_prefix_down<4>, dim3(grid), dim3(256), 0, stream, q);
-    else         hipLaunchKernelGGL(k_prefix_down_bf16, dim3(grid), dim3(256), 0, stream, q);
+    else if (es == 4) hipLaunchKernelGGL((probe ? k_prefix_down<4, true> : k_prefix_down<4, false>), dim3(grid), dim3(256), 0, stream, q);
+    else         hipLaunchKernelGGL((probe ? k_prefix_down_bf16<true> : k_prefix_down_bf16<false>), dim3(grid), dim3(256), 0, stream, q);
     return hipGetLastError();
 }
 
