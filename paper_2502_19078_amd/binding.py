@@ -136,6 +136,8 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(t: torch.Tensor):
+    if not t.is_cuda:                                        # (the raw call takes a host tensor's -1 for the current device)
+        raise ValueError(f"expected a tensor on the GPU, got one on {t.device}")
     if _raw_stream is not None:
         return _raw_stream(t.get_device())
     return torch.cuda.current_stream(t.device).cuda_stream

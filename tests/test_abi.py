@@ -119,3 +119,29 @@ def test_bench_refuses_more_than_one_gpu():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode == 2 and "ONE GPU" in r.stderr
+
+
+def test_host_tensors_are_refused_before_the_library_is_called(monkeypatch):
+    """A host pointer must never reach a kernel: the calls without a check of their own rely on the stream lookup for it.
+    (torch's raw lookup answers a host tensor's device index -1 with the current device's stream, as the stand-in here does.)"""
+    import torch
+    import paper_2502_19078_amd.binding as b
+
+    class Lib:
+        def __getattr__(self, name):
+            def call(*args):
+                raise AssertionError(f"{name} was called")
+            return call
+
+    class Ctx:
+        _lib, _h = Lib(), None
+
+        def check(self, st):
+            pass
+
+    monkeypatch.setattr(b, "_raw_stream", lambda index: 0)
+    src, dst = torch.zeros(8192, dtype=torch.uint8), torch.zeros(8192, dtype=torch.uint8)
+    with pytest.raises(ValueError):
+        b.diag_copy(Ctx(), src, dst)
+    with pytest.raises(ValueError):
+        b.diag_stream_read(Ctx(), src)
