@@ -187,6 +187,11 @@ __global__ void __launch_bounds__(256) k_calib_finish(CalibState *st, float *tau
     }
 }
 
+__global__ void __launch_bounds__(256) k_calib_clear(CalibState *st)
+{
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < BINS1 + COARSE; i += gridDim.x * 256) st->fine1[i] = 0ull;
+}
+
 }  // namespace
 
 size_t clada_ws_calibrate(void) { return 256; }      // (the histograms are in the header)
@@ -213,9 +218,22 @@ extern "C" clada_status clada_threshold_calibrate(clada_ctx *ctx, const float *a
     const long long want = ((n >> 2) + CHUNK4 - 1) / CHUNK4;
     const int cap = ctx->num_cu;
     const int blocks = (int)(want < 1 ? 1 : (want > cap ? cap : want));
+    // The first histogram is zero between calls because the last kernel clears it.  A call that a refused launch cut short
+    // may leave it filled: the next one clears it first.  (Recorded into a graph, that clearing has not run yet: the mark stays.)
+    hipStreamCaptureStatus cap_status = hipStreamCaptureStatusNone;
+    if (ctx->calib_dirty) {
+        CLADA_CHECK_HIP(ctx, hipStreamIsCapturing(stream, &cap_status));
+        hipLaunchKernelGGL(k_calib_clear, dim3(32), dim3(256), 0, stream, st);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+    }
+    const int mark = cap_status != hipStreamCaptureStatusNone;
+    ctx->calib_dirty = 1;
     hipLaunchKernelGGL(k_calib_hist<1>, dim3(blocks), dim3(CALIB_THREADS), 0, stream, abs_act_pool, (long long)n, (unsigned long long)k, st);
+    CLADA_CHECK_HIP(ctx, hipGetLastError());
     hipLaunchKernelGGL(k_calib_hist<2>, dim3(blocks), dim3(CALIB_THREADS), 0, stream, abs_act_pool, (long long)n, (unsigned long long)k, st);
+    CLADA_CHECK_HIP(ctx, hipGetLastError());
     hipLaunchKernelGGL(k_calib_finish, dim3(32), dim3(256), 0, stream, st, tau_base_out);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
+    ctx->calib_dirty = mark;
     return CLADA_OK;
 }

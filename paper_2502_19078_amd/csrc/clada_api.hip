@@ -75,6 +75,7 @@ clada_status clada_create(clada_ctx **out, int device_id, size_t workspace_bytes
     ctx->n_occ = 0;
     ctx->opt_prefix_tile = 0;
     ctx->capturing = 0;
+    ctx->calib_dirty = 0;
     ctx->opt_diag_events = 0;
     ctx->ev[0] = ctx->ev[1] = ctx->ev[2] = ctx->ev[3] = nullptr;
     for (int i = 0; i < 3; ++i) ctx->lane_stream[i] = nullptr;

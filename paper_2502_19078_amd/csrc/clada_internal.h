@@ -25,6 +25,7 @@ struct clada_ctx {
     int opt_diag_events;         // 1: decode calls record HIP events around their kernels (clada_diag_kernel_times)
     hipEvent_t ev[4];            // start/stop of the main decode kernel, start/stop of the final reduction
     int capturing;               // a clada_graph_begin is open
+    int calib_dirty;             // a threshold calibration was cut short: its histograms may not be zero
     hipStream_t lane_stream[3];  // further lanes of the whole-stack calls (created at the first such call, default priority)
     hipEvent_t ev_lane[4];       // fork, and the join of every further lane
     // workgroups per compute unit of the balanced batch-1 kernel instances on this context's device

@@ -1,0 +1,30 @@
+"""Which kernels a call launches, and what a refused launch leaves behind: the library's host side on the CPU, over a runtime
+that only writes the launches down (fake_hip.py)."""
+import shutil
+
+import pytest
+
+from fake_hip import run_steps
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")
+
+
+def _names(result):
+    assert result["status"] == 0, result
+    return [r[0] for r in result["launches"]]
+
+
+def test_a_calibration_that_was_cut_short_does_not_reach_the_next_one(tmp_path):
+    """The histograms are zero between calls only if the last kernel of a call ran: after a refused launch the next call clears
+    them before it counts, and no call after that."""
+    calib = {"do": "calibrate", "n": 1 << 20}
+    clear = lambda r: [i for i, n in enumerate(_names(r)) if "k_calib_clear" in n]
+    for refused in (0, 1, 2):                                # the first, second, third launch of the call
+        r = run_steps([{"do": "ctx", "sizes": [0, 0, 0, 64, 0]}, calib, {"do": "fail", "in": refused}, calib, calib, calib], tmp_path)
+        assert clear(r[1]) == [] and r[3]["status"] == 7     # CLADA_ERR_HIP
+        assert len(r[3]["launches"]) == refused              # nothing is launched behind the refused one
+        assert clear(r[4]) == [0] and clear(r[5]) == []
+    # a clearing that was only recorded has not run: the next call clears again
+    r = run_steps([{"do": "ctx", "sizes": [0, 0, 0, 64, 0]}, {"do": "fail", "in": 2}, calib, {"do": "capturing", "on": 1}, calib,
+                   {"do": "capturing", "on": 0}, calib, calib], tmp_path)
+    assert clear(r[4]) == [0] and clear(r[6]) == [0] and clear(r[7]) == []
