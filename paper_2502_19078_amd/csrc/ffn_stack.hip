@@ -46,14 +46,15 @@ __device__ __forceinline__ unsigned int lds_offset(const void *p)
 }
 // Loads into LDS and the reads of what they bring are written as assembly: the compiler cannot tell the ring's slots apart
 // and would wait for every load in flight before any LDS access.  A load has no register result; its slot is read only
-// after the wait for the vector-memory counter below, and is refilled only after that read has returned.
+// after the wait for the vector-memory counter below, and is refilled only after that read has returned.  The slot's address
+// reaches m0 through its constraint, so the compiler knows what m0 holds.
 __device__ __forceinline__ void ring_load(const char *base, unsigned int voff, unsigned int slot)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(slot) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "{m0}"(slot) : "memory");
 }
 __device__ __forceinline__ void ring_load_lanes(const char *p, unsigned int slot)
 {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(p), "s"(slot) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(p), "{m0}"(slot) : "memory");
 }
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 template <int DW> struct RingWords;
