@@ -177,6 +177,10 @@ __global__ void k_cett_finish(const CettState *st, float *tau_out, float *mean_o
 constexpr int SAMPLES = 4096;      // sorted sample of the pool; neighbours are 2.7 magnitudes per token apart at 11008 neurons
 constexpr int CLOSE = 24;          // sample places left between the bracket's ends when the dense probes end
 constexpr int DENSE_PROBES = 10;   // launched; those past the end return at once
+// Tokens up to which every workgroup of a probe forms the previous one's mean itself: that saves a launch a probe, and costs
+// T^2 reads.  In place / by a launch of its own, us per search: 533 / 564 and 1142 / 1171 (512 tokens, 1024 x 4096 and
+// 4096 x 11008), 631 / 633 and 1805 / 1785 (1024), 949 / 870 and 3119 / 2910 (2048), 3848 / 2271 (8192), 92600 / 8200 (65536).
+constexpr int MEAN_IN_PLACE = 1024;
 
 __device__ __forceinline__ unsigned int sample_hash(unsigned int x)
 {
@@ -364,13 +368,40 @@ k_cett_list(CettState *st, const float *__restrict__ pool, int F, int *__restric
     }
 }
 
-// One probe inside the bracket.  First every workgroup takes in the previous one (the same state and the same norms, so the
-// same result; workgroup 0 leaves it for the next launch), then, a workgroup per token and part of the columns: the cut sums
-// at `base` plus h_j W_down[j,:] of the neurons with base <= |a_j| < probe in ascending order, to the other buffer; their
-// sum of squares to rowsq.
+// A probe's answer: the bracket, the sums' threshold and buffer, and the bisection up to the next probe.
+__device__ __forceinline__ void take_in(CettState &s, float mean, float bound)
+{
+    if (mean <= bound) {
+        s.known_lo = s.base = s.mid;
+        s.known_mean = mean;
+        s.sel ^= 1;
+    } else {
+        s.known_hi = s.mid;                                  // NaN: over the bound
+    }
+    bisect_on(s);
+}
+
+// The same as a launch of its own, in place, for more than MEAN_IN_PLACE tokens.
+__global__ void __launch_bounds__(1024)
+k_cett_take(CettState *st, const float *__restrict__ rowsq, int parts, int T, const float *__restrict__ den, float bound)
+{
+    __shared__ float s_sum[1024];
+    if (st->done) return;
+    const float mean = mean_cett(rowsq, parts, T, den, s_sum);
+    if (threadIdx.x == 0) {
+        CettState s = *st;
+        take_in(s, mean, bound);
+        *st = s;
+    }
+}
+
+// One probe inside the bracket.  Up to MEAN_IN_PLACE tokens every workgroup first takes in the previous one (the same state
+// and the same norms, so the same result; workgroup 0 leaves it for the next launch), beyond k_cett_take has done that (taken).
+// Then, a workgroup per token and part of the columns: the cut sums at `base` plus h_j W_down[j,:] of the neurons with
+// base <= |a_j| < probe in ascending order, to the other buffer; their sum of squares to rowsq.
 template <int ES, int NV>
 __global__ void __launch_bounds__(256)
-k_cett_between(CettState *__restrict__ sts, int launch, const float *__restrict__ pool, const char *__restrict__ h,
+k_cett_between(CettState *__restrict__ sts, int launch, int taken, const float *__restrict__ pool, const char *__restrict__ h,
                const char *__restrict__ wd, const int *__restrict__ list, int cap, const int *__restrict__ count,
                float *__restrict__ buf0, float *__restrict__ buf1, const float *__restrict__ rowsq_in, float *__restrict__ rowsq,
                const float *__restrict__ den, float bound, int T, int F, int Fp, int d)
@@ -381,7 +412,8 @@ k_cett_between(CettState *__restrict__ sts, int launch, const float *__restrict_
     __shared__ CettState s_st;
     const int tid = threadIdx.x, parts = gridDim.y, part = blockIdx.y;
     const CettState *in = sts + (launch & 1);
-    if (!in->done && launch > 0) {
+    const bool take = !taken && launch > 0 && !in->done;
+    if (take) {
         float acc = 0.0f;
         for (int t = tid; t < T; t += 256) {
             float s = 0.0f;
@@ -398,17 +430,7 @@ k_cett_between(CettState *__restrict__ sts, int launch, const float *__restrict_
     }
     if (tid == 0) {
         CettState s = *in;
-        if (!s.done && launch > 0) {
-            const float mean = s_sq[0] / (float)T;
-            if (mean <= bound) {
-                s.known_lo = s.base = s.mid;
-                s.known_mean = mean;
-                s.sel ^= 1;
-            } else {
-                s.known_hi = s.mid;                          // NaN: over the bound
-            }
-            bisect_on(s);
-        }
+        if (take) take_in(s, s_sq[0] / (float)T, bound);
         s_st = s;
         if (blockIdx.x == 0 && part == 0) sts[(launch + 1) & 1] = s;
     }
@@ -585,7 +607,10 @@ void launch_between(const CettWs &w, const clada_layer *layer, int T, int Fp, in
     const BetweenShape sh = between_shape(d, ES);
     auto kern = sh.nv == 1 ? k_cett_between<ES, 1> : k_cett_between<ES, 2>;
     float *sq[2] = {w.rowsq_num, w.rowsq_den};
-    hipLaunchKernelGGL(kern, dim3(T, sh.parts), dim3(256), 0, st, w.state, launch, w.pool, w.h, (const char *)layer->w_down,
+    const bool taken = T > MEAN_IN_PLACE;
+    if (taken && launch > 0)
+        hipLaunchKernelGGL(k_cett_take, dim3(1), dim3(1024), 0, st, w.state + (launch & 1), sq[launch & 1], sh.parts, T, w.den, bound);
+    hipLaunchKernelGGL(kern, dim3(T, sh.parts), dim3(256), 0, st, w.state, launch, taken ? 1 : 0, w.pool, w.h, (const char *)layer->w_down,
                        list, cap, count, reinterpret_cast<float *>(w.ytmp), reinterpret_cast<float *>(w.hcut),
                        sq[launch & 1], sq[(launch + 1) & 1], w.den, bound, T, layer->d_ff, Fp, d);
 }

@@ -240,3 +240,44 @@ def test_large_search_without_a_largest_threshold(clada):
     ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
     tau, mean = clada.threshold_search_cett(ctx, layer, x, 0.2)
     assert float(tau) == float(np.finfo(np.float32).max) and 0.0 < float(mean) < 0.2
+
+
+# Above 1024 tokens the mean of a probe is formed by a launch of its own; the edge, ragged counts, rows in one and two parts.
+@pytest.mark.parametrize("T,d,F,dtype", [(1024, 512, 1100, "bf16"), (1025, 512, 1100, "bf16"), (3001, 256, 1000, "bf16"),
+                                          (2050, 2056, 2100, "bf16"), (1500, 512, 800, "f32")])
+def test_large_search_over_many_tokens(clada, T, d, F, dtype):
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(T + d)
+    n = lambda *s, k: torch.randn(s, generator=g, device=DEV) * k
+    layer = clada.Layer(*[n(F, d, k=d ** -0.5).to(dt) for _ in range(3)])
+    x = n(T, d, k=1.0).to(dt)
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    for bound in (0.05, 0.3):
+        t30, m30 = clada.threshold_search_cett(ctx, layer, x, bound, n_probes=30)
+        t31, m31 = clada.threshold_search_cett(ctx, layer, x, bound)
+        assert float(t31) == pytest.approx(float(t30), rel=2e-6), bound
+        assert float(m31) == pytest.approx(float(m30), rel=1e-5) and float(m31) <= bound
+        assert float(clada.cett_eval(ctx, layer, x, float(t31))[1]) == pytest.approx(float(m31), rel=2e-6)
+
+
+def test_search_cost_grows_with_the_tokens_not_with_their_square(clada):
+    """65536 tokens of a narrow layer: 30 probes are the plain bisection, whose cost is linear in the tokens; the search with 31
+    measures 0.8 of it (with a mean per workgroup and probe it was more than six times as slow)."""
+    d, F, T = 512, 2048, 65536
+    g = torch.Generator(device=DEV).manual_seed(3)
+    layer = clada.Layer(*[(torch.randn((F, d), generator=g, device=DEV) * 0.03).bfloat16() for _ in range(3)])
+    x = torch.randn((T, d), generator=g, device=DEV).bfloat16()
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    best = {}
+    for n in (30, 31):
+        clada.threshold_search_cett(ctx, layer, x, 0.2, n_probes=n)
+        times = []
+        for _ in range(3):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            clada.threshold_search_cett(ctx, layer, x, 0.2, n_probes=n)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        best[n] = min(times)
+    assert best[31] < 2.0 * best[30], best

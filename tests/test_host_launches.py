@@ -28,3 +28,12 @@ def test_a_calibration_that_was_cut_short_does_not_reach_the_next_one(tmp_path):
     r = run_steps([{"do": "ctx", "sizes": [0, 0, 0, 64, 0]}, {"do": "fail", "in": 2}, calib, {"do": "capturing", "on": 1}, calib,
                    {"do": "capturing", "on": 0}, calib, calib], tmp_path)
     assert clear(r[4]) == [0] and clear(r[6]) == [0] and clear(r[7]) == []
+
+
+def test_search_forms_the_mean_once_per_probe_above_1024_tokens(tmp_path):
+    """In place (every workgroup reads all tokens' norms) only up to 1024 tokens."""
+    d, F = 1024, 4096
+    r = run_steps([{"do": "ctx", "sizes": [d, F, 0, 1025, 0]}] + [{"do": "search", "d": d, "F": F, "T": T} for T in (1024, 1025)], tmp_path)
+    count = lambda res, name: sum(name in n for n in _names(res))
+    assert (count(r[1], "k_cett_between"), count(r[1], "k_cett_take")) == (32, 0)
+    assert (count(r[2], "k_cett_between"), count(r[2], "k_cett_take")) == (32, 31)
