@@ -182,20 +182,16 @@ constexpr int DENSE_PROBES = 10;   // launched; those past the end return at onc
 // 4096 x 11008), 631 / 633 and 1805 / 1785 (1024), 949 / 870 and 3119 / 2910 (2048), 3848 / 2271 (8192), 92600 / 8200 (65536).
 constexpr int MEAN_IN_PLACE = 1024;
 
-__device__ __forceinline__ unsigned int sample_hash(unsigned int x)
-{
-    x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
-    return x;
-}
-
-// One workgroup: the sorted bit patterns of SAMPLES pool entries drawn by a fixed hash, and the first probe.
+// One workgroup: the sorted bit patterns of SAMPLES pool entries, and the first probe.  The entries lie at the fractions
+// i * phi mod 1 of the pool (phi the golden ratio, 2^64 phi^-1 below): evenly spread over the tokens, without a stride that
+// could meet the same neurons of every token.
 __global__ void __launch_bounds__(1024)
 k_cett_sample(CettState *st, const float *__restrict__ pool, unsigned long long n, unsigned int *__restrict__ sample, float bound)
 {
     __shared__ unsigned int s[SAMPLES];
     const int tid = threadIdx.x;
     for (int i = tid; i < SAMPLES; i += 1024) {
-        const unsigned long long r = ((unsigned long long)sample_hash(2 * i + 1) << 32) | sample_hash(2 * i + 2);
+        const unsigned long long r = (unsigned long long)(i + 1) * 0x9e3779b97f4a7c15ull;
         const unsigned int u = __float_as_uint(pool[__umul64hi(r, n)]) & 0x7fffffffu;
         s[i] = u < 0x7f800000u ? u : 0x7f800000u;
     }
