@@ -37,3 +37,13 @@ def test_search_forms_the_mean_once_per_probe_above_1024_tokens(tmp_path):
     count = lambda res, name: sum(name in n for n in _names(res))
     assert (count(r[1], "k_cett_between"), count(r[1], "k_cett_take")) == (32, 0)
     assert (count(r[2], "k_cett_between"), count(r[2], "k_cett_take")) == (32, 31)
+
+
+@pytest.mark.parametrize("T,d,F,dtype,large", [
+    (4096, 256, 512, "bf16", True), (4097, 256, 512, "bf16", False), (16384, 64, 512, "bf16", False), (65536, 256, 1024, "bf16", False),
+    (65536, 64, 2048, "bf16", True), (16384, 64, 512, "f32", True), (2048, 520, 512, "bf16", False), (2047, 512, 512, "bf16", False),
+])
+def test_search_over_many_tokens_of_a_narrow_layer_is_the_plain_bisection(tmp_path, T, d, F, dtype, large):
+    """A probe inside the bracket costs a workgroup per token, which a bf16 projection of a few hundred neurons does not."""
+    r = run_steps([{"do": "ctx", "sizes": [d, F, 0, T, 0]}, {"do": "search", "d": d, "F": F, "T": T, "dtype": dtype}], tmp_path)
+    assert any("k_cett_between" in n for n in _names(r[1])) == large
