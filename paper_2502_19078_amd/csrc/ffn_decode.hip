@@ -1296,20 +1296,17 @@ hipError_t launch_b1(clada_ctx *ctx, const B1Params &p, int P, bool dense, bool 
     return launch_b1_variant<ES, NCH, DCH, false, false, RELU>(ctx, p, P, st);
 }
 
-// The two-per-unit instances (bf16, gated, one round of neurons) of the stacks that still run in lanes: 4 KiB rows, and the
-// dense twin with 8 KiB rows; the other widths have none.
+// The two-per-unit instances (bf16, gated, dense, one round of neurons) of the stacks that still run in lanes: 4 and 8 KiB rows.
+// (10 KiB rows: the instance needs 128 registers and a few spills, and was measured 6 % slower than the one-per-unit instance.)
 bool b1_occ2_shape_ok(int es, int nch, bool relu, bool dense)
 {
-    // (10 KiB rows: the instance needs 128 registers and a few spills, and was measured 6 % slower than the
-    // one-per-unit instance in two lanes)
-    return es == 2 && !relu && (nch == 4 || (nch == 8 && dense));
+    return es == 2 && !relu && dense && (nch == 4 || nch == 8);
 }
 
-hipError_t launch_b1_occ2(const B1Params &p, int P, int nch, bool dense, hipStream_t st)
+hipError_t launch_b1_occ2(const B1Params &p, int P, int nch, hipStream_t st)
 {
     if (nch == 8) hipLaunchKernelGGL((k_ffn_decode_b1<2, 8, 8, 8, true, false, false, false, false, true>), dim3(P), dim3(512), 0, st, p);
-    else if (dense) hipLaunchKernelGGL((k_ffn_decode_b1<2, 4, 8, 8, true, false, false, false, false, true>), dim3(P), dim3(512), 0, st, p);
-    else hipLaunchKernelGGL((k_ffn_decode_b1<2, 4, 8, 8, false, false, false, false, false, true>), dim3(P), dim3(512), 0, st, p);
+    else hipLaunchKernelGGL((k_ffn_decode_b1<2, 4, 8, 8, true, false, false, false, false, true>), dim3(P), dim3(512), 0, st, p);
     return hipGetLastError();
 }
 
@@ -1746,8 +1743,8 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
         if (persistent) return CLADA_OK;
     }
     // ---- launches issued by the library itself.  Three things the per-layer calls cannot do:
-    // * one launch over all layers (the default where it is the fastest: clada_stack_b1_fits), ffn_stack.hip
-    // * lanes (the default elsewhere): the layers of a stack are independent problems, so they go round two or three
+    // * launches over many layers (the default where they are the fastest: clada_stack_b1_fits), ffn_stack.hip
+    // * lanes (the default elsewhere): the layers of a stack are independent problems, so they go round two (batches: three)
     //   HIP streams (the caller's and the context's own, forked and joined by events, which a stream
     //   capture follows).  A compute unit that has finished its share of layer l takes a workgroup of
     //   layer l+1 at once: the start-up and the ragged end of every kernel are covered by its neighbour
@@ -1770,11 +1767,10 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
     }
     if (own_launches) {
         static_assert(COOP_MAX_WGS == 256, "the chained reduction is laid out for 256 partial outputs");
-        // With the two-per-unit instance workgroups of different layers share every compute unit (measured, 7B
-        // shape, ms per step of 32 layers at sparsity 0.45 / dense: two lanes 1.038 / 1.379 with the one-per-unit
-        // instance, 1.031 / 1.330 with this one; three lanes 1.085 / 1.460 and 1.006 / 1.357; four lanes 1.041 / 1.391)
+        // With the two-per-unit instance workgroups of different layers share every compute unit (dense 7B shape, ms per step of
+        // 32 layers: two lanes 1.379 with the one-per-unit instance, 1.330 with this one; three lanes 1.460 and 1.357)
         const bool occ2 = b1_occ2_shape_ok(es, nch, relu, dense) && ni_b <= 64 && ctx->opt_decode_lane_occ2 != 0;
-        const int n_lanes = (smode == 3 && L >= 4) ? ((occ2 && !dense) ? 3 : 2) : 1;
+        const int n_lanes = (smode == 3 && L >= 4) ? 2 : 1;
         const bool chained = smode == 2;
         unsigned int *epoch = reinterpret_cast<unsigned int *>(ctx->ws + COOP_EPOCH);
         float *part = reinterpret_cast<float *>(ctx->ws + CLADA_WS_HEADER);
@@ -1807,7 +1803,7 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
             b.prev_bias = (sums_prev && relu) ? layers[lp].b_out : nullptr;
             b.epoch_out = epoch;                             // only the balanced instance writes it
             if (n_lanes >= 2 && occ2)
-                CLADA_CHECK_HIP(ctx, launch_b1_occ2(b, Pb, nch, dense, st));
+                CLADA_CHECK_HIP(ctx, launch_b1_occ2(b, Pb, nch, st));
             else
                 CLADA_CHECK_HIP(ctx, launch_b1_shape(ctx, b, Pb, es, nch, relu, dense, &balance, st));
             if (!chained || l + n_lanes >= L) {              // nobody after it in its lane: its own reduction launch

@@ -454,20 +454,24 @@ void launch_rows(const StackLaunch &p, dim3 grid, bool relu, hipStream_t st)
 
 size_t clada_ws_stack(int32_t d) { return sizeof(float) * (size_t)CLADA_STACK_LAUNCH_LAYERS * SLICES * d; }
 
-// Where the launch over all layers is the faster one (against lanes of per-layer launches; us per step of L layers, sparsity
-// 0.45): 2 KiB rows 91 / 197 (L = 24, 1024 x 4096), 5 KiB ReLU rows 92 / 110 (L = 6), 8 KiB rows 960 / 995 (L = 32,
-// 4096 x 11008), 148 / 154 (L = 4), 10 KiB rows 1850 / 1940 (L = 40, 5120 x 13824).  4 KiB rows gain up to mid-sized layers
-// or with many of them (245 / 263 at L = 18 x 8192 neurons, 824 / 835 at 36 x 16384, but 464 / 446 at 18 x 16384); rows of
-// 12 and 16 KiB do not (685 / 670, 1180 / 1145 at L = 12), nor long dense stacks with 8 KiB rows (1360 / 1325 at L = 32,
-// 245 / 270 at L = 6), where the lanes' kernels have nothing to wait for.
+// Where the launches over all layers are the faster way (us per step of L layers against lanes of per-layer launches, sparsity
+// 0.45).  Nearly everywhere: 2 KiB rows 91 / 197 (L = 24, 1024 x 4096), 4 KiB 521 / 557 (24, 2048 x 16384), 5 KiB ReLU 92 / 110
+// (6, 2560 x 10240), 8 KiB 967 / 1040 (32, 4096 x 11008), 10 KiB 1425 / 1546 (32, 5120 x 13824); rows of 12 and 16 KiB gain
+// nothing (685 / 670, 1180 / 1145 at L = 12).  The lanes stay where they have as little to wait for:
+//   - a few layers of 10 KiB rows, dense or of more than 400 MB (4 layers: 1.01 - 1.05 of the lanes' time)
+//   - dense gated layers of 4 and 8 KiB rows, for which the lanes have a kernel of which two workgroups fit a unit, once one
+//     layer fills the chip for 30 us (4096 x 11008, one launch / lanes: 333 / 353 at L = 8, 522 / 515 at 12, 1331 / 1328 at 32;
+//     4096 x 8192: 993 / 1013 at 32; 2048 x 16384: 1.03 at L = 7, 0.98 at 32)
 bool clada_stack_b1_fits(const clada_layer *layer, int32_t L, bool dense)
 {
-    const int es = (int)dtype_size(layer->dtype), nch = layer->d * es / 1024;
+    const int es = (int)dtype_size(layer->dtype), nch = layer->d * es / 1024, F = layer->d_ff;
+    const bool gated = layer->kind != CLADA_FFN_RELU;
     if (layer->d * es % 1024 != 0 || L < 2) return false;
     if (es == 4) return nch == 2 || nch == 8;
-    if (nch == 4) return layer->d_ff <= 12288 || L >= 32;
-    if (nch == 8 && dense && layer->kind != CLADA_FFN_RELU && layer->d_ff > 8192 && L > 8) return false;
-    return nch == 2 || nch == 5 || nch == 8 || nch == 10;
+    if (nch == 4) return !(dense && gated && F > 12288 && L < 32);
+    if (nch == 8) return !(dense && gated && F > 8192 && L > 8);
+    if (nch == 10) return L >= 6 || (!dense && (gated ? 3.0 : 2.0) * F * layer->d * es < 400e6);
+    return nch == 2 || nch == 5;
 }
 
 hipError_t clada_stack_b1(const clada_layer *layers, int32_t L, const void *x, const float *tau, void *y, bool dense,
@@ -475,17 +479,30 @@ hipError_t clada_stack_b1(const clada_layer *layers, int32_t L, const void *x, c
 {
     const int d = layers[0].d, es = (int)dtype_size(layers[0].dtype), nch = d * es / 1024;
     const bool relu = layers[0].kind == CLADA_FFN_RELU;
-    const size_t rows = partial_bytes / (sizeof(float) * (size_t)d);
-    // Whole slices leave an eighth of the partial outputs and start an eighth of the workgroups, but there have to be enough
-    // of them: 6 layers are 192 workgroups (196 us against 216 us for 6 layers of 4096 x 11008; 167 against 148 us for 4),
-    // 8 layers with 2 KiB rows, whose workgroups have four waves (40 and 39 us at 8 layers of 1024 x 4096, 40 and 35 at 6).
-    const int chain = L >= (nch == 2 ? 8 : 6) ? CHAIN : 1;
-    const int P = CLASSES / chain;
-    int per_launch = (int)(rows / P < CLADA_STACK_LAUNCH_LAYERS ? rows / P : CLADA_STACK_LAUNCH_LAYERS);
-    const int n_launch = (L + per_launch - 1) / per_launch;
-    per_launch = (L + n_launch - 1) / n_launch;
-    for (int l0 = 0; l0 < L; l0 += per_launch) {
-        const int n = L - l0 < per_launch ? L - l0 : per_launch;
+    const size_t rows = partial_bytes / (sizeof(float) * (size_t)d);         // at least 1024: the workspace of a per-layer call
+    const int room = rows < 65536 ? (int)rows : 65536;
+    if (room < CLASSES) return hipErrorInvalidValue;
+    // Whole slices leave an eighth of the partial outputs and start an eighth of the workgroups, but there have to be enough of
+    // them (us, whole slices / single classes: 162 / 176 at 5 layers of 4096 x 11008, 155 / 141 at 4; 5 KiB rows 1.08 / 0.98 of
+    // the lanes at 5 of 2560 x 10240, 0.88 / 0.94 at 6; 4 KiB rows 1.04 / 0.95 at 7 of 2048 x 14336, 0.91 / 0.93 at 8; 2 KiB
+    // rows 40 / 39 at 8 of 1024 x 4096, 40 / 35 at 6: their workgroups have four waves).
+    const int whole = nch == 2 || nch == 4 ? 8 : nch == 5 ? 6 : 5;
+    int most = room / SLICES < CLADA_STACK_LAUNCH_LAYERS ? room / SLICES : CLADA_STACK_LAUNCH_LAYERS;
+    if (most > 8) most -= most % 8;
+    for (int l0 = 0, n; l0 < L; l0 += n) {
+        n = L - l0 < most ? L - l0 : most;
+        // A whole slice keeps a unit busy for a round of eight layers (32 workgroups a layer, 256 units), and one to three layers
+        // more are a round that leaves most units idle: they go as single classes, in a launch of their own (9 layers of
+        // 4096 x 11008: 352 us in one launch, 275 in two, 303 in lanes; 17: 584, 510, 537; at four more the two are even, but for
+        // 5 KiB rows: 1.10 at 12 dense layers of 2560 x 10240).  Rows of 4 KiB, whose workgroups are half as wide, notice from the
+        // third round on, rows of 2 KiB not at all.
+        const int more = n % 8, thin = nch == 2 ? 0 : nch == 5 ? 4 : 3;
+        if (n > (nch == 4 ? 16 : 8) && more <= thin) n -= more;
+        const int chain = n >= whole ? CHAIN : 1, P = CLASSES / chain;
+        if (n > room / P) {                                  // (single classes: launches of like size)
+            const int k = (n + room / P - 1) / (room / P);
+            n = (n + k - 1) / k;
+        }
         StackLaunch p;
         StackReduceArgs r;
         memset(&p, 0, sizeof(p));

@@ -25,16 +25,22 @@ class CLayer(C.Structure):
                 ("dtype", C.c_int32), ("kind", C.c_int32), ("b_in", C.c_void_p), ("b_out", C.c_void_p)]
 
 
-def run_steps(steps, tmp_path):
-    """The steps in a child process; builds the stand-in runtime first."""
+def build_runtime(folder):
+    """Compiles the stand-in runtime; returns its path."""
+    fake = os.path.join(str(folder), "libfake_hip.so")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "san", "fake_hip.cpp")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I/opt/rocm/include", src, "-o", fake], check=True,
+                   capture_output=True, text=True)
+    return fake
+
+
+def run_steps(fake, steps):
+    """The steps in a child process over the runtime at the path `fake`."""
     here = os.path.dirname(os.path.abspath(__file__))
     import paper_2502_19078_amd as pkg
     if not os.path.exists(pkg.lib_path()):
         from paper_2502_19078_amd import build
         build.build()
-    fake = str(tmp_path / "libfake_hip.so")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I/opt/rocm/include", os.path.join(here, "san", "fake_hip.cpp"),
-                    "-o", fake], check=True, capture_output=True, text=True)
     r = subprocess.run([sys.executable, os.path.join(here, "fake_hip.py"), fake, pkg.lib_path()], input=json.dumps(steps),
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]

@@ -219,6 +219,9 @@ ONE_LAUNCH = [
     (2560, 3333, 7, False, "bf16"), (2560, 2600, 5, True, "bf16"),
     (4096, 2817, 6, False, "bf16"), (4096, 1000, 50, True, "bf16"), (5120, 2222, 6, True, "bf16"), (5120, 2600, 5, False, "bf16"),
     (512, 1376, 8, False, "f32"), (512, 5000, 3, True, "f32"), (2048, 3000, 6, False, "f32"),
+    # a thin last round in a launch of its own, of single classes; single classes in two launches
+    (4096, 1030, 9, False, "bf16"), (2560, 2600, 12, True, "bf16"), (2048, 1100, 18, False, "bf16"), (1024, 1000, 7, False, "bf16"),
+    (5120, 700, 51, False, "bf16"), (2048, 900, 11, False, "f32"),
 ]
 
 

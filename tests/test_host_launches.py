@@ -4,9 +4,14 @@ import shutil
 
 import pytest
 
-from fake_hip import run_steps
+from fake_hip import build_runtime, run_steps
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    return build_runtime(tmp_path_factory.mktemp("fake_hip"))
 
 
 def _names(result):
@@ -14,26 +19,26 @@ def _names(result):
     return [r[0] for r in result["launches"]]
 
 
-def test_a_calibration_that_was_cut_short_does_not_reach_the_next_one(tmp_path):
+def test_a_calibration_that_was_cut_short_does_not_reach_the_next_one(fake):
     """The histograms are zero between calls only if the last kernel of a call ran: after a refused launch the next call clears
     them before it counts, and no call after that."""
     calib = {"do": "calibrate", "n": 1 << 20}
     clear = lambda r: [i for i, n in enumerate(_names(r)) if "k_calib_clear" in n]
     for refused in (0, 1, 2):                                # the first, second, third launch of the call
-        r = run_steps([{"do": "ctx", "sizes": [0, 0, 0, 64, 0]}, calib, {"do": "fail", "in": refused}, calib, calib, calib], tmp_path)
+        r = run_steps(fake, [{"do": "ctx", "sizes": [0, 0, 0, 64, 0]}, calib, {"do": "fail", "in": refused}, calib, calib, calib])
         assert clear(r[1]) == [] and r[3]["status"] == 7     # CLADA_ERR_HIP
         assert len(r[3]["launches"]) == refused              # nothing is launched behind the refused one
         assert clear(r[4]) == [0] and clear(r[5]) == []
     # a clearing that was only recorded has not run: the next call clears again
-    r = run_steps([{"do": "ctx", "sizes": [0, 0, 0, 64, 0]}, {"do": "fail", "in": 2}, calib, {"do": "capturing", "on": 1}, calib,
-                   {"do": "capturing", "on": 0}, calib, calib], tmp_path)
+    r = run_steps(fake, [{"do": "ctx", "sizes": [0, 0, 0, 64, 0]}, {"do": "fail", "in": 2}, calib, {"do": "capturing", "on": 1}, calib,
+                   {"do": "capturing", "on": 0}, calib, calib])
     assert clear(r[4]) == [0] and clear(r[6]) == [0] and clear(r[7]) == []
 
 
-def test_search_forms_the_mean_once_per_probe_above_1024_tokens(tmp_path):
+def test_search_forms_the_mean_once_per_probe_above_1024_tokens(fake):
     """In place (every workgroup reads all tokens' norms) only up to 1024 tokens."""
     d, F = 1024, 4096
-    r = run_steps([{"do": "ctx", "sizes": [d, F, 0, 1025, 0]}] + [{"do": "search", "d": d, "F": F, "T": T} for T in (1024, 1025)], tmp_path)
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 0, 1025, 0]}] + [{"do": "search", "d": d, "F": F, "T": T} for T in (1024, 1025)])
     count = lambda res, name: sum(name in n for n in _names(res))
     assert (count(r[1], "k_cett_between"), count(r[1], "k_cett_take")) == (32, 0)
     assert (count(r[2], "k_cett_between"), count(r[2], "k_cett_take")) == (32, 31)
@@ -43,7 +48,36 @@ def test_search_forms_the_mean_once_per_probe_above_1024_tokens(tmp_path):
     (4096, 256, 512, "bf16", True), (4097, 256, 512, "bf16", False), (16384, 64, 512, "bf16", False), (65536, 256, 1024, "bf16", False),
     (65536, 64, 2048, "bf16", True), (16384, 64, 512, "f32", True), (2048, 520, 512, "bf16", False), (2047, 512, 512, "bf16", False),
 ])
-def test_search_over_many_tokens_of_a_narrow_layer_is_the_plain_bisection(tmp_path, T, d, F, dtype, large):
+def test_search_over_many_tokens_of_a_narrow_layer_is_the_plain_bisection(fake, T, d, F, dtype, large):
     """A probe inside the bracket costs a workgroup per token, which a bf16 projection of a few hundred neurons does not."""
-    r = run_steps([{"do": "ctx", "sizes": [d, F, 0, T, 0]}, {"do": "search", "d": d, "F": F, "T": T, "dtype": dtype}], tmp_path)
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 0, T, 0]}, {"do": "search", "d": d, "F": F, "T": T, "dtype": dtype}])
     assert any("k_cett_between" in n for n in _names(r[1])) == large
+
+
+def _stack_grid(r):
+    """[(partial outputs per layer, layers)] of the launches over several layers; None if the call ran another way."""
+    names = _names(r)
+    if not all("k_ffn_stack" in n and "persistent" not in n for n in names):
+        return None
+    return [tuple(x[1:3]) for x in r["launches"] if "k_ffn_stack_reduce" not in x[0]]
+
+
+@pytest.mark.parametrize("d,F,L,kw,want", [
+    # rounds of eight layers as whole slices (32 workgroups a layer), the thin rest as single classes
+    (4096, 11008, 8, {}, [(32, 8)]), (4096, 11008, 9, {}, [(32, 8), (256, 1)]), (4096, 11008, 11, {}, [(32, 8), (256, 3)]),
+    (4096, 11008, 12, {}, [(32, 12)]), (4096, 11008, 17, {}, [(32, 16), (256, 1)]), (4096, 11008, 32, {}, [(32, 32)]),
+    (4096, 11008, 50, {}, [(32, 48), (256, 2)]), (4096, 11008, 54, {}, [(32, 48), (32, 6)]), (4096, 11008, 5, {}, [(32, 5)]),
+    (4096, 11008, 4, {}, [(256, 4)]), (2560, 10240, 10, {"kind": "relu"}, [(32, 8), (256, 2)]), (2560, 10240, 5, {}, [(256, 5)]),
+    (2560, 10240, 12, {}, [(32, 8), (256, 4)]), (2560, 10240, 13, {}, [(32, 13)]),
+    (2048, 16384, 10, {}, [(32, 10)]), (2048, 16384, 17, {}, [(32, 16), (256, 1)]), (2048, 16384, 18, {}, [(32, 16), (256, 2)]),
+    (2048, 8192, 7, {}, [(256, 4), (256, 3)]), (1024, 4096, 17, {}, [(32, 17)]), (1024, 4096, 7, {}, [(256, 4), (256, 3)]),
+    (2048, 5504, 9, {"dtype": "f32"}, [(32, 8), (256, 1)]), (5120, 13824, 33, {}, [(32, 32), (256, 1)]),
+    # the lanes' side of the rule
+    (5120, 13824, 5, {}, None), (5120, 13824, 6, {}, [(32, 6)]), (5120, 5120, 4, {}, [(256, 4)]), (5120, 5120, 5, {"dense": True}, None),
+    (4096, 11008, 9, {"dense": True}, None), (4096, 11008, 8, {"dense": True}, [(32, 8)]), (4096, 8192, 9, {"dense": True}, [(32, 8), (256, 1)]),
+    (4096, 16384, 9, {"dense": True, "kind": "relu"}, [(32, 8), (256, 1)]), (2048, 16384, 9, {"dense": True}, None),
+    (2048, 12288, 9, {"dense": True}, [(32, 9)]), (6144, 12288, 9, {}, None), (512, 1376, 3, {"dtype": "f32"}, [(256, 3)]),
+])
+def test_batch_1_stacks_fill_their_rounds(fake, d, F, L, kw, want):
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 1, 0, 0]}, dict({"do": "stack", "d": d, "F": F, "L": L, "B": 1}, **kw)])
+    assert _stack_grid(r[1]) == want
