@@ -443,11 +443,20 @@ k_ffn_stack_reduce(const StackReduceArgs a)
     }
 }
 
+// (The non-gated family has bf16 rows of 2, 5, 8 and 10 KiB only.)
 template <int ES, int NCH>
-void launch_rows(const StackLaunch &p, dim3 grid, bool relu, hipStream_t st)
+hipError_t launch_rows(const StackLaunch &p, dim3 grid, bool relu, hipStream_t st)
 {
-    if (relu) hipLaunchKernelGGL((k_ffn_stack<ES, NCH, true>), grid, dim3(RowShape<NCH>::NW * 64), 0, st, p);
-    else hipLaunchKernelGGL((k_ffn_stack<ES, NCH, false>), grid, dim3(RowShape<NCH>::NW * 64), 0, st, p);
+    constexpr int threads = RowShape<NCH>::NW * 64;
+    if (!relu) {
+        hipLaunchKernelGGL((k_ffn_stack<ES, NCH, false>), grid, dim3(threads), 0, st, p);
+        return hipGetLastError();
+    }
+    if constexpr (ES == 2 && NCH != 4) {
+        hipLaunchKernelGGL((k_ffn_stack<ES, NCH, true>), grid, dim3(threads), 0, st, p);
+        return hipGetLastError();
+    }
+    return hipErrorNotSupported;
 }
 
 }  // namespace
@@ -519,17 +528,17 @@ hipError_t clada_stack_b1(const clada_layer *layers, int32_t L, const void *x, c
         p.F = layers[0].d_ff; p.d = d; p.chain = chain; p.dense = dense ? 1 : 0;
         p.gelu = layers[0].kind == CLADA_FFN_GEGLU ? 1 : 0;
         const dim3 grid(P, n);
+        hipError_t e;
         switch (es == 2 ? nch : 100 + nch) {
-        case 2: launch_rows<2, 2>(p, grid, relu, stream); break;
-        case 4: launch_rows<2, 4>(p, grid, relu, stream); break;
-        case 5: launch_rows<2, 5>(p, grid, relu, stream); break;
-        case 8: launch_rows<2, 8>(p, grid, relu, stream); break;
-        case 10: launch_rows<2, 10>(p, grid, relu, stream); break;
-        case 102: launch_rows<4, 2>(p, grid, relu, stream); break;
-        case 108: launch_rows<4, 8>(p, grid, relu, stream); break;
-        default: return hipErrorNotSupported;
+        case 2: e = launch_rows<2, 2>(p, grid, relu, stream); break;
+        case 4: e = launch_rows<2, 4>(p, grid, relu, stream); break;
+        case 5: e = launch_rows<2, 5>(p, grid, relu, stream); break;
+        case 8: e = launch_rows<2, 8>(p, grid, relu, stream); break;
+        case 10: e = launch_rows<2, 10>(p, grid, relu, stream); break;
+        case 102: e = launch_rows<4, 2>(p, grid, relu, stream); break;
+        case 108: e = launch_rows<4, 8>(p, grid, relu, stream); break;
+        default: e = hipErrorNotSupported;
         }
-        hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         r.partial = partial;
         r.y = (char *)y + (size_t)l0 * d * es;
