@@ -56,7 +56,7 @@ struct BatParams {
 
 // One launch runs n units: pass blockIdx.y of the tokens of layer blockIdx.z.  A call of one layer is a
 // launch of one unit; the whole-stack call runs as many layers per launch as the workspace has room for.
-constexpr int BAT_LAYERS = 48;
+constexpr int BAT_LAYERS = 48;                  // BAT_UNITS below fits
 struct BatArgs {
     BatParams p;                // of unit 0; B: the tokens of a layer
     int n_pass, per_pass;
@@ -655,25 +655,29 @@ static clada_status bat_launch(clada_ctx *ctx, BatArgs &a, int n_layers, bool re
     return CLADA_OK;
 }
 
-// The layers of a whole-stack call, as many per launch as `bytes` of scratch hold (*ran: the shape fits and did).  Three
-// launches cover them all: against three lanes of three launches per layer and pass (us per step) 180 / 307 for 24 layers of
-// 1024 x 4096 at two tokens, 395 / 466 for 18 of 2048 x 8192 at 16, 243 / 277 for 5 of 4096 x 11008 at 4, 1904 / 1928 for 32
-// of 4096 x 14336 at 8, 2152 / 2315 and 1295 / 1350 for 40 and 20 of 5120 x 13824 at two and six, 908 / 990 for 20 of
-// 5120 x 8192 at 16.  The lanes stay ahead (2903 / 2873) for 40 of 5120 x 13824 at 16: the gate/up
-// workgroups of gated 10 KiB rows have five waves, not eight, and a second unit's kernels fill the gaps of a full pass.
+// The layers of a whole-stack call in launches of up to 48 units (layer, pass of tokens), or as many layers as `bytes` of scratch
+// hold (*ran: the shape fits and did).  Three launches against three lanes of three launches per unit, us per step: 180 / 307 for
+// 24 layers of 1024 x 4096 at two tokens, 395 / 466 for 18 of 2048 x 8192 at 16, 243 / 277 for 5 of 4096 x 11008 at 4, 940 / 999
+// for 20 of 5120 x 8192 at 16, 2313 / 2415 for 40 of 5120 x 13824 at two.  What they save is ends: long stacks of large layers have
+// few of them for their size, and there a second unit's kernels in the gaps of the first one's are worth 1 - 4 % (2822 / 2718 for
+// 40 of 4096 x 16384 at 16 tokens, 5350 / 5168 for 40 of 8192 x 16384, 2952 / 2932 for 40 of 5120 x 13824; but 1492 / 1503 for 20
+// of the latter, 1829 / 1845 for 40 of 4096 x 11056 at 8 and 0.96 of the lanes' time at two tokens).  More units a launch gain
+// nothing (2809 us at 48, 3031 at 80, lanes 2928: 40 layers of 5120 x 5120 at 32 tokens).
+constexpr int BAT_UNITS = 48;
 clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int32_t L, const void *x, int32_t B,
                                  const float *tau, void *y, bool dense, char *scratch, size_t bytes, hipStream_t stream, bool *ran)
 {
     *ran = false;
     const int d = layers[0].d, F = layers[0].d_ff;
     const int n_pass = (B + 15) / 16, per = (B + n_pass - 1) / n_pass;
-    if (L < 2 || (d == 5120 && F > 8192 && per > 8 && layers[0].kind != CLADA_FFN_RELU)) return CLADA_OK;
+    const double layer_bytes = (layers[0].kind == CLADA_FFN_RELU ? 2.0 : 3.0) * F * d * 2;
+    if (L < 2 || (per > 4 && layer_bytes > 340e6 && layer_bytes * L * n_pass > 12e9)) return CLADA_OK;
     int P, CG, RG;
     if (!bat_plan(ctx, &layers[0], B - (n_pass - 1) * per, &P, &CG, &RG) || !bat_plan(ctx, &layers[0], per, &P, &CG, &RG)) return CLADA_OK;
     const size_t part = sizeof(float) * (size_t)RG * B * d;
     const size_t per_layer = part + n_pass * (sizeof(float) * 16 * (size_t)F + sizeof(int) * ((size_t)F + COOP_MAX_WGS));
     int nl = bytes < 768 ? 0 : (int)((bytes - 768) / per_layer < (size_t)L ? (bytes - 768) / per_layer : (size_t)L);
-    if (nl > BAT_LAYERS) nl = BAT_LAYERS;
+    if (nl > BAT_UNITS / n_pass) nl = BAT_UNITS / n_pass;
     if (nl < 2) return CLADA_OK;
     const int n_launch = (L + nl - 1) / nl;
     nl = (L + n_launch - 1) / n_launch;

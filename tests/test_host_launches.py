@@ -81,3 +81,22 @@ def _stack_grid(r):
 def test_batch_1_stacks_fill_their_rounds(fake, d, F, L, kw, want):
     r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 1, 0, 0]}, dict({"do": "stack", "d": d, "F": F, "L": L, "B": 1}, **kw)])
     assert _stack_grid(r[1]) == want
+
+
+def _batched_layers(r):
+    """Layers of the batched launches over several layers; None if the units went round the lanes (a layer per launch)."""
+    z = [x[3] for x in r["launches"] if "k_bat_down" in x[0]]
+    _names(r)
+    return z if z and max(z) > 1 else None
+
+
+@pytest.mark.parametrize("d,F,L,B,kw,want", [
+    (4096, 14336, 32, 8, {}, [32]), (4096, 11008, 40, 16, {}, [20, 20]), (5120, 13824, 20, 16, {}, [20]), (5120, 13824, 40, 2, {}, [40]),
+    (5120, 5120, 40, 32, {}, [20, 20]), (2048, 2048, 50, 2, {}, [25, 25]), (4096, 900, 7, 33, {}, [7]), (1024, 2048, 20, 64, {}, [7, 7, 6]),
+    # long stacks of large layers stay with the lanes
+    (5120, 13824, 40, 16, {}, None), (4096, 16384, 40, 16, {}, None), (4096, 16384, 20, 32, {}, None), (5120, 20480, 40, 16, {"kind": "relu"}, None),
+    (4096, 16384, 40, 4, {}, [20, 20]), (4096, 16384, 40, 5, {}, None), (4096, 16384, 20, 16, {"dense": True}, [20]),
+])
+def test_batched_stacks_are_launched_over_many_layers(fake, d, F, L, B, kw, want):
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, B, 0, 0]}, dict({"do": "stack", "d": d, "F": F, "L": L, "B": B}, **kw)])
+    assert _batched_layers(r[1]) == want
