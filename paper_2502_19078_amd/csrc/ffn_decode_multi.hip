@@ -241,15 +241,39 @@ hipError_t launch_tokens(const MultiParams &p, int P, bool relu, hipStream_t st)
 
 }  // namespace
 
-// Where it is the faster one (us against the generic kernel).  Several tokens: from 8 MB of weights on -- 17 / 24 (fp32 ReLU,
-// 1024 x 4096, 4 tokens), 21 / 26 (bf16, 768 x 3072, 8 tokens), 59 / 131 (bf16, 3584 x 12032, 4 tokens); a smaller layer
-// stays in the caches between the tokens (16.7 / 13.7: bf16, 512 x 2000, 8 tokens).  One token: fp32 rows above 8 KiB,
-// 75 / 106 (4096 x 11008), where the generic kernel's accumulators leave it one row in flight; not bf16 (41 / 36, 3584 x 12032).
+static void multi_passes(const clada_layer *layer, int B, int *n_pass, int *per)
+{
+    const int most = (size_t)layer->d * dtype_size(layer->dtype) > 8192 && layer->dtype == CLADA_BF16 ? 4 : 8;
+    *n_pass = (B + most - 1) / most;                         // (eight tokens of wide bf16 rows do not fit the registers)
+    *per = (B + *n_pass - 1) / *n_pass;
+}
+
+// Where it is the faster one (time over the generic kernel's, weights from HBM).  A row is requested in groups of four KiB and
+// every pass pays for 1, 2, 4 or 8 tokens, so it is the row's length and how full the passes are that decide, not the layer's
+// size (768 x 1536 and 768 x 3072 bf16: 0.81 and 0.84 at 8 tokens, 1.20 and 1.23 at 2; 1536 x 3072 and x 6144: 0.48, 0.50 and
+// 0.75, 0.85):
+//   - rows of more than 1024 values: 0.17 - 0.94; the non-gated family, whose generic kernel has one phase less, 0.25 - 0.99, but
+//     0.97 - 1.1 with two tokens up to 1280 values;
+//   - 512 < d <= 1024: fp32 0.74 - 0.97 with 3 to 8 tokens, in several passes where the row nearly fills its group (1024: 0.66 -
+//     0.96; 640 and 768: 1.02 and less from seven tokens a pass on, 1.07 - 1.1 below) and 1.07 - 1.2 with two; bf16 0.79 - 1.0
+//     with 5 to 8 tokens and full passes of eight, 0.97 - 1.24 else; non-gated fp32 0.68 - 0.95 at 4, 6 - 8 tokens and passes of
+//     eight, 0.95 - 1.23 else, bf16 0.88 - 1.5;
+//   - up to 512 values: 1.0 - 2.2;
+//   - fewer neurons than workgroups: 0.75 - 1.3;
+//   - one token: gated fp32 rows above 8 KiB, 0.43 - 0.73 (the generic kernel's accumulators leave it one row in flight); the
+//     non-gated family 0.91 - 1.10, bf16 41 / 36 us (3584 x 12032).
 bool clada_decode_multi_fits(const clada_layer *layer, int32_t B)
 {
-    const size_t rowb = (size_t)layer->d * dtype_size(layer->dtype);
-    if (B == 1) return layer->dtype == CLADA_F32 && rowb > 8192;
-    return rowb * (size_t)layer->d_ff * (layer->kind == CLADA_FFN_RELU ? 2 : 3) >= 8000000u;
+    const int d = layer->d;
+    const bool f32 = layer->dtype == CLADA_F32, relu = layer->kind == CLADA_FFN_RELU;
+    if (B == 1) return f32 && !relu && d > 2048;
+    if (layer->d_ff < 256 || d <= 512) return false;
+    int n_pass, per;
+    multi_passes(layer, B, &n_pass, &per);
+    if (d > 1024) return !relu || B >= 3 || d > 1280;
+    if (relu) return f32 && (per == 8 || per == 4 || (n_pass == 1 && per >= 6));
+    if (f32) return d > 768 ? B >= 3 : per >= 7 || (n_pass == 1 && B >= 3);
+    return per == 8 || (n_pass == 1 && per >= 5);
 }
 
 hipError_t clada_decode_multi(const clada_layer *layer, const void *x, int32_t B, const float *tau, char *y,
@@ -260,8 +284,8 @@ hipError_t clada_decode_multi(const clada_layer *layer, const void *x, int32_t B
     const int es = (int)dtype_size(layer->dtype), d = layer->d;
     const bool relu = layer->kind == CLADA_FFN_RELU;
     const bool wide = (size_t)d * es > 8192;
-    const int most = wide && es == 2 ? 4 : 8;                // (eight tokens of wide bf16 rows do not fit the registers)
-    const int n_pass = (B + most - 1) / most, per = (B + n_pass - 1) / n_pass;
+    int n_pass, per;
+    multi_passes(layer, B, &n_pass, &per);
     for (int b0 = 0; b0 < B; b0 += per) {
         MultiParams p;
         p.wg = (const char *)layer->w_gate; p.wu = (const char *)layer->w_up; p.wd = (const char *)layer->w_down;

@@ -333,10 +333,11 @@ def test_limits_of_batch_width_and_neuron_count(clada, cfg_name, d, F, B):
     ("c2", 3584, 500, 5),        # bf16 widths without a matrix-core instance
     ("c2", 4360, 400, 5),        # wide bf16 rows: passes of at most four tokens
     ("c2", 776, 3000, 17),       # three passes, 1.5 KiB rows
+    ("c2", 776, 3000, 8), ("c2", 1032, 2000, 17), ("c1", 4096, 170, 1), ("c1", 1028, 16500, 3), ("c1", 516, 300, 3),
 ])
 def test_several_tokens_per_pass_on_the_vector_units(clada, cfg_name, d, F, B):
-    """Layers from 8 MB of weights on that no other batched path takes, with thresholds spread over the tokens (one keeps
-    nothing); the dense twin and a list run of the union go through the same kernel."""
+    """Batches that no other path takes, with thresholds spread over the tokens (one keeps nothing); the dense twin and a list run
+    of the union go through the same kernel."""
     cfg, w, x = _case(cfg_name, 21, d, F, B)
     tau = _tau_for(w, x, 0.45) * np.resize(np.array([1.0, 1.8, 1e9, 0.08], np.float32), B)
     ctx, layer, xd, y, idx, cnt, mask = _run_sparse(clada, cfg, w, x, tau)

@@ -100,3 +100,23 @@ def _batched_layers(r):
 def test_batched_stacks_are_launched_over_many_layers(fake, d, F, L, B, kw, want):
     r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, B, 0, 0]}, dict({"do": "stack", "d": d, "F": F, "L": L, "B": B}, **kw)])
     assert _batched_layers(r[1]) == want
+
+
+@pytest.mark.parametrize("d,F,B,dtype,kind,multi", [
+    # rows of more than 1024 values
+    (3584, 7168, 2, "bf16", "swiglu", True), (3584, 7168, 2, "bf16", "relu", True), (1032, 300, 2, "bf16", "swiglu", True),
+    (1280, 3072, 2, "bf16", "relu", False), (1296, 3072, 2, "bf16", "relu", True), (1032, 3072, 3, "bf16", "relu", True),
+    (1536, 3072, 9, "bf16", "relu", True), (4360, 400, 5, "bf16", "swiglu", True), (1028, 2000, 2, "f32", "geglu", True),
+    # shorter rows: passes that are full enough
+    (768, 3072, 4, "bf16", "swiglu", False), (768, 3072, 8, "bf16", "swiglu", True), (768, 3072, 9, "bf16", "swiglu", False),
+    (768, 3072, 16, "bf16", "swiglu", True), (768, 3072, 8, "bf16", "relu", False), (1024, 4096, 2, "f32", "swiglu", False),
+    (1024, 4096, 3, "f32", "swiglu", True), (1024, 4096, 9, "f32", "swiglu", True), (768, 4096, 9, "f32", "swiglu", False),
+    (768, 4096, 33, "f32", "swiglu", True), (1024, 4096, 4, "f32", "relu", True), (1024, 4096, 5, "f32", "relu", False),
+    # 512 values and fewer, fewer neurons than workgroups
+    (512, 49152, 8, "bf16", "swiglu", False), (512, 2048, 4, "f32", "swiglu", False), (1536, 255, 8, "bf16", "swiglu", False),
+    # one token
+    (2052, 300, 1, "f32", "swiglu", True), (2052, 300, 1, "f32", "relu", False), (3584, 7168, 1, "bf16", "swiglu", False),
+])
+def test_decode_of_several_tokens_takes_the_faster_kernel(fake, d, F, B, dtype, kind, multi):
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, B, 0, 0]}, {"do": "decode", "d": d, "F": F, "B": B, "dtype": dtype, "kind": kind}])
+    assert any("k_ffn_multi" in n for n in _names(r[1])) == multi
