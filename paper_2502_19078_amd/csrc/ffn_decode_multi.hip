@@ -13,6 +13,11 @@
 // What bounds it: HBM, and the 256 partial outputs (17 MB written and read at four tokens of 4096).  A 4096 x 11008 fp32
 // layer at sparsity 0.45, union of independent tokens: 107 us at four tokens (526 MB: 4.9 TB/s), 132 us at eight; the generic
 // kernel, one token per grid row, reads the weights once per token and takes 394 and 772 us.
+//
+// Arithmetic.  fp32: one chain of fmaf per lane and a fixed tree over the wave for the dots; the kept neurons of a workgroup are
+// one chain per column, where the generic kernel folds eight waves' shorter chains (error of that layer at four tokens against
+// 64 bits: 2.58e-7 here, 2.48e-7 there).  bf16 dots: v_dot2_f32_bf16, which keeps subnormal inputs, products and sums, and adds
+// both products with one rounding (rms error over random operands 2.7e-8, two fmaf 2.9e-8).
 #include "clada_internal.h"
 
 namespace {

@@ -489,3 +489,33 @@ def test_rows_of_12_and_16_kib_on_the_split_d_kernel(clada, d, F, q):
         assert_close_y(to_np(yd), oracle.dense_decode(*w, x), TOL_Y[cfg.dtype], f"dense twin decode.b1={b1}")
     assert all(np.array_equal(m, masks[0]) for m in masks)
     assert not ctx.device_fault()
+
+
+@pytest.mark.parametrize("d,B", [(1032, 2), (3584, 5), (776, 8)])
+def test_bf16_dots_of_the_vector_kernel_keep_subnormals_and_full_precision(clada, d, B):
+    """Weights of 2^-129 and below (subnormal in bf16) against inputs of 2^60: every product counts.  W_down scaled so that the
+    outputs are ordinary numbers; 64-bit reference, bf16 outputs (2^-9 of a value, and kept sums that cancel a little)."""
+    from paper_2502_19078_amd import binding
+    F = 512
+    g = torch.Generator(device=DEV).manual_seed(d)
+    n = lambda *s: torch.randn(s, generator=g, device=DEV, dtype=torch.float64)
+    wg = (n(F, d) * 2.0 ** -129).bfloat16()
+    assert (wg != 0).float().mean() > 0.9 and wg.double().abs().max() < 2.0 ** -126
+    wd = (n(F, d) * 2.0 ** 60).bfloat16()
+    x = (n(B, d) * 2.0 ** 60).bfloat16()
+    b_in = torch.zeros(F, device=DEV)
+    if d > 1280:                                             # the non-gated family: y is linear in the activation
+        layer = clada.Layer(wg, None, wd, kind=binding.RELU, b_in=b_in, b_out=None)
+        up = None
+    else:                                                    # gated: SiLU(g) = g / 2 for such a g
+        up = (n(F, d) * 0.02).bfloat16()
+        wd = (n(F, d)).bfloat16()
+        layer = clada.Layer(wg, up, wd)
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, B, 0, 0))
+    y = clada.sparse_ffn_decode(ctx, layer, x, torch.zeros(B, device=DEV))
+    gd = x.double() @ wg.double().t()
+    h = torch.clamp_min(gd, 0.0) if up is None else 0.5 * gd * (x.double() @ up.double().t())
+    want = h @ wd.double()
+    assert want.abs().min() > 0 and torch.isfinite(y.float()).all()
+    err = (y.double() - want).norm(dim=1) / want.norm(dim=1)
+    assert float(err.max()) < 4e-3, err
