@@ -1439,27 +1439,34 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
     // tiles, 91 / 106 at 256, 157 / 119 at 258, 167 / 120 at 344, 258 / 248 at 688; non-gated, d = 2560: 50 / 85 at 240,
     // 79 / 75 at 320, 119 / 79 at 640).
     const bool wide = wide_ok && (tile_mode == 2 || (tile_mode == 0 && T > 128 && total > (num_cu > 0 ? num_cu : 256)));
-    // One workgroup fills a compute unit: with 32 or more units left over (prefixes of some hundred tokens) they take the
-    // norms of W_down along, instead of a second pass over it (7B layer, 512 tokens: k_prefix_reduce 16.5 -> 4.5 us).
+    // One workgroup fills a compute unit, and the units left over take the norms of W_down along, instead of a second pass over it
+    // (7B layer, 512 tokens: k_prefix_reduce 16.5 -> 4.5 us), if they are done by the time the tiles are: a wave takes a row in
+    // 0.8 (512 wide) to 2.5 us (8192), so `most` rows a wave.  With norms / without, us: 128-token tiles 88.9 / 98.1 at 48 rows a
+    // wave (64 units spare, 4096 x 12288), 152 / 113 at 112 (32, 4096 x 14336), 90 / 45 at 112 (1024 x 14336); 256-token tiles
+    // 0.94 - 0.97 up to 57 rows from 1024 columns on, 1.04 at 48 of 512, 1.14 at 69 of 1024; one operand 0.87 at 35 rows of 2560,
+    // 1.02 at 48, 1.08 at 35 of 1024, 0.84 at 48 of 4096.
     if (has_norm2) *has_norm2 = false;
-    auto with_norms = [&](int blocks) -> int {
+    auto with_norms = [&](int blocks, int most, int cap) -> int {
+        if (most > cap) most = cap;
+        const int spare = num_cu - blocks;
         g.gemm_blocks = blocks;
-        g.norm_blocks = wnorm2 && has_norm2 && num_cu - blocks >= 32 ? num_cu - blocks : 0;
+        g.norm_blocks = wnorm2 && has_norm2 && spare > 0 && F <= 4 * spare * most ? spare : 0;
         if (g.norm_blocks) *has_norm2 = true;
         return blocks + g.norm_blocks;
     };
+    const int most_wide = 24 + d / 32, most_two = 16 + d / 64, most_one = 20 + d / 128;
     if (wide && relu) {                                     // one GEMM over 256-neuron tiles
         const int n_tn2 = (F + 2 * BN - 1) / (2 * BN);
         const int blocks = n_tmw % 8 == 0 ? n_tmw * ((n_tn2 + 3) / 4 * 4) : n_tmw * n_tn2;
-        hipLaunchKernelGGL(k_prefix_gateup_bf16_wide<true>, dim3(with_norms((blocks + 7) / 8 * 8)), dim3(256), 0, stream, g);
+        hipLaunchKernelGGL(k_prefix_gateup_bf16_wide<true>, dim3(with_norms((blocks + 7) / 8 * 8, most_wide, 57)), dim3(256), 0, stream, g);
     }
     else if (wide) {
         const int blocks = n_tmw % 8 == 0 ? n_tmw * ((g.n_tn + 3) / 4 * 4) : n_tmw * g.n_tn;
-        hipLaunchKernelGGL(k_prefix_gateup_bf16_wide<false>, dim3(with_norms((blocks + 7) / 8 * 8)), dim3(256), 0, stream, g);
+        hipLaunchKernelGGL(k_prefix_gateup_bf16_wide<false>, dim3(with_norms((blocks + 7) / 8 * 8, most_wide, 57)), dim3(256), 0, stream, g);
     }
     else if (es == 4) hipLaunchKernelGGL(k_prefix_gateup<4>, dim3(grid), dim3(256), 0, stream, g);
-    else if (d % 64 == 0 && relu) hipLaunchKernelGGL(k_prefix_gateup_bf16<1>, dim3(with_norms((total_blk + 7) / 8 * 8)), dim3(256), 0, stream, g);
-    else if (d % 64 == 0) hipLaunchKernelGGL(k_prefix_gateup_bf16<2>, dim3(with_norms((total_blk + 7) / 8 * 8)), dim3(256), 0, stream, g);
+    else if (d % 64 == 0 && relu) hipLaunchKernelGGL(k_prefix_gateup_bf16<1>, dim3(with_norms((total_blk + 7) / 8 * 8, most_one, 50)), dim3(256), 0, stream, g);
+    else if (d % 64 == 0) hipLaunchKernelGGL(k_prefix_gateup_bf16<2>, dim3(with_norms((total_blk + 7) / 8 * 8, most_two, 50)), dim3(256), 0, stream, g);
     else         hipLaunchKernelGGL(k_prefix_gateup<2>, dim3(grid), dim3(256), 0, stream, g);
     return hipGetLastError();
 }

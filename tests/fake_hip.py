@@ -6,7 +6,7 @@ torch): `python fake_hip.py FAKE LIB`, with a JSON list of steps on stdin, and a
   {"do": "ctx", "bytes": n}                        a new context with a workspace of n bytes (0: clada_workspace_bytes of "sizes")
   {"do": "option", "name": .., "value": ..}
   {"do": "stack" | "decode", "d", "F", "L", "B", "kind", "dtype", "dense"}
-  {"do": "calibrate", "n": ..} / {"do": "search", "d", "F", "T", "bound", "n_probes"}
+  {"do": "prefix", "d", "F", "T", "kind"} / {"do": "calibrate", "n": ..} / {"do": "search", "d", "F", "T", "bound", "n_probes"}
   {"do": "fail", "in": n} / {"do": "capturing", "on": 0 | 1}
 
 A result is {"status": .., "launches": [[kernel, gx, gy, gz, bx], ..]}."""
@@ -76,6 +76,9 @@ def _main(fake_path, lib_path):
                   else lib.clada_sparse_ffn_stack_decode(ctx, arr, s["L"], p, s["B"], p, p, None, None))
         elif do == "decode":
             st = lib.clada_sparse_ffn_decode(ctx, C.byref(layer), p, s["B"], p, p, None, None, None, None)
+        elif do == "prefix":
+            outs = (C.c_void_p * 6)(*[p] * 6)
+            st = lib.clada_prefix_stats(ctx, C.byref(layer), p, s["T"], p, outs, None)
         elif do == "calibrate":
             st = lib.clada_threshold_calibrate(ctx, p, C.c_int64(s["n"]), C.c_float(0.45), p, None)
         elif do == "search":

@@ -120,3 +120,20 @@ def test_batched_stacks_are_launched_over_many_layers(fake, d, F, L, B, kw, want
 def test_decode_of_several_tokens_takes_the_faster_kernel(fake, d, F, B, dtype, kind, multi):
     r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, B, 0, 0]}, {"do": "decode", "d": d, "F": F, "B": B, "dtype": dtype, "kind": kind}])
     assert any("k_ffn_multi" in n for n in _names(r[1])) == multi
+
+
+@pytest.mark.parametrize("d,F,T,kind,tiles,spare", [
+    # gated, 128-token tiles (2 x neurons / 128), the units that are left take the norms of at most 16 + d / 64 rows a wave
+    (4096, 11008, 129, "swiglu", 176, 80), (4096, 12288, 256, "swiglu", 192, 64), (4096, 14336, 129, "swiglu", 224, 0),
+    (1024, 14336, 200, "swiglu", 224, 0), (1024, 12288, 200, "swiglu", 192, 0), (1024, 10240, 200, "swiglu", 160, 96),
+    (5120, 13824, 129, "swiglu", 216, 0),
+    # 256-token tiles, 24 + d / 32 rows, at most 57
+    (4096, 11008, 512, "swiglu", 176, 80), (4096, 14336, 512, "swiglu", 224, 0), (512, 12288, 300, "swiglu", 192, 0),
+    (512, 11264, 300, "swiglu", 176, 80), (5120, 13824, 384, "swiglu", 216, 0),
+    # the non-gated family: one operand, 20 + d / 128 rows; tiles of 256 tokens x 256 neurons
+    (2560, 10240, 129, "relu", 160, 96), (2560, 12288, 129, "relu", 192, 0), (4096, 12288, 129, "relu", 192, 64),
+    (2048, 13312, 513, "relu", 160, 96),
+])
+def test_prefill_norms_on_spare_units_only_where_they_are_done_in_time(fake, d, F, T, kind, tiles, spare):
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 0, T, 0]}, {"do": "prefix", "d": d, "F": F, "T": T, "kind": kind}])
+    assert [x[1] for x in r[1]["launches"] if "k_prefix_gateup" in x[0]] == [tiles + spare]
