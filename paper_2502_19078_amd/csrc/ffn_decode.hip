@@ -1644,14 +1644,34 @@ hipError_t launch_stack(clada_ctx *ctx, const StackParams &p, int P, bool dense,
 // Lanes of the whole-stack calls: lane 0 is the caller's stream, the others belong to the context.  lanes_fork
 // makes the further lanes wait for what the caller's stream holds so far, lanes_join makes the caller's stream
 // wait for them; both are events, so a capture of the caller's stream takes the lanes in.
-hipError_t lanes_fork(clada_ctx *ctx, int n_lanes, hipStream_t stream)
+constexpr int MAX_LANES = 3;
+hipError_t lanes_create(clada_ctx *ctx)
 {
-    if (n_lanes < 2) return hipSuccess;
     hipError_t e;
-    for (int i = 0; i < n_lanes - 1; ++i)
+    for (int i = 0; i < MAX_LANES - 1; ++i)
         if (!ctx->lane_stream[i] && (e = hipStreamCreateWithFlags(&ctx->lane_stream[i], hipStreamNonBlocking)) != hipSuccess) return e;
     for (int i = 0; i < 4; ++i)
         if (!ctx->ev_lane[i] && (e = hipEventCreateWithFlags(&ctx->ev_lane[i], hipEventDisableTiming)) != hipSuccess) return e;
+    return hipSuccess;
+}
+
+// The first call in mode 3 makes the lanes, whichever way its own shape takes: a later one may be a capture, and need them.
+hipError_t lanes_first_call(clada_ctx *ctx, hipStream_t stream)
+{
+    if (ctx->ev_lane[3]) return hipSuccess;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();                             // (the launches will tell)
+        return hipSuccess;
+    }
+    return cap == hipStreamCaptureStatusNone ? lanes_create(ctx) : hipSuccess;
+}
+
+hipError_t lanes_fork(clada_ctx *ctx, int n_lanes, hipStream_t stream)
+{
+    if (n_lanes < 2) return hipSuccess;
+    hipError_t e = lanes_create(ctx);
+    if (e != hipSuccess) return e;
     if ((e = hipEventRecord(ctx->ev_lane[0], stream)) != hipSuccess) return e;
     for (int i = 0; i < n_lanes - 1; ++i)
         if ((e = hipStreamWaitEvent(ctx->lane_stream[i], ctx->ev_lane[0], 0)) != hipSuccess) return e;
@@ -1758,6 +1778,7 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
     // Counts per layer need the flag arrays and the list kernel of the per-layer call, so a call that asks
     // for them runs the per-layer calls below.
     const int smode = ctx->opt_decode_stack;
+    if (smode == 3) CLADA_CHECK_HIP(ctx, lanes_first_call(ctx, stream));
     const bool own_launches = B == 1 && smode >= 2 && ctx->opt_decode_b1 >= 1 && !n_active && (d * es) % 1024 == 0 &&
                               b1_shape_ok(es, nch, relu) && Pb == COOP_MAX_WGS && F >= Pb && ni_b <= 1024 && L >= 2;
     if (own_launches && smode == 3 && clada_stack_b1_fits(&layers[0], L, dense)) {

@@ -9,7 +9,7 @@ torch): `python fake_hip.py FAKE LIB`, with a JSON list of steps on stdin, and a
   {"do": "prefix", "d", "F", "T", "kind"} / {"do": "calibrate", "n": ..} / {"do": "search", "d", "F", "T", "bound", "n_probes"}
   {"do": "fail", "in": n} / {"do": "capturing", "on": 0 | 1}
 
-A result is {"status": .., "launches": [[kernel, gx, gy, gz, bx], ..]}."""
+A result is {"status": .., "launches": [[kernel, gx, gy, gz, bx], ..], "created": streams and events}."""
 import ctypes as C
 import json
 import os
@@ -90,7 +90,8 @@ def _main(fake_path, lib_path):
         else:
             raise ValueError(do)
         rows = [r.split() for r in fake.fake_take_log().decode().splitlines()]
-        out.append({"status": st, "launches": [[r[0]] + [int(v) for v in r[1:]] for r in rows]})
+        out.append({"status": st, "launches": [[r[0]] + [int(v) for v in r[1:]] for r in rows],
+                    "created": fake.fake_take_streams() + fake.fake_take_events()})
     json.dump(out, sys.stdout)
 
 

@@ -15,6 +15,7 @@ static std::map<const void *, std::string> &names() { static std::map<const void
 static std::string g_log, g_out;
 static long g_fail_in = -1;          // launches until one is refused, or -1
 static int g_capture;                // what hipStreamIsCapturing answers
+static int g_streams, g_events;      // created since they were last asked for
 static hipError_t g_last = hipSuccess;
 static struct { dim3 grid, block; size_t lds; hipStream_t st; } g_cfg;
 
@@ -33,6 +34,8 @@ extern "C" {
 const char *fake_take_log(void) { g_out.swap(g_log); g_log.clear(); return g_out.c_str(); }
 void fake_fail_launch(long n) { g_fail_in = n; }
 void fake_capturing(int on) { g_capture = on; }
+int fake_take_streams(void) { const int n = g_streams; g_streams = 0; return n; }
+int fake_take_events(void) { const int n = g_events; g_events = 0; return n; }
 
 // what the compiler emits around kernels
 void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
@@ -55,11 +58,11 @@ hipError_t hipMalloc(void **p, size_t n) { return posix_memalign(p, 256, n ? n :
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
 hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
-hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { static char h; *s = (hipStream_t)&h; return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { static char h; ++g_streams; *s = (hipStream_t)&h; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = g_capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t *e) { static char h; *e = (hipEvent_t)&h; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { static char h; ++g_events; *e = (hipEvent_t)&h; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }

@@ -83,6 +83,19 @@ def test_batch_1_stacks_fill_their_rounds(fake, d, F, L, kw, want):
     assert _stack_grid(r[1]) == want
 
 
+@pytest.mark.parametrize("first", [{"d": 4096, "F": 11008, "L": 8, "B": 1}, {"d": 4096, "F": 11008, "L": 8, "B": 4}, {"d": 1024, "F": 300, "L": 1, "B": 1}])
+def test_first_stack_call_makes_the_lanes_whichever_way_it_takes(fake, first):
+    """A capture must not have to create streams: not one that needs the lanes after a first call that did not."""
+    lanes = [{"d": 6144, "F": 12288, "L": 5, "B": 1}, {"d": 5120, "F": 13824, "L": 40, "B": 16}]
+    r = run_steps(fake, [{"do": "ctx", "sizes": [6144, 13824, 16, 0, 0]}, dict({"do": "stack"}, **first), {"do": "capturing", "on": 1}]
+                  + [dict({"do": "stack"}, **kw) for kw in lanes])
+    assert r[1]["created"] == 6 and r[3]["created"] == r[4]["created"] == 0
+    assert len(r[3]["launches"]) == 2 * 5 and _batched_layers(r[4]) is None        # (they do go round the lanes)
+    # a first call that is captured creates nothing it does not need
+    r = run_steps(fake, [{"do": "ctx", "sizes": [4096, 11008, 4, 0, 0]}, {"do": "capturing", "on": 1}, dict({"do": "stack"}, **first)])
+    assert r[2]["created"] == 0
+
+
 def _batched_layers(r):
     """Layers of the batched launches over several layers; None if the units went round the lanes (a layer per launch)."""
     z = [x[3] for x in r["launches"] if "k_bat_down" in x[0]]
