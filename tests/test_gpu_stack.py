@@ -1,7 +1,8 @@
 """GPU parity: the whole-stack calls against the per-layer calls, bit for bit, and against the fp64 oracle.
-Modes of the call (option decode.stack): 3 = lanes, the default (the layers go round two or three streams);
-2 = chained launches (every layer's kernel also sums the previous layer's partial outputs); 1 = one
-persistent launch for the L layers; 0 = the per-layer calls."""
+Modes of the call (option decode.stack): 3, the default = launches over many layers, or lanes (the layers go
+round two or three streams), by shape; 2 = chained launches (every layer's kernel also sums the previous
+layer's partial outputs); 1 = one persistent launch for the L layers; 0 = the per-layer calls.  Which of the
+two ways a row of the lists below takes is asserted in test_host_launches.py."""
 import numpy as np
 import pytest
 import torch
@@ -72,7 +73,7 @@ def test_stack_call_is_the_per_layer_calls_bit_for_bit(clada, mode, cfg_name, d,
     tau[L - 1] *= 1.92                                  # thresholds differ per layer
     xd, td = to_dev(x, cfg.dtype), torch.from_numpy(tau).to(DEV)
     y_ref, cnt_ref = [], []
-    if mode >= 3:                                       # the two-lane modes run the unbalanced instances: those are their bits
+    if mode >= 3:                                       # mode 3 runs the unbalanced instances: those are its bits
         ctx.set_option("decode.b1", 2)
     for l in range(L):
         yl, _, cl, _ = clada.sparse_ffn_decode(ctx, layers[l], xd[l:l + 1].contiguous(), td[l:l + 1].contiguous(), want_lists=True)
@@ -144,7 +145,7 @@ def test_stack_call_rejects_mixed_layers_and_bad_arguments(clada):
         ctx.check(ctx._lib.clada_sparse_ffn_stack_decode(ctx._h, None, 2, xd.data_ptr(), 1, td.data_ptr(), xd.data_ptr(), None, None))
 
 
-@pytest.mark.parametrize("mode", [1, 2])      # (the lanes run kernels that wait for nobody)
+@pytest.mark.parametrize("mode", [1, 2])      # (mode 3 runs kernels that wait for nobody)
 def test_bounded_waits_of_the_stack_kernel_give_up_cleanly(clada, mode):
     """Spin limit forced to zero from the host: every workgroup still runs to its end, the outputs are NaN
     and the context reports the fault."""
@@ -163,27 +164,32 @@ def test_bounded_waits_of_the_stack_kernel_give_up_cleanly(clada, mode):
         assert torch.isnan(bad.float()).all()
 
 
-def test_stack_call_modes_agree_and_replay_from_a_graph(clada):
-    """The modes give the same bits; captured calls (lanes: a fork and a join inside the capture; chained
-    launches) replay correctly on changed inputs."""
-    cfg, ws, layers, x = _stack(clada, "c2", 4096, 11008, 4, seed=26)
-    ctx = clada.Context(0, clada.workspace_bytes(4096, 11008, 1, 0, 0))
+# one launch over the layers; lanes
+GRAPH_SHAPES = [(4096, 11008, 4), (6144, 1500, 5)]
+
+
+@pytest.mark.parametrize("d,F,L", GRAPH_SHAPES)
+def test_stack_call_modes_agree_and_replay_from_a_graph(clada, d, F, L):
+    """The modes give the same bits; captured calls (one launch over the layers; lanes: a fork and a join inside
+    the capture; chained launches) replay correctly on changed inputs."""
+    cfg, ws, layers, x = _stack(clada, "c2", d, F, L, seed=26)
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 1, 0, 0))
     ctx.set_option("decode.b1", 2)                      # no balancing: every mode then adds in the same order
-    xd, td = to_dev(x, cfg.dtype), torch.full((4,), 0.25, dtype=torch.float32, device=DEV)
+    xd, td = to_dev(x, cfg.dtype), torch.full((L,), 0.25, dtype=torch.float32, device=DEV)
     y2, cnt = clada.sparse_ffn_stack_decode(ctx, layers, xd, td, want_counts=True)
-    y2 = clada.sparse_ffn_stack_decode(ctx, layers, xd, td).clone()          # default: lanes
+    y2 = clada.sparse_ffn_stack_decode(ctx, layers, xd, td).clone()          # default: mode 3
     for mode in (0, 1, 2):
         ctx.set_option("decode.stack", mode)
         assert torch.equal(clada.sparse_ffn_stack_decode(ctx, layers, xd, td), y2), f"mode {mode}"
     ctx.set_option("decode.stack", 3)
     ctx2 = ctx                                          # (unbalanced per-layer calls: the reference bits below)
-    for l in range(4):
+    for l in range(L):
         yl, _, cl, _ = clada.sparse_ffn_decode(ctx, layers[l], xd[l:l + 1].contiguous(), td[l:l + 1].contiguous(), want_lists=True)
         assert torch.equal(y2[l], yl[0]) and torch.equal(cnt[l], cl)
     # graph: static input and output buffers, replays with other inputs and thresholds in between eager work;
-    # lanes, and chained launches of the balanced kernel (whose call counter the chain advances itself)
+    # mode 3, and chained launches of the balanced kernel (whose call counter the chain advances itself)
     for mode, b1 in ((3, 1), (2, 1), (2, 2)):
-        ctx = clada.Context(0, clada.workspace_bytes(4096, 11008, 1, 0, 0))
+        ctx = clada.Context(0, clada.workspace_bytes(d, F, 1, 0, 0))
         ctx.set_option("decode.stack", mode)
         ctx.set_option("decode.b1", b1)
         xs, ts = xd.clone(), td.clone()
@@ -215,10 +221,12 @@ def test_stack_call_modes_agree_and_replay_from_a_graph(clada):
 # eight classes, single classes), one and several rounds of 64 neurons, neuron counts that leave classes of unequal length
 ONE_LAUNCH = [
     (1024, 4096, 8, True, "bf16"), (1024, 3001, 9, False, "bf16"), (1024, 300, 7, False, "bf16"),
-    (2048, 2300, 6, False, "bf16"), (2048, 16385, 2, False, "bf16"),
+    (2048, 2300, 6, False, "bf16"), (2048, 2300, 3, False, "bf16"), (2048, 16385, 2, False, "bf16"),
+    # single classes of more than 64 neurons
+    (1024, 16641, 3, False, "bf16"), (4096, 16385, 2, False, "bf16"), (2560, 16900, 3, True, "bf16"),
     (2560, 3333, 7, False, "bf16"), (2560, 2600, 5, True, "bf16"),
     (4096, 2817, 6, False, "bf16"), (4096, 1000, 50, True, "bf16"), (5120, 2222, 6, True, "bf16"), (5120, 2600, 5, False, "bf16"),
-    (512, 1376, 8, False, "f32"), (512, 5000, 3, True, "f32"), (2048, 3000, 6, False, "f32"),
+    (512, 1376, 8, False, "f32"), (512, 5000, 3, False, "f32"), (2048, 3000, 6, False, "f32"),
     # a thin last round in a launch of its own, of single classes; single classes in two launches
     (4096, 1030, 9, False, "bf16"), (2560, 2600, 12, True, "bf16"), (2048, 1100, 18, False, "bf16"), (1024, 1000, 7, False, "bf16"),
     (5120, 700, 51, False, "bf16"), (2048, 900, 11, False, "f32"),
@@ -232,7 +240,6 @@ def test_one_launch_over_the_layers_is_the_per_layer_calls_bit_for_bit(clada, d,
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
     g = torch.Generator(device=DEV).manual_seed(d + F + L)
     n = lambda *s, std=0.02: torch.randn(s, generator=g, device=DEV) * std
-    relu = relu and dtype == "bf16"                          # (the fp32 non-gated family has no batch-1 kernel)
     layers = []
     for _ in range(L):
         w = [n(F, d).to(dt) for _ in range(2 if relu else 3)]
@@ -258,8 +265,8 @@ def _batch_stack(clada, cfg_name, d, F, L, B, seed, shared_frac=0.5):
     return cfg, ws, layers, x
 
 
-# cfg, d, F, L, B: three lanes on the matrix-core path (one and two passes of tokens per layer, 4 and 10 KiB
-# rows, fewer units than lanes), and batches that path does not take (fp32; a width it has no instance for)
+# cfg, d, F, L, B: launches over many units of the matrix-core path (one to four passes of tokens per layer, 4, 8 and 10 KiB
+# rows, a single layer), and batches that path does not take (fp32; a width it has no instance for)
 BATCH_CASES = [
     ("c3", 4096, 3000, 5, 8),
     ("c5", 5120, 2100, 4, 16),
@@ -332,6 +339,77 @@ def test_batched_launches_over_all_units_are_the_per_layer_calls_bit_for_bit(cla
             assert torch.equal(yd[l], clada.dense_ffn_decode(ctx, layers[l], x[l])), f"dense, layer {l}"
 
 
+# d, F, L, relu, B, dense, option lane_occ2: stacks that go round the lanes.  Batch 1: rows of 12 and 16 KiB, a few 10 KiB rows
+# of large layers, dense stacks of 4 and 8 KiB rows with both kernel instances; batches: long stacks of large layers, one and
+# two passes of tokens.  Two layers' weights are listed in turn; every output row has its own input row and threshold.
+LANES = [
+    (6144, 1500, 5, False, 1, False, 1), (8192, 700, 4, False, 1, False, 1), (8192, 700, 6, False, 1, True, 1),
+    (5120, 13824, 5, False, 1, False, 1), (5120, 2600, 5, True, 1, True, 1),
+    (4096, 8200, 9, False, 1, True, 1), (4096, 8200, 9, False, 1, True, 0), (4096, 16641, 10, False, 1, True, 1),
+    (2048, 12300, 9, False, 1, True, 1), (2048, 12300, 8, False, 1, True, 0),
+    (5120, 13824, 30, False, 16, False, 1), (5120, 13824, 15, False, 20, False, 1), (8192, 16384, 16, False, 5, True, 1),
+]
+
+
+def _two_layers(clada, d, F, relu, seed):
+    from paper_2502_19078_amd import binding
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    n = lambda *s, std=0.02: torch.randn(s, generator=g, device=DEV, dtype=torch.float32) * std
+    pair = []
+    for _ in range(2):
+        w = [n(F, d).bfloat16() for _ in range(2 if relu else 3)]
+        pair.append(clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=n(F), b_out=n(d)) if relu else clada.Layer(*w))
+    return pair, n
+
+
+@pytest.mark.parametrize("d,F,L,relu,B,dense,occ2", LANES)
+def test_lanes_are_the_per_layer_calls_bit_for_bit(clada, d, F, L, relu, B, dense, occ2):
+    pair, n = _two_layers(clada, d, F, relu, d + F + L)
+    layers = (pair * L)[:L]
+    x = n(L, B, d, std=1.0).bfloat16()
+    tau = n(L, B, std=0.3).abs()
+    tau[0], tau[L - 1, 0] = 1e9, 0.0                         # a layer that keeps nothing, a token that keeps everything
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, B, 0, 0))
+    ctx.set_option("decode.b1", 2)
+    ctx.set_option("decode.lane_occ2", occ2)
+    if B == 1:
+        x, tau = x[:, 0].contiguous(), tau[:, 0].contiguous()
+    row = lambda t, l: t[l:l + 1] if B == 1 else t[l]
+    for rep in range(2):
+        y = clada.dense_ffn_stack_decode(ctx, layers, x) if dense else clada.sparse_ffn_stack_decode(ctx, layers, x, tau)
+        for l in range(L):
+            want = (clada.dense_ffn_decode(ctx, layers[l], row(x, l)) if dense
+                    else clada.sparse_ffn_decode(ctx, layers[l], row(x, l), row(tau, l)))
+            assert torch.equal(row(y, l), want), f"rep {rep} layer {l}"
+    assert not ctx.device_fault()
+
+
+def test_lanes_of_a_batch_replay_from_a_graph(clada):
+    d, F, L, B = 5120, 13824, 30, 16
+    pair, n = _two_layers(clada, d, F, False, 34)
+    layers = (pair * L)[:L]
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, B, 0, 0))
+    xd, td = n(L, B, d, std=1.0).bfloat16(), torch.full((L, B), 0.2, device=DEV)
+    xs, ys = xd.clone(), torch.empty_like(xd)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        clada.sparse_ffn_stack_decode(ctx, layers, xs, td, y=ys)
+        stream.synchronize()
+        clada.graph_begin(ctx)
+        clada.sparse_ffn_stack_decode(ctx, layers, xs, td, y=ys)
+        g = clada.graph_end(ctx)
+        for rep in range(3):
+            xs.copy_(torch.roll(xd, rep, dims=0))
+            g.launch()
+            stream.synchronize()
+            got = ys.clone()
+            for l in (0, 7, L - 1):
+                assert torch.equal(got[l], clada.sparse_ffn_decode(ctx, layers[l], xs[l], td[l])), f"replay {rep} layer {l}"
+            stream.synchronize()
+    assert not ctx.device_fault()
+
+
 def test_batched_stack_call_replays_from_a_graph(clada):
     cfg, ws, layers, x = _batch_stack(clada, "c3", 4096, 2048, 6, 8, seed=32)
     ctx = clada.Context(0, clada.workspace_bytes(4096, 2048, 8, 0, 0))
@@ -358,13 +436,14 @@ def test_batched_stack_call_replays_from_a_graph(clada):
     assert not ctx.device_fault()
 
 
-def test_stack_call_inside_a_torch_graph(clada):
-    """A capture that the library does not own (torch.cuda.graph on a side stream): the lanes join it through
+@pytest.mark.parametrize("d,F,L", GRAPH_SHAPES)
+def test_stack_call_inside_a_torch_graph(clada, d, F, L):
+    """A capture that the library does not own (torch.cuda.graph on a side stream): lanes join it through
     their fork and join events; replays on changed inputs give the eager bits."""
-    cfg, ws, layers, x = _stack(clada, "c2", 4096, 11008, 6, seed=27)
-    ctx = clada.Context(0, clada.workspace_bytes(4096, 11008, 1, 0, 0))
+    cfg, ws, layers, x = _stack(clada, "c2", d, F, L, seed=27)
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 1, 0, 0))
     xd = to_dev(x, cfg.dtype)
-    xs, ts, ys = xd.clone(), torch.full((6,), 0.25, dtype=torch.float32, device=DEV), torch.empty_like(xd)
+    xs, ts, ys = xd.clone(), torch.full((L,), 0.25, dtype=torch.float32, device=DEV), torch.empty_like(xd)
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):

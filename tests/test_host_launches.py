@@ -4,6 +4,7 @@ import shutil
 
 import pytest
 
+import test_gpu_stack
 from fake_hip import build_runtime, run_steps
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")
@@ -94,6 +95,39 @@ def test_first_stack_call_makes_the_lanes_whichever_way_it_takes(fake, first):
     # a first call that is captured creates nothing it does not need
     r = run_steps(fake, [{"do": "ctx", "sizes": [4096, 11008, 4, 0, 0]}, {"do": "capturing", "on": 1}, dict({"do": "stack"}, **first)])
     assert r[2]["created"] == 0
+
+
+def _row(mod, name):
+    return [pytest.param(*r, id="-".join(map(str, r))) for r in getattr(mod, name)]
+
+
+@pytest.mark.parametrize("d,F,L,relu,dtype", _row(test_gpu_stack, "ONE_LAUNCH"))
+def test_the_device_tests_of_one_launch_take_it(fake, d, F, L, relu, dtype):
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 1, 0, 0]}, {"do": "option", "name": "decode.b1", "value": 2}]
+                  + [{"do": "stack", "d": d, "F": F, "L": L, "B": 1, "kind": "relu" if relu else "swiglu", "dtype": dtype, "dense": x} for x in (False, True)])
+    assert _stack_grid(r[2]) is not None
+    # (the dense twin of the same row may go round the lanes: few layers of 10 KiB rows, large ones of 4 KiB)
+    assert _stack_grid(r[3]) is not None or (d, L < 6) == (5120, True) or (d, F > 12288) == (2048, True)
+
+
+@pytest.mark.parametrize("d,F,L,relu,B,dense,occ2", _row(test_gpu_stack, "LANES"))
+def test_the_device_tests_of_the_lanes_take_them(fake, d, F, L, relu, B, dense, occ2):
+    """A gate/up launch per layer and pass, of the two-per-unit instance where it is asked for and the layer is short enough."""
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, B, 0, 0]}, {"do": "option", "name": "decode.lane_occ2", "value": occ2}]
+                  + [{"do": "stack", "d": d, "F": F, "L": L, "B": B, "kind": "relu" if relu else "swiglu", "dense": dense}])
+    main = [n for n in _names(r[2]) if ("k_bat_gateup" if B > 1 else "k_ffn_decode_b1") in n]
+    assert len(main) == L * -(-B // 16) and all(x[3] == 1 for x in r[2]["launches"])
+    if B == 1:
+        two = dense and not relu and d in (2048, 4096) and occ2 == 1 and F <= 64 * 256
+        assert r[2]["created"] == 6 and len(set(main)) == 1
+        # (the instance's last template flag)
+        assert ("Lb0ELb0ELb0ELb0ELb1EEEv" in main[0]) == two, main[0]
+
+
+@pytest.mark.parametrize("d,F,L", test_gpu_stack.GRAPH_SHAPES)
+def test_the_device_tests_of_captures_take_both_ways(fake, d, F, L):
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 1, 0, 0]}, {"do": "stack", "d": d, "F": F, "L": L, "B": 1}])
+    assert (_stack_grid(r[1]) is None) == (d == 6144)
 
 
 def _batched_layers(r):
