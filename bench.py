@@ -374,7 +374,7 @@ def main():
             for name, (ts, th), reg in (("natural", (tau_s, tau_H), nat), ("indicators_off", (INF, INF), off)):
                 load_inputs(W)
                 if mode == 3:
-                    ctx.set_option("decode.b1", 2)          # the lanes run the unbalanced instances: those are their bits
+                    ctx.set_option("decode.b1", 2)          # mode 3 runs the unbalanced instances: those are its bits
                 step_body(False, ts, th, lam, gam, per_layer=True)       # per-layer calls on the same inputs: the reference bits
                 torch.cuda.synchronize()
                 ctx.set_option("decode.b1", b1_opt)
@@ -400,8 +400,8 @@ def main():
                 m["dense_ms_per_step"] = round(ms_dense_stack, 4)
             stack[mode_name] = m
         ctx.set_option("decode.stack", 3)
-        stack["what"] = ("modes of clada_sparse_ffn_stack_decode (option decode.stack).  lanes (default; value and "
-                         "ms_per_step of this line): one launch over all layers, or the layers go round two or three streams, "
+        stack["what"] = ("modes of clada_sparse_ffn_stack_decode (option decode.stack).  lanes (the default; value and ms_per_step "
+                         "of this line): launches over many layers, or the layers go round two or three streams, "
                          "so that the compute units one layer has released run the next already.  chained_launches: one stream, the kernel of "
                          "layer l also sums the partial outputs of layer l-1.  persistent_kernel: one launch walks "
                          "the L layers; slower for sparse stacks, kept for the record")
@@ -428,17 +428,32 @@ def main():
     torch.cuda.synchronize()
     ceil_gbs = min(L, 8) * F * d * es / (e0.elapsed_time(e1) * 1e-3) / 1e9
 
-    nch = d * es // 1024
-    # what the library chooses for sparse stacks: batch-1 rows of 2, 5, 8 and 10 KiB run as one launch over all layers (lanes = 1)
-    one_launch = B == 1 and d * es % 1024 == 0 and (nch in (2, 5, 8, 10) or (nch == 4 and (F <= 12288 or L >= 32)))
-    # (as do batches, save gated 10 KiB rows of more than eight tokens per pass)
-    one_launch = one_launch or (B >= 2 and not (nch == 10 and F > 8192 and -(-B // -(-B // 16)) > 8 and not relu))
-    n_lanes = 1 if (not use_stack or L < 4 or one_launch) else 3 if (B >= 2 or nch == 4) else 2
     main_kernel = ("k_ffn_decode_b1 (input rows dense + output rows of kept neurons)" if B == 1 and relu
                    else "k_ffn_decode_b1 (gate rows dense + up/down rows of kept neurons)" if B == 1
                    else "k_bat_gateup + k_bat_down (batched decode, timed as one)")
     achieved = bytes_probe / (main_us * 1e-6) / 1e9          # dominant kernel alone
     achieved_call = bytes_probe / (call_us * 1e-6) / 1e9     # whole call: main kernel + final reduction + launch gap
+    # a per-layer call with the chip to itself: its kernel by kernel-own HIP events on the timed steps' inputs, and the whole
+    # C-ABI call = that kernel + the fixed-order final reduction (k_ffn_finalize) + the launch gap between them
+    lone = {"kernel": main_kernel, "achieved": round(achieved, 1), "frac": round(achieved / HBM_PEAK_GBS, 4),
+            "bytes_per_launch": round(bytes_probe), "us_per_launch": round(main_us, 2),
+            **_traffic(args.config, B, bytes_probe, "layer"),
+            "call": {"us": round(call_us, 2), "finalize_us": round(nat["finalize_us"], 2),
+                     "achieved": round(achieved_call, 1), "frac": round(achieved_call / HBM_PEAK_GBS, 4)}}
+    # the timed step: the layers of a whole-stack call share the chip, so what counts is the rate at which they complete
+    achieved_step = bytes_layer / (step_us_per_layer * 1e-6) / 1e9
+    roofline = {"bound": "hbm",
+                "kernel": ("the kernels of clada_sparse_ffn_stack_decode in the timed step" if use_stack
+                           else "the kernels of L clada_sparse_ffn_decode calls in the timed step"),
+                "achieved": round(achieved_step, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": round(achieved_step / HBM_PEAK_GBS, 4),
+                "bytes_per_layer": round(bytes_layer), "us_per_layer": round(step_us_per_layer, 2),
+                **_traffic(args.config, B, bytes_layer, "stack" if use_stack else "layer"),
+                "in_step": {"us_per_layer": round(step_us_per_layer, 2), "achieved": round(achieved_step, 1),
+                            "frac": round(achieved_step / HBM_PEAK_GBS, 4)},
+                "per_layer_call": lone,
+                "note": ("achieved/frac, also in_step: algorithmic bytes of a layer over step time / L, the signals launch included.  "
+                         "per_layer_call: a layer's call alone on the chip (kernel-own HIP events)")}
     out = {
         "metric": "sparse-FFN decode tokens/s (7B shape, bs=1), HBM GB/s on bytes touched, speedup vs dense",
         "value": round(B * 1e3 / ms_sparse, 2),
@@ -482,7 +497,7 @@ def main():
             "call_frac": round(off["bytes_probe"] / (off["call_us"] * 1e-6) / 1e9 / HBM_PEAK_GBS, 4)},
         "regime_indicators_on": _light(on, ms_dense, ideal, B, L) if on else None,
         "regime_negative_coefficients": dict(_light(neg, ms_dense, ideal, B, L), **{"lambda": -0.80, "gamma": -0.12}) if neg else None,
-        "step_path": (f"clada_signals_threshold, then clada_sparse_ffn_stack_decode (one launch over the layers, or lanes on two or three streams) on the "
+        "step_path": (f"clada_signals_threshold, then clada_sparse_ffn_stack_decode (launches over many layers, or lanes on two or three streams) on the "
                       "L independent layers" if use_stack else "clada_signals_threshold, then L calls of clada_sparse_ffn_decode"),
         "per_layer_calls": per_layer,
         "stack_modes": stack,
@@ -494,26 +509,7 @@ def main():
                     "layer_ms_gpu_without_y": round(prefill_stats_ms, 3),
                     "tflops_layer_without_y": round(2.0 * (nmat - 1) * T * d * F / (prefill_stats_ms * 1e-3) / 1e12, 1),
                     "cett_search": cett_info},
-        "roofline": {"bound": "hbm", "kernel": main_kernel,
-                     "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "bytes_per_launch": round(bytes_probe), "us_per_launch": round(main_us, 2),
-                     **_traffic(args.config, B, bytes_probe),
-                     # the whole C-ABI call = that kernel + the fixed-order final reduction (k_ffn_finalize)
-                     # + the launch gap between them, timed with HIP events around the call
-                     "call": {"us": round(call_us, 2), "finalize_us": round(nat["finalize_us"], 2),
-                              "achieved": round(achieved_call, 1), "frac": round(achieved_call / HBM_PEAK_GBS, 4)},
-                     "us_per_layer_in_step": round(step_us_per_layer, 2),
-                     "note": ("achieved/frac: the kernel of a per-layer call with the chip to itself, timed by kernel-own HIP "
-                              "events on the timed steps' inputs (rocprofv3 row of the balanced instance at B = 1).  The "
-                              "layers of the timed step overlap (one launch over all of them, or lanes): in_step divides the "
-                              "same bytes by the interval at which layers complete, step time / L"),
-                     # the timed step itself: several layers share the chip at any time; what counts is the rate at
-                     # which they complete (step time / L, the signals launch included)
-                     "in_step": {"lanes": n_lanes,
-                                 "us_per_launch_completed": round(step_us_per_layer, 2),
-                                 "achieved": round(bytes_layer / (step_us_per_layer * 1e-6) / 1e9, 1),
-                                 "frac": round(bytes_layer / (step_us_per_layer * 1e-6) / 1e9 / HBM_PEAK_GBS, 4)}},
+        "roofline": roofline,
         "setup_s": round(time.time() - t_setup, 1),
     }
 
@@ -542,10 +538,10 @@ def main():
 
 
 def pmc_probe(cfg, args, clada, binding, synth, torch, dev):
-    """Short fixed workload for hardware-counter runs: 4 seeded layers of the configuration, 3 rounds of
-    sparse calls at three sparsities (0.45, 0.62 and 0.66), 4 dense-twin calls, 3 copies of a 256 MiB buffer
-    (the known-size transfer the FETCH_SIZE / WRITE_SIZE counters are scaled by).  Batch 1 unless --batch
-    is given (then --shared-frac applies to the tokens of the batch)."""
+    """Short fixed workload for hardware-counter runs: 8 seeded layers of the configuration, at each of three sparsities
+    (0.45, 0.62 and 0.66) 2 rounds of sparse per-layer calls and 3 whole-stack calls over the layers (all distinct: a layer
+    listed twice would be read once), 8 dense-twin calls, 3 copies of a 256 MiB buffer (the known-size transfer the
+    FETCH_SIZE / WRITE_SIZE counters are scaled by).  Batch 1 unless --batch is given (then --shared-frac applies to the tokens of the batch)."""
     d, F = cfg.d, cfg.d_ff
     B = args.batch or 1
     ctx = clada.Context(0, clada.workspace_bytes(d, F, B, cfg.T, 0))
@@ -558,7 +554,7 @@ def pmc_probe(cfg, args, clada, binding, synth, torch, dev):
             return torch.from_numpy(synth.bf16_bits(a).view(np.int16)).to(dev).view(torch.bfloat16)
         return torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(dev)
 
-    layers = [clada.Layer(*[to_dev(a) for a in synth.layer_weights(cfg, args.seed, l)]) for l in range(4)]
+    layers = [clada.Layer(*[to_dev(a) for a in synth.layer_weights(cfg, args.seed, l)]) for l in range(8)]
     x = to_dev(synth.decode_hidden(cfg, args.seed, 0, 0, B=B, shared_frac=args.shared_frac))
     # thresholds at the two sparsities from the library's own prefill statistics of layer 0
     st = clada.prefix_stats(ctx, layers[0], to_dev(synth.prefix_hidden(cfg, args.seed, 0)), want_y=False)
@@ -567,10 +563,15 @@ def pmc_probe(cfg, args, clada, binding, synth, torch, dev):
     for q in (0.45, 0.62, 0.66):
         tau = clada.threshold_calibrate(ctx, st.abs_act_pool, q).expand(B).contiguous()
         kept = []
-        for _ in range(3):
+        for _ in range(2):
             for layer in layers:
                 _, _, cnt, _ = clada.sparse_ffn_decode(ctx, layer, x, tau, want_lists=True)
                 kept.append(int(cnt[0]))
+        x8, tau8 = x.expand(8, B, d).contiguous(), tau.expand(8, B).contiguous()
+        if B == 1:
+            x8, tau8 = x8[:, 0], tau8[:, 0]
+        for _ in range(3):
+            clada.sparse_ffn_stack_decode(ctx, layers, x8, tau8)
         print(f"pmc-probe q={q}: kept per call {kept}")
     for layer in layers:
         clada.dense_ffn_decode(ctx, layer, x)
@@ -623,22 +624,22 @@ def _light(r, ms_dense, ideal, B, L):
             "step_frac_of_hbm_peak": round(r["bytes_layer"] * L / (r["ms"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
 
 
-def _traffic(config, B, bytes_per_launch):
-    """HBM bytes per launch of the dominant kernel from the committed rocprofv3 counter summary: the entry
-    whose algorithmic bytes are within 3 % of this run's (counters cannot be read inside the run), else null."""
+def _traffic(config, B, bytes_layer, call):
+    """HBM bytes per layer of the main kernels of a call ("stack" or "layer") from the committed rocprofv3 counter summary:
+    the entry whose algorithmic bytes are within 3 % of this run's (counters cannot be read inside the run), else null."""
     p = os.path.join(ROOT, "profiles", f"traffic_sparse_ffn_decode_{config}.json")
     try:
         with open(p) as f:
             entries = json.load(f)["entries"]
     except Exception:
         return {"traffic": None, "traffic_note": "no committed counter summary for this workload"}
-    entries = [e for e in entries if e.get("B", 1) == B]
+    entries = [e for e in entries if e["B"] == B and e["call"] == call]
     if entries:
-        e = min(entries, key=lambda e: abs(e["algorithmic_bytes_per_launch"] - bytes_per_launch))
-        if abs(e["algorithmic_bytes_per_launch"] - bytes_per_launch) <= 0.03 * bytes_per_launch:
-            return {"traffic": e["hbm_bytes_per_launch"],
+        e = min(entries, key=lambda e: abs(e["algorithmic_bytes_per_layer"] - bytes_layer))
+        if abs(e["algorithmic_bytes_per_layer"] - bytes_layer) <= 0.03 * bytes_layer:
+            return {"traffic": e["hbm_bytes_per_layer"],
                     "traffic_source": f"profiles/{os.path.basename(p)}: rocprofv3 FETCH_SIZE + WRITE_SIZE of a committed "
-                                      f"run at sparsity {e['rho']:.3f} ({e['algorithmic_bytes_per_launch']} algorithmic bytes)"}
+                                      f"run at sparsity {e['rho']:.3f} ({e['algorithmic_bytes_per_layer']} algorithmic bytes)"}
     return {"traffic": None, "traffic_note": "the committed counter runs are at other sparsities than this run"}
 
 
