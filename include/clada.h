@@ -72,7 +72,7 @@ const char *clada_last_error(const clada_ctx *ctx);
  * the launch allows it, 0 = the generic kernels), "decode.own_first" (1..14, neurons a
  * workgroup keeps for itself before the balanced hand-over; 0 = default),
  * "decode.wgs_per_cu" (1 or 2 workgroups per compute unit for the generic kernel),
- * "decode.stack" (how the whole-stack calls run: 3 = one launch over the layers or lanes [default], 2 = chained
+ * "decode.stack" (how the whole-stack calls run: 3 = launches over many layers or lanes [default], 2 = chained
  * launches, 1 = one persistent kernel for all layers where the shape has one, 0 = the L
  * per-layer calls; see clada_sparse_ffn_stack_decode), "decode.lane_occ2" (1 = where the lanes of
  * a batch-1 stack have a kernel instance of which two workgroups fit a compute unit, they use
@@ -170,11 +170,21 @@ clada_status clada_threshold_calibrate(clada_ctx *ctx, const float *abs_act_pool
  * is the decode call's, so the result feeds clada_threshold directly.  A token
  * whose dense output is zero counts as CETT = 0.
  * The search bisects the bit pattern of eps between 0 (cuts nothing) and +inf
- * (cuts everything) with the bracket on the device: n_probes in [1,31] probes,
- * each one masked down projection; 31 resolve the float exactly, fewer return
- * the lower, feasible end of the remaining bracket.  Where the mean is not
- * monotone in eps at the scale of single neurons the result is a boundary of
- * the feasible set, not necessarily its last one.  bound in [0,1).
+ * (cuts everything) with the bracket on the device, n_probes in [1,31] times: 31
+ * resolve the float exactly, fewer return the lower, feasible end of the
+ * remaining bracket.  Every probe is one masked down projection, save in the full
+ * search (31) of a large layer (T >= 64, T d_ff >= 2^20, d_ff >= d and >= 512,
+ * bound > 0; not bf16 layers of fewer than 2048 neurons over more than 4096
+ * tokens).  There at most ten masked projections, placed by the order statistics
+ * of a sample of the pool, close a bracket in on the threshold; the bisection
+ * answers a probe outside the bracket from its ends, as on a monotone curve, and
+ * one inside by adding the few neurons between the ends to the lower end's sums.
+ * That takes 0.4 to 0.8 of the time (so 30 probes of such a layer are slower than
+ * 31).  On a monotone curve all ways end at the same float.  Where the mean is not
+ * monotone in eps at the scale of single neurons the result is a boundary of the
+ * feasible set -- the mean at it is within the bound, at the next magnitude up it
+ * is not -- but not necessarily the last one, nor the one that the plain bisection
+ * would have met.  bound in [0,1).
  * Outputs (device): tau_base_out [1]; mean_cett_out [1] = the mean at
  * tau_base_out, or NULL.  bf16 layers round h to bf16 before the projections. */
 clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_layer *layer, const void *x_val,
@@ -251,9 +261,10 @@ clada_status clada_cognitive_signals_static(clada_ctx *ctx, const void *logits, 
  * The result is bit-reproducible from run to run (fixed summation order).
  * Paths: B = 1 with rows of whole KiB runs the row-streaming kernel (vector ALUs); bf16
  * batches of 2 and more run on the matrix cores, 16 tokens per pass, every weight row read
- * once per pass.  Other batches (fp32, other widths) of layers from 8 MB on, and fp32 rows above
- * 8 KiB at B = 1, run a vector kernel that reads every row once per pass of up to eight tokens;
- * the rest runs a generic kernel that works through the tokens one by one. */
+ * once per pass.  Other batches (fp32, other widths) of rows longer than 1024 values, shorter
+ * ones down to 512 where the passes are full enough, and gated fp32 rows above 8 KiB at B = 1,
+ * run a vector kernel that reads every row once per pass of up to eight tokens (256 neurons and
+ * more); the rest runs a generic kernel that works through the tokens one by one. */
 clada_status clada_sparse_ffn_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
                                      int32_t B, const float *tau_final, void *y,
                                      int32_t *active_idx, int32_t *n_active,
@@ -272,16 +283,19 @@ clada_status clada_dense_ffn_decode(clada_ctx *ctx, const clada_layer *layer, co
  * future-work paragraphs leave open; this is the second.  Knowing the whole stack, the
  * library can hide what every per-layer call pays: the start-up of a kernel, its ragged
  * end, and the launch of the final reduction.  Option "decode.stack" chooses how:
- *   3 (default)  at batch 1, where it is the fastest (rows of 2, 4, 5, 8 and 10 KiB, fp32
- *                rows of 2 and 8 KiB, by size): one launch over all layers on hip_stream, whose
- *                workgroups follow each other without a gap, and one reduction launch.
- *                Otherwise lanes: the layers go round two or three streams -- hip_stream and streams
+ *   3 (default)  at batch 1, for rows of 2, 4, 5, 8 and 10 KiB and fp32 rows of 2 and 8
+ *                KiB: launches over many layers on hip_stream (all of them, up to 48), whose
+ *                workgroups follow each other without a gap, each with a reduction launch;
+ *                layers beyond a multiple of eight may go in a launch of their own.
+ *                Lanes for the rest (rows of 12 and 16 KiB; fewer than six layers of 10 KiB
+ *                rows, dense or above 400 MB a layer; dense gated stacks of large 4 and
+ *                8 KiB layers): the layers go round two streams -- hip_stream and one
  *                that the context owns (default priority), forked and joined by events
  *                inside the call.  To the caller the call is ordered on hip_stream like any
  *                other, and a stream capture of hip_stream records all lanes.  The compute
  *                units that layer l has released run layer l+1 already; where the kernel
- *                has an instance of which two workgroups fit a compute unit (rows of 4 KiB,
- *                dense stacks with 8 KiB), workgroups of different layers share every unit.  The lanes use
+ *                has an instance of which two workgroups fit a compute unit (dense, rows of
+ *                4 and 8 KiB), workgroups of different layers share every unit.  Both ways use
  *                the kernels without cross-workgroup balancing (kernels that wait for
  *                their own workgroups must not share the chip).
  *   2            chained launches on hip_stream: the kernel of layer l also sums the
@@ -297,12 +311,13 @@ clada_status clada_dense_ffn_decode(clada_ctx *ctx, const clada_layer *layer, co
  * kernels' order of summation.  For B = 1, modes 2 and 3 need the batch-1 kernel's shapes
  * (rows of whole KiB), 256 compute units or more and n_active = NULL.  For B >= 2 there is
  * mode 3 only, where the matrix-core path applies (bf16, its widths) and n_active = NULL: its
- * kernels run over all units (layer, pass of up to 16 tokens) in one launch each, as many
- * layers at a time as the workspace holds, or (gated layers of 10 KiB rows, more than eight
- * tokens per pass) the units go round three lanes.  Every mode falls back to mode 0 where it does not apply.  The remarks on clada_device_fault apply to modes 0 - 2
+ * kernels run over up to 48 units (layer, pass of up to 16 tokens) in one launch each, or as
+ * many layers as the context's workspace has room for; long stacks of large layers (above
+ * 340 MB each and 12 GB a step, more than four tokens per pass) go round three lanes unit by
+ * unit.  Every mode falls back to mode 0 where it does not apply.  The remarks on clada_device_fault apply to modes 0 - 2
  * (balanced kernels wait, bounded, for their own workgroups).  A context serves one call
  * at a time, on whatever stream.  The first call in mode 3 creates the context's lane streams
- * and events: make it before hip_stream is captured.  clada_dense_ffn_stack_decode is the
+ * and events, whichever way it takes: make it before hip_stream is captured.  clada_dense_ffn_stack_decode is the
  * dense twin. */
 clada_status clada_sparse_ffn_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t L,
                                            const void *x, int32_t B, const float *tau_final, void *y,
