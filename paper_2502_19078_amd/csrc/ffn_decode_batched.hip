@@ -28,6 +28,7 @@
 //     A-fragments (two MFMAs), so the down projection keeps ~fp32 accuracy of h.
 //   kernel C: k_ffn_finalize adds the R partials in fixed order.
 #include <atomic>
+#include <type_traits>
 
 #include "clada_internal.h"
 
@@ -54,8 +55,10 @@ struct BatParams {
     int row0, rows;             // this unit's first row of the launch's tokens, and their number (stride of the partials)
 };
 
-// One launch runs n units: pass blockIdx.y of the tokens of layer blockIdx.z.  A call of one layer is a
-// launch of one unit; the whole-stack call runs as many layers per launch as the workspace has room for.
+// A launch of the whole-stack call runs n units, pass blockIdx.y of the tokens of layer blockIdx.z, as many layers as the workspace
+// has room for (BatArgs).  A launch of one unit has kernels of its own, which take BatParams as it stands: through BatArgs, whose
+// arrays are a second trip to the kernel arguments, a lone call took 0.3 - 0.8 us longer (16.7 / 17.0 at four tokens of 1024 x 4096,
+// 26.4 / 26.9 at two of 3072 x 7674 ReLU, 28.9 / 29.3 at 15 of 2048 x 5792, 100.8 / 101.7 at 25 of 5120 x 10272 ReLU).
 constexpr int BAT_LAYERS = 48;                  // BAT_UNITS below fits
 struct BatArgs {
     BatParams p;                // of unit 0; B: the tokens of a layer
@@ -63,9 +66,11 @@ struct BatArgs {
     const char *wg[BAT_LAYERS], *wu[BAT_LAYERS], *wd[BAT_LAYERS];
     const float *b_in[BAT_LAYERS];
 };
-// (read through the kernel-argument segment: scalar loads at the unit's index)
-__device__ __forceinline__ BatParams bat_unit(const __attribute__((address_space(4))) BatArgs *a)
+__device__ __forceinline__ BatParams bat_unit(const BatParams &p) { return p; }
+__device__ __forceinline__ BatParams bat_unit(const BatArgs &)
 {
+    // (read through the kernel-argument segment: scalar loads at the unit's index)
+    const auto *a = (const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     BatParams p;
     __builtin_memcpy(&p, &a->p, sizeof(p));
     const int layer = blockIdx.z, unit = layer * gridDim.y + blockIdx.y, t0 = blockIdx.y * a->per_pass;
@@ -100,11 +105,11 @@ constexpr int MAX_TILES = 4;    // 16-neuron tiles per workgroup in kernel A (on
 // indices are plain arithmetic on the run's start (fewer registers: the 10 and 16 KiB rows need that).
 // RELU: the non-gated family (gate tiles only).  A template flag: as a run-time one it cost the
 // 10 and 16 KiB rows ~25 registers and pushed them into scratch (52 -> 68 us at the 13B shape).
-template <int KSTEPS, int NW, bool DENSE, bool LIST = false, bool RELU = false>
+template <int KSTEPS, int NW, bool DENSE, bool LIST, bool RELU, class Args>
 __global__ void __launch_bounds__(NW * 64)
-k_bat_gateup(const BatArgs)
+k_bat_gateup(const Args args)
 {
-    const BatParams p = bat_unit((const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr());
+    const BatParams p = bat_unit(args);
     static_assert(!LIST || DENSE, "a list run keeps every listed neuron");
     static_assert(NW >= 4 && NW <= 8, "the tile reductions run on waves 0..3");
     __shared__ float s_part[2][NW][256];
@@ -351,10 +356,11 @@ constexpr int DN_TILE_BYTES = 32 * DN_PITCH;    // one wave's staging tile: 32 n
 constexpr int DN_MAX_ROWS = 2048;               // union neurons per row group
 constexpr int DN_MAX_WGS = 64;                  // gate/up workgroups per row group
 
+template <class Args>
 __global__ void __launch_bounds__(512, 4)
-k_bat_down(const BatArgs)
+k_bat_down(const Args args)
 {
-    const BatParams p = bat_unit((const __attribute__((address_space(4))) BatArgs *)__builtin_amdgcn_kernarg_segment_ptr());
+    const BatParams p = bat_unit(args);
     extern __shared__ __align__(16) unsigned char smem_dn[];
     unsigned char *s_tile = smem_dn;                                    // [8][DN_TILE_BYTES], later the fold buffers
     int *s_rows = reinterpret_cast<int *>(smem_dn + 8 * DN_TILE_BYTES); // [DN_MAX_ROWS]
@@ -621,17 +627,21 @@ size_t clada_ws_decode_batched_partial(int32_t d)
     return align_up(sizeof(float) * 64 * 16 * (size_t)d, 256);
 }
 
-// Launches the two kernels for the units of n_layers layers.
-static clada_status bat_launch(clada_ctx *ctx, BatArgs &a, int n_layers, bool relu, bool dense, hipStream_t stream)
+// Launches the two kernels for n_layers layers in n_pass passes of tokens: args are BatArgs, or BatParams p for a single unit
+// (the only one that may have a list).
+template <class Args>
+static clada_status bat_launch(clada_ctx *ctx, const Args &args, const BatParams &p, int n_pass, int n_layers, bool relu, bool dense,
+                               hipStream_t stream)
 {
-    const int d = a.p.d, P = a.p.P;
-    const bool list = a.p.list != nullptr;
-    const dim3 grid(P, a.n_pass, n_layers);
-#define CLADA_BAT_LAUNCH(KS, NW, RELU)                                                                                    \
-    {                                                                                                                      \
-        if (list)       hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, true, RELU>), grid, dim3(NW * 64), 0, stream, a);   \
-        else if (dense) hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, false, RELU>), grid, dim3(NW * 64), 0, stream, a);  \
-        else            hipLaunchKernelGGL((k_bat_gateup<KS, NW, false, false, RELU>), grid, dim3(NW * 64), 0, stream, a); \
+    constexpr bool LONE = std::is_same_v<Args, BatParams>;
+    const int d = p.d;
+    const bool list = p.list != nullptr;
+    const dim3 grid(p.P, n_pass, n_layers);
+#define CLADA_BAT_LAUNCH(KS, NW, RELU)                                                                                                \
+    {                                                                                                                                  \
+        if (list)       hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, LONE, RELU, Args>), grid, dim3(NW * 64), 0, stream, args);   \
+        else if (dense) hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, false, RELU, Args>), grid, dim3(NW * 64), 0, stream, args);  \
+        else            hipLaunchKernelGGL((k_bat_gateup<KS, NW, false, false, RELU, Args>), grid, dim3(NW * 64), 0, stream, args); \
     }
 #define CLADA_BAT_CASE(D, KS, NW)                                                                            \
     if (d == D) {                                                                                             \
@@ -644,13 +654,13 @@ static clada_status bat_launch(clada_ctx *ctx, BatArgs &a, int n_layers, bool re
 #undef CLADA_BAT_CASE
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     const size_t lds = 8 * (size_t)DN_TILE_BYTES + sizeof(int) * DN_MAX_ROWS;
-    static std::atomic<bool> attr_set{false};                           // set once per process (two first callers may both set it)
+    static std::atomic<bool> attr_set{false};                           // set once per process and kernel (two first callers may both set it)
     if (!attr_set.load(std::memory_order_relaxed)) {
-        CLADA_CHECK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_bat_down),
+        CLADA_CHECK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_bat_down<Args>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set.store(true, std::memory_order_relaxed);
     }
-    hipLaunchKernelGGL(k_bat_down, dim3(a.p.CG * a.p.RG, a.n_pass, n_layers), dim3(512), lds, stream, a);
+    hipLaunchKernelGGL(k_bat_down<Args>, dim3(p.CG * p.RG, n_pass, n_layers), dim3(512), lds, stream, args);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     return CLADA_OK;
 }
@@ -704,7 +714,7 @@ clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int3
             a.b_in[l] = s.b_in;
             bias = bias || (relu && s.b_out);
         }
-        const clada_status st = bat_launch(ctx, a, n, relu, dense, stream);
+        const clada_status st = bat_launch(ctx, a, p, n_pass, n, relu, dense, stream);
         if (st != CLADA_OK) return st;
         char *y0 = (char *)y + row * d * 2;
         if (!bias) {
@@ -734,22 +744,19 @@ clada_status clada_decode_batched(clada_ctx *ctx, const clada_layer *layer, cons
     int P, CG, RG;
     if (!bat_plan(ctx, layer, B, &P, &CG, &RG)) return CLADA_OK;
 
-    BatArgs a;
-    memset(&a, 0, sizeof(a));
-    BatParams &p = a.p;
-    a.n_pass = 1; a.per_pass = B;
-    a.wg[0] = (const char *)layer->w_gate; a.wu[0] = (const char *)layer->w_up; a.wd[0] = (const char *)layer->w_down;
-    a.b_in[0] = layer->b_in;
+    BatParams p;
+    p.wg = (const char *)layer->w_gate; p.wu = (const char *)layer->w_up; p.wd = (const char *)layer->w_down;
+    p.b_in = layer->b_in;
     p.x = (const char *)x; p.tau = tau;
     p.hbuf = reinterpret_cast<float *>(scratch);
     p.ulist = reinterpret_cast<int *>(scratch + align_up(sizeof(float) * 16 * (size_t)F, 256));
     p.ucnt = reinterpret_cast<int *>(scratch + align_up(sizeof(float) * 16 * (size_t)F, 256) + align_up(sizeof(int) * (size_t)F, 256));
     p.keep = keep; p.partial = partial;
-    p.d = d; p.F = F; p.B = B; p.P = P; p.RG = RG; p.CG = CG; p.rows = B;
+    p.d = d; p.F = F; p.B = B; p.P = P; p.RG = RG; p.CG = CG; p.row0 = 0; p.rows = B;
     p.gelu = layer->kind == CLADA_FFN_GEGLU ? 1 : 0;
     const bool relu = layer->kind == CLADA_FFN_RELU;
     p.list = list; p.list_n = list_n;
-    const clada_status st = bat_launch(ctx, a, 1, relu, dense, stream);
+    const clada_status st = bat_launch(ctx, p, p, 1, 1, relu, dense, stream);
     if (st != CLADA_OK) return st;
     clada_launch_finalize(2, partial, RG, B, d, (char *)y, stream, relu ? layer->b_out : nullptr);
     CLADA_CHECK_HIP(ctx, hipGetLastError());

@@ -149,6 +149,16 @@ def test_batched_stacks_are_launched_over_many_layers(fake, d, F, L, B, kw, want
     assert _batched_layers(r[1]) == want
 
 
+def test_a_single_unit_has_kernels_of_its_own(fake):
+    """Lone batched calls, and the units that go round the lanes, take their parameters directly; launches over several units
+    take the arrays of their layers' weights."""
+    r = run_steps(fake, [{"do": "ctx", "sizes": [5120, 13824, 16, 0, 0]}, {"do": "decode", "d": 4096, "F": 11008, "B": 16},
+                   {"do": "stack", "d": 5120, "F": 13824, "L": 40, "B": 16}, {"do": "stack", "d": 4096, "F": 11008, "L": 3, "B": 4}])
+    for res, args in ((r[1], "BatParams"), (r[2], "BatParams"), (r[3], "BatArgs")):
+        bat = [n for n in _names(res) if "k_bat_gateup" in n or "k_bat_down" in n]
+        assert bat and all(args in n for n in bat), bat[:2]
+
+
 @pytest.mark.parametrize("d,F,B,dtype,kind,multi", [
     # rows of more than 1024 values
     (3584, 7168, 2, "bf16", "swiglu", True), (3584, 7168, 2, "bf16", "relu", True), (1032, 300, 2, "bf16", "swiglu", True),
