@@ -502,11 +502,12 @@ k_cett_between(CettState *__restrict__ sts, int launch, int taken, const float *
 
 struct CettWs {
     float *part, *pool, *rowsq_den, *rowsq_num, *den, *splitk;
+    size_t splitk_bytes;
     char *h, *hcut, *ytmp;
     CettState *state;
 };
 
-CettWs carve(char *ws, int d, int F, int T)
+CettWs carve(char *ws, size_t bytes, int d, int F, int T)
 {
     const size_t n_tm = (size_t)clada_prefix_token_tiles(T), n_tn = (size_t)clada_prefix_col_tiles(d);
     const size_t Fp = align_up((size_t)F, 64);
@@ -522,8 +523,8 @@ CettWs carve(char *ws, int d, int F, int T)
     w.den = reinterpret_cast<float *>(take(sizeof(float) * (size_t)T));
     w.state = reinterpret_cast<CettState *>(take(sizeof(CettState)));
     w.ytmp = take((size_t)T * d * 4);
-    const size_t sk = clada_ws_down_splitk(d, F, T);
-    w.splitk = sk ? reinterpret_cast<float *>(take(sk)) : nullptr;
+    w.splitk = reinterpret_cast<float *>(ws + off);          // whatever room is left
+    w.splitk_bytes = bytes - off;
     return w;
 }
 
@@ -546,11 +547,11 @@ clada_status begin(clada_ctx *ctx, const clada_layer *layer, const void *x, int 
                    float eps, hipStream_t stream)
 {
     const int n_tn = clada_prefix_col_tiles(layer->d);
-    CLADA_CHECK_HIP(ctx, clada_prefix_gateup(layer, x, T, w.part, w.pool, w.h, ctx->opt_prefix_tile, stream, nullptr, ctx->num_cu));
+    CLADA_CHECK_HIP(ctx, clada_prefix_gateup(layer, x, T, w.part, w.pool, w.h, ctx->opt_prefix_tile, stream, ctx->num_cu));
     const float *rowsq_den = w.rowsq_den;
     if (layer->kind == CLADA_FFN_RELU) {
         // || sum_j a_j W_out[j,:] + b_out ||: through the stored output, which carries the bias
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, w.ytmp, nullptr, w.splitk, ctx->opt_prefix_tile, stream));
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, w.ytmp, nullptr, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu));
         if (layer->dtype == CLADA_BF16)
             hipLaunchKernelGGL(k_cett_row_norm<2>, dim3((T + 3) / 4), dim3(256), 0, stream, w.ytmp, T, layer->d, w.den);
         else
@@ -558,7 +559,7 @@ clada_status begin(clada_ctx *ctx, const clada_layer *layer, const void *x, int 
         CLADA_CHECK_HIP(ctx, hipGetLastError());
         rowsq_den = nullptr;
     } else {
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, nullptr, w.rowsq_den, w.splitk, ctx->opt_prefix_tile, stream));
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, nullptr, w.rowsq_den, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu));
     }
     hipLaunchKernelGGL(k_cett_begin, dim3((T + 255) / 256), dim3(256), 0, stream, w.state, rowsq_den, n_tn, T,
                        w.den, search, eps);
@@ -579,7 +580,7 @@ clada_status probe(clada_ctx *ctx, const clada_layer *layer, int T, const CettWs
     else
         hipLaunchKernelGGL(k_cett_mask<4>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, 0);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
-    CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, ctx->opt_prefix_tile, stream));
+    CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu));
     hipLaunchKernelGGL(k_cett_update, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound,
                        search, cett_out, mean_out);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
@@ -630,14 +631,14 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     for (int it = 0; it < DENSE_PROBES; ++it) {
         CLADA_CHECK_HIP(ctx, mask(1));
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, ctx->opt_prefix_tile, stream, nullptr, &w.state->skip));
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu, nullptr, &w.state->skip));
         hipLaunchKernelGGL(k_cett_next, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound, sample);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
     }
     hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 0);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     CLADA_CHECK_HIP(ctx, mask(0));
-    CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, w.splitk, ctx->opt_prefix_tile, stream, reinterpret_cast<float *>(w.ytmp)));
+    CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu, reinterpret_cast<float *>(w.ytmp)));
     hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 1);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     // behind the second buffer of cut sums there is room for Fp - d neurons per token; the counts go behind the sample
@@ -665,6 +666,11 @@ size_t clada_ws_cett(int32_t d, int32_t d_ff, int32_t T)
            align_up(sizeof(float) * (size_t)T, 256) + 256 + align_up((size_t)T * d * 4, 256) +
            clada_ws_down_splitk(d, d_ff, T);
 }
+size_t clada_ws_cett_room(int32_t d, int32_t d_ff, int32_t T)
+{
+    if (T <= 0) return 0;
+    return clada_ws_cett(d, d_ff, T) - clada_ws_down_splitk(d, d_ff, T) + clada_ws_down_room(d, d_ff, T);
+}
 
 extern "C" clada_status clada_cett_eval(clada_ctx *ctx, const clada_layer *layer, const void *x_val, int32_t T,
                                         float eps, float *cett_out, float *mean_out, void *hip_stream)
@@ -674,7 +680,7 @@ extern "C" clada_status clada_cett_eval(clada_ctx *ctx, const clada_layer *layer
     if (!cett_out && !mean_out) return clada_fail(ctx, CLADA_ERR_NULL, "cett_out and mean_out are both NULL");
     if (eps != eps) return clada_fail(ctx, CLADA_ERR_VALUE, "eps is NaN");
     hipStream_t stream = (hipStream_t)hip_stream;
-    const CettWs w = carve(ctx->ws + CLADA_WS_HEADER, layer->d, layer->d_ff, T);
+    const CettWs w = carve(ctx->ws + CLADA_WS_HEADER, ctx->ws_bytes - CLADA_WS_HEADER, layer->d, layer->d_ff, T);
     st = begin(ctx, layer, x_val, T, w, 0, eps, stream);
     if (st != CLADA_OK) return st;
     return probe(ctx, layer, T, w, 0.0f, 0, cett_out, mean_out, stream);
@@ -691,7 +697,7 @@ extern "C" clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_
     clada_status st = check_common(ctx, layer, x_val, T);
     if (st != CLADA_OK) return st;
     hipStream_t stream = (hipStream_t)hip_stream;
-    const CettWs w = carve(ctx->ws + CLADA_WS_HEADER, layer->d, layer->d_ff, T);
+    const CettWs w = carve(ctx->ws + CLADA_WS_HEADER, ctx->ws_bytes - CLADA_WS_HEADER, layer->d, layer->d_ff, T);
     st = begin(ctx, layer, x_val, T, w, 1, 0.0f, stream);
     if (st != CLADA_OK) return st;
     // The large search pays where a dense probe costs more than a workgroup per token (0.1 us of a probe inside the bracket), and

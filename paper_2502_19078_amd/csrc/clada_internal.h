@@ -106,19 +106,22 @@ void clada_launch_finalize(int es, const float *partial, int P, int B, int d, ch
 size_t clada_ws_decode(int32_t d, int32_t d_ff, int32_t B);
 size_t clada_ws_signals(int32_t B, int32_t V);
 size_t clada_ws_prefix(int32_t d, int32_t d_ff, int32_t T, bool want_y);
+size_t clada_ws_prefix_room(int32_t d, int32_t d_ff, int32_t T);
 size_t clada_ws_calibrate(void);
 size_t clada_ws_cett(int32_t d, int32_t d_ff, int32_t T);
+size_t clada_ws_cett_room(int32_t d, int32_t d_ff, int32_t T);
 
 // Prefill GEMMs shared by the prefix statistics and the CETT search (128 x 128 output tiles).
 int clada_prefix_token_tiles(int T);
 int clada_prefix_col_tiles(int d);
 hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, float *part, float *pool,
-                               char *hbuf, int tile_mode, hipStream_t stream, float *wnorm2 = nullptr, int num_cu = 0,
-                               bool *has_norm2 = nullptr);      // wnorm2: filled where compute units are left over (*has_norm2)
-hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq,
-                             float *splitk_ws, int tile_mode, hipStream_t stream, float *y32 = nullptr, const int *skip = nullptr);
+                               char *hbuf, int tile_mode, hipStream_t stream, int num_cu, int *n_part = nullptr, float *wnorm2 = nullptr,
+                               int *norm_rows = nullptr);      // wnorm2: the first *norm_rows are filled where compute units are left over
+hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, float *splitk_ws, size_t splitk_bytes,
+                             int tile_mode, hipStream_t stream, int num_cu, float *y32 = nullptr, const int *skip = nullptr);
 int clada_prefix_down_splits(int d, int F, int T);
 size_t clada_ws_down_splitk(int d, int F, int T);
+size_t clada_ws_down_room(int d, int F, int T);
 
 #ifdef __HIPCC__
 // ---------------------------------------------------------------- device helpers

@@ -207,3 +207,58 @@ def test_prefill_tiles_of_short_prefixes_and_norms_on_spare_units(clada, d, F, T
         assert _rel(to_np(getattr(got, k)), v.numpy()) < 2e-5, k
     y = h @ w[-1] + (b_out.double().cpu() if relu else 0.0)
     assert _rel(to_np(got.y), y.numpy()) < 5e-3              # h and y each rounded once to bf16: 2^-9 of a value
+
+
+@pytest.mark.parametrize("d,F,T,kind,tile", [
+    (64, 4100, 2050, "swiglu", 0),      # one k-tile a tile, more tiles than compute units: the transfers run tiles ahead
+    (256, 4100, 2050, "geglu", 2), (192, 8300, 2500, "relu", 0),       # 297 and 330 tiles, ragged both ways
+    (1024, 2905, 1300, "swiglu", 0),    # tiles of 96 neurons
+    (256, 130, 64, "swiglu", 0), (512, 6401, 127, "geglu", 0),         # tiles of 64 neurons; d_ff off every multiple
+    (256, 4097, 100, "relu", 0), (256, 16300, 129, "swiglu", 0), (256, 16500, 129, "swiglu", 0),
+    (8192, 70, 2300, "swiglu", 0),      # 288 tiles of the down projection, not split
+    (2048, 1000, 65, "relu", 0), (256, 63, 257, "swiglu", 2),
+])
+def test_pipelined_prefill_tiles(clada, d, F, T, kind, tile):
+    """Every output against a float64 reference, and the same bits from a second call; d_ff is no multiple of the k-tile of the down
+    projection, whose last rows of W_down do not exist."""
+    from paper_2502_19078_amd import binding
+    g = torch.Generator(device=DEV).manual_seed(d + F + T)
+    n = lambda *s, k: (torch.randn(s, generator=g, device=DEV) * k)
+    relu = kind == "relu"
+    w = [n(F, d, k=d ** -0.5).bfloat16() for _ in range(2 if relu else 3)]
+    x = n(T, d, k=1.0).bfloat16()
+    b_in, b_out = n(F, k=0.1), n(d, k=0.1)
+    layer = (clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=b_in, b_out=b_out) if relu
+             else clada.Layer(*w, kind=binding.GEGLU if kind == "geglu" else binding.SWIGLU))
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    ctx.set_option("prefix.tile", tile)
+    got, again = clada.prefix_stats(ctx, layer, x), clada.prefix_stats(ctx, layer, x)
+    xd, wd = x.double(), [a.double() for a in w]
+    pre = xd @ wd[0].t()
+    if relu:
+        h = a = torch.relu(pre + b_in.double())
+    else:
+        a = torch.nn.functional.gelu(pre, approximate="tanh") if kind == "geglu" else torch.nn.functional.silu(pre)
+        h = a * (xd @ wd[1].t())
+    sq = (h * h).sum(0)
+    want = {"sum_abs_act": a.abs().sum(0), "sum_sq_act": (a * a).sum(0), "max_abs_act": a.abs().amax(0), "sum_sq_h": sq,
+            "A": sq.sqrt() * wd[-1].norm(dim=1), "abs_act_pool": a.abs()}
+    for k, v in want.items():                                # fp32 accumulation over d and T terms, a hardware exp2 of a few ulp
+        assert _rel(to_np(getattr(got, k)), v.cpu().numpy()) < 2e-5, k
+        assert torch.equal(getattr(got, k), getattr(again, k)), k
+    y = h @ wd[-1] + (b_out.double() if relu else 0.0)
+    assert _rel(to_np(got.y), y.cpu().numpy()) < 5e-3        # h and y each rounded once to bf16: 2^-9 of a value
+    assert torch.equal(got.y, again.y)
+
+
+def test_rows_past_d_ff_do_not_reach_the_output(clada):
+    """An infinite last row of W_down: the k-tile's rows past d_ff are zeros, not that row again (0 * inf would be a NaN)."""
+    d, F, T = 256, 70, 40
+    g = torch.Generator(device=DEV).manual_seed(1)
+    w = [(torch.randn(F, d, generator=g, device=DEV) * 0.06).bfloat16() for _ in range(3)]
+    w[2][-1] = float("inf")
+    x = torch.randn(T, d, generator=g, device=DEV).bfloat16()
+    y = clada.prefix_stats(clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0)), clada.Layer(*w), x).y
+    g64, u64 = x.double() @ w[0].double().t(), x.double() @ w[1].double().t()
+    h = (torch.nn.functional.silu(g64) * u64)[:, -1:]
+    assert torch.equal(y.double(), h.sign().expand(T, d) * float("inf"))
