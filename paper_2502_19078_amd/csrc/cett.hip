@@ -7,6 +7,8 @@
 // projection whose epilogue reduces the output rows to sums of squares.  The search is a
 // bisection on the bit pattern of the non-negative float eps (monotone in eps), with the bracket
 // kept on the device: lo always satisfies the bound, hi never does, 31 probes resolve the float.
+#include <type_traits>
+
 #include "clada_internal.h"
 
 namespace {
@@ -20,6 +22,7 @@ struct CettState {
     unsigned int known_lo, known_hi;      // largest feasible / smallest infeasible bit pattern measured
     float known_mean;             // mean CETT at known_lo
     int xlo, xhi, x, side;        // their places in the sorted sample, the probe's, which side moved last
+    int same;                     // probes since the start while only one side has been measured
     float glo, ghi;               // mean - bound there (one is halved while the other side keeps moving)
     unsigned int base;            // the cut sums in buffer `sel` hold the neurons below this bit pattern
     int sel;
@@ -36,6 +39,7 @@ k_cett_begin(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, fl
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t < T && rowsq) {                 // (the non-gated family's denominators come from k_cett_row_norm)
         float s = 0.0f;
+#pragma unroll 8
         for (int i = 0; i < n_tn; ++i) s += rowsq[(size_t)i * T + t];
         den[t] = sqrtf(s);
     }
@@ -166,57 +170,187 @@ __global__ void k_cett_finish(const CettState *st, float *tau_out, float *mean_o
 // The large search.  A dense probe costs a masked projection (80 us for 512 tokens of a 7B layer), and bisecting the bit
 // pattern from 0 .. +inf spends 31 of them, most on thresholds whose answer is known from a neighbour.  Here
 //   (1) some dense probes close a bracket around the answer, at thresholds taken from a sorted sample of the pool: as a
-//       function of the rank the mean is smooth (as one of the threshold it is not: SiLU's minimum piles the magnitudes up),
-//       so that false position with the Illinois rule needs six or seven probes to leave about fifty magnitudes per token;
-//   (2) one more projection leaves the cut sums at the bracket's lower end in fp32;
+//       function of the rank the mean is smooth (as one of the threshold it is not: SiLU's minimum piles the magnitudes up).
+//       The curve of sqrt(sum of the cut h^2 / sum of all h^2) over a few tokens -- what the mean would be if the rows of W_down
+//       were orthogonal and of one length -- says where to probe first and, scaled through a measured point, second; from then
+//       on false position with the Illinois rule.  Three or four probes leave about forty magnitudes per token (without the
+//       curve six or seven);
+//   (2) the last feasible probe leaves the cut sums at the bracket's lower end in fp32;
 //   (3) the plain bisection then runs; a probe outside the bracket is answered by it, one inside adds the rows of
-//       the neurons between the sums' threshold and the probe to the sums, token by token, and a feasible probe's sums
-//       become the new ones.
-// 512 tokens of 4096 x 11008: 2670 us with 31 dense probes, 1150 us so.  The bracket answers for thresholds outside it as a
+//       the neurons between the sums' threshold and the probe to the sums, token by token, for the next few probes
+//       at a time.
+// 512 tokens of 4096 x 11008: 2370 us with 31 dense probes, 580 - 640 us so.  The bracket answers for thresholds outside it as a
 // monotone mean would; inside, every probe is measured.
 constexpr int SAMPLES = 4096;      // sorted sample of the pool; neighbours are 2.7 magnitudes per token apart at 11008 neurons
-constexpr int CLOSE = 24;          // sample places left between the bracket's ends when the dense probes end
-constexpr int DENSE_PROBES = 10;   // launched; those past the end return at once
+constexpr int CLOSE = 16;          // sample places left between the bracket's ends when the dense probes end
+constexpr int DENSE_PROBES = 5;    // launched; those past the end return at once
+constexpr int CURVE_TOKENS = 32, CURVE_BINS = 256, CURVE_STEP = SAMPLES / CURVE_BINS;
 // Tokens up to which every workgroup of a probe forms the previous one's mean itself: that saves a launch a probe, and costs
 // T^2 reads.  In place / by a launch of its own, us per search: 533 / 564 and 1142 / 1171 (512 tokens, 1024 x 4096 and
 // 4096 x 11008), 631 / 633 and 1805 / 1785 (1024), 949 / 870 and 3119 / 2910 (2048), 3848 / 2271 (8192), 92600 / 8200 (65536).
 constexpr int MEAN_IN_PLACE = 1024;
 
-// One workgroup: the sorted bit patterns of SAMPLES pool entries, and the first probe.  The entries lie at the fractions
-// i * phi mod 1 of the pool (phi the golden ratio, 2^64 phi^-1 below): evenly spread over the tokens, without a stride that
-// could meet the same neurons of every token.
-__global__ void __launch_bounds__(1024)
+// The sorted bit patterns of SAMPLES pool entries.  The entries lie at the fractions i * phi mod 1 of the pool (phi the golden
+// ratio, 2^64 phi^-1 below): evenly spread over the tokens, without a stride that could meet the same neurons of every token.
+// Every workgroup reads them all and places 64 of them by counting the smaller ones, four threads an entry (34 us as a sorting network
+// in one workgroup, 17 so).
+__global__ void __launch_bounds__(256)
 k_cett_sample(CettState *st, const float *__restrict__ pool, unsigned long long n, unsigned int *__restrict__ sample, float bound)
 {
-    __shared__ unsigned int s[SAMPLES];
+    __shared__ __align__(16) unsigned int s[SAMPLES];
     const int tid = threadIdx.x;
-    for (int i = tid; i < SAMPLES; i += 1024) {
+#pragma unroll
+    for (int k = 0; k < SAMPLES / 256; ++k) {
+        const int i = k * 256 + tid;
         const unsigned long long r = (unsigned long long)(i + 1) * 0x9e3779b97f4a7c15ull;
         const unsigned int u = __float_as_uint(pool[__umul64hi(r, n)]) & 0x7fffffffu;
         s[i] = u < 0x7f800000u ? u : 0x7f800000u;
     }
     __syncthreads();
-    for (int k = 2; k <= SAMPLES; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int q = tid; q < SAMPLES / 2; q += 1024) {
-                const int i = 2 * q - (q & (j - 1)), l = i + j;
-                const unsigned int a = s[i], b = s[l];
-                if ((a > b) == ((i & k) == 0)) { s[i] = b; s[l] = a; }
-            }
-            // up to j = 64 a wave's pairs stay within its own 128 entries, and its LDS accesses are in order
-            if (j > 64 || (j == 1 && k >= 128)) __syncthreads();
-            else asm volatile("" ::: "memory");
-        }
-    __syncthreads();
-    for (int i = tid; i < SAMPLES; i += 1024) sample[i] = s[i];
-    if (tid == 0) {
-        st->skip = 0; st->done = 0;
-        st->known_lo = 0u; st->known_hi = 0x7f800000u; st->known_mean = 0.0f;
-        st->xlo = -1; st->xhi = SAMPLES; st->side = 0;
-        st->glo = -bound; st->ghi = 1.0f - bound;
-        st->x = SAMPLES / 2;
-        st->mid = s[SAMPLES / 2];
+    const int i = blockIdx.x * 64 + (tid >> 2), quarter = tid & 3;
+    const unsigned int mine = s[i];
+    int below = 0;
+    // groups of four entries, the quarters in turn: those in front of this workgroup's, which also win ties, its own, those behind
+    const int own = blockIdx.x * 16;
+    auto group = [&](int j) { return reinterpret_cast<const u32x4 *>(s)[j]; };
+#pragma unroll 4
+    for (int j = quarter; j < own; j += 4) {
+        const u32x4 v = group(j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) below += v[e] <= mine ? 1 : 0;
     }
+    for (int j = own + quarter; j < own + 16; j += 4) {
+        const u32x4 v = group(j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) below += v[e] < mine || (v[e] == mine && 4 * j + e < i) ? 1 : 0;
+    }
+#pragma unroll 4
+    for (int j = own + 16 + quarter; j < SAMPLES / 4; j += 4) {
+        const u32x4 v = group(j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) below += v[e] < mine ? 1 : 0;
+    }
+    below += __shfl_xor(below, 1);
+    below += __shfl_xor(below, 2);
+    if (quarter == 0) sample[below] = mine;
+    if (blockIdx.x == 0 && tid == 0) {
+        st->skip = 0; st->done = 0; st->sel = 1;
+        st->known_lo = 0u; st->known_hi = 0x7f800000u; st->known_mean = 0.0f;
+        st->xlo = -1; st->xhi = SAMPLES; st->side = 0; st->same = 0;
+        st->glo = -bound; st->ghi = 1.0f - bound;
+    }
+}
+
+// One token of the curve: entry b = sqrt(sum of h^2 where |a| is below the sample's place 16 b, over the sum of all).  The sums are
+// integers (a bin's share of 2^40), so that the order of the additions does not matter.
+template <int ES>
+__global__ void __launch_bounds__(1024)
+k_cett_curve(const float *__restrict__ pool, const char *__restrict__ h, const unsigned int *__restrict__ sample, int T, int F, int Fp,
+             float *__restrict__ curve)
+{
+    constexpr int AHEAD = 12;                                // values of a thread in hand at a time (all of them up to 12288 neurons)
+    __shared__ unsigned int s_edge[CURVE_BINS];
+    __shared__ unsigned long long s_sum[CURVE_BINS];
+    __shared__ float s_part[16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const size_t t = (size_t)blockIdx.x * T / gridDim.x;
+    float sq[AHEAD];
+    auto squares = [&](int j0) {
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            const int j = j0 + k * 1024 + tid;
+            const size_t at = t * Fp + (j < F ? j : 0);
+            const float v = ES == 4 ? reinterpret_cast<const float *>(h)[at]
+                                    : __uint_as_float((unsigned int)reinterpret_cast<const unsigned short *>(h)[at] << 16);
+            sq[k] = j < F ? v * v : 0.0f;
+        }
+    };
+    if (tid < CURVE_BINS) {
+        s_edge[tid] = sample[tid * CURVE_STEP];
+        s_sum[tid] = 0ull;
+    }
+    float sum = 0.0f;
+    for (int j0 = 0; j0 < F; j0 += AHEAD * 1024) {
+        squares(j0);
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) sum += sq[k];
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) s_part[tid >> 6] = sum;
+    __syncthreads();
+    float all = 0.0f;
+    for (int w = 0; w < 16; ++w) all += s_part[w];
+    const float scale = all > 0.0f && all < 1e38f ? 1099511627776.0f / all : 0.0f;
+    for (int j0 = 0; j0 < F; j0 += AHEAD * 1024) {
+        unsigned int a[AHEAD];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            const int j = j0 + k * 1024 + tid;
+            a[k] = __float_as_uint(pool[t * F + (j < F ? j : 0)]) & 0x7fffffffu;
+        }
+        if (F > AHEAD * 1024) squares(j0);
+        int bin[AHEAD];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) bin[k] = 0;          // the last edge that a reaches; below the first: bin 0 as well
+#pragma unroll
+        for (int w = CURVE_BINS / 2; w > 0; w >>= 1)
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) bin[k] += s_edge[bin[k] + w] <= a[k] ? w : 0;
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            const float v = sq[k] * scale;
+            if (v > 0.0f && v < 2e12f) atomicAdd(&s_sum[bin[k]], (unsigned long long)v);       // (a NaN fails the test)
+        }
+    }
+    __syncthreads();
+    if (tid >= CURVE_BINS) return;                           // (four whole waves stay; the others are not waited for any more)
+    unsigned long long run = 0ull;                           // below edge tid + 1: the bins up to this one
+    for (int b = 0; b < CURVE_BINS; b += 64) {
+        unsigned long long c = s_sum[b + lane];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long x = __shfl_up(c, o);
+            if (lane >= o) c += x;
+        }
+        if (b == (tid & ~63)) run += c;
+        else if (b < tid) run += __shfl(c, 63);
+    }
+    curve[(size_t)blockIdx.x * CURVE_BINS + tid] = sqrtf((float)run * (1.0f / 1099511627776.0f));
+}
+
+// The curve at a place of the sample, and the place where it reaches a value (linear between its entries; m[b] at place 16 (b + 1)).
+__device__ __forceinline__ float curve_at(const float *m, int x)
+{
+    const int b = x / CURVE_STEP;
+    const float lo = b > 0 ? m[b - 1] : 0.0f, hi = b < CURVE_BINS ? m[b] : 1.0f;
+    return lo + (hi - lo) * (float)(x - b * CURVE_STEP) / (float)CURVE_STEP;
+}
+__device__ __forceinline__ int curve_place(const float *m, float v)
+{
+    int b = 0;                                               // entries below v
+    for (int w = CURVE_BINS / 2; w > 0; w >>= 1) b += m[b + w - 1] < v ? w : 0;
+    const float lo = b > 0 ? m[b - 1] : 0.0f, hi = m[b];
+    return b * CURVE_STEP + (hi > lo && v > lo ? (int)fminf((v - lo) / (hi - lo) * CURVE_STEP, (float)CURVE_STEP) : 0);
+}
+
+// The mean of the tokens' curves, and the first probe.
+__global__ void __launch_bounds__(CURVE_BINS)
+k_cett_first(CettState *st, const float *__restrict__ curve, int tokens, float *__restrict__ mean, const unsigned int *__restrict__ sample, float bound)
+{
+    __shared__ float s_m[CURVE_BINS];
+    const int tid = threadIdx.x;
+    float m = 0.0f;
+#pragma unroll 8
+    for (int i = 0; i < tokens; ++i) m += curve[(size_t)i * CURVE_BINS + tid];
+    m /= (float)tokens;
+    mean[tid] = m;
+    s_m[tid] = m;
+    __syncthreads();
+    if (tid != 0) return;
+    int x = curve_place(s_m, bound);
+    x = x < 1 ? 1 : x > SAMPLES - 2 ? SAMPLES - 2 : x;
+    st->x = x;
+    st->mid = sample[x];
 }
 
 // Mean CETT of the probe (as in k_cett_update; the sum over the column tiles and over the tokens in the same order).
@@ -256,15 +390,16 @@ __device__ __forceinline__ void bisect_on(CettState &s)
 // After a dense probe: the bracket, and the next probe between its ends.
 __global__ void __launch_bounds__(1024)
 k_cett_next(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, const float *__restrict__ den, float bound,
-            const unsigned int *__restrict__ sample)
+            const unsigned int *__restrict__ sample, const float *__restrict__ curve)
 {
-    __shared__ float s_sum[1024];
+    __shared__ float s_sum[1024], s_m[CURVE_BINS];
     if (st->skip) return;
+    if (threadIdx.x < CURVE_BINS) s_m[threadIdx.x] = curve[threadIdx.x];
     const float mean = mean_cett(rowsq, n_tn, T, den, s_sum);
     if (threadIdx.x != 0) return;
     CettState s = *st;
     const bool feasible = mean <= bound;                     // NaN: over the bound
-    if (feasible) { if (s.mid > s.known_lo) { s.known_lo = s.mid; s.known_mean = mean; } }
+    if (feasible) { if (s.mid > s.known_lo) { s.known_lo = s.mid; s.known_mean = mean; s.sel ^= 1; } }     // (its sums are kept)
     else if (s.mid < s.known_hi) s.known_hi = s.mid;
     auto take = [&](bool low, float g) {                     // the place x becomes an end of the bracket
         if (low) { s.xlo = s.x; s.glo = g; if (s.side < 0) s.ghi *= 0.5f; s.side = -1; }
@@ -273,6 +408,21 @@ k_cett_next(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, con
     float g = mean - bound;
     if (!feasible && !(g > 0.0f)) g = 1.0f;                  // (NaN)
     take(feasible, g);
+    const bool one_side = s.xlo < 0 || s.xhi >= SAMPLES;     // only one end of the bracket is a measured one
+    if (one_side && s.same < 4 && mean > 0.0f && mean < 1e30f) {
+        // the curve through the measured point, a little past its answer (further each time the answer stays on one side)
+        const int at = curve_place(s_m, curve_at(s_m, s.x) * (bound / mean)), past = (CLOSE / 2) << (2 * s.same);
+        int x = feasible ? at + past : at - past;
+        if (feasible && x <= s.xlo) x = s.xlo + past;
+        if (!feasible && x >= s.xhi) x = s.xhi - past;
+        ++s.same;
+        if (x > s.xlo && x < s.xhi && sample[x] > s.known_lo && sample[x] < s.known_hi) {
+            s.x = x;
+            s.mid = sample[x];
+            *st = s;
+            return;
+        }
+    }
     for (int guard = 0;; ++guard) {
         if (s.xhi - s.xlo <= CLOSE || guard >= 64) { s.skip = 1; break; }
         const float pos = (float)s.xlo + (float)(s.xhi - s.xlo) * (-s.glo / (s.ghi - s.glo));
@@ -288,14 +438,15 @@ k_cett_next(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, con
     *st = s;
 }
 
-// The threshold of the cut sums (the bracket's lower end), and the start of the bisection.
+// The threshold of the cut sums (the bracket's lower end), and the start of the bisection.  stage 1: the sums were formed by a pass of
+// their own, in the first buffer; stage 2: by the probe that measured the threshold.
 __global__ void k_cett_base(CettState *st, int stage)
 {
     if (threadIdx.x != 0) return;
     if (stage == 0) { st->mid = st->known_lo; return; }      // for the masking pass
     CettState s = *st;
     s.base = s.known_lo;
-    s.sel = 0;
+    if (stage == 1) s.sel = 0;
     s.listed = 1;
     s.lo = 0u;
     s.hi = 0x7f800000u;
@@ -348,156 +499,328 @@ __device__ __forceinline__ void list_ascending(int n, int *s_cnt, Want want, Put
 
 // The neurons of every token with known_lo <= |a| < known_hi, the only ones that later probes add: cap of them per token
 // fit; a token with more leaves `listed` at zero, and the probes look through the whole pool.
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 k_cett_list(CettState *st, const float *__restrict__ pool, int F, int *__restrict__ list, int cap, int *__restrict__ count)
 {
-    __shared__ int s_cnt[64];
+    constexpr int PER = 4;                                   // consecutive neurons of a thread in a round of 4096
+    __shared__ int s_part[2][16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const size_t t = blockIdx.x;
     const float lo = __uint_as_float(st->known_lo), hi = __uint_as_float(st->known_hi);
     int *mine = list + t * cap;
+    float a[PER], next[PER];
+    auto ask = [&](float (&v)[PER], int seg) {
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            const int j = seg + PER * tid + e;
+            v[e] = pool[t * F + (j < F ? j : F - 1)];
+        }
+    };
+    ask(a, 0);
     int at = 0;
-    list_ascending(F, s_cnt, [&](int j) { const float a = pool[t * F + j]; return a >= lo && a < hi; },
-                   [&](int i, int j) { if (at + i < cap) mine[at + i] = j; }, [&](int n) { at += n; });
-    if (threadIdx.x == 0) {
+    for (int seg = 0, turn = 0; seg < F; seg += PER * 1024, turn ^= 1) {
+        if (seg + PER * 1024 < F) ask(next, seg + PER * 1024);
+        int c = 0, in = 0;
+#pragma unroll
+        for (int e = 0; e < PER; ++e)
+            if (a[e] >= lo && a[e] < hi && seg + PER * tid + e < F) { in |= 1 << e; ++c; }
+        int inc = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(inc, o);
+            if (lane >= o) inc += x;
+        }
+        if (lane == 63) s_part[turn][wave] = inc;
+        __syncthreads();                                     // (two buffers: a wave writes the next one while another reads this)
+        int put = at + inc - c;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) put += s_part[turn][w];
+            at += s_part[turn][w];
+        }
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            if ((in >> e) & 1) {
+                if (put < cap) mine[put] = seg + PER * tid + e;
+                ++put;
+            }
+            a[e] = next[e];
+        }
+    }
+    if (tid == 0) {
         count[t] = min(at, cap);
         if (at > cap) st->listed = 0;
     }
 }
 
-// A probe's answer: the bracket, the sums' threshold and buffer, and the bisection up to the next probe.
-__device__ __forceinline__ void take_in(CettState &s, float mean, float bound)
+// The probes inside the bracket.  A launch measures the thresholds that the next LEVELS steps of the bisection can ask for, a binary
+// tree of NODES = 2^LEVELS - 1 of them, and the walk down the tree afterwards is the bisection's own: seven thresholds cost little
+// more than one (the rows up to the highest are read once), and the launches follow each other 7 us apart whatever they do
+// (one threshold a launch: 224 us of a search of 512 tokens of 4096 x 11008, seven: 170, most of it launches that find nothing left).
+
+// A measured threshold's answer, and the bisection up to the next one.
+__device__ __forceinline__ void answer(CettState &s, bool feasible, float mean)
 {
-    if (mean <= bound) {
-        s.known_lo = s.base = s.mid;
+    if (feasible) {
+        s.known_lo = s.mid;
         s.known_mean = mean;
-        s.sel ^= 1;
     } else {
         s.known_hi = s.mid;                                  // NaN: over the bound
     }
     bisect_on(s);
 }
 
-// The same as a launch of its own, in place, for more than MEAN_IN_PLACE tokens.
+// Down the tree with the means of its thresholds in ascending order.
+template <int LEVELS>
+__device__ __forceinline__ void walk(CettState &s, const float *mean, float bound)
+{
+    int at = (1 << LEVELS) / 2 - 1;
+    for (int l = LEVELS - 2; l >= -1 && !s.done; --l) {
+        const bool feasible = mean[at] <= bound;
+        answer(s, feasible, mean[at]);
+        if (l >= 0) at += feasible ? 1 << l : -(1 << l);
+    }
+}
+
+// Threshold `node` (ascending) of the tree below s, or the next one up the path where the bisection ends before it gets there.
+template <int LEVELS>
+__device__ __forceinline__ unsigned int node_threshold(CettState s, int node)
+{
+    int at = (1 << LEVELS) / 2 - 1;
+    unsigned int mid = s.mid;
+    for (int l = LEVELS - 2; l >= 0 && at != node; --l) {
+        const bool right = node > at;
+        answer(s, right, 0.0f);
+        if (s.done) break;
+        mid = s.mid;
+        at += right ? 1 << l : -(1 << l);
+    }
+    return mid;
+}
+
+// The means of the previous launch's thresholds (its row norms: [node][part][T]), by a workgroup of NT threads: to s_mean.
+template <int NODES, int NT>
+__device__ __forceinline__ void node_means(const float *__restrict__ rowsq, int parts, int T, const float *__restrict__ den, float (*s_sum)[NODES], float *s_mean)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    float acc[NODES];
+#pragma unroll
+    for (int v = 0; v < NODES; ++v) acc[v] = 0.0f;
+    for (int t = tid; t < T; t += NT) {
+        float sq[NODES];
+#pragma unroll
+        for (int v = 0; v < NODES; ++v) sq[v] = 0.0f;
+        for (int i = 0; i < parts; ++i)
+#pragma unroll
+            for (int v = 0; v < NODES; ++v) sq[v] += rowsq[((size_t)v * parts + i) * T + t];
+        const float dn = den[t];
+#pragma unroll
+        for (int v = 0; v < NODES; ++v) acc[v] += dn > 0.0f ? sqrtf(sq[v]) / dn : 0.0f;
+    }
+#pragma unroll
+    for (int v = 0; v < NODES; ++v) {
+        const float w = wave_sum(acc[v]);
+        if (lane == 0) s_sum[tid >> 6][v] = w;
+    }
+    __syncthreads();
+    if (tid < NODES) {
+        float m = 0.0f;
+        for (int w = 0; w < NT / 64; ++w) m += s_sum[w][tid];
+        s_mean[tid] = m / (float)T;
+    }
+    __syncthreads();
+}
+
+// The walk as a launch of its own, in place, for more than MEAN_IN_PLACE tokens.
+template <int LEVELS>
 __global__ void __launch_bounds__(1024)
 k_cett_take(CettState *st, const float *__restrict__ rowsq, int parts, int T, const float *__restrict__ den, float bound)
 {
-    __shared__ float s_sum[1024];
+    constexpr int NODES = (1 << LEVELS) - 1;
+    __shared__ float s_sum[16][NODES], s_mean[NODES];
     if (st->done) return;
-    const float mean = mean_cett(rowsq, parts, T, den, s_sum);
+    node_means<NODES, 1024>(rowsq, parts, T, den, s_sum, s_mean);
     if (threadIdx.x == 0) {
         CettState s = *st;
-        take_in(s, mean, bound);
+        walk<LEVELS>(s, s_mean, bound);
         *st = s;
     }
 }
 
-// One probe inside the bracket.  Up to MEAN_IN_PLACE tokens every workgroup first takes in the previous one (the same state
-// and the same norms, so the same result; workgroup 0 leaves it for the next launch), beyond k_cett_take has done that (taken).
-// Then, a workgroup per token and part of the columns: the cut sums at `base` plus h_j W_down[j,:] of the neurons with
-// base <= |a_j| < probe in ascending order, to the other buffer; their sum of squares to rowsq.
-template <int ES, int NV>
+// Up to MEAN_IN_PLACE tokens every workgroup first takes in the previous launch's answers (the same state and the same norms, so the
+// same result; workgroup 0 leaves it for the next launch), beyond k_cett_take has done that (taken).  Then, a workgroup per
+// token and part of the columns: the cut sums at `base` plus h_j W_down[j,:] of the neurons up to the largest feasible threshold,
+// stored as the new sums, and on to the thresholds of the tree, threshold after threshold, ascending within each; the
+// sums of squares at each of them to rowsq.
+template <int ES, int NV, int LEVELS>
 __global__ void __launch_bounds__(256)
 k_cett_between(CettState *__restrict__ sts, int launch, int taken, const float *__restrict__ pool, const char *__restrict__ h,
                const char *__restrict__ wd, const int *__restrict__ list, int cap, const int *__restrict__ count,
                float *__restrict__ buf0, float *__restrict__ buf1, const float *__restrict__ rowsq_in, float *__restrict__ rowsq,
                const float *__restrict__ den, float bound, int T, int F, int Fp, int d)
 {
-    constexpr int VEC = 16 / ES, SEG = 4096;
-    __shared__ int s_cnt[64], s_j[SEG];
-    __shared__ float s_h[SEG], s_sq[256];
+    constexpr int VEC = 16 / ES, SEG = 4096, NODES = (1 << LEVELS) - 1, AHEAD = 8;
+    __shared__ int s_cnt[64], s_j[SEG], s_end[NODES + 1];
+    __shared__ float s_h[SEG], s_sum[4][NODES], s_mean[NODES], s_edge[NODES + 2];
     __shared__ CettState s_st;
-    const int tid = threadIdx.x, parts = gridDim.y, part = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, parts = gridDim.y, part = blockIdx.y;
     const CettState *in = sts + (launch & 1);
     const bool take = !taken && launch > 0 && !in->done;
-    if (take) {
-        float acc = 0.0f;
-        for (int t = tid; t < T; t += 256) {
-            float s = 0.0f;
-            for (int i = 0; i < parts; ++i) s += rowsq_in[(size_t)i * T + t];
-            const float dn = den[t];
-            acc += dn > 0.0f ? sqrtf(s) / dn : 0.0f;
-        }
-        s_sq[tid] = acc;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (tid < w) s_sq[tid] += s_sq[tid + w];
-            __syncthreads();
-        }
-    }
+    if (take) node_means<NODES, 256>(rowsq_in, parts, T, den, s_sum, s_mean);
     if (tid == 0) {
         CettState s = *in;
-        if (take) take_in(s, s_sq[0] / (float)T, bound);
+        if (take) walk<LEVELS>(s, s_mean, bound);
         s_st = s;
-        if (blockIdx.x == 0 && part == 0) sts[(launch + 1) & 1] = s;
+        if (blockIdx.x == 0 && part == 0) {
+            if (!s.done && s.base != s.known_lo) { s.base = s.known_lo; s.sel ^= 1; }       // what this launch leaves
+            sts[(launch + 1) & 1] = s;
+        }
     }
     __syncthreads();
     if (s_st.done) return;
+    if (tid == 0) { s_edge[0] = __uint_as_float(s_st.base); s_edge[1] = __uint_as_float(s_st.known_lo); }
+    if (tid < NODES) s_edge[2 + tid] = __uint_as_float(node_threshold<LEVELS>(s_st, tid));
+    __syncthreads();
+    float edge[NODES + 2];                                   // segment i: edge[i] <= |a| < edge[i + 1]; a threshold that is not needed repeats
+    edge[0] = s_edge[0]; edge[1] = s_edge[1];                // another one and leaves the order: made ascending here
+#pragma unroll
+    for (int v = 0; v < NODES; ++v) edge[2 + v] = fmaxf(edge[1 + v], s_edge[2 + v]);
     const size_t t = blockIdx.x;
-    const float lo = __uint_as_float(s_st.base), hi = __uint_as_float(s_st.mid);
-    const bool listed = s_st.listed != 0;
+    const bool listed = s_st.listed != 0, moved = s_st.base != s_st.known_lo;
     const float *src = (s_st.sel ? buf1 : buf0) + t * d;
     float *dst = (s_st.sel ? buf0 : buf1) + t * d;
     const int col0 = (part * NV * 256 + tid) * VEC;          // group v of this thread: columns col0 + v 256 VEC ..
-    float acc[NV][VEC];
+    float acc[NV][VEC], sq[NODES];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const int col = col0 + v * 256 * VEC;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[v][e] = col < d ? src[col + e] : 0.0f;
+        for (int e = 0; e < VEC; ++e) acc[v][e] = col < d && s_st.base != 0u ? src[col + e] : 0.0f;      // (nothing lies below 0)
     }
     const int *mine = list + t * cap;
-    auto neuron = [&](int i) -> int { return listed ? mine[i] : i; };
-    list_ascending(listed ? count[t] : F, s_cnt,
-        [&](int i) { const float a = pool[t * F + neuron(i)]; return a >= lo && a < hi; },
-        [&](int at, int i) {
-            const int j = neuron(i);
-            s_j[at] = j;
-            s_h[at] = ES == 4 ? reinterpret_cast<const float *>(h)[t * Fp + j]
-                              : __uint_as_float((unsigned int)reinterpret_cast<const unsigned short *>(h)[t * Fp + j] << 16);
-        },
-        [&](int total) {
-            for (int e0 = 0; e0 < total; e0 += 4) {
-                u32x4 w[4][NV];
+    auto magnitude = [&](int i) { return pool[t * F + (listed ? mine[i] : i)]; };
+    auto put = [&](int at, int i) {
+        const int j = listed ? mine[i] : i;
+        s_j[at] = j;
+        s_h[at] = ES == 4 ? reinterpret_cast<const float *>(h)[t * Fp + j]
+                          : __uint_as_float((unsigned int)reinterpret_cast<const unsigned short *>(h)[t * Fp + j] << 16);
+    };
+    // the end of segment i: the new sums, or the norm at a threshold
+    auto ended = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        float q = 0.0f;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const char *row = wd + (size_t)s_j[min(e0 + q, total - 1)] * d * ES;
+        for (int v = 0; v < NV; ++v) {
+            const int col = col0 + v * 256 * VEC;
+            if (col < d) {
+                if constexpr (i == 0) {
+                    if (moved)
+#pragma unroll
+                        for (int e = 0; e < VEC; e += 4)
+                            *reinterpret_cast<float4 *>(dst + col + e) = make_float4(acc[v][e], acc[v][e + 1], acc[v][e + 2], acc[v][e + 3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) q = fmaf(acc[v][e], acc[v][e], q);
+                }
+            }
+        }
+        if constexpr (i > 0) sq[i - 1] = q;
+    };
+    // entries [0, total) of s_j / s_h added in order, AHEAD rows requested together; before entry e is added, done(e)
+    auto add_rows = [&](int total, auto done) {
+        for (int e0 = 0; e0 < total; e0 += AHEAD) {
+            u32x4 w[AHEAD][NV];
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) {
+                const char *row = wd + (size_t)s_j[min(e0 + q, total - 1)] * d * ES;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const int col = col0 + v * 256 * VEC;
+                    w[q][v] = *reinterpret_cast<const u32x4 *>(row + (size_t)(col < d ? col : 0) * ES);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) {
+                if (e0 + q < total) {
+                    done(e0 + q);
+                    const float hv = s_h[e0 + q];
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
-                        const int col = col0 + v * 256 * VEC;
-                        w[q][v] = *reinterpret_cast<const u32x4 *>(row + (size_t)(col < d ? col : 0) * ES);
-                    }
-                }
+                        float f[VEC];
+                        unpack_row16(w[q][v], f);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (e0 + q < total) {
-                        const float hv = s_h[e0 + q];
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) {
-                            float f[VEC];
-                            unpack_row16(w[q][v], f);
-#pragma unroll
-                            for (int e = 0; e < VEC; ++e) acc[v][e] = fmaf(hv, f[e], acc[v][e]);
-                        }
+                        for (int e = 0; e < VEC; ++e) acc[v][e] = fmaf(hv, f[e], acc[v][e]);
                     }
                 }
             }
-        });
-    float sq = 0.0f;
+        }
+    };
+    const int n = listed ? count[t] : F;
+    if (listed && n <= 256) {                                // an entry per thread: all segments in one go, in their order
+        const float a = tid < n ? magnitude(tid) : -1.0f;
+        int seg = -1;                                        // NaN and everything outside: none
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int col = col0 + v * 256 * VEC;
-        if (col < d) {
+        for (int i = 0; i <= NODES; ++i) seg = a >= edge[i] && a < edge[i + 1] ? i : seg;
+        int before = 0;
 #pragma unroll
-            for (int e = 0; e < VEC; e += 4)
-                *reinterpret_cast<float4 *>(dst + col + e) = make_float4(acc[v][e], acc[v][e + 1], acc[v][e + 2], acc[v][e + 3]);
+        for (int i = 0; i <= NODES; ++i) {
+            const unsigned long long who = __ballot(seg == i);
+            if (lane == 0) s_cnt[i * 4 + wave] = __popcll(who);
+            if (seg == i) before = __popcll(who & ((1ull << lane) - 1ull));
+        }
+        __syncthreads();
+        int at = 0, run = 0;
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) sq = fmaf(acc[v][e], acc[v][e], sq);
+        for (int i = 0; i <= NODES; ++i) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if (seg == i && w == wave) at = run;
+                run += s_cnt[i * 4 + w];
+            }
+            if (tid == 0) s_end[i] = run;
+        }
+        if (seg >= 0) put(at + before, tid);
+        __syncthreads();
+        int open = 0;                                        // segments that have ended (uniform)
+        auto close = [&](int e, bool all) {
+            while (open <= NODES && (all || s_end[open] <= e)) {
+                switch (open) {
+                case 0: ended(std::integral_constant<int, 0>{}); break;
+                case 1: ended(std::integral_constant<int, 1>{}); break;
+                case 2: if constexpr (NODES >= 2) ended(std::integral_constant<int, 2 < NODES ? 2 : NODES>{}); break;
+                case 3: if constexpr (NODES >= 3) ended(std::integral_constant<int, 3 < NODES ? 3 : NODES>{}); break;
+                case 4: if constexpr (NODES >= 4) ended(std::integral_constant<int, 4 < NODES ? 4 : NODES>{}); break;
+                case 5: if constexpr (NODES >= 5) ended(std::integral_constant<int, 5 < NODES ? 5 : NODES>{}); break;
+                case 6: if constexpr (NODES >= 6) ended(std::integral_constant<int, 6 < NODES ? 6 : NODES>{}); break;
+                case 7: if constexpr (NODES >= 7) ended(std::integral_constant<int, 7 < NODES ? 7 : NODES>{}); break;
+                }
+                ++open;
+            }
+        };
+        add_rows(run, [&](int e) { close(e, false); });
+        close(0, true);
+    } else {
+        auto one = [&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            if (edge[i] < edge[i + 1])
+                list_ascending(n, s_cnt, [&](int k) { const float a = magnitude(k); return a >= edge[i] && a < edge[i + 1]; }, put,
+                               [&](int total) { add_rows(total, [](int) {}); __syncthreads(); });
+            ended(ic);
+        };
+        one(std::integral_constant<int, 0>{});
+        one(std::integral_constant<int, 1>{});
+        if constexpr (NODES >= 3) { one(std::integral_constant<int, 2>{}); one(std::integral_constant<int, 3>{}); }
+        if constexpr (NODES >= 7) {
+            one(std::integral_constant<int, 4>{}); one(std::integral_constant<int, 5>{});
+            one(std::integral_constant<int, 6>{}); one(std::integral_constant<int, 7>{});
         }
     }
-    sq = wave_sum(sq);
-    if ((tid & 63) == 0) s_sq[tid >> 6] = sq;
+#pragma unroll
+    for (int v = 0; v < NODES; ++v) {
+        const float q = wave_sum(sq[v]);
+        if (lane == 0) s_sum[wave][v] = q;
+    }
     __syncthreads();
-    if (tid == 0) rowsq[(size_t)part * T + t] = (s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3]);
+    if (tid < NODES) rowsq[((size_t)tid * parts + part) * T + t] = (s_sum[0][tid] + s_sum[1][tid]) + (s_sum[2][tid] + s_sum[3][tid]);
 }
 
 struct CettWs {
@@ -598,28 +921,41 @@ BetweenShape between_shape(int d, int es)
 
 template <int ES>
 void launch_between(const CettWs &w, const clada_layer *layer, int T, int Fp, int launch, const int *list, int cap, const int *count,
-                    float bound, hipStream_t st)
+                    float *const (&sums)[2], float bound, hipStream_t st)
 {
     const int d = layer->d;
     const BetweenShape sh = between_shape(d, ES);
-    auto kern = sh.nv == 1 ? k_cett_between<ES, 1> : k_cett_between<ES, 2>;
+    // as many thresholds a launch as the row norms' buffers take
+    const int room = clada_prefix_col_tiles(d) / sh.parts, levels = room >= 7 ? 3 : room >= 3 ? 2 : 1;
+    auto kern = sh.nv == 1 ? (levels == 3 ? k_cett_between<ES, 1, 3> : levels == 2 ? k_cett_between<ES, 1, 2> : k_cett_between<ES, 1, 1>)
+                           : (levels == 3 ? k_cett_between<ES, 2, 3> : levels == 2 ? k_cett_between<ES, 2, 2> : k_cett_between<ES, 2, 1>);
+    auto take = levels == 3 ? k_cett_take<3> : levels == 2 ? k_cett_take<2> : k_cett_take<1>;
     float *sq[2] = {w.rowsq_num, w.rowsq_den};
     const bool taken = T > MEAN_IN_PLACE;
     if (taken && launch > 0)
-        hipLaunchKernelGGL(k_cett_take, dim3(1), dim3(1024), 0, st, w.state + (launch & 1), sq[launch & 1], sh.parts, T, w.den, bound);
+        hipLaunchKernelGGL(take, dim3(1), dim3(1024), 0, st, w.state + (launch & 1), sq[launch & 1], sh.parts, T, w.den, bound);
     hipLaunchKernelGGL(kern, dim3(T, sh.parts), dim3(256), 0, st, w.state, launch, taken ? 1 : 0, w.pool, w.h, (const char *)layer->w_down,
-                       list, cap, count, reinterpret_cast<float *>(w.ytmp), reinterpret_cast<float *>(w.hcut),
+                       list, cap, count, sums[0], sums[1],
                        sq[launch & 1], sq[(launch + 1) & 1], w.den, bound, T, layer->d_ff, Fp, d);
 }
 
-// The large search after begin(): ytmp and hcut (free once the dense probes are over) hold the cut sums.
+// Words that the large search keeps in the place of the partial aggregates, and whether they fit there.
+bool large_fits(int T, int F)
+{
+    return (size_t)4 * clada_prefix_token_tiles(T) * F >= SAMPLES + CURVE_BINS * (size_t)(1 + CURVE_TOKENS) + T;
+}
+
+// The large search after begin().
 clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const CettWs &w, float bound, hipStream_t stream)
 {
     const int d = layer->d, F = layer->d_ff, n_tn = clada_prefix_col_tiles(d);
     const int Fp = (int)align_up((size_t)F, 64);
     const size_t groups = (size_t)T * (Fp / 8);
     const int grid = (int)((groups + 255) / 256 < 4096 ? (groups + 255) / 256 : 4096);
-    unsigned int *sample = reinterpret_cast<unsigned int *>(w.part);         // (the partial aggregates are not used here)
+    // (the partial aggregates are not used here: large_fits)
+    unsigned int *sample = reinterpret_cast<unsigned int *>(w.part);
+    float *curve = reinterpret_cast<float *>(sample + SAMPLES), *curves = curve + CURVE_BINS;
+    int *count = reinterpret_cast<int *>(curves + CURVE_TOKENS * CURVE_BINS);
     auto mask = [&](int may_skip) {
         if (layer->dtype == CLADA_BF16)
             hipLaunchKernelGGL(k_cett_mask<2>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, may_skip);
@@ -627,28 +963,44 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
             hipLaunchKernelGGL(k_cett_mask<4>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, may_skip);
         return hipGetLastError();
     };
-    hipLaunchKernelGGL(k_cett_sample, dim3(1), dim3(1024), 0, stream, w.state, w.pool, (unsigned long long)T * F, sample, bound);
+    hipLaunchKernelGGL(k_cett_sample, dim3(SAMPLES / 64), dim3(256), 0, stream, w.state, w.pool, (unsigned long long)T * F, sample, bound);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
+    hipLaunchKernelGGL((layer->dtype == CLADA_BF16 ? k_cett_curve<2> : k_cett_curve<4>), dim3(CURVE_TOKENS), dim3(1024), 0, stream, w.pool, w.h,
+                       sample, T, F, Fp, curves);
+    CLADA_CHECK_HIP(ctx, hipGetLastError());
+    hipLaunchKernelGGL(k_cett_first, dim3(1), dim3(CURVE_BINS), 0, stream, w.state, curves, CURVE_TOKENS, curve, sample, bound);
+    CLADA_CHECK_HIP(ctx, hipGetLastError());
+    // The cut sums at the bracket's lower end are the output of the last feasible probe.  With room for two buffers of them beside
+    // the masked h (bf16: the upper half of h's part, which is sized for fp32) the probes alternate between them; else one more
+    // projection forms them (68 us for 512 tokens of 4096 x 11008, against 2 a probe).
+    const bool two = layer->dtype == CLADA_BF16 && Fp >= 2 * d;
+    float *sums[2] = {reinterpret_cast<float *>(w.ytmp), reinterpret_cast<float *>(two ? w.h + (size_t)T * Fp * 2 : w.hcut)};
     for (int it = 0; it < DENSE_PROBES; ++it) {
         CLADA_CHECK_HIP(ctx, mask(1));
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu, nullptr, &w.state->skip));
-        hipLaunchKernelGGL(k_cett_next, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound, sample);
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu,
+                                               two ? sums[0] : nullptr, &w.state->skip, two ? sums[1] : nullptr, two ? &w.state->sel : nullptr));
+        hipLaunchKernelGGL(k_cett_next, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound, sample, curve);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
     }
-    hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 0);
-    CLADA_CHECK_HIP(ctx, hipGetLastError());
-    CLADA_CHECK_HIP(ctx, mask(0));
-    CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu, reinterpret_cast<float *>(w.ytmp)));
-    hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 1);
-    CLADA_CHECK_HIP(ctx, hipGetLastError());
-    // behind the second buffer of cut sums there is room for Fp - d neurons per token; the counts go behind the sample
-    int *list = reinterpret_cast<int *>(w.hcut) + (size_t)T * d, *count = reinterpret_cast<int *>(sample + SAMPLES);
-    const int cap = Fp - d;
-    hipLaunchKernelGGL(k_cett_list, dim3(T), dim3(256), 0, stream, w.state, w.pool, F, list, cap, count);
+    if (two) {
+        hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 2);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+    } else {
+        hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 0);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+        CLADA_CHECK_HIP(ctx, mask(0));
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu, sums[0]));
+        hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 1);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+    }
+    // the masked h is not needed any more: its part takes the lists, behind the second buffer of cut sums if that is there
+    int *list = reinterpret_cast<int *>(w.hcut) + (two ? 0 : (size_t)T * d);
+    const int cap = two ? Fp : Fp - d;
+    hipLaunchKernelGGL(k_cett_list, dim3(T), dim3(1024), 0, stream, w.state, w.pool, F, list, cap, count);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     for (int it = 0; it <= 31; ++it) {                       // (the last one only takes in the 31st probe)
-        if (layer->dtype == CLADA_BF16) launch_between<2>(w, layer, T, Fp, it, list, cap, count, bound, stream);
-        else launch_between<4>(w, layer, T, Fp, it, list, cap, count, bound, stream);
+        if (layer->dtype == CLADA_BF16) launch_between<2>(w, layer, T, Fp, it, list, cap, count, sums, bound, stream);
+        else launch_between<4>(w, layer, T, Fp, it, list, cap, count, sums, bound, stream);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
     }
     return CLADA_OK;
@@ -701,13 +1053,14 @@ extern "C" clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_
     st = begin(ctx, layer, x_val, T, w, 1, 0.0f, stream);
     if (st != CLADA_OK) return st;
     // The large search pays where a dense probe costs more than a workgroup per token (0.1 us of a probe inside the bracket), and
-    // its bracket is only trusted where single neurons do not move the mean; fewer probes than the full 31 end somewhere on the
+    // its bracket is only trusted where single neurons do not move the mean (ms, plain / large at 2^18 magnitudes and more: 0.80 / 0.25 for 64
+    // tokens of 1024 x 4096, 1.43 / 0.33 of 4096 x 11008, 0.86 / 0.27 for 256 of 512 x 1999); fewer probes than the full 31 end somewhere on the
     // way, which only the plain bisection passes through.  A bf16 projection of fewer than 2048 neurons costs less once the
     // tokens fill the chip (ms, large / plain: 6.6 / 3.9 and 8.2 / 6.4 at 65536 tokens of 64 and 512 x 512, 7.9 / 7.1 of
     // 256 x 1024, 1.9 / 1.7 at 16384 of 256 x 512; 0.79 / 1.04 at 4096 of 256 x 512, 8.2 / 11.1 at 65536 of 64 x 2048); an fp32
     // one never does (2.1 / 2.7 at 16384 of 64 x 512).
-    const bool large = n_probes == 31 && bound > 0.0f && (size_t)T * layer->d_ff >= (1u << 20) && T >= 64 && layer->d_ff >= layer->d &&
-                       layer->d_ff >= 512 && (layer->dtype == CLADA_F32 || T <= 4096 || layer->d_ff >= 2048);
+    const bool large = n_probes == 31 && bound > 0.0f && (size_t)T * layer->d_ff >= (1u << 18) && T >= 64 && layer->d_ff >= layer->d &&
+                       layer->d_ff >= 512 && large_fits(T, layer->d_ff) && (layer->dtype == CLADA_F32 || T <= 4096 || layer->d_ff >= 2048);
     if (large) {
         st = search_large(ctx, layer, T, w, bound, stream);
         if (st != CLADA_OK) return st;

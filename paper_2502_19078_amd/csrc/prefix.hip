@@ -440,6 +440,8 @@ struct DownParams {
     float *part_out;               // split-K (256 x 256 kernel): fp32 partial outputs [S][T][d] instead of y / rowsq
     int S;                         // number of k ranges the neurons are split into (1 = no split)
     float *y32;                    // [T][d] the fp32 rows without a bias, or nullptr
+    float *y32_alt;                // they go there instead when *alt is 0 (alt: device flag or nullptr)
+    const int *alt;
     const int *skip;               // device flag: nothing to do when set (a probe that is not needed), or nullptr
 };
 
@@ -467,9 +469,13 @@ __device__ __forceinline__ void down_rowsq(const f32x16 (&acc)[2][2], const Down
     }
 }
 
+// Where the fp32 rows go.
+__device__ __forceinline__ float *rows32_of(const DownParams &p) { return p.alt && *p.alt == 0 ? p.y32_alt : p.y32; }
+
 // The fp32 rows of a 128 x 128 tile, without a bias.
 __device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const DownParams &p, int tm, int tn, int wm, int wn, int lane)
 {
+    float *rows = rows32_of(p);
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
         const int col = tn * BN + wn * 64 + nb * 32 + (lane & 31);
@@ -478,7 +484,7 @@ __device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const Do
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int t = tm * BM + wm * 64 + mb * 32 + acc_row(r, lane);
-                if (t < p.T && col < p.d) p.y32[(size_t)t * p.d + col] = acc[mb][nb][r];
+                if (t < p.T && col < p.d) rows[(size_t)t * p.d + col] = acc[mb][nb][r];
             }
     }
 }
@@ -740,7 +746,7 @@ k_prefix_down_tiles(const DownParams p)
         const int t0 = id.tm * S::TM + wm * 64, c0 = id.tn * 256 + wn * 32 * S::NB;
         const bool full = t0 + 64 <= p.T;
         if (p.part_out || (PROBE && p.y32)) {               // split: fp32 partial sums, added up by k_prefix_down_combine
-            float *rows32 = !PROBE || p.part_out ? p.part_out + (size_t)id.ks * p.T * p.d : p.y32;
+            float *rows32 = !PROBE || p.part_out ? p.part_out + (size_t)id.ks * p.T * p.d : rows32_of(p);
             const unsigned int v = (unsigned int)(4 * q * p.d + n) * 4u;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -794,9 +800,11 @@ k_prefix_down_tiles(const DownParams p)
 // 8 rows x 128 columns: thread = (row tid >> 5, four columns 4 (tid & 31) ..).
 __global__ void __launch_bounds__(256)
 k_prefix_down_combine(const float *__restrict__ part, int S, int T, int d, char *__restrict__ y,
-                      const float *__restrict__ bias, float *__restrict__ rowsq, float *__restrict__ y32, const int *__restrict__ skip)
+                      const float *__restrict__ bias, float *__restrict__ rowsq, float *__restrict__ y32, const int *__restrict__ skip,
+                      float *__restrict__ y32_alt, const int *__restrict__ alt)
 {
     if (skip && *skip) return;
+    if (alt && *alt == 0) y32 = y32_alt;
     const int t = blockIdx.x * 8 + (threadIdx.x >> 5);
     const int col = blockIdx.y * 128 + 4 * (threadIdx.x & 31);
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -984,14 +992,14 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
 
 // Down projection of h [T][Fp]: y [T][d] in the layer dtype and/or rowsq [col tiles][T], the
 // per-column-tile sums of squares of the fp32 output rows, and/or y32 [T][d], those rows without a bias (any may be
-// nullptr).  splitk_ws: room for the partial outputs of a split, splitk_bytes of it.  skip: device flag, nothing is computed when it
+// nullptr; with alt, a device flag, y32 is y32_alt when it is 0).  splitk_ws: room for the partial outputs of a split, splitk_bytes of it.  skip: device flag, nothing is computed when it
 // is set (nullptr: always computed).
 hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq,
-                             float *splitk_ws, size_t splitk_bytes, int tile_mode, hipStream_t stream, int num_cu, float *y32, const int *skip)
+                             float *splitk_ws, size_t splitk_bytes, int tile_mode, hipStream_t stream, int num_cu, float *y32, const int *skip, float *y32_alt, const int *alt)
 {
     const int d = layer->d, F = layer->d_ff, es = (int)dtype_size(layer->dtype);
     DownParams q;
-    q.y32 = y32; q.skip = skip;
+    q.y32 = y32; q.skip = skip; q.y32_alt = y32_alt; q.alt = alt;
     q.h = h; q.wd = (const char *)layer->w_down; q.y = y; q.rowsq = rowsq;
     q.bias = (layer->kind == CLADA_FFN_RELU && y) ? layer->b_out : nullptr;
     q.T = T; q.d = d; q.F = F; q.Fp = (int)align_up((size_t)F, 64);
@@ -1014,7 +1022,7 @@ hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, cha
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || S < 2) return e;
         hipLaunchKernelGGL(k_prefix_down_combine, dim3((T + 7) / 8, d / 128), dim3(256), 0, stream, splitk_ws, S, T, d,
-                           y, q.bias, rowsq, y32, skip);
+                           y, q.bias, rowsq, y32, skip, y32_alt, alt);
     }
     else if (es == 4) hipLaunchKernelGGL((probe ? k_prefix_down<4, true> : k_prefix_down<4, false>), dim3(grid), dim3(256), 0, stream, q);
     else         hipLaunchKernelGGL((probe ? k_prefix_down_bf16<true> : k_prefix_down_bf16<false>), dim3(grid), dim3(256), 0, stream, q);

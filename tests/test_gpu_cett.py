@@ -281,3 +281,27 @@ def test_search_cost_grows_with_the_tokens_not_with_their_square(clada):
             times.append(a.elapsed_time(b))
         best[n] = min(times)
     assert best[31] < 2.0 * best[30], best
+
+
+# d, F, T, dtype: one, three and seven thresholds a launch of the last stage (by the row norms' room: 1, 2, 4, 6 and more of them), just above
+# the smallest search that is bracketed, d_ff below and above 2 d (the probes' sums kept or formed again), more magnitudes in
+# the bracket than threads.
+@pytest.mark.parametrize("d,F,T,dtype", [(64, 4099, 64, "bf16"), (256, 3300, 80, "bf16"), (512, 2100, 130, "bf16"), (512, 1000, 263, "f32"),
+                                         (1536, 2000, 140, "f32"), (1104, 4111, 64, "bf16"), (64, 140000, 64, "bf16")])
+def test_search_thresholds_per_launch(clada, d, F, T, dtype):
+    """Against the plain bisection of 30 probes.  The sums' order differs (rel. 1e-6 of a norm, so 1e-6 of a mean whose slope over the
+    ranks is about one): the result may move by T F 1e-6 magnitudes and the one next to them, which lie up to 10 / (T F) apart."""
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(d + F)
+    n = lambda *s, k: torch.randn(s, generator=g, device=DEV) * k
+    layer = clada.Layer(*[n(F, d, k=d ** -0.5).to(dt) for _ in range(3)])
+    x = n(T, d, k=1.0).to(dt)
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    for bound in (0.03, 0.25, 0.7):
+        t30, m30 = clada.threshold_search_cett(ctx, layer, x, bound, n_probes=30)
+        t31, m31 = clada.threshold_search_cett(ctx, layer, x, bound)
+        again = clada.threshold_search_cett(ctx, layer, x, bound)
+        assert torch.equal(t31, again[0]) and torch.equal(m31, again[1])
+        assert float(t31) == pytest.approx(float(t30), rel=1e-5 + 20.0 / (T * F)), bound
+        assert float(m31) <= bound and float(m31) == pytest.approx(float(m30), rel=1e-5 + 20.0 / (T * F))
+        assert float(clada.cett_eval(ctx, layer, x, float(t31))[1]) == pytest.approx(float(m31), rel=2e-6)
