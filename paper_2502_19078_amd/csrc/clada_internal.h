@@ -120,7 +120,6 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
 hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, float *splitk_ws, size_t splitk_bytes,
                              int tile_mode, hipStream_t stream, int num_cu, float *y32 = nullptr, const int *skip = nullptr,
                              float *y32_alt = nullptr, const int *alt = nullptr);
-int clada_prefix_down_splits(int d, int F, int T);
 size_t clada_ws_down_splitk(int d, int F, int T);
 size_t clada_ws_down_room(int d, int F, int T);
 

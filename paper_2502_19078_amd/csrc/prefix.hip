@@ -698,7 +698,7 @@ k_prefix_down_bf16(const DownParams p)
 }
 
 // bf16 down projection on the pipelined tiles (d % 256 == 0), 256 columns of W_down a tile as they lie in memory: S::TM tokens x 256
-// columns x one of the S ranges the neurons are split into.
+// columns x one of the S ranges the neurons are split into.  (128 tokens: split only, for a wave then holds half a tile of the row norms.)
 template <class S, bool PROBE>
 __global__ void __launch_bounds__(512, 2)
 k_prefix_down_tiles(const DownParams p)
@@ -795,56 +795,23 @@ k_prefix_down_tiles(const DownParams p)
 #endif
 }
 
-// Sum of the S split-K partial outputs [S][T][d] in ascending order, then what the direct epilogue does:
-// y in bf16 (+ bias) and / or the per-row sums of squares of every 128-column tile.  A workgroup takes
-// 8 rows x 128 columns: thread = (row tid >> 5, four columns 4 (tid & 31) ..).
-__global__ void __launch_bounds__(256)
-k_prefix_down_combine(const float *__restrict__ part, int S, int T, int d, char *__restrict__ y,
-                      const float *__restrict__ bias, float *__restrict__ rowsq, float *__restrict__ y32, const int *__restrict__ skip,
-                      float *__restrict__ y32_alt, const int *__restrict__ alt)
-{
-    if (skip && *skip) return;
-    if (alt && *alt == 0) y32 = y32_alt;
-    const int t = blockIdx.x * 8 + (threadIdx.x >> 5);
-    const int col = blockIdx.y * 128 + 4 * (threadIdx.x & 31);
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (t < T) {
-        for (int k = 0; k < S; ++k) {
-            const float4 v = *reinterpret_cast<const float4 *>(part + ((size_t)k * T + t) * d + col);
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-        }
-    }
-    if (rowsq) {
-        float v = fmaf(s.x, s.x, fmaf(s.y, s.y, fmaf(s.z, s.z, s.w * s.w)));
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 8);
-        v += __shfl_xor(v, 4);
-        v += __shfl_xor(v, 2);
-        v += __shfl_xor(v, 1);
-        if ((threadIdx.x & 31) == 0 && t < T) rowsq[(size_t)blockIdx.y * T + t] = v;
-    }
-    if (y32 && t < T) *reinterpret_cast<float4 *>(y32 + (size_t)t * d + col) = s;
-    if (y && t < T) {
-        if (bias) {
-            const float4 b = *reinterpret_cast<const float4 *>(bias + col);
-            s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
-        }
-        uint2 o;
-        o.x = f32_to_bf16_bits(s.x) | (f32_to_bf16_bits(s.y) << 16);
-        o.y = f32_to_bf16_bits(s.z) | (f32_to_bf16_bits(s.w) << 16);
-        *reinterpret_cast<uint2 *>(y + ((size_t)t * d + col) * 2) = o;
-    }
-}
-
 // One wave per neuron: ||W_down[j,:]||^2, then fold the token-tile partials (fixed order)
 // and write the requested aggregates.
+struct ReduceParams {
+    const char *wd;
+    const float *part;          // [n_tm][4][F]
+    int d, F, n_tm, norm_rows;  // ||W_down[j,:]||^2 of the first norm_rows neurons lies in out.A already
+    clada_prefix_out out;
+};
 template <int ES>
-__global__ void __launch_bounds__(256)
-k_prefix_reduce(const char *__restrict__ wd, int d, int F, const float *__restrict__ part, int n_tm,
-                const clada_prefix_out out, int norm_rows)
+__device__ __forceinline__ void reduce_neurons(const ReduceParams &p, int block)
 {
+    const char *wd = p.wd;
+    const float *part = p.part;
+    const int d = p.d, F = p.F, n_tm = p.n_tm, norm_rows = p.norm_rows;
+    const clada_prefix_out &out = p.out;
     const int lane = threadIdx.x & 63;
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int j = block * 4 + (threadIdx.x >> 6);
     if (j >= F) return;
     float wn2 = 0.0f;
     if (out.A) {
@@ -878,6 +845,57 @@ k_prefix_reduce(const char *__restrict__ wd, int d, int F, const float *__restri
     }
 }
 
+template <int ES>
+__global__ void __launch_bounds__(256) k_prefix_reduce(const ReduceParams p) { reduce_neurons<ES>(p, blockIdx.x); }
+
+// Sum of the S split-K partial outputs [S][T][d] in ascending order, then what the direct epilogue does:
+// y in bf16 (+ bias) and / or the per-row sums of squares of every 128-column tile.  A workgroup takes
+// 8 rows x 128 columns: thread = (row tid >> 5, four columns 4 (tid & 31) ..).  The workgroups behind the first `blocks` do the
+// per-neuron reductions of the same call, which need nothing of this (bf16; 512 tokens of 4096 x 11008: 22.6 us in two launches and eight parts,
+// 16.8 so and with four).
+__global__ void __launch_bounds__(256)
+k_prefix_down_combine(int blocks, const ReduceParams red, const float *__restrict__ part, int S, int T, int d, char *__restrict__ y,
+                      const float *__restrict__ bias, float *__restrict__ rowsq, float *__restrict__ y32, const int *__restrict__ skip,
+                      float *__restrict__ y32_alt, const int *__restrict__ alt)
+{
+    if ((int)blockIdx.x >= blocks) {
+        reduce_neurons<2>(red, blockIdx.x - blocks);
+        return;
+    }
+    if (skip && *skip) return;
+    if (alt && *alt == 0) y32 = y32_alt;
+    const int tiles = (T + 7) / 8, tile = blockIdx.x / tiles;
+    const int t = (blockIdx.x - tile * tiles) * 8 + (threadIdx.x >> 5);
+    const int col = tile * 128 + 4 * (threadIdx.x & 31);
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (t < T) {
+        for (int k = 0; k < S; ++k) {
+            const float4 v = *reinterpret_cast<const float4 *>(part + ((size_t)k * T + t) * d + col);
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
+    }
+    if (rowsq) {
+        float v = fmaf(s.x, s.x, fmaf(s.y, s.y, fmaf(s.z, s.z, s.w * s.w)));
+        v += __shfl_xor(v, 16);
+        v += __shfl_xor(v, 8);
+        v += __shfl_xor(v, 4);
+        v += __shfl_xor(v, 2);
+        v += __shfl_xor(v, 1);
+        if ((threadIdx.x & 31) == 0 && t < T) rowsq[(size_t)tile * T + t] = v;
+    }
+    if (y32 && t < T) *reinterpret_cast<float4 *>(y32 + (size_t)t * d + col) = s;
+    if (y && t < T) {
+        if (bias) {
+            const float4 b = *reinterpret_cast<const float4 *>(bias + col);
+            s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
+        }
+        uint2 o;
+        o.x = f32_to_bf16_bits(s.x) | (f32_to_bf16_bits(s.y) << 16);
+        o.y = f32_to_bf16_bits(s.z) | (f32_to_bf16_bits(s.w) << 16);
+        *reinterpret_cast<uint2 *>(y + ((size_t)t * d + col) * 2) = o;
+    }
+}
+
 }  // namespace
 
 // Bytes a call needs for certain.  With room for them behind, the down projection splits d_ff further (clada_ws_prefix_room).
@@ -897,9 +915,9 @@ size_t clada_ws_prefix_room(int32_t d, int32_t d_ff, int32_t T)
 
 int clada_prefix_token_tiles(int T) { return (T + BM - 1) / BM; }
 
-// Parts that the bf16 down projection splits d_ff into where its 256 x 256 tiles leave compute units idle (fewer than 192): about one
+// Parts that 256 x 256 tiles of the bf16 down projection split d_ff into where they leave compute units idle (fewer than 192): about one
 // workgroup per unit, every part at least 256 neurons, at most 8.  1 = no split.
-int clada_prefix_down_splits(int d, int F, int T)
+static int down_splits(int d, int F, int T)
 {
     if (T <= 0 || d % 256 != 0) return 1;
     const int tiles = ((T + 255) / 256) * (d / 256);
@@ -909,15 +927,29 @@ int clada_prefix_down_splits(int d, int F, int T)
     if (S > F / 256) S = F / 256;
     return S < 2 ? 1 : S;
 }
+// The same for tiles of 128 tokens, up to 12 parts, if they are taken: where a part is short, the partial outputs weigh more than the
+// operands that a smaller tile reads again (whole calls, us, 256 / 128 tokens: 333 x 2560 x 10240 77.5 / 72.8, 512 x 4096 x 11008 136 / 130, 16 x
+// 4096 x 11008 81.9 / 71.3, 200 x 2048 x 8191 56 / 52; parts of more than 4096 neurons: 512 x 5120 x 13824 213 / 220, 333 x 8192 x
+// 20011 423 / 438, 777 x 4096 x 11008 218 / 211).  0: not taken.
+static int down_splits_half(int d, int F, int T)
+{
+    if (T <= 0 || d % 256 != 0) return 0;
+    int S = 256 / (((T + 127) / 128) * (d / 256));
+    if (S > 12) S = 12;
+    if (S > F / 256) S = F / 256;
+    return S < 2 || F / S > 4096 ? 0 : S;
+}
 // What is asked for at least (d_ff in multiples of 32 only), and what the split takes if it is there.
 size_t clada_ws_down_splitk(int d, int F, int T)
 {
-    return F % 32 == 0 ? clada_ws_down_room(d, F, T) : 0;
+    const int S = F % 32 == 0 ? down_splits(d, F, T) : 1;
+    return S > 1 ? align_up(sizeof(float) * (size_t)S * T * d, 256) : 0;
 }
 size_t clada_ws_down_room(int d, int F, int T)
 {
-    const int S = clada_prefix_down_splits(d, F, T);
-    return S > 1 ? align_up(sizeof(float) * (size_t)S * T * d, 256) : 0;
+    const int S = down_splits_half(d, F, T) ? down_splits_half(d, F, T) : down_splits(d, F, T);
+    const size_t need = clada_ws_down_splitk(d, F, T), room = S > 1 ? align_up(sizeof(float) * (size_t)S * T * d, 256) : 0;
+    return room > need ? room : need;
 }
 int clada_prefix_col_tiles(int d) { return (d + BN - 1) / BN; }
 
@@ -994,8 +1026,10 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
 // per-column-tile sums of squares of the fp32 output rows, and/or y32 [T][d], those rows without a bias (any may be
 // nullptr; with alt, a device flag, y32 is y32_alt when it is 0).  splitk_ws: room for the partial outputs of a split, splitk_bytes of it.  skip: device flag, nothing is computed when it
 // is set (nullptr: always computed).
-hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq,
-                             float *splitk_ws, size_t splitk_bytes, int tile_mode, hipStream_t stream, int num_cu, float *y32, const int *skip, float *y32_alt, const int *alt)
+// red: the call's per-neuron reductions, done along where a pass combines the parts of a split (*red_done).
+static hipError_t prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, float *splitk_ws, size_t splitk_bytes,
+                              int tile_mode, hipStream_t stream, int num_cu, float *y32, const int *skip, float *y32_alt, const int *alt,
+                              const ReduceParams *red, bool *red_done)
 {
     const int d = layer->d, F = layer->d_ff, es = (int)dtype_size(layer->dtype);
     DownParams q;
@@ -1009,24 +1043,37 @@ hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, cha
     q.part_out = nullptr; q.S = 1;
     // tile_mode 1 = 128 x 128 tiles of the plain kernel always
     if (es == 2 && d % 256 == 0 && tile_mode != 1) {
-        const int n_tmw = (T + 255) / 256, tiles = n_tmw * (d / 256);
-        int S = clada_prefix_down_splits(d, F, T);
         const size_t one = sizeof(float) * (size_t)T * d;
-        if (!splitk_ws) S = 1;
-        else if (S * one > splitk_bytes) S = (int)(splitk_bytes / one);
+        const int fit = splitk_ws ? (int)(splitk_bytes / one < 16 ? splitk_bytes / one : 16) : 0;      // parts there is room for
+        int S = down_splits_half(d, F, T);
+        const bool half = tile_mode != 2 && S >= 2 && fit >= S;
+        if (!half) S = down_splits(d, F, T);
+        if (S > fit) S = fit;
+        const int tiles = (half ? (T + 127) / 128 : (T + 255) / 256) * (d / 256);
         const int units = num_cu / 8 * 8 > 8 ? num_cu / 8 * 8 : 256;
-        const auto kern = probe ? k_prefix_down_tiles<TileShape<4, 4, 2, true>, true> : k_prefix_down_tiles<TileShape<4, 4, 2, true>, false>;
+        const auto kern = half ? (probe ? k_prefix_down_tiles<TileShape<2, 2, 2, true>, true> : k_prefix_down_tiles<TileShape<2, 2, 2, true>, false>)
+                               : (probe ? k_prefix_down_tiles<TileShape<4, 4, 2, true>, true> : k_prefix_down_tiles<TileShape<4, 4, 2, true>, false>);
         if (S > 1) { q.part_out = splitk_ws; q.S = S; }
         const int padded = (tiles * q.S + 7) / 8 * 8;
         hipLaunchKernelGGL(kern, dim3(padded < units ? padded : units), dim3(512), 0, stream, q);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || S < 2) return e;
-        hipLaunchKernelGGL(k_prefix_down_combine, dim3((T + 7) / 8, d / 128), dim3(256), 0, stream, splitk_ws, S, T, d,
+        const int blocks = (T + 7) / 8 * (d / 128);
+        ReduceParams r = {};
+        if (red) r = *red;
+        hipLaunchKernelGGL(k_prefix_down_combine, dim3(blocks + (red ? (F + 3) / 4 : 0)), dim3(256), 0, stream, blocks, r, splitk_ws, S, T, d,
                            y, q.bias, rowsq, y32, skip, y32_alt, alt);
+        if (red) *red_done = true;
     }
     else if (es == 4) hipLaunchKernelGGL((probe ? k_prefix_down<4, true> : k_prefix_down<4, false>), dim3(grid), dim3(256), 0, stream, q);
     else         hipLaunchKernelGGL((probe ? k_prefix_down_bf16<true> : k_prefix_down_bf16<false>), dim3(grid), dim3(256), 0, stream, q);
     return hipGetLastError();
+}
+
+hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, float *splitk_ws, size_t splitk_bytes,
+                             int tile_mode, hipStream_t stream, int num_cu, float *y32, const int *skip, float *y32_alt, const int *alt)
+{
+    return prefix_down(layer, h, T, y, rowsq, splitk_ws, splitk_bytes, tile_mode, stream, num_cu, y32, skip, y32_alt, alt, nullptr, nullptr);
 }
 
 extern "C" clada_status clada_prefix_stats(clada_ctx *ctx, const clada_layer *layer, const void *x,
@@ -1053,16 +1100,17 @@ extern "C" clada_status clada_prefix_stats(clada_ctx *ctx, const clada_layer *la
     int norm_rows = 0, n_part = 0;                          // || W_down[j,:] ||^2 of the first norm_rows neurons already lies in out->A
     CLADA_CHECK_HIP(ctx, clada_prefix_gateup(layer, x, T, part, out->abs_act_pool, hbuf, ctx->opt_prefix_tile, stream, ctx->num_cu, &n_part,
                                              out->A, &norm_rows));
+    const bool wanted = out->sum_abs_act || out->sum_sq_act || out->max_abs_act || out->sum_sq_h || out->A;
+    const ReduceParams red = {(const char *)layer->w_down, part, d, F, n_part, norm_rows, *out};
+    bool reduced = !wanted;
     if (y) {
         const size_t split_at = h_at + align_up((size_t)T * align_up((size_t)F, 64) * 4, 256);
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, hbuf, T, (char *)y, nullptr, reinterpret_cast<float *>(ws + split_at),
-                                               ctx->ws_bytes - CLADA_WS_HEADER - split_at, ctx->opt_prefix_tile, stream, ctx->num_cu));
+        CLADA_CHECK_HIP(ctx, prefix_down(layer, hbuf, T, (char *)y, nullptr, reinterpret_cast<float *>(ws + split_at),
+                                         ctx->ws_bytes - CLADA_WS_HEADER - split_at, ctx->opt_prefix_tile, stream, ctx->num_cu, nullptr, nullptr,
+                                         nullptr, nullptr, wanted ? &red : nullptr, &reduced));
     }
-    if (out->sum_abs_act || out->sum_sq_act || out->max_abs_act || out->sum_sq_h || out->A) {
-        if (es == 4) hipLaunchKernelGGL(k_prefix_reduce<4>, dim3((F + 3) / 4), dim3(256), 0, stream,
-                                        (const char *)layer->w_down, d, F, part, n_part, *out, norm_rows);
-        else         hipLaunchKernelGGL(k_prefix_reduce<2>, dim3((F + 3) / 4), dim3(256), 0, stream,
-                                        (const char *)layer->w_down, d, F, part, n_part, *out, norm_rows);
+    if (!reduced) {
+        hipLaunchKernelGGL((es == 4 ? k_prefix_reduce<4> : k_prefix_reduce<2>), dim3((F + 3) / 4), dim3(256), 0, stream, red);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
     }
     return CLADA_OK;
