@@ -11,8 +11,8 @@
 // One partial output [tokens][d] per workgroup; k_ffn_finalize adds them in fixed order.
 //
 // What bounds it: HBM, and the 256 partial outputs (17 MB written and read at four tokens of 4096).  A 4096 x 11008 fp32
-// layer at sparsity 0.45, union of independent tokens: 107 us at four tokens (526 MB: 4.9 TB/s), 132 us at eight; the generic
-// kernel, one token per grid row, reads the weights once per token and takes 394 and 772 us.
+// layer at sparsity 0.45, union of independent tokens: 98.6 us at four tokens (526 MB: 5.3 TB/s; 107 with 92 MB of rows requested twice); the generic
+// kernel, one token per grid row, reads the weights once per token and takes 394 us.
 //
 // Arithmetic.  fp32: one chain of fmaf per lane and a fixed tree over the wave for the dots; the kept neurons of a workgroup are
 // one chain per column, where the generic kernel folds eight waves' shorter chains (error of that layer at four tokens against
@@ -83,13 +83,16 @@ k_ffn_multi(const MultiParams p)
 #pragma unroll
             for (int k = 0; k < VEC; ++k) acc[t][s][k] = 0.0f;
 
-    // UQ chunks of a row; a lane beyond the row reads its start instead, and its value counts as zero
-    auto request = [&](u32x4 (&b)[UQ], const char *w, int j, int part) {
-        const char *row = w + (size_t)j * rowb;
+    // UQ chunks of a row; a lane beyond the row reads its start instead, and its value counts as zero.  Without a row (real: uniform) the
+    // request goes to the start of x, which the caches hold: no branch around the loads, and no row of weights twice (a wave's
+    // last request of a phase used to: 618 MB for 526 of the 4096 x 11008 layer at four tokens).
+    auto request = [&](u32x4 (&b)[UQ], const char *w, int j, int part, bool real) {
+        const char *row = real ? w + (size_t)j * rowb + part * UQ * 1024 : p.x;
+        const int end = real ? (int)rowb - part * UQ * 1024 : 0;
 #pragma unroll
         for (int c = 0; c < UQ; ++c) {
-            const int o = (part * UQ + c) * 1024 + lane * 16;
-            b[c] = ld_stream16(row + (o < (int)rowb ? o : 0));
+            const int o = c * 1024 + lane * 16;
+            b[c] = ld_stream16(row + (o < end ? o : 0));
         }
     };
     auto reduce = [&](const u32x4 (&b)[UQ], int part, float (&s)[TB]) {
@@ -108,12 +111,12 @@ k_ffn_multi(const MultiParams p)
         u32x4 b0[UQ], b1[UQ];
         float s[TB];
         int i = first, q = 0;                                // request being reduced
-        request(b0, w, row_of(i), 0);
+        request(b0, w, row_of(i), 0, true);
         auto step = [&](const u32x4 (&cur)[UQ], u32x4 (&nxt)[UQ]) -> bool {
             int ni = i, nq = q + 1;
             if (nq == parts) { nq = 0; ni += NW; }
             const bool more = ni < n;
-            request(nxt, w, row_of(more ? ni : i), nq);      // (after the last one: some valid row again)
+            request(nxt, w, row_of(more ? ni : i), nq, more);
             if (q == 0) {
 #pragma unroll
                 for (int t = 0; t < TB; ++t) s[t] = 0.0f;
