@@ -1003,7 +1003,7 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
     const int most_wide = 24 + d / 32, most_two = 16 + d / 64, most_one = 20 + d / 128;
     if (relu) {
         if (wide) return launch(k_prefix_gateup_tiles<TileShape<4, 4, 2, false>, true>, n_tmw * ((F + 255) / 256), n_tmw, most_wide, 57);
-        return launch(k_prefix_gateup_tiles<TileShape<2, 1, 4, false>, true>, total, g.n_tm, most_one, 50);
+        return launch(k_prefix_gateup_tiles<TileShape<2, 1, 4, false, true>, true>, total, g.n_tm, most_one, 50);
     }
     if (wide) {
         // Tiles of 96 neurons where rounds of three quarters the length do not grow by more than an eighth in number: the last round
@@ -1018,7 +1018,7 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
     // one token tile and units left over: 64 neurons a tile (us, 128 / 64 neurons: 4096 x 11008 at 64 tokens 64.5 / 49.5, 2560 x 10240 38.5 /
     // 32.6, 4096 x 14336 79.5 / 73.7; more than one round: 8192 x 20011 183 / 212)
     if (T <= 128 && 2 * total <= num_cu)
-        return launch(k_prefix_gateup_tiles<TileShape<2, 1, 4, false>, false>, g.n_tm * ((F + 63) / 64), g.n_tm, most_two, 50);
+        return launch(k_prefix_gateup_tiles<TileShape<2, 1, 4, false, true>, false>, g.n_tm * ((F + 63) / 64), g.n_tm, most_two, 50);
     return launch(k_prefix_gateup_tiles<TileShape<2, 2, 2, false>, false>, total, g.n_tm, most_two, 50);
 }
 

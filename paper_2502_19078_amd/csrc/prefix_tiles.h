@@ -25,10 +25,13 @@ typedef __attribute__((address_space(3))) char lds_char;
 
 // WM x (8 / WM) waves of 64 x 32 NB outputs; D k-tiles in flight.  X tiles ([TM rows][64 k], 128 bytes a row) ring over D slots, W tiles
 // over D + 1.  TR = false: W as it lies for the gate / up product, [TN rows][64 k]; TR = true: [64 k][TN columns], read transposed.
-template <int WM_, int NB_, int D_, bool TR_>
+// WHOLE: a group reads and multiplies a whole k-tile between barriers, else half of one: for the smallest tile, whose half is eight
+// products (128 clocks) a wave (gate/up of 333 x 2560 x 10240 ReLU 42 -> 38 us with its reduction; 128 x 128 neurons, sixteen
+// products a half: 66 -> 72 at 200 x 4096 x 11008).
+template <int WM_, int NB_, int D_, bool TR_, bool WHOLE_ = false>
 struct TileShape {
     static constexpr int WM = WM_, NB = NB_, D = D_, WN = 8 / WM, TM = 64 * WM, TN = 32 * NB * WN;
-    static constexpr bool TR = TR_;
+    static constexpr bool TR = TR_, WHOLE = WHOLE_;
     static constexpr int XB = TM * 128, WB = TN * 128, LDS = D * XB + (D + 1) * WB;
     static constexpr int PX = TM / 64, PW = TN / 64;        // 1 KiB transfers of a wave per k-tile
     static_assert(LDS <= 160 * 1024 && 2 * NB >= PX && 2 * NB >= PW && (!TR || TN == 256), "tile shape");
@@ -135,8 +138,9 @@ __device__ __forceinline__ void tile_products(char *lds, int x_pitch, const int 
     unsigned int tj[2 * NB];
 #pragma unroll
     for (int j = 0; j < 2 * NB; ++j) tj[j] = ta + (unsigned int)(((wn * 2 * NB + j) ^ sw) * 32);
-    u32x4 fx[4], fw[2 * NB];
-    u32x2 ft[2 * NB][2];
+    constexpr int SETS = S::WHOLE ? 2 : 1;
+    u32x4 fx[SETS][4], fw[SETS][2 * NB];
+    u32x2 ft[SETS][2 * NB][2];
     auto read = [&](u32x4 (&fx)[4], u32x4 (&fw)[2 * NB], u32x2 (&ft)[2 * NB][2], unsigned int xs, unsigned int wslot, auto hc) {
         constexpr int H = decltype(hc)::value;              // half of the k-tile
         const unsigned int px = (xa ^ (unsigned int)(H * 64)) + xs, pw = (wa ^ (unsigned int)(H * 64)) + wslot;
@@ -205,27 +209,37 @@ __device__ __forceinline__ void tile_products(char *lds, int x_pitch, const int 
         if (grp == 1) __builtin_amdgcn_s_barrier();         // half a k-tile behind the other group
         for (int k = 0; k < nk; ++k) {
 #define TILE_SB __builtin_amdgcn_sched_barrier(0);
+            using H0 = std::integral_constant<int, 0>;
+            using H1 = std::integral_constant<int, 1>;
+            constexpr int L = SETS - 1;                     // fragment set of the second half
             TILE_SB
-            read(fx, fw, ft, xs, ws, std::integral_constant<int, 0>{});
+            read(fx[0], fw[0], ft[0], xs, ws, H0{});
+            if constexpr (S::WHOLE) {
+                read(fx[L], fw[L], ft[L], xs, ws, H1{});
+                wait_vmcnt<FLY - PW>();                     // this wave's part of the next W tile
+            }
             advance();
-            landed(fx, fw, ft);
+            landed(fx[0], fw[0], ft[0]);
+            if constexpr (S::WHOLE) landed(fx[L], fw[L], ft[L]);
             TILE_SB
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_s_setprio(1);
             TILE_SB
-            products(acc, fx, fw, ft, send_w, NW{}, D * XB + wf);       // the slot that both groups left a k-tile ago
+            products(acc, fx[0], fw[0], ft[0], send_w, NW{}, D * XB + wf);      // the slot that both groups left a k-tile ago
             TILE_SB
-            __builtin_amdgcn_s_setprio(0);
-            __builtin_amdgcn_s_barrier();
-            TILE_SB
-            read(fx, fw, ft, xs, ws, std::integral_constant<int, 1>{});
-            wait_vmcnt<FLY>();                              // this wave's part of the next W tile
-            landed(fx, fw, ft);
-            TILE_SB
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_s_setprio(1);
-            TILE_SB
-            products(acc, fx, fw, ft, send_x, NX{}, xs);    // the rows that this group has just read for the last time
+            if constexpr (!S::WHOLE) {
+                __builtin_amdgcn_s_setprio(0);
+                __builtin_amdgcn_s_barrier();
+                TILE_SB
+                read(fx[0], fw[0], ft[0], xs, ws, H1{});
+                wait_vmcnt<FLY>();                          // this wave's part of the next W tile
+                landed(fx[0], fw[0], ft[0]);
+                TILE_SB
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_s_setprio(1);
+                TILE_SB
+            }
+            products(acc, fx[L], fw[L], ft[L], send_x, NX{}, xs);       // the rows that this group has just read for the last time
             TILE_SB
             __builtin_amdgcn_s_setprio(0);
             wait_vmcnt<FLY>();                              // and of the next X tile
