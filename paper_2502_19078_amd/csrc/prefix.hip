@@ -11,8 +11,8 @@
 //   kernel 3: fixed-order reduction of the per-token-tile partials,
 //     A_j = sqrt(sum_t h_tj^2) * ||W_down[j,:]||_2.
 // bf16 layers run on the pipelined tiles of prefix_tiles.h; fp32 layers, and bf16 ones whose rows are no
-// multiple of the k-tile, on plain 128x128 tiles: four wavefronts of 64x64, MFMA 32x32x16 (bf16) or 32x32x2
-// (fp32), fp32 accumulation.  Block ids are remapped so that the eight XCDs each walk their own range of tiles
+// multiple of the k-tile, on plain tiles (gate/up 128 or 64 tokens x 64 neurons, down 128 x 128) of four
+// wavefronts, MFMA 32x32x16 (bf16) or 32x32x2 (fp32), fp32 accumulation.  Block ids are remapped so that the eight XCDs each walk their own range of tiles
 // (operand slices stay in that XCD's L2).
 #include <math.h>
 
@@ -32,44 +32,44 @@ template <int ES> struct Tile {
     static constexpr int PER_THREAD = BM * CHUNKS / 256; // chunks each thread moves per tile
 };
 
-// One k-tile of MFMAs for a 64x64 wave tile.  sa / sb point at the wave's first
+// One k-tile of MFMAs for a wave tile of 32 MB x 32 NK.  sa / sb point at the wave's first
 // row of the A / B tile in LDS.
-template <int ES, int NB>
-__device__ __forceinline__ void mma_tile(const char *sa, const char *const (&sb)[NB], f32x16 (&acc)[NB][2][2], int lane)
+template <int ES, int NB, int MB, int NK>
+__device__ __forceinline__ void mma_tile(const char *sa, const char *const (&sb)[NB], f32x16 (&acc)[NB][MB][NK], int lane)
 {
     constexpr int ROW = Tile<ES>::ROW;
     const int r = lane & 31, q = lane >> 5;
     if (ES == 2) {
 #pragma unroll
         for (int ks = 0; ks < BKV<ES> / 16; ++ks) {
-            bf16x8 a[2];
+            bf16x8 a[MB];
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
                 a[mb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(sa + (mb * 32 + r) * ROW + (ks * 16 + q * 8) * 2));
 #pragma unroll
             for (int w = 0; w < NB; ++w)
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
+                for (int nb = 0; nb < NK; ++nb) {
                     const bf16x8 bv = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(sb[w] + (nb * 32 + r) * ROW + (ks * 16 + q * 8) * 2));
 #pragma unroll
-                    for (int mb = 0; mb < 2; ++mb)
+                    for (int mb = 0; mb < MB; ++mb)
                         acc[w][mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mb], bv, acc[w][mb][nb], 0, 0, 0);
                 }
         }
     } else {
 #pragma unroll
         for (int ks = 0; ks < BKV<ES> / 2; ++ks) {
-            float a[2];
+            float a[MB];
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
                 a[mb] = *reinterpret_cast<const float *>(sa + (mb * 32 + r) * ROW + (ks * 2 + q) * 4);
 #pragma unroll
             for (int w = 0; w < NB; ++w)
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
+                for (int nb = 0; nb < NK; ++nb) {
                     const float bv = *reinterpret_cast<const float *>(sb[w] + (nb * 32 + r) * ROW + (ks * 2 + q) * 4);
 #pragma unroll
-                    for (int mb = 0; mb < 2; ++mb)
+                    for (int mb = 0; mb < MB; ++mb)
                         acc[w][mb][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mb], bv, acc[w][mb][nb], 0, 0, 0);
                 }
         }
@@ -120,22 +120,22 @@ struct GateUpParams {
 
 // Epilogue of the gate/up GEMM on the accumulators (shared by the fp32 and bf16 kernels):
 // a = SiLU(C_g), h = a*C_u, per-neuron partial sums over the tile's tokens, |a| pool, h store.
-template <int ES>
-__device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[2][2][2], const GateUpParams &p, int tm, int tn,
-                                                int wm, int wn, int lane, int tid, float (&s_stat)[2][4][BN])
+template <int ES, int WMN, int MB, int NK, int NEU>
+__device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[2][MB][NK], const GateUpParams &p, int tm, int tn,
+                                                int wm, int wn, int lane, int tid, float (&s_stat)[WMN][4][NEU])
 {
     // ------------------------------------------------------------------ epilogue
     const int n = lane & 31;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const int jl = wn * 64 + nb * 32 + n;          // neuron inside the tile
-        const int j = tn * BN + jl;
+    for (int nb = 0; nb < NK; ++nb) {
+        const int jl = wn * 32 * NK + nb * 32 + n;          // neuron inside the tile
+        const int j = tn * NEU + jl;
         float s_abs = 0.f, s_sq = 0.f, mx = 0.f, s_h2 = 0.f;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int t = tm * BM + wm * 64 + mb * 32 + acc_row(r, lane);
+                const int t = (tm * WMN + wm) * 32 * MB + mb * 32 + acc_row(r, lane);
                 float a, h;
                 if (p.relu) {
                     const float g = acc[0][mb][nb][r] + ((p.b_in && j < p.F) ? p.b_in[j] : 0.0f);
@@ -173,59 +173,65 @@ __device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[2][2][2], co
         }
     }
     __syncthreads();
-    if (tid < BN) {
-        const int j = tn * BN + tid;
+    if (tid < NEU) {
+        const int j = tn * NEU + tid;
         if (j < p.F) {
             float *dst = p.part + (size_t)tm * 4 * p.F + j;
-            dst[0] = s_stat[0][0][tid] + s_stat[1][0][tid];
-            dst[(size_t)p.F] = s_stat[0][1][tid] + s_stat[1][1][tid];
-            const float m0 = s_stat[0][2][tid], m1 = s_stat[1][2][tid];
+            dst[0] = s_stat[0][0][tid] + (WMN > 1 ? s_stat[WMN - 1][0][tid] : 0.0f);
+            dst[(size_t)p.F] = s_stat[0][1][tid] + (WMN > 1 ? s_stat[WMN - 1][1][tid] : 0.0f);
+            const float m0 = s_stat[0][2][tid], m1 = s_stat[WMN - 1][2][tid];
             dst[2 * (size_t)p.F] = (m1 > m0 || m1 != m1) ? m1 : m0;
-            dst[3 * (size_t)p.F] = s_stat[0][3][tid] + s_stat[1][3][tid];
+            dst[3 * (size_t)p.F] = s_stat[0][3][tid] + (WMN > 1 ? s_stat[WMN - 1][3][tid] : 0.0f);
         }
     }
 }
 
-template <int ES>
+// TT tokens x 64 neurons a workgroup, four waves of (TT / 2) x 32: two workgroups fit a compute unit (148 registers), so that one's
+// products cover the other's staging, and a short prefix still has tiles for the chip.  Before, 128 x 128 with 280 registers (fp32, us,
+// without y): 4096 x 11008 at 512 tokens 1217 / 927, at 128 618 / 359, 2048 x 6000 at 200 299 / 167; 64-token tiles for up to 64 tokens,
+// 4096 x 9000 at 32: 594 / 225.
+template <int ES, int TT>
 __global__ void __launch_bounds__(256)
 k_prefix_gateup(const GateUpParams p)
 {
-    constexpr int ROW = Tile<ES>::ROW, CH = Tile<ES>::CHUNKS, PT = Tile<ES>::PER_THREAD;
-    __shared__ __align__(16) char s_a[BM * ROW];
-    __shared__ __align__(16) char s_g[BN * ROW];
-    __shared__ __align__(16) char s_u[BN * ROW];
-    __shared__ float s_stat[2][4][BN];
+    constexpr int NEU = 64, ROW = Tile<ES>::ROW, CH = Tile<ES>::CHUNKS, PT = NEU * CH / 256, PX = TT * CH / 256;
+    constexpr int WMN = 2, MB = TT / 64, NK = 1;
+    static_assert(PX >= PT, "the token tile is the larger one");
+    __shared__ __align__(16) char s_a[TT * ROW];
+    __shared__ __align__(16) char s_g[NEU * ROW];
+    __shared__ __align__(16) char s_u[NEU * ROW];
+    __shared__ float s_stat[WMN][4][NEU];
 
     const int total = p.n_tm * p.n_tn;
     const int tile = remap_block(blockIdx.x, total);
     if (tile >= total) return;
     const int tm = tile % p.n_tm, tn = tile / p.n_tm;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave & 1, wn = wave >> 1;
+    const int wm = wave % WMN, wn = wave / WMN;
     const size_t rowbytes = (size_t)p.d * ES;
 
-    f32x16 acc[2][2][2];
+    f32x16 acc[2][MB][NK];
 #pragma unroll
     for (int w = 0; w < 2; ++w)
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+            for (int nb = 0; nb < NK; ++nb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[w][mb][nb][r] = 0.0f;
 
-    u32x4 ra[PT], rg[PT], ru[PT];
+    u32x4 ra[PX], rg[PT], ru[PT];
     auto load_tile = [&](int kt) {
 #pragma unroll
-        for (int i = 0; i < PT; ++i) {
+        for (int i = 0; i < PX; ++i) {
             const int c = tid + i * 256, row = c / CH, ch = c % CH;
             const int kbyte = kt * BKV<ES> * ES + ch * 16;
             const bool kin = (size_t)kbyte < rowbytes;
-            const int t = tm * BM + row, j = tn * BN + row;
+            const int t = tm * TT + row, j = tn * NEU + row;
             u32x4 z = {0u, 0u, 0u, 0u};
             ra[i] = (kin && t < p.T) ? *reinterpret_cast<const u32x4 *>(p.x + (size_t)t * rowbytes + kbyte) : z;
-            rg[i] = (kin && j < p.F) ? *reinterpret_cast<const u32x4 *>(p.wg + (size_t)j * rowbytes + kbyte) : z;
-            ru[i] = (kin && j < p.F) ? *reinterpret_cast<const u32x4 *>(p.wu + (size_t)j * rowbytes + kbyte) : z;
+            if (i < PT) rg[i < PT ? i : 0] = (kin && j < p.F) ? *reinterpret_cast<const u32x4 *>(p.wg + (size_t)j * rowbytes + kbyte) : z;
+            if (i < PT) ru[i < PT ? i : 0] = (kin && j < p.F) ? *reinterpret_cast<const u32x4 *>(p.wu + (size_t)j * rowbytes + kbyte) : z;
         }
     };
     const int nk = (p.d + BKV<ES> - 1) / BKV<ES>;
@@ -233,19 +239,19 @@ k_prefix_gateup(const GateUpParams p)
     for (int kt = 0; kt < nk; ++kt) {
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < PT; ++i) {
+        for (int i = 0; i < PX; ++i) {
             const int c = tid + i * 256, row = c / CH, ch = c % CH;
             *reinterpret_cast<u32x4 *>(s_a + row * ROW + ch * 16) = ra[i];
-            *reinterpret_cast<u32x4 *>(s_g + row * ROW + ch * 16) = rg[i];
-            *reinterpret_cast<u32x4 *>(s_u + row * ROW + ch * 16) = ru[i];
+            if (i < PT) *reinterpret_cast<u32x4 *>(s_g + row * ROW + ch * 16) = rg[i < PT ? i : 0];
+            if (i < PT) *reinterpret_cast<u32x4 *>(s_u + row * ROW + ch * 16) = ru[i < PT ? i : 0];
         }
         __syncthreads();
         if (kt + 1 < nk) load_tile(kt + 1);
-        const char *const sb[2] = {s_g + wn * 64 * ROW, s_u + wn * 64 * ROW};
-        mma_tile<ES, 2>(s_a + wm * 64 * ROW, sb, acc, lane);
+        const char *const sb[2] = {s_g + wn * 32 * NK * ROW, s_u + wn * 32 * NK * ROW};
+        mma_tile<ES, 2, MB, NK>(s_a + wm * 32 * MB * ROW, sb, acc, lane);
     }
 
-    gateup_epilogue<ES>(acc, p, tm, tn, wm, wn, lane, tid, s_stat);
+    gateup_epilogue<ES, WMN, MB, NK, NEU>(acc, p, tm, tn, wm, wn, lane, tid, s_stat);
 }
 
 // Sum of squares of a row of W_down, by one wave: 16-byte chunks, lane l takes chunks l, l + 64, .. (eight loads in flight).
@@ -473,9 +479,8 @@ __device__ __forceinline__ void down_rowsq(const f32x16 (&acc)[2][2], const Down
 __device__ __forceinline__ float *rows32_of(const DownParams &p) { return p.alt && *p.alt == 0 ? p.y32_alt : p.y32; }
 
 // The fp32 rows of a 128 x 128 tile, without a bias.
-__device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const DownParams &p, int tm, int tn, int wm, int wn, int lane)
+__device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const DownParams &p, float *rows, int tm, int tn, int wm, int wn, int lane)
 {
-    float *rows = rows32_of(p);
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
         const int col = tn * BN + wn * 64 + nb * 32 + (lane & 31);
@@ -502,9 +507,10 @@ k_prefix_down(const DownParams p)
     __shared__ __align__(16) char s_b[BN * ROW];      // [n][k]: W_down tile transposed
     __shared__ float s_rs[2][BM];
 
-    const int total = p.n_tm * p.n_tn;
-    const int tile = remap_block(blockIdx.x, total);
-    if (tile >= total) return;
+    const int total = p.n_tm * p.n_tn * p.S;
+    const int o = remap_block(blockIdx.x, total);
+    if (o >= total) return;
+    const int ks = o / (p.n_tm * p.n_tn), tile = o - ks * p.n_tm * p.n_tn;
     const int tm = tile % p.n_tm, tn = tile / p.n_tm;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 1, wn = wave >> 1;
@@ -541,9 +547,11 @@ k_prefix_down(const DownParams p)
             rb[i] = (j < p.F && nbyte < wrow) ? *reinterpret_cast<const u32x4 *>(p.wd + (size_t)j * wrow + nbyte) : z;
         }
     };
-    const int nk = (p.F + BKV<ES> - 1) / BKV<ES>;
-    load_tile(0);
-    for (int kt = 0; kt < nk; ++kt) {
+    // this part's k-tiles (parts of a split hold at least 256 neurons each)
+    const int nk_all = (p.F + BKV<ES> - 1) / BKV<ES>;
+    const int kt0 = (int)((long long)ks * nk_all / p.S), nk = (int)((long long)(ks + 1) * nk_all / p.S);
+    load_tile(kt0);
+    for (int kt = kt0; kt < nk; ++kt) {
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < PT; ++i) {
@@ -564,10 +572,14 @@ k_prefix_down(const DownParams p)
         __syncthreads();
         if (kt + 1 < nk) load_tile(kt + 1);
         const char *const sb[1] = {s_b + wn * 64 * ROW};
-        mma_tile<ES, 1>(s_a + wm * 64 * ROW, sb, acc, lane);
+        mma_tile<ES, 1, 2, 2>(s_a + wm * 64 * ROW, sb, acc, lane);
+    }
+    if (p.part_out) {                                       // split: fp32 partial sums, added up by k_prefix_down_combine
+        down_store32(acc[0], p, p.part_out + (size_t)ks * p.T * p.d, tm, tn, wm, wn, lane);
+        return;
     }
     if (p.rowsq) down_rowsq(acc[0], p, tm, tn, wm, wn, lane, tid, s_rs);
-    if (PROBE && p.y32) down_store32(acc[0], p, tm, tn, wm, wn, lane);
+    if (PROBE && p.y32) down_store32(acc[0], p, rows32_of(p), tm, tn, wm, wn, lane);
     if (!p.y) return;
     const int n = lane & 31;
 #pragma unroll
@@ -679,7 +691,7 @@ k_prefix_down_bf16(const DownParams p)
         }
     }
     if (p.rowsq) down_rowsq(acc, p, tm, tn, wm, wn, lane, tid, s_rs);
-    if (PROBE && p.y32) down_store32(acc, p, tm, tn, wm, wn, lane);
+    if (PROBE && p.y32) down_store32(acc, p, rows32_of(p), tm, tn, wm, wn, lane);
     if (!p.y) return;
     const int n = lane & 31;
 #pragma unroll
@@ -853,13 +865,14 @@ __global__ void __launch_bounds__(256) k_prefix_reduce(const ReduceParams p) { r
 // 8 rows x 128 columns: thread = (row tid >> 5, four columns 4 (tid & 31) ..).  The workgroups behind the first `blocks` do the
 // per-neuron reductions of the same call, which need nothing of this (bf16; 512 tokens of 4096 x 11008: 22.6 us in two launches and eight parts,
 // 16.8 so and with four).
+template <int ES>
 __global__ void __launch_bounds__(256)
 k_prefix_down_combine(int blocks, const ReduceParams red, const float *__restrict__ part, int S, int T, int d, char *__restrict__ y,
                       const float *__restrict__ bias, float *__restrict__ rowsq, float *__restrict__ y32, const int *__restrict__ skip,
                       float *__restrict__ y32_alt, const int *__restrict__ alt)
 {
     if ((int)blockIdx.x >= blocks) {
-        reduce_neurons<2>(red, blockIdx.x - blocks);
+        reduce_neurons<ES>(red, blockIdx.x - blocks);
         return;
     }
     if (skip && *skip) return;
@@ -868,7 +881,8 @@ k_prefix_down_combine(int blocks, const ReduceParams red, const float *__restric
     const int t = (blockIdx.x - tile * tiles) * 8 + (threadIdx.x >> 5);
     const int col = tile * 128 + 4 * (threadIdx.x & 31);
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (t < T) {
+    const bool here = t < T && col < d;                     // (d is a multiple of 4)
+    if (here) {
         for (int k = 0; k < S; ++k) {
             const float4 v = *reinterpret_cast<const float4 *>(part + ((size_t)k * T + t) * d + col);
             s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
@@ -883,11 +897,15 @@ k_prefix_down_combine(int blocks, const ReduceParams red, const float *__restric
         v += __shfl_xor(v, 1);
         if ((threadIdx.x & 31) == 0 && t < T) rowsq[(size_t)tile * T + t] = v;
     }
-    if (y32 && t < T) *reinterpret_cast<float4 *>(y32 + (size_t)t * d + col) = s;
-    if (y && t < T) {
+    if (y32 && here) *reinterpret_cast<float4 *>(y32 + (size_t)t * d + col) = s;
+    if (y && here) {
         if (bias) {
             const float4 b = *reinterpret_cast<const float4 *>(bias + col);
             s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
+        }
+        if (ES == 4) {
+            *reinterpret_cast<float4 *>(y + ((size_t)t * d + col) * 4) = s;
+            return;
         }
         uint2 o;
         o.x = f32_to_bf16_bits(s.x) | (f32_to_bf16_bits(s.y) << 16);
@@ -975,8 +993,9 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
     const int total = g.n_tm * g.n_tn;
     if (es == 4 || d % 64 != 0) {
         if (n_part) *n_part = g.n_tm;
-        if (es == 4) hipLaunchKernelGGL(k_prefix_gateup<4>, dim3((total + 7) / 8 * 8), dim3(256), 0, stream, g);
-        else         hipLaunchKernelGGL(k_prefix_gateup<2>, dim3((total + 7) / 8 * 8), dim3(256), 0, stream, g);
+        g.n_tn = (F + 63) / 64;
+        const auto kern = T <= 64 ? (es == 4 ? k_prefix_gateup<4, 64> : k_prefix_gateup<2, 64>) : (es == 4 ? k_prefix_gateup<4, 128> : k_prefix_gateup<2, 128>);
+        hipLaunchKernelGGL(kern, dim3((g.n_tm * g.n_tn + 7) / 8 * 8), dim3(256), 0, stream, g);
         return hipGetLastError();
     }
     // tile_mode: 0 = choose, 1 = 128-token tiles, 2 = 256-token tiles
@@ -1041,6 +1060,15 @@ static hipError_t prefix_down(const clada_layer *layer, const char *h, int T, ch
     const int tot = q.n_tm * q.n_tn, grid = (tot + 7) / 8 * 8;
     const bool probe = y32 || skip;
     q.part_out = nullptr; q.S = 1;
+    auto combine = [&](int S) {
+        const int blocks = (T + 7) / 8 * q.n_tn;
+        ReduceParams r = {};
+        if (red) r = *red;
+        hipLaunchKernelGGL((es == 4 ? k_prefix_down_combine<4> : k_prefix_down_combine<2>), dim3(blocks + (red ? (F + 3) / 4 : 0)), dim3(256), 0, stream,
+                           blocks, r, splitk_ws, S, T, d, y, q.bias, rowsq, y32, skip, y32_alt, alt);
+        if (red) *red_done = true;
+        return hipGetLastError();
+    };
     // tile_mode 1 = 128 x 128 tiles of the plain kernel always
     if (es == 2 && d % 256 == 0 && tile_mode != 1) {
         const size_t one = sizeof(float) * (size_t)T * d;
@@ -1058,15 +1086,22 @@ static hipError_t prefix_down(const clada_layer *layer, const char *h, int T, ch
         hipLaunchKernelGGL(kern, dim3(padded < units ? padded : units), dim3(512), 0, stream, q);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || S < 2) return e;
-        const int blocks = (T + 7) / 8 * (d / 128);
-        ReduceParams r = {};
-        if (red) r = *red;
-        hipLaunchKernelGGL(k_prefix_down_combine, dim3(blocks + (red ? (F + 3) / 4 : 0)), dim3(256), 0, stream, blocks, r, splitk_ws, S, T, d,
-                           y, q.bias, rowsq, y32, skip, y32_alt, alt);
-        if (red) *red_done = true;
+        return combine(S);
     }
-    else if (es == 4) hipLaunchKernelGGL((probe ? k_prefix_down<4, true> : k_prefix_down<4, false>), dim3(grid), dim3(256), 0, stream, q);
-    else         hipLaunchKernelGGL((probe ? k_prefix_down_bf16<true> : k_prefix_down_bf16<false>), dim3(grid), dim3(256), 0, stream, q);
+    // fp32: 128 x 128 tiles, d_ff split where they leave units idle (us: 4096 x 11008 at 512 tokens 1037 / 500, 4096 x 9000 at 32 869 / 116,
+    // 2048 x 6000 at 200 585 / 81)
+    if (es == 4) {
+        const size_t one = sizeof(float) * (size_t)T * d;
+        int S = 256 / tot < 12 ? 256 / tot : 12;
+        if (S > F / 256) S = F / 256;
+        if (!splitk_ws) S = 1;
+        else if (S * one > splitk_bytes) S = (int)(splitk_bytes / one);
+        if (S > 1) { q.part_out = splitk_ws; q.S = S; }
+        hipLaunchKernelGGL((probe ? k_prefix_down<4, true> : k_prefix_down<4, false>), dim3((tot * q.S + 7) / 8 * 8), dim3(256), 0, stream, q);
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess || S < 2 ? e : combine(S);
+    }
+    hipLaunchKernelGGL((probe ? k_prefix_down_bf16<true> : k_prefix_down_bf16<false>), dim3(grid), dim3(256), 0, stream, q);
     return hipGetLastError();
 }
 

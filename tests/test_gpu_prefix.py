@@ -262,3 +262,43 @@ def test_rows_past_d_ff_do_not_reach_the_output(clada):
     g64, u64 = x.double() @ w[0].double().t(), x.double() @ w[1].double().t()
     h = (torch.nn.functional.silu(g64) * u64)[:, -1:]
     assert torch.equal(y.double(), h.sign().expand(T, d) * float("inf"))
+
+
+@pytest.mark.parametrize("d,F,T,dtype,kind", [
+    (512, 700, 33, "f32", "swiglu"), (260, 513, 64, "f32", "geglu"), (1024, 3001, 65, "f32", "relu"),      # 64- and 128-token tiles
+    (132, 4099, 20, "f32", "swiglu"),   # 16 parts asked for, 12 taken; columns past d in the last tile
+    (2048, 1111, 300, "f32", "relu"),   # four parts, output biases
+    (72, 129, 60, "bf16", "swiglu"), (200, 65, 130, "bf16", "relu"),       # bf16 rows off the pipelined tiles
+])
+def test_plain_prefill_tiles_and_the_fp32_split(clada, d, F, T, dtype, kind):
+    """Against a float64 reference, the same bits from a second call, and the same to rounding in a workspace without room for a split."""
+    from paper_2502_19078_amd import binding
+    g = torch.Generator(device=DEV).manual_seed(d + F + T)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    n = lambda *s, k: (torch.randn(s, generator=g, device=DEV) * k)
+    relu = kind == "relu"
+    w = [n(F, d, k=d ** -0.5).to(dt) for _ in range(2 if relu else 3)]
+    x = n(T, d, k=1.0).to(dt)
+    b_in, b_out = n(F, k=0.1), n(d, k=0.1)
+    layer = (clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=b_in, b_out=b_out) if relu
+             else clada.Layer(*w, kind=binding.GEGLU if kind == "geglu" else binding.SWIGLU))
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    got, again = clada.prefix_stats(ctx, layer, x), clada.prefix_stats(ctx, layer, x)
+    xd, wd = x.double(), [a.double() for a in w]
+    pre = xd @ wd[0].t()
+    if relu:
+        h = a = torch.relu(pre + b_in.double())
+    else:
+        a = torch.nn.functional.gelu(pre, approximate="tanh") if kind == "geglu" else torch.nn.functional.silu(pre)
+        h = a * (xd @ wd[1].t())
+    sq = (h * h).sum(0)
+    want = {"sum_abs_act": a.abs().sum(0), "sum_sq_act": (a * a).sum(0), "max_abs_act": a.abs().amax(0), "sum_sq_h": sq,
+            "A": sq.sqrt() * wd[-1].norm(dim=1), "abs_act_pool": a.abs()}
+    for k, v in want.items():                                # fp32 accumulation over d and T terms, a hardware exp2 of a few ulp
+        assert _rel(to_np(getattr(got, k)), v.cpu().numpy()) < 2e-5, k
+        assert torch.equal(getattr(got, k), getattr(again, k)), k
+    y = (h @ wd[-1] + (b_out.double() if relu else 0.0)).cpu().numpy()
+    tol = 1e-5 if dtype == "f32" else 5e-3                   # bf16: h and y each rounded once, 2^-9 of a value
+    assert _rel(to_np(got.y), y) < tol and torch.equal(got.y, again.y)
+    tight = -(-T // 128) * 16 * F + T * (-(-F // 64) * 64) * 4 + 1024      # partial aggregates and h alone
+    assert _rel(to_np(clada.prefix_stats(clada.Context(0, tight), layer, x).y), y) < tol
