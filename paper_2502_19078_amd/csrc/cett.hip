@@ -179,7 +179,7 @@ __global__ void k_cett_finish(const CettState *st, float *tau_out, float *mean_o
 //   (3) the plain bisection then runs; a probe outside the bracket is answered by it, one inside adds the rows of
 //       the neurons between the sums' threshold and the probe to the sums, token by token, for the next few probes
 //       at a time.
-// 512 tokens of 4096 x 11008: 2370 us with 31 dense probes, 580 - 640 us so.  The bracket answers for thresholds outside it as a
+// 512 tokens of 4096 x 11008: 2370 us with 31 dense probes, 510 - 640 us so.  The bracket answers for thresholds outside it as a
 // monotone mean would; inside, every probe is measured.
 constexpr int SAMPLES = 4096;      // sorted sample of the pool; neighbours are 2.7 magnitudes per token apart at 11008 neurons
 constexpr int CLOSE = 16;          // sample places left between the bracket's ends when the dense probes end

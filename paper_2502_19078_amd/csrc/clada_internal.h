@@ -111,7 +111,7 @@ size_t clada_ws_calibrate(void);
 size_t clada_ws_cett(int32_t d, int32_t d_ff, int32_t T);
 size_t clada_ws_cett_room(int32_t d, int32_t d_ff, int32_t T);
 
-// Prefill GEMMs shared by the prefix statistics and the CETT search (128 x 128 output tiles).
+// Prefill GEMMs shared by the prefix statistics and the CETT search (partial aggregates and row norms are laid out by 128).
 int clada_prefix_token_tiles(int T);
 int clada_prefix_col_tiles(int d);
 hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, float *part, float *pool,
