@@ -361,6 +361,19 @@ __device__ __forceinline__ void gateup_tile_epilogue(const f32x4 (&acc)[4][2 * S
         const float v = q == 0 ? s_abs : q == 1 ? s_sq : q == 2 ? mx : s_h2;     // lane group q keeps sum q
         scratch_put(at + (unsigned int)(q * S::WM * NEUR) * 4u, v);
     }
+    // The down projection reads h in whole k-tiles, up to column Fp, and counts on zeros there.  Tiles of a multiple of 64 neurons reach
+    // that far; others may end up to 32 columns short of it (d_ff mod 192 from 65 to 96 with 96 neurons).
+    if constexpr (NEUR % 64 != 0) {
+        static_assert(NEUR % 8 == 0, "whole 16-byte chunks behind the tile");
+        const int c0 = (tn + 1) * NEUR;
+        if (p.hbuf && c0 >= p.F && c0 < p.Fp) {
+            const int chunks = (p.Fp - c0) / 8, rows = min(p.T - tm * S::TM, S::TM);
+            for (int v = threadIdx.x; v < rows * chunks; v += 512) {
+                const int r = v / chunks, c = v - r * chunks;
+                *reinterpret_cast<u32x4 *>(p.hbuf + ((size_t)(tm * S::TM + r) * Fp1 + c0 + 8 * c) * 2) = u32x4{0u, 0u, 0u, 0u};
+            }
+        }
+    }
     lds_barrier();
     for (int v = threadIdx.x; v < 4 * NEUR; v += 512) {
         const int s = v / NEUR, jl = v % NEUR, j = tn * NEUR + jl;

@@ -93,3 +93,19 @@ def check_mask_band(mask_gpu, act_ref, tau, what=""):
         print(f"[band] {what}: {int(floor_only.sum())} of {int(diff.sum())} flips lie in the absolute floor "
               f"(tau < {TAU_SMALL}: {np.unique(tau[floor_only.any(1)])[:4]})")
     return int(diff.sum())
+
+
+def nan_workspace(clada, d, F, T, dtype=torch.bfloat16):
+    """A context big enough for a prefix of T tokens of a d x F layer whose scratch holds NaNs: a longer and wider one over NaN
+    inputs came before."""
+    F2, T2 = -(-F // 64) * 64 + 64, 2 * T + 256
+    ctx = clada.Context(0, clada.workspace_bytes(d, F2, 0, T2, 0))
+    w = torch.ones(F2, d, dtype=dtype, device=DEV)
+    x = torch.full((T2, d), float("nan"), dtype=dtype, device=DEV)
+    layer = clada.Layer(w, w, w)
+    for tile in (1, 2):
+        ctx.set_option("prefix.tile", tile)
+        clada.cett_eval(ctx, layer, x, 1.0)
+        clada.prefix_stats(ctx, layer, x)
+    ctx.set_option("prefix.tile", 0)
+    return ctx

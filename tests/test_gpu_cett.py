@@ -5,7 +5,7 @@ import torch
 
 import oracle
 import synth
-from gpu_util import BAND, DEV, band_width, to_dev, to_np
+from gpu_util import BAND, DEV, band_width, nan_workspace, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -305,3 +305,31 @@ def test_search_thresholds_per_launch(clada, d, F, T, dtype):
         assert float(t31) == pytest.approx(float(t30), rel=1e-5 + 20.0 / (T * F)), bound
         assert float(m31) <= bound and float(m31) == pytest.approx(float(m30), rel=1e-5 + 20.0 / (T * F))
         assert float(clada.cett_eval(ctx, layer, x, float(t31))[1]) == pytest.approx(float(m31), rel=2e-6)
+
+
+@pytest.mark.parametrize("d,F,T,dtype,tile", [(768, 96, 257, "bf16", 2), (576, 288, 300, "bf16", 2), (1024, 2960, 1300, "bf16", 0), (576, 4128, 64, "bf16", 2),
+                                              (768, 2015, 300, "bf16", 2), (512, 129, 200, "bf16", 1), (72, 97, 130, "bf16", 0), (256, 96, 70, "f32", 0)])
+def test_what_the_workspace_held_does_not_reach_the_search(clada, d, F, T, dtype, tile):
+    """The projections read h in columns of 64; a NaN behind d_ff would pass as a token that loses nothing.  Plain and bracketed searches."""
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(d + F + T)
+    w = [(torch.randn(F, d, generator=g, device=DEV) * d ** -0.5).to(dt) for _ in range(3)]
+    x = torch.randn(T, d, generator=g, device=DEV).to(dt)
+    layer = clada.Layer(*w)
+    ctx = nan_workspace(clada, d, F, T, dt)
+    ctx.set_option("prefix.tile", tile)
+    pool = clada.prefix_stats(ctx, layer, x, want_y=False).abs_act_pool.double()
+    h = torch.nn.functional.silu(x.double() @ w[0].double().t()) * (x.double() @ w[1].double().t())
+    dense = (h @ w[2].double()).norm(dim=1)
+    exact = lambda eps: ((torch.where(pool < eps, h, 0.0) @ w[2].double()).norm(dim=1) / dense).cpu().numpy()      # (the device's own cut set)
+    ctx = nan_workspace(clada, d, F, T, dt)
+    ctx.set_option("prefix.tile", tile)
+    eps = float(pool.flatten()[: 1 << 20].median())
+    got, mean = clada.cett_eval(ctx, layer, x, eps)
+    np.testing.assert_allclose(to_np(got), exact(eps), rtol=TOL_CETT[dtype], atol=1e-6)
+    for bound in (0.05, 0.25):
+        ctx = nan_workspace(clada, d, F, T, dt)
+        ctx.set_option("prefix.tile", tile)
+        tau, mean = clada.threshold_search_cett(ctx, layer, x, bound)
+        assert float(mean) <= bound
+        assert float(mean) == pytest.approx(exact(float(tau)).mean(), rel=TOL_CETT[dtype], abs=1e-6)

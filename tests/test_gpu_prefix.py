@@ -5,7 +5,7 @@ import torch
 
 import oracle
 import synth
-from gpu_util import DEV, TOL_Y, assert_close_y, to_dev, to_np
+from gpu_util import DEV, TOL_Y, assert_close_y, nan_workspace, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -302,3 +302,36 @@ def test_plain_prefill_tiles_and_the_fp32_split(clada, d, F, T, dtype, kind):
     assert _rel(to_np(got.y), y) < tol and torch.equal(got.y, again.y)
     tight = -(-T // 128) * 16 * F + T * (-(-F // 64) * 64) * 4 + 1024      # partial aggregates and h alone
     assert _rel(to_np(clada.prefix_stats(clada.Context(0, tight), layer, x).y), y) < tol
+
+
+@pytest.mark.parametrize("d,F,T,kind,tile", [
+    # tiles of 96 neurons that end at, before and behind d_ff rounded up to 64 (d_ff mod 192 = 64, 65, 80, 95, 96, 97), d a multiple of 256 or not
+    (768, 64, 257, "swiglu", 2), (768, 257, 512, "geglu", 2), (1024, 272, 700, "swiglu", 2), (576, 95, 333, "swiglu", 2),
+    (768, 287, 300, "geglu", 2), (768, 96, 257, "swiglu", 2), (576, 288, 512, "geglu", 2), (832, 289, 333, "swiglu", 2),
+    (1024, 2976, 1300, "swiglu", 0), (1024, 2960, 1300, "geglu", 0),
+    # 64, 128 and 256 neurons
+    (256, 65, 100, "swiglu", 1), (256, 96, 60, "relu", 1), (512, 129, 200, "geglu", 1), (512, 97, 300, "relu", 1), (256, 300, 257, "relu", 2),
+    (512, 65, 257, "swiglu", 2),
+    # the plain tiles, bf16 and fp32
+    (72, 97, 130, "swiglu", 0), (256, 96, 70, "f32", 0), (260, 65, 40, "f32", 0),
+])
+def test_h_is_zero_past_d_ff(clada, d, F, T, kind, tile):
+    """h is read in columns of 64, against rows of W_down that count as zero: what the workspace held there must not matter, and NaNs do."""
+    from paper_2502_19078_amd import binding
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(d + F + T)
+    w = [(torch.randn(F, d, generator=g, device=DEV) * d ** -0.5).to(dt) for _ in range(3)]
+    x = torch.randn(T, d, generator=g, device=DEV).to(dt)
+    layer = (clada.Layer(w[0], None, w[2], kind=binding.RELU) if kind == "relu"
+             else clada.Layer(*w, kind=binding.GEGLU if kind == "geglu" else binding.SWIGLU))
+    ctx = nan_workspace(clada, d, F, T, dt)
+    ctx.set_option("prefix.tile", tile)
+    y = clada.prefix_stats(ctx, layer, x).y
+    pre = x.double() @ w[0].double().t()
+    if kind == "relu":
+        h = torch.relu(pre)
+    else:
+        a = torch.nn.functional.gelu(pre, approximate="tanh") if kind == "geglu" else torch.nn.functional.silu(pre)
+        h = a * (x.double() @ w[1].double().t())
+    want = (h @ w[2].double()).cpu().numpy()
+    assert _rel(to_np(y), want) < (1e-5 if kind == "f32" else 5e-3)      # bf16: h and y each rounded once, 2^-9 of a value
