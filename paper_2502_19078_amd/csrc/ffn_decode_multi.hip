@@ -11,7 +11,8 @@
 // One partial output [tokens][d] per workgroup; k_ffn_finalize adds them in fixed order.
 //
 // What bounds it: HBM, and the 256 partial outputs (17 MB written and read at four tokens of 4096).  A 4096 x 11008 fp32
-// layer at sparsity 0.45, union of independent tokens: 98.6 us at four tokens (526 MB: 5.3 TB/s; 107 with 92 MB of rows requested twice); the generic
+// layer at sparsity 0.45, union of independent tokens: 97.4 us at four tokens (526 MB: 5.4 TB/s; 106 with 92 MB of rows requested
+// twice), 135 at eight (136); the generic
 // kernel, one token per grid row, reads the weights once per token and takes 394 us.
 //
 // Arithmetic.  fp32: one chain of fmaf per lane and a fixed tree over the wave for the dots; the kept neurons of a workgroup are
@@ -83,15 +84,24 @@ k_ffn_multi(const MultiParams p)
 #pragma unroll
             for (int k = 0; k < VEC; ++k) acc[t][s][k] = 0.0f;
 
-    // UQ chunks of a row; a lane beyond the row reads its start instead, and its value counts as zero.  Without a row (real: uniform) the
-    // request goes to the start of x, which the caches hold: no branch around the loads, and no row of weights twice (a wave's
-    // last request of a phase used to: 618 MB for 526 of the 4096 x 11008 layer at four tokens).
+    // UQ chunks of a row; a lane beyond the row reads the request's start instead, and its value counts as zero.  A wave's last request of
+    // a phase has no row (real: uniform): it goes to the start of x, which the caches hold, so that there is no branch around the loads
+    // and no row of weights is read twice (618 MB for 526 at 4096 x 11008 fp32, four tokens).  How the address is formed decides over
+    // registers and the schedule; us with the row read again / offsets from the part / offsets from the row's start:
+    //   offsets from the part: fp32 4096 x 11008 at 1, 2, 4 tokens 75.0 / 67.6 / 68.3, 92.7 / 82.1 / 82.8, 106 / 97.4 / 98.3; 2048 x
+    //     5504 at 8 tokens 48.9 / 47.1 / 48.8; bf16 3080 x 8192 at 4 46.6 / 45.0 / 46.6
+    //   from the row's start (ROW0), 64 accumulators, which leave no registers, and few of them with short fp32 rows: bf16 4104 x 9000 at
+    //     4 tokens 73.1 / 76.3 / 71.0, 6152 x 13000 113 / 115 / 108, fp32 3072 x 8192 at 8 97.0 / 97.1 / 95.9, 1536 x 4099 at 4 27.3 /
+    //     28.7 / 27.1, 1024 x 2752 16.8 / 17.6 / 16.7
+    //   the row again (AGAIN): bf16 2056 x 5504 at 8 tokens 49.2 / 49.8 / 49.5, bounded by the products
+    constexpr bool ROW0 = TB * SL * VEC == 64 || (ES == 4 && SL == 1 && TB <= 4), AGAIN = ES == 2 && SL == 1 && TB == 8;
     auto request = [&](u32x4 (&b)[UQ], const char *w, int j, int part, bool real) {
-        const char *row = real ? w + (size_t)j * rowb + part * UQ * 1024 : p.x;
-        const int end = real ? (int)rowb - part * UQ * 1024 : 0;
+        const int from = ROW0 ? 0 : part * UQ * 1024;
+        const char *row = real || AGAIN ? w + (size_t)j * rowb + from : p.x;
+        const int end = real || ROW0 ? (int)rowb - from : 0;
 #pragma unroll
         for (int c = 0; c < UQ; ++c) {
-            const int o = c * 1024 + lane * 16;
+            const int o = ((ROW0 ? part * UQ : 0) + c) * 1024 + lane * 16;
             b[c] = ld_stream16(row + (o < end ? o : 0));
         }
     };

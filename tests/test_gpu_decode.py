@@ -519,3 +519,41 @@ def test_bf16_dots_of_the_vector_kernel_keep_subnormals_and_full_precision(clada
     assert want.abs().min() > 0 and torch.isfinite(y.float()).all()
     err = (y.double() - want).norm(dim=1) / want.norm(dim=1)
     assert float(err.max()) < 4e-3, err
+
+
+@pytest.mark.parametrize("dtype,d,F", [("f32", 1028, 257), ("f32", 2048, 300), ("f32", 2052, 259), ("f32", 4096, 513),
+                                       ("bf16", 1032, 300), ("bf16", 4088, 259), ("bf16", 4104, 300), ("bf16", 6152, 513)])
+@pytest.mark.parametrize("kind", ["swiglu", "relu"])
+def test_vector_kernel_row_requests(clada, dtype, d, F, kind):
+    """Rows a little longer and shorter than whole requests, one to three rows per workgroup, through every number of tokens that has an
+    instance: dense, sparse and by lists of no, one and all neurons, against float64."""
+    from paper_2502_19078_amd import binding
+    dt, tol = (torch.float32, TOL_Y["f32"]) if dtype == "f32" else (torch.bfloat16, 5e-3)      # bf16: y rounded once, 2^-9 of a value
+    g = torch.Generator(device=DEV).manual_seed(d + F)
+    w = [(torch.randn(F, d, generator=g, device=DEV) * d ** -0.5).to(dt) for _ in range(3)]
+    layer = clada.Layer(w[0], None, w[2], kind=binding.RELU) if kind == "relu" else clada.Layer(*w)
+    for B in (1, 2, 3, 4, 5, 8):
+        x = torch.randn(B, d, generator=g, device=DEV).to(dt)
+        ctx = clada.Context(0, clada.workspace_bytes(d, F, B, 0, 0))
+        ctx.set_option("decode.batched", 0)
+        pre = x.double() @ w[0].double().t()
+        a = torch.relu(pre) if kind == "relu" else torch.nn.functional.silu(pre)
+        up = x.double() @ w[1].double().t()
+        h = a if kind == "relu" else a * up
+        # one neuron alone: its dots' cancellation goes straight through, eps32 sum|x_i w_i| / |dot| each (sigma passes on at most 1 + |g| of it)
+        kappa = lambda m, dot: (x.abs().double() @ m[0].abs().double()) / dot[:, 0].abs()
+        one = EPS32 * (kappa(w[0], pre) * (1 + pre[:, 0].abs()) + (0 if kind == "relu" else kappa(w[1], up)))
+        ref = lambda keep: (torch.where(keep, h, 0.0) @ w[2].double()).cpu().numpy()
+        every = torch.ones_like(a, dtype=torch.bool)
+        assert_close_y(to_np(clada.dense_ffn_decode(ctx, layer, x)), ref(every), tol, f"dense B={B}")
+        s = a.abs().flatten().sort().values
+        k = int(0.7 * len(s))
+        k += int((s[k + 1:k + 33] - s[k:k + 32]).argmax())   # a gap, so that rounding decides nothing
+        tau = ((s[k] + s[k + 1]) / 2).float().expand(B).contiguous()
+        y = clada.sparse_ffn_decode(ctx, layer, x, tau)
+        assert_close_y(to_np(y), ref(a.abs() >= tau.double()[:, None]), tol, f"sparse B={B}")
+        for n in (0, 1, F):
+            idx = torch.arange(F, dtype=torch.int32, device=DEV)
+            y = clada.static_ffn_decode(ctx, layer, x, idx, torch.tensor([n], dtype=torch.int32, device=DEV))
+            assert_close_y(to_np(y), ref(every & (torch.arange(F, device=DEV) < n)), tol, f"list of {n} B={B}",
+                           one if n == 1 else None)
