@@ -101,9 +101,11 @@ clada_status clada_set_option(clada_ctx *ctx, const char *name, int32_t value);
  * faulted must be destroyed. */
 clada_status clada_device_fault(clada_ctx *ctx, int32_t *fault_out);
 
-/* Upper bound of the workspace any call needs for these sizes.  Pass 0 for a
+/* Upper bound of the workspace any call makes use of for these sizes.  Pass 0 for a
  * size whose call will not be used (T for prefix_stats/calibrate/the CETT calls, V for
- * cognitive_signals, B for the decode calls). */
+ * cognitive_signals, B for the decode calls).  A call that needs less is accepted with
+ * less; its results are the same bits then, but the down projections of the prefill and
+ * CETT calls and the batched stacks may take more launches and more time. */
 size_t clada_workspace_bytes(int32_t d, int32_t d_ff, int32_t B, int32_t T, int32_t V);
 
 /* FFN family.  CLADA_FFN_SWIGLU (0, the default of a zeroed struct): the gated

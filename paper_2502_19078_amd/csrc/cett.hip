@@ -828,6 +828,8 @@ struct CettWs {
     size_t splitk_bytes;
     char *h, *hcut, *ytmp;
     CettState *state;
+    // room for the parts of a down projection; `one` ([T][d] fp32) is free while it runs, or receives its fp32 rows
+    DownRoom room(void *one) const { return {splitk, splitk_bytes, reinterpret_cast<float *>(one)}; }
 };
 
 CettWs carve(char *ws, size_t bytes, int d, int F, int T)
@@ -874,7 +876,9 @@ clada_status begin(clada_ctx *ctx, const clada_layer *layer, const void *x, int 
     const float *rowsq_den = w.rowsq_den;
     if (layer->kind == CLADA_FFN_RELU) {
         // || sum_j a_j W_out[j,:] + b_out ||: through the stored output, which carries the bias
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, w.ytmp, nullptr, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu));
+        // (the masked h is not there yet, and holds [T][d] where a bf16 layer is split without room for it: d_ff >= 2 d)
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, w.ytmp, nullptr, w.room(layer->dtype == CLADA_BF16 ? w.hcut : w.ytmp), ctx->opt_prefix_tile,
+                                               stream, ctx->num_cu));
         if (layer->dtype == CLADA_BF16)
             hipLaunchKernelGGL(k_cett_row_norm<2>, dim3((T + 3) / 4), dim3(256), 0, stream, w.ytmp, T, layer->d, w.den);
         else
@@ -882,7 +886,7 @@ clada_status begin(clada_ctx *ctx, const clada_layer *layer, const void *x, int 
         CLADA_CHECK_HIP(ctx, hipGetLastError());
         rowsq_den = nullptr;
     } else {
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, nullptr, w.rowsq_den, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu));
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, nullptr, w.rowsq_den, w.room(w.ytmp), ctx->opt_prefix_tile, stream, ctx->num_cu));
     }
     hipLaunchKernelGGL(k_cett_begin, dim3((T + 255) / 256), dim3(256), 0, stream, w.state, rowsq_den, n_tn, T,
                        w.den, search, eps);
@@ -903,7 +907,7 @@ clada_status probe(clada_ctx *ctx, const clada_layer *layer, int T, const CettWs
     else
         hipLaunchKernelGGL(k_cett_mask<4>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, 0);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
-    CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu));
+    CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.room(w.ytmp), ctx->opt_prefix_tile, stream, ctx->num_cu));
     hipLaunchKernelGGL(k_cett_update, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound,
                        search, cett_out, mean_out);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
@@ -975,9 +979,11 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
     // projection forms them (68 us for 512 tokens of 4096 x 11008, against 2 a probe).
     const bool two = layer->dtype == CLADA_BF16 && Fp >= 2 * d;
     float *sums[2] = {reinterpret_cast<float *>(w.ytmp), reinterpret_cast<float *>(two ? w.h + (size_t)T * Fp * 2 : w.hcut)};
+    // (with both buffers of sums taken, the half of the masked h's part that a bf16 one leaves is free)
+    const DownRoom room = w.room(two ? w.hcut + (size_t)T * Fp * 2 : w.ytmp);
     for (int it = 0; it < DENSE_PROBES; ++it) {
         CLADA_CHECK_HIP(ctx, mask(1));
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu,
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, room, ctx->opt_prefix_tile, stream, ctx->num_cu,
                                                two ? sums[0] : nullptr, &w.state->skip, two ? sums[1] : nullptr, two ? &w.state->sel : nullptr));
         hipLaunchKernelGGL(k_cett_next, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound, sample, curve);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
@@ -989,7 +995,7 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
         hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 0);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
         CLADA_CHECK_HIP(ctx, mask(0));
-        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, w.splitk, w.splitk_bytes, ctx->opt_prefix_tile, stream, ctx->num_cu, sums[0]));
+        CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, room, ctx->opt_prefix_tile, stream, ctx->num_cu, sums[0]));
         hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 1);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
     }

@@ -117,9 +117,12 @@ int clada_prefix_col_tiles(int d);
 hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, float *part, float *pool,
                                char *hbuf, int tile_mode, hipStream_t stream, int num_cu, int *n_part = nullptr, float *wnorm2 = nullptr,
                                int *norm_rows = nullptr);      // wnorm2: the first *norm_rows are filled where compute units are left over
-hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, float *splitk_ws, size_t splitk_bytes,
-                             int tile_mode, hipStream_t stream, int num_cu, float *y32 = nullptr, const int *skip = nullptr,
-                             float *y32_alt = nullptr, const int *alt = nullptr);
+// Where the partial outputs [T][d] of a split down projection go: as many as there are `bytes` for at `parts`; or, where not even
+// one fits there, one at `one`, which may be the fp32 y or y32 of the call itself.
+struct DownRoom { float *parts; size_t bytes; float *one; };
+hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, const DownRoom &room, int tile_mode,
+                             hipStream_t stream, int num_cu, float *y32 = nullptr, const int *skip = nullptr, float *y32_alt = nullptr,
+                             const int *alt = nullptr);
 size_t clada_ws_down_splitk(int d, int F, int T);
 size_t clada_ws_down_room(int d, int F, int T);
 

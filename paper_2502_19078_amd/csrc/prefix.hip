@@ -456,8 +456,11 @@ struct DownParams {
     const float *bias;             // output bias [d] of the non-gated family, or nullptr
     float *rowsq;                  // [n_tn][T] per column-tile sums of squares of the fp32 rows, or nullptr
     int T, d, F, Fp, n_tm, n_tn;   // Fp = F rounded up to a multiple of BK (row stride of h)
-    float *part_out;               // split-K (256 x 256 kernel): fp32 partial outputs [S][T][d] instead of y / rowsq
+    float *part_out;               // split: fp32 partial outputs [parts][T][d] instead of y / rowsq
     int S;                         // number of k ranges the neurons are split into (1 = no split)
+    // SOME kernels: ranges ks0 .. ks0 + parts of them, the first one added to what lies in part_out (add); or all of them one after the
+    // other by the same workgroups, added up in registers (chain = S, parts = 1; otherwise chain = 1)
+    int ks0, parts, add, chain;
     float *y32;                    // [T][d] the fp32 rows without a bias, or nullptr
     float *y32_alt;                // they go there instead when *alt is 0 (alt: device flag or nullptr)
     const int *alt;
@@ -491,8 +494,9 @@ __device__ __forceinline__ void down_rowsq(const f32x16 (&acc)[2][2], const Down
 // Where the fp32 rows go.
 __device__ __forceinline__ float *rows32_of(const DownParams &p) { return p.alt && *p.alt == 0 ? p.y32_alt : p.y32; }
 
-// The fp32 rows of a 128 x 128 tile, without a bias.
-__device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const DownParams &p, float *rows, int tm, int tn, int wm, int wn, int lane)
+// f(word, mb, nb, r) of the fp32 rows of a 128 x 128 tile.
+template <class Fn>
+__device__ __forceinline__ void down_rows32(const DownParams &p, float *rows, int tm, int tn, int wm, int wn, int lane, Fn f)
 {
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
@@ -502,14 +506,20 @@ __device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const Do
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int t = tm * BM + wm * 64 + mb * 32 + acc_row(r, lane);
-                if (t < p.T && col < p.d) rows[(size_t)t * p.d + col] = acc[mb][nb][r];
+                if (t < p.T && col < p.d) f(rows[(size_t)t * p.d + col], mb, nb, r);
             }
     }
+}
+// Those rows, without a bias.
+__device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const DownParams &p, float *rows, int tm, int tn, int wm, int wn, int lane)
+{
+    down_rows32(p, rows, tm, tn, wm, wn, lane, [&](float &at, int mb, int nb, int r) { at = acc[mb][nb][r]; });
 }
 
 // PROBE (the three down kernels): the error-bounded search's form, with y32 and skip.  The others are built without: the
 // extra store loop alone raised k_prefix_down_bf16's registers (330 -> 401 us at 2368 x 4096 x 9728).
-template <int ES, bool PROBE>
+// SOME: some parts of a split at a time, for a workspace that does not hold all of them; also with skip.
+template <int ES, bool PROBE, bool SOME = false>
 __global__ void __launch_bounds__(256)
 k_prefix_down(const DownParams p)
 {
@@ -520,22 +530,24 @@ k_prefix_down(const DownParams p)
     __shared__ __align__(16) char s_b[BN * ROW];      // [n][k]: W_down tile transposed
     __shared__ float s_rs[2][BM];
 
-    const int total = p.n_tm * p.n_tn * p.S;
+    const int total = p.n_tm * p.n_tn * (SOME ? p.parts : p.S);
     const int o = remap_block(blockIdx.x, total);
     if (o >= total) return;
-    const int ks = o / (p.n_tm * p.n_tn), tile = o - ks * p.n_tm * p.n_tn;
+    const int slot = o / (p.n_tm * p.n_tn), tile = o - slot * p.n_tm * p.n_tn;
     const int tm = tile % p.n_tm, tn = tile / p.n_tm;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 1, wn = wave >> 1;
     const size_t hrow = (size_t)p.Fp * ES, wrow = (size_t)p.d * ES;
 
     f32x16 acc[1][2][2];
+    auto clear = [](f32x16 (&a)[2][2]) {
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
+            for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[0][mb][nb][r] = 0.0f;
+                for (int r = 0; r < 16; ++r) a[mb][nb][r] = 0.0f;
+    };
 
     // B tile in global memory: BK rows (neurons) x BN columns -> BK * BN*ES/16 chunks
     constexpr int BCH = BN * ES / 16;                  // chunks per neuron row of the tile
@@ -560,35 +572,56 @@ k_prefix_down(const DownParams p)
             rb[i] = (j < p.F && nbyte < wrow) ? *reinterpret_cast<const u32x4 *>(p.wd + (size_t)j * wrow + nbyte) : z;
         }
     };
-    // this part's k-tiles (parts of a split hold at least 256 neurons each)
+    // a part's k-tiles (parts of a split hold at least 256 neurons each)
     const int nk_all = (p.F + BKV<ES> - 1) / BKV<ES>;
-    const int kt0 = (int)((long long)ks * nk_all / p.S), nk = (int)((long long)(ks + 1) * nk_all / p.S);
-    load_tile(kt0);
-    for (int kt = kt0; kt < nk; ++kt) {
-        __syncthreads();
+    auto product = [&](int ks) {
+        const int kt0 = (int)((long long)ks * nk_all / p.S), nk = (int)((long long)(ks + 1) * nk_all / p.S);
+        clear(acc[0]);
+        load_tile(kt0);
+        for (int kt = kt0; kt < nk; ++kt) {
+            __syncthreads();
 #pragma unroll
-        for (int i = 0; i < PT; ++i) {
-            const int c = tid + i * 256, row = c / CH, ch = c % CH;
-            *reinterpret_cast<u32x4 *>(s_a + row * ROW + ch * 16) = ra[i];
-        }
-#pragma unroll
-        for (int i = 0; i < BPT; ++i) {
-            const int c = tid + i * 256, k = c / BCH, ch = c % BCH;
-            const unsigned int w[4] = {rb[i].x, rb[i].y, rb[i].z, rb[i].w};
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const int nloc = ch * VEC + e;
-                if (ES == 4) *reinterpret_cast<unsigned int *>(s_b + nloc * ROW + k * 4) = w[e];
-                else *reinterpret_cast<unsigned short *>(s_b + nloc * ROW + k * 2) = (unsigned short)(w[e >> 1] >> (16 * (e & 1)));
+            for (int i = 0; i < PT; ++i) {
+                const int c = tid + i * 256, row = c / CH, ch = c % CH;
+                *reinterpret_cast<u32x4 *>(s_a + row * ROW + ch * 16) = ra[i];
             }
+#pragma unroll
+            for (int i = 0; i < BPT; ++i) {
+                const int c = tid + i * 256, k = c / BCH, ch = c % BCH;
+                const unsigned int w[4] = {rb[i].x, rb[i].y, rb[i].z, rb[i].w};
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const int nloc = ch * VEC + e;
+                    if (ES == 4) *reinterpret_cast<unsigned int *>(s_b + nloc * ROW + k * 4) = w[e];
+                    else *reinterpret_cast<unsigned short *>(s_b + nloc * ROW + k * 2) = (unsigned short)(w[e >> 1] >> (16 * (e & 1)));
+                }
+            }
+            __syncthreads();
+            if (kt + 1 < nk) load_tile(kt + 1);
+            const char *const sb[1] = {s_b + wn * 64 * ROW};
+            mma_tile<ES, 1, 2, 2>(s_a + wm * 64 * ROW, sb, acc, lane);
         }
-        __syncthreads();
-        if (kt + 1 < nk) load_tile(kt + 1);
-        const char *const sb[1] = {s_b + wn * 64 * ROW};
-        mma_tile<ES, 1, 2, 2>(s_a + wm * 64 * ROW, sb, acc, lane);
+    };
+    product(slot + (SOME ? p.ks0 : 0));
+    if constexpr (SOME) {
+        f32x16 sum[2][2];
+        clear(sum);
+        for (int c = 1;; ++c) {
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) sum[mb][nb] += acc[0][mb][nb];
+            if (c >= p.chain) break;
+            product(c);
+        }
+        float *rows = p.part_out + (size_t)slot * p.T * p.d;
+        if (p.add && slot == 0)                             // (all loads before the first store)
+            down_rows32(p, rows, tm, tn, wm, wn, lane, [&](float &at, int mb, int nb, int r) { sum[mb][nb][r] += at; });
+        down_store32(sum, p, rows, tm, tn, wm, wn, lane);
+        return;
     }
     if (p.part_out) {                                       // split: fp32 partial sums, added up by k_prefix_down_combine
-        down_store32(acc[0], p, p.part_out + (size_t)ks * p.T * p.d, tm, tn, wm, wn, lane);
+        down_store32(acc[0], p, p.part_out + (size_t)slot * p.T * p.d, tm, tn, wm, wn, lane);
         return;
     }
     if (p.rowsq) down_rowsq(acc[0], p, tm, tn, wm, wn, lane, tid, s_rs);
@@ -724,7 +757,7 @@ k_prefix_down_bf16(const DownParams p)
 
 // bf16 down projection on the pipelined tiles (d % 256 == 0), 256 columns of W_down a tile as they lie in memory: S::TM tokens x 256
 // columns x one of the S ranges the neurons are split into.  (128 tokens: split only, for a wave then holds half a tile of the row norms.)
-template <class S, bool PROBE>
+template <class S, bool PROBE, bool SOME = false>
 __global__ void __launch_bounds__(512, 2)
 k_prefix_down_tiles(const DownParams p)
 {
@@ -732,18 +765,20 @@ k_prefix_down_tiles(const DownParams p)
     if (PROBE && p.skip && *p.skip) return;
     __shared__ __align__(16) char s_w[S::LDS];
     struct Tile {
-        struct Id { int tm, tn, ks; };
-        int blocks, n_tm, n_tn, parts;
+        struct Id { int tm, tn, ks, pos; };                 // pos: place in a chain
+        int blocks, n_tm, n_tn, parts, chain;
         __device__ __forceinline__ bool operator()(int it, Id &id) const
         {
-            const int o = tile_order(it, blocks, n_tm * n_tn * parts);
+            const int tile = SOME ? it / chain : it;
+            const int o = tile_order(tile, blocks, n_tm * n_tn * parts);
             if (o < 0) return false;
+            id.pos = it - tile * (SOME ? chain : 1);
             id.ks = o / (n_tm * n_tn);                      // the tiles of one range side by side: they share rows of W_down and columns of h
             tile_coords(o - id.ks * n_tm * n_tn, n_tm, n_tn, id.tm, id.tn);
             return true;
         }
     };
-    const Tile tile{(int)gridDim.x, (p.T + S::TM - 1) / S::TM, p.d / 256, p.S};
+    const Tile tile{(int)gridDim.x, (p.T + S::TM - 1) / S::TM, p.d / 256, SOME ? p.parts : p.S, SOME ? p.chain : 1};
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t hrow = (size_t)p.Fp * 2, wrow = (size_t)p.d * 2;
     int vw[S::PW];
@@ -754,9 +789,9 @@ k_prefix_down_tiles(const DownParams p)
     }
     const int nk_all = p.Fp / 64;                           // h is zero past d_ff, W_down is taken as zero there
     auto src = [&](const typename Tile::Id &id) {
-        const int kt0 = (int)((long long)id.ks * nk_all / p.S);
+        const int ks = id.ks + (SOME ? p.ks0 + id.pos : 0), kt0 = (int)((long long)ks * nk_all / p.S);
         TileSrc s;
-        s.nk = (int)((long long)(id.ks + 1) * nk_all / p.S) - kt0;
+        s.nk = (int)((long long)(ks + 1) * nk_all / p.S) - kt0;
         s.x = p.h + (size_t)id.tm * S::TM * hrow + (size_t)kt0 * 128;
         s.x_bytes = (unsigned int)(min(p.T - id.tm * S::TM, S::TM) * (int)hrow - kt0 * 128);
         s.w = p.wd + (size_t)kt0 * 64 * wrow + (size_t)id.tn * 512;
@@ -766,23 +801,37 @@ k_prefix_down_tiles(const DownParams p)
         s.w_col = id.tn * 512;
         return s;
     };
+    f32x4 sum[SOME ? 4 : 1][SOME ? 2 * S::NB : 1];
     auto epi = [&](const f32x4 (&acc)[4][2 * S::NB], const typename Tile::Id &id, unsigned int, int wm, int wn) {
         const int n = lane & 15, q = lane >> 4;
         const int t0 = id.tm * S::TM + wm * 64, c0 = id.tn * 256 + wn * 32 * S::NB;
         const bool full = t0 + 64 <= p.T;
-        if (p.part_out || (PROBE && p.y32)) {               // split: fp32 partial sums, added up by k_prefix_down_combine
-            float *rows32 = !PROBE || p.part_out ? p.part_out + (size_t)id.ks * p.T * p.d : rows32_of(p);
+        if (SOME || p.part_out || (PROBE && p.y32)) {       // split: fp32 partial sums, added up by k_prefix_down_combine
+            float *rows32 = !PROBE || SOME || p.part_out ? p.part_out + (size_t)id.ks * p.T * p.d : rows32_of(p);
             const unsigned int v = (unsigned int)(4 * q * p.d + n) * 4u;
+            auto each = [&](auto f) {                       // the fp32 words of this lane
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    char *dst = reinterpret_cast<char *>(rows32 + (size_t)(t0 + 16 * i + r) * p.d + c0);
-                    if (full || t0 + 16 * i + 4 * q + r < p.T)
+                    for (int r = 0; r < 4; ++r) {
+                        char *dst = reinterpret_cast<char *>(rows32 + (size_t)(t0 + 16 * i + r) * p.d + c0);
+                        if (full || t0 + 16 * i + 4 * q + r < p.T)
 #pragma unroll
-                        for (int j = 0; j < 2 * S::NB; ++j) *reinterpret_cast<float *>(dst + v + 64 * j) = acc[i][j][r];
-                }
-            if (!PROBE || p.part_out) return;
+                            for (int j = 0; j < 2 * S::NB; ++j) f(i, j, r, *reinterpret_cast<float *>(dst + v + 64 * j));
+                    }
+            };
+            if constexpr (SOME) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2 * S::NB; ++j) sum[i][j] = id.pos == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
+                if (id.pos + 1 < p.chain) return;
+                if (p.add && id.ks == 0) each([&](int i, int j, int r, float &at) { sum[i][j][r] += at; });      // (all loads before the first store)
+                each([&](int i, int j, int r, float &at) { at = sum[i][j][r]; });
+            } else {
+                each([&](int i, int j, int r, float &at) { at = acc[i][j][r]; });
+            }
+            if (!PROBE || SOME || p.part_out) return;
         }
         if constexpr (S::NB == 4) {                         // a wave holds one 128-column tile of the row norms
             if (p.rowsq) {
@@ -877,12 +926,12 @@ __global__ void __launch_bounds__(256) k_prefix_reduce(const ReduceParams p) { r
 // y in bf16 (+ bias) and / or the per-row sums of squares of every 128-column tile.  A workgroup takes
 // 8 rows x 128 columns: thread = (row tid >> 5, four columns 4 (tid & 31) ..).  The workgroups behind the first `blocks` do the
 // per-neuron reductions of the same call, which need nothing of this (bf16; 512 tokens of 4096 x 11008: 22.6 us in two launches and eight parts,
-// 16.8 so and with four).
+// 16.8 so and with four).  y (fp32) or y32 may be the first part itself: a thread writes what only it has read.
 template <int ES>
 __global__ void __launch_bounds__(256)
-k_prefix_down_combine(int blocks, const ReduceParams red, const float *__restrict__ part, int S, int T, int d, char *__restrict__ y,
-                      const float *__restrict__ bias, float *__restrict__ rowsq, float *__restrict__ y32, const int *__restrict__ skip,
-                      float *__restrict__ y32_alt, const int *__restrict__ alt)
+k_prefix_down_combine(int blocks, const ReduceParams red, const float *part, int S, int T, int d, char *y,
+                      const float *__restrict__ bias, float *__restrict__ rowsq, float *y32, const int *__restrict__ skip,
+                      float *y32_alt, const int *__restrict__ alt)
 {
     if ((int)blockIdx.x >= blocks) {
         reduce_neurons<ES>(red, blockIdx.x - blocks);
@@ -929,7 +978,7 @@ k_prefix_down_combine(int blocks, const ReduceParams red, const float *__restric
 
 }  // namespace
 
-// Bytes a call needs for certain.  With room for them behind, the down projection splits d_ff further (clada_ws_prefix_room).
+// Bytes a call needs for certain, and with room for all parts of the down projection's split.
 size_t clada_ws_prefix(int32_t d, int32_t d_ff, int32_t T, bool want_y)
 {
     if (T <= 0) return 0;
@@ -970,17 +1019,41 @@ static int down_splits_half(int d, int F, int T)
     if (S > F / 256) S = F / 256;
     return S < 2 || F / S > 4096 ? 0 : S;
 }
-// What is asked for at least (d_ff in multiples of 32 only), and what the split takes if it is there.
+// The split of a call, by its shape alone: the order of the additions, and with it the last bits of y, must not depend on how much
+// workspace there is.  Where not all parts fit, they are formed some at a time (prefix_down).
+struct DownSplit { int S; bool half; };                     // parts; bf16: tiles of 128 tokens
+// Room that a bf16 call asks for at least (an old rule: d_ff in multiples of 32 only).
 size_t clada_ws_down_splitk(int d, int F, int T)
 {
     const int S = F % 32 == 0 ? down_splits(d, F, T) : 1;
     return S > 1 ? align_up(sizeof(float) * (size_t)S * T * d, 256) : 0;
 }
+static DownSplit down_split(bool f32, int d, int F, int T, int tile_mode)
+{
+    if (f32) {
+        // 128 x 128 tiles, d_ff split where they leave units idle (us: 4096 x 11008 at 512 tokens 1037 / 500, 4096 x 9000 at 32 869 / 116,
+        // 2048 x 6000 at 200 585 / 81)
+        const int tiles = ((T + BM - 1) / BM) * ((d + BN - 1) / BN);
+        int S = 256 / tiles < 12 ? 256 / tiles : 12;
+        if (S > F / 256) S = F / 256;
+        return {S < 2 ? 1 : S, false};
+    }
+    // (tile_mode 1: the plain kernel.)  At least one [T][d] must be there in any workspace that the call accepts: what it asks for, or
+    // the half of h's part that a bf16 h leaves.
+    if (d % 256 != 0 || tile_mode == 1 || !(clada_ws_down_splitk(d, F, T) > 0 || align_up((size_t)F, 64) >= 2 * (size_t)d)) return {1, false};
+    const int S = down_splits_half(d, F, T);
+    if (tile_mode != 2 && S >= 2) return {S, true};
+    return {down_splits(d, F, T), false};
+}
 size_t clada_ws_down_room(int d, int F, int T)
 {
-    const int S = down_splits_half(d, F, T) ? down_splits_half(d, F, T) : down_splits(d, F, T);
-    const size_t need = clada_ws_down_splitk(d, F, T), room = S > 1 ? align_up(sizeof(float) * (size_t)S * T * d, 256) : 0;
-    return room > need ? room : need;
+    size_t room = clada_ws_down_splitk(d, F, T);
+    for (int k = 0; T > 0 && k < 4; ++k) {                  // either type; prefix.tile 0 and 2
+        const int S = down_split(k & 1, d, F, T, k & 2).S;
+        const size_t n = S > 1 ? align_up(sizeof(float) * (size_t)S * T * d, 256) : 0;
+        if (n > room) room = n;
+    }
+    return room;
 }
 int clada_prefix_col_tiles(int d) { return (d + BN - 1) / BN; }
 
@@ -1056,10 +1129,10 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
 
 // Down projection of h [T][Fp]: y [T][d] in the layer dtype and/or rowsq [col tiles][T], the
 // per-column-tile sums of squares of the fp32 output rows, and/or y32 [T][d], those rows without a bias (any may be
-// nullptr; with alt, a device flag, y32 is y32_alt when it is 0).  splitk_ws: room for the partial outputs of a split, splitk_bytes of it.  skip: device flag, nothing is computed when it
-// is set (nullptr: always computed).
+// nullptr; with alt, a device flag, y32 is y32_alt when it is 0).  room: where the partial outputs of a split go.  skip: device
+// flag, nothing is computed when it is set (nullptr: always computed).
 // red: the call's per-neuron reductions, done along where a pass combines the parts of a split (*red_done).
-static hipError_t prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, float *splitk_ws, size_t splitk_bytes,
+static hipError_t prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, const DownRoom &room,
                               int tile_mode, hipStream_t stream, int num_cu, float *y32, const int *skip, float *y32_alt, const int *alt,
                               const ReduceParams *red, bool *red_done)
 {
@@ -1070,58 +1143,67 @@ static hipError_t prefix_down(const clada_layer *layer, const char *h, int T, ch
     q.bias = (layer->kind == CLADA_FFN_RELU && y) ? layer->b_out : nullptr;
     q.T = T; q.d = d; q.F = F; q.Fp = (int)align_up((size_t)F, 64);
     q.n_tm = (T + BM - 1) / BM; q.n_tn = (d + BN - 1) / BN;
-    const int tot = q.n_tm * q.n_tn, grid = (tot + 7) / 8 * 8;
+    q.part_out = nullptr; q.ks0 = q.add = 0; q.chain = 1;
     const bool probe = y32 || skip;
-    q.part_out = nullptr; q.S = 1;
-    auto combine = [&](int S) {
-        const int blocks = (T + 7) / 8 * q.n_tn;
-        ReduceParams r = {};
-        if (red) r = *red;
-        hipLaunchKernelGGL((es == 4 ? k_prefix_down_combine<4> : k_prefix_down_combine<2>), dim3(blocks + (red ? (F + 3) / 4 : 0)), dim3(256), 0, stream,
-                           blocks, r, splitk_ws, S, T, d, y, q.bias, rowsq, y32, skip, y32_alt, alt);
-        if (red) *red_done = true;
+    const DownSplit split = down_split(es == 4, d, F, T, tile_mode);
+    q.S = split.S;
+    const size_t one = sizeof(float) * (size_t)T * d;
+    float *parts = room.bytes >= one ? room.parts : room.one;
+    const int fit = room.bytes >= one ? (room.bytes / one < (size_t)q.S ? (int)(room.bytes / one) : q.S) : 1;
+    if (q.S > 1 && !parts) return hipErrorInvalidValue;     // (every caller has room for one)
+    if (q.S > 1) q.part_out = parts;
+    auto product = [&](int n) {                             // n parts, from ks0 on
+        q.parts = n;
+        const bool some = n < q.S || q.chain > 1;
+        if (es == 4) {
+            const auto kern = some ? k_prefix_down<4, true, true> : probe ? k_prefix_down<4, true> : k_prefix_down<4, false>;
+            hipLaunchKernelGGL(kern, dim3((q.n_tm * q.n_tn * n + 7) / 8 * 8), dim3(256), 0, stream, q);
+        } else if (d % 256 != 0 || tile_mode == 1) {        // tile_mode 1 = 128 x 128 tiles of the plain kernel always
+            hipLaunchKernelGGL((probe ? k_prefix_down_bf16<true> : k_prefix_down_bf16<false>), dim3((q.n_tm * q.n_tn + 7) / 8 * 8), dim3(256), 0,
+                               stream, q);
+        } else {                                            // (some: 128-token tiles always, an element's sum is the same)
+            using Half = TileShape<2, 2, 2, true>;
+            using Whole = TileShape<4, 4, 2, true>;
+            const auto kern = some ? k_prefix_down_tiles<Half, true, true>
+                            : split.half ? (probe ? k_prefix_down_tiles<Half, true> : k_prefix_down_tiles<Half, false>)
+                                         : (probe ? k_prefix_down_tiles<Whole, true> : k_prefix_down_tiles<Whole, false>);
+            const int tiles = (some || split.half ? (T + 127) / 128 : (T + 255) / 256) * (d / 256);
+            const int units = num_cu / 8 * 8 > 8 ? num_cu / 8 * 8 : 256, padded = (tiles * n + 7) / 8 * 8;
+            hipLaunchKernelGGL(kern, dim3(padded < units ? padded : units), dim3(512), 0, stream, q);
+        }
         return hipGetLastError();
     };
-    // tile_mode 1 = 128 x 128 tiles of the plain kernel always
-    if (es == 2 && d % 256 == 0 && tile_mode != 1) {
-        const size_t one = sizeof(float) * (size_t)T * d;
-        const int fit = splitk_ws ? (int)(splitk_bytes / one < 16 ? splitk_bytes / one : 16) : 0;      // parts there is room for
-        int S = down_splits_half(d, F, T);
-        const bool half = tile_mode != 2 && S >= 2 && fit >= S;
-        if (!half) S = down_splits(d, F, T);
-        if (S > fit) S = fit;
-        const int tiles = (half ? (T + 127) / 128 : (T + 255) / 256) * (d / 256);
-        const int units = num_cu / 8 * 8 > 8 ? num_cu / 8 * 8 : 256;
-        const auto kern = half ? (probe ? k_prefix_down_tiles<TileShape<2, 2, 2, true>, true> : k_prefix_down_tiles<TileShape<2, 2, 2, true>, false>)
-                               : (probe ? k_prefix_down_tiles<TileShape<4, 4, 2, true>, true> : k_prefix_down_tiles<TileShape<4, 4, 2, true>, false>);
-        if (S > 1) { q.part_out = splitk_ws; q.S = S; }
-        const int padded = (tiles * q.S + 7) / 8 * 8;
-        hipLaunchKernelGGL(kern, dim3(padded < units ? padded : units), dim3(512), 0, stream, q);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess || S < 2) return e;
-        return combine(S);
+    auto combine = [&](int n, bool last) {                  // of n parts; not the last ones: in place of the first
+        const int blocks = (T + 7) / 8 * q.n_tn;
+        ReduceParams r = {};
+        const bool reduce = last && red;
+        if (reduce) { r = *red; *red_done = true; }
+        hipLaunchKernelGGL((es == 4 ? k_prefix_down_combine<4> : k_prefix_down_combine<2>), dim3(blocks + (reduce ? (F + 3) / 4 : 0)), dim3(256), 0,
+                           stream, blocks, r, parts, n, T, d, last ? y : nullptr, last ? q.bias : nullptr, last ? rowsq : nullptr,
+                           last ? y32 : parts, skip, last ? y32_alt : nullptr, last ? alt : nullptr);
+        return hipGetLastError();
+    };
+    if (q.S == 1) return product(1);
+    if (fit == 1) {                                         // all parts one after the other by the same workgroups (whole calls, us, a launch
+        q.chain = q.S;                                      // per part / so: 768 x 2111 at 300 tokens 96 / 60, 4096 x 9001 at 64 208 / 156)
+        const hipError_t e = product(1);
+        return e != hipSuccess ? e : combine(1, true);
     }
-    // fp32: 128 x 128 tiles, d_ff split where they leave units idle (us: 4096 x 11008 at 512 tokens 1037 / 500, 4096 x 9000 at 32 869 / 116,
-    // 2048 x 6000 at 200 585 / 81)
-    if (es == 4) {
-        const size_t one = sizeof(float) * (size_t)T * d;
-        int S = 256 / tot < 12 ? 256 / tot : 12;
-        if (S > F / 256) S = F / 256;
-        if (!splitk_ws) S = 1;
-        else if (S * one > splitk_bytes) S = (int)(splitk_bytes / one);
-        if (S > 1) { q.part_out = splitk_ws; q.S = S; }
-        hipLaunchKernelGGL((probe ? k_prefix_down<4, true> : k_prefix_down<4, false>), dim3((tot * q.S + 7) / 8 * 8), dim3(256), 0, stream, q);
-        const hipError_t e = hipGetLastError();
-        return e != hipSuccess || S < 2 ? e : combine(S);
+    for (;;) {
+        const int n = q.S - q.ks0 < fit ? q.S - q.ks0 : fit;
+        hipError_t e = product(n);
+        if (e != hipSuccess) return e;
+        q.ks0 += n;
+        if (q.ks0 == q.S) return combine(n, true);
+        if (n > 1 && (e = combine(n, false)) != hipSuccess) return e;
+        q.add = 1;
     }
-    hipLaunchKernelGGL((probe ? k_prefix_down_bf16<true> : k_prefix_down_bf16<false>), dim3(grid), dim3(256), 0, stream, q);
-    return hipGetLastError();
 }
 
-hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, float *splitk_ws, size_t splitk_bytes,
-                             int tile_mode, hipStream_t stream, int num_cu, float *y32, const int *skip, float *y32_alt, const int *alt)
+hipError_t clada_prefix_down(const clada_layer *layer, const char *h, int T, char *y, float *rowsq, const DownRoom &room, int tile_mode,
+                             hipStream_t stream, int num_cu, float *y32, const int *skip, float *y32_alt, const int *alt)
 {
-    return prefix_down(layer, h, T, y, rowsq, splitk_ws, splitk_bytes, tile_mode, stream, num_cu, y32, skip, y32_alt, alt, nullptr, nullptr);
+    return prefix_down(layer, h, T, y, rowsq, room, tile_mode, stream, num_cu, y32, skip, y32_alt, alt, nullptr, nullptr);
 }
 
 extern "C" clada_status clada_prefix_stats(clada_ctx *ctx, const clada_layer *layer, const void *x,
@@ -1152,9 +1234,11 @@ extern "C" clada_status clada_prefix_stats(clada_ctx *ctx, const clada_layer *la
     const ReduceParams red = {(const char *)layer->w_down, part, d, F, n_part, norm_rows, *out};
     bool reduced = !wanted;
     if (y) {
-        const size_t split_at = h_at + align_up((size_t)T * align_up((size_t)F, 64) * 4, 256);
-        CLADA_CHECK_HIP(ctx, prefix_down(layer, hbuf, T, (char *)y, nullptr, reinterpret_cast<float *>(ws + split_at),
-                                         ctx->ws_bytes - CLADA_WS_HEADER - split_at, ctx->opt_prefix_tile, stream, ctx->num_cu, nullptr, nullptr,
+        // a bf16 h fills half of its part, and the partial outputs begin behind it; an fp32 y is room for one
+        const size_t split_at = h_at + align_up((size_t)T * align_up((size_t)F, 64) * es, 256);
+        const DownRoom room = {reinterpret_cast<float *>(ws + split_at), ctx->ws_bytes - CLADA_WS_HEADER - split_at,
+                               es == 4 ? reinterpret_cast<float *>(y) : nullptr};
+        CLADA_CHECK_HIP(ctx, prefix_down(layer, hbuf, T, (char *)y, nullptr, room, ctx->opt_prefix_tile, stream, ctx->num_cu, nullptr, nullptr,
                                          nullptr, nullptr, wanted ? &red : nullptr, &reduced));
     }
     if (!reduced) {

@@ -1,4 +1,6 @@
 """Shared helpers of the GPU parity tests (marshalling and the comparison rules)."""
+import re
+
 import numpy as np
 import torch
 
@@ -109,3 +111,13 @@ def nan_workspace(clada, d, F, T, dtype=torch.bfloat16):
         clada.prefix_stats(ctx, layer, x)
     ctx.set_option("prefix.tile", 0)
     return ctx
+
+
+def least_workspace(clada, call):
+    """Bytes of the smallest context that call(ctx) is accepted with, from the text of its refusal."""
+    try:
+        call(clada.Context(0, 256))
+    except clada.CladaError as e:
+        has, need = map(int, re.search(r"workspace (\d+) < (\d+) bytes", str(e)).groups())
+        return need - (has - 256)
+    return 256

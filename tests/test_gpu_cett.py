@@ -5,7 +5,7 @@ import torch
 
 import oracle
 import synth
-from gpu_util import BAND, DEV, band_width, nan_workspace, to_dev, to_np
+from gpu_util import BAND, DEV, band_width, least_workspace, nan_workspace, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -333,3 +333,25 @@ def test_what_the_workspace_held_does_not_reach_the_search(clada, d, F, T, dtype
         tau, mean = clada.threshold_search_cett(ctx, layer, x, bound)
         assert float(mean) <= bound
         assert float(mean) == pytest.approx(exact(float(tau)).mean(), rel=TOL_CETT[dtype], abs=1e-6)
+
+
+# as above, in the calls of the error bound: plain and bracketed searches, kept sums in two buffers (d_ff >= 2 d) and formed again, biases
+@pytest.mark.parametrize("d,F,T,dtype,kind", [
+    (1024, 4096, 64, "bf16", "swiglu"), (512, 3333, 100, "bf16", "swiglu"), (512, 3333, 100, "bf16", "relu"), (512, 900, 300, "bf16", "geglu"),
+    (1024, 1984, 140, "bf16", "swiglu"), (256, 2085, 40, "bf16", "relu"), (260, 3001, 90, "f32", "swiglu"), (512, 1111, 140, "f32", "relu"),
+    (512, 2222, 256, "f32", "swiglu"), (256, 1031, 40, "f32", "relu")])
+def test_cett_does_not_depend_on_the_room_for_a_split(clada, d, F, T, dtype, kind):
+    from test_gpu_prefix import _split_layer
+    layer, x = _split_layer(clada, d, F, T, dtype, kind)
+    least = least_workspace(clada, lambda c: clada.cett_eval(c, layer, x, 0.1))
+    advised = clada.workspace_bytes(d, F, 0, T, 0)
+    want = None
+    for n in (advised, least, least + 4 * T * d, least + 8 * T * d, least + 20 * T * d):
+        ctx = clada.Context(0, n)
+        got = [*clada.cett_eval(ctx, layer, x, 0.1), *clada.threshold_search_cett(ctx, layer, x, 0.2),
+               *clada.threshold_search_cett(ctx, layer, x, 0.2, n_probes=30)]
+        if want is None:
+            want = got
+            assert 0.0 < float(got[1]) < 1.0 and float(got[3]) <= 0.2
+        for i, (a, b) in enumerate(zip(got, want)):
+            assert torch.equal(a, b), (i, n - least)

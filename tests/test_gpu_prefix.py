@@ -5,7 +5,7 @@ import torch
 
 import oracle
 import synth
-from gpu_util import DEV, TOL_Y, assert_close_y, nan_workspace, to_dev, to_np
+from gpu_util import DEV, TOL_Y, assert_close_y, least_workspace, nan_workspace, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -335,3 +335,37 @@ def test_h_is_zero_past_d_ff(clada, d, F, T, kind, tile):
         h = a * (x.double() @ w[1].double().t())
     want = (h @ w[2].double()).cpu().numpy()
     assert _rel(to_np(y), want) < (1e-5 if kind == "f32" else 5e-3)      # bf16: h and y each rounded once, 2^-9 of a value
+
+
+# d, F, T, dtype, kind, tile: bf16 whose smallest workspace has room for 10 of 12 parts, for 3 of 12, for 4 of 8, for all, for one; d_ff below 2 d off
+# multiples of 32 (not split); fp32 with room for none (y takes them) and for all
+SPLITS = [(1024, 4096, 16, "bf16", "swiglu", 0), (512, 3333, 100, "bf16", "relu", 0), (256, 2085, 40, "bf16", "geglu", 0), (1024, 2720, 300, "bf16", "swiglu", 0),
+          (768, 2111, 300, "bf16", "swiglu", 2), (1024, 1919, 64, "bf16", "swiglu", 0), (260, 3001, 40, "f32", "swiglu", 0), (512, 1111, 140, "f32", "relu", 0),
+          (512, 4096, 300, "f32", "swiglu", 0)]
+
+
+def _split_layer(clada, d, F, T, dtype, kind):
+    from paper_2502_19078_amd import binding
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(d + F + T)
+    w = [(torch.randn(F, d, generator=g, device=DEV) * d ** -0.5).to(dt) for _ in range(3)]
+    layer = (clada.Layer(w[0], None, w[2], kind=binding.RELU, b_out=torch.randn(d, generator=g, device=DEV)) if kind == "relu"
+             else clada.Layer(*w, kind=binding.GEGLU if kind == "geglu" else binding.SWIGLU))
+    return layer, torch.randn(T, d, generator=g, device=DEV).to(dt)
+
+
+@pytest.mark.parametrize("d,F,T,dtype,kind,tile", SPLITS)
+def test_y_does_not_depend_on_the_room_for_a_split(clada, d, F, T, dtype, kind, tile):
+    """The same bits from a context of the advised size, from the smallest one, and from some between and beyond."""
+    layer, x = _split_layer(clada, d, F, T, dtype, kind)
+    least = least_workspace(clada, lambda c: clada.prefix_stats(c, layer, x))
+    advised = clada.workspace_bytes(d, F, 0, T, 0)
+    want = None
+    for n in (advised, least, least + 4 * T * d, least + 8 * T * d, least + 20 * T * d, advised + 64 * T * d):
+        ctx = clada.Context(0, n)
+        ctx.set_option("prefix.tile", tile)
+        got = clada.prefix_stats(ctx, layer, x)
+        if want is None:
+            want = got
+        for k in ("y", "A", "sum_sq_h"):
+            assert torch.equal(getattr(got, k), getattr(want, k)), (k, n - least)

@@ -55,6 +55,42 @@ def test_search_over_many_tokens_of_a_narrow_layer_is_the_plain_bisection(fake, 
     assert any("k_cett_between" in n for n in _names(r[1])) == large
 
 
+@pytest.mark.parametrize("d,F,T,dtype,room,want", [
+    # parts per launch (1: or all of them by the same workgroups) in a workspace with `room` times [T][d] behind h (0: the smallest that the call accepts), and the launches that add up
+    (1024, 4096, 16, "bf16", 12, ([12], 1)), (1024, 4096, 16, "bf16", 11, ([11, 1], 2)), (1024, 4096, 16, "bf16", 0, ([10, 2], 2)),
+    (512, 3333, 100, "bf16", 0, ([3] * 4, 4)), (512, 3333, 100, "bf16", 5, ([5, 5, 2], 3)), (512, 3333, 100, "bf16", 100, ([12], 1)),
+    (1024, 2111, 100, "bf16", 0, ([1], 1)), (1024, 2111, 100, "bf16", 2, ([2] * 4, 4)),
+    (1024, 1919, 64, "bf16", 100, ([1], 0)), (260, 3001, 40, "f32", 0, ([1], 1)), (260, 3001, 40, "f32", 3, ([3, 3, 3, 2], 4)),
+    (260, 3001, 40, "f32", 11, ([11], 1)),
+])
+def test_parts_of_the_down_projection_by_the_room_there_is(fake, d, F, T, dtype, room, want):
+    up = lambda n: (n + 255) // 256 * 256
+    es, Fp, tiles = 4 if dtype == "f32" else 2, -(-F // 64) * 64, -(-T // 128) * -(-d // (256 if dtype == "bf16" else 128))
+    part = up(-(-T // 128) * 16 * F)
+    least = part + up(T * Fp * 4) + (8 * 4 * T * d if (F % 32, d % 256) == (0, 0) else 0)
+    step = {"do": "prefix", "d": d, "F": F, "T": T, "dtype": dtype}
+    assert run_steps(fake, [{"do": "ctx", "bytes": least - 256}, step])[1]["status"] == 5      # CLADA_ERR_WORKSPACE
+    r = run_steps(fake, [{"do": "ctx", "bytes": part + up(T * Fp * es) + room * 4 * T * d if room else least}, step])[1]
+    down = [x[1] for x in r["launches"] if "k_prefix_down" in x[0] and "combine" not in x[0]]
+    assert r["status"] == 0 and down == [-(-tiles * n // 8) * 8 for n in want[0]]      # (padded to a multiple of eight workgroups)
+    assert sum("combine" in n for n in _names(r)) == want[1]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,F,T", [(260, 3001, 90), (512, 3333, 100), (1024, 4096, 16), (2048, 8191, 200), (4096, 9001, 64), (1024, 1919, 64), (8192, 20011, 300)])
+def test_the_advised_workspace_holds_all_parts_of_either_type(fake, d, F, T, dtype):
+    if d == 8192 and dtype == "f32":
+        d = 4096                                             # (the widest fp32 row)
+    if d % 8 and dtype == "bf16":
+        d = 264
+    for tile in (0, 1, 2):
+        r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 0, T, 0]}, {"do": "option", "name": "prefix.tile", "value": tile}]
+                      + [{"do": do, "d": d, "F": F, "T": T, "dtype": dtype, "kind": kind} for do in ("prefix", "search") for kind in ("swiglu", "relu")])
+        for x in r[2:]:
+            down = [n for n in _names(x) if "k_prefix_down" in n and "combine" not in n]
+            assert down and not any("Lb1ELb1E" in n for n in down), down      # (the instances that form some parts at a time)
+
+
 def _stack_grid(r):
     """[(partial outputs per layer, layers)] of the launches over several layers; None if the call ran another way."""
     names = _names(r)
