@@ -680,8 +680,9 @@ k_cett_between(CettState *__restrict__ sts, int launch, int taken, const float *
     if (tid == 0) { s_edge[0] = __uint_as_float(s_st.base); s_edge[1] = __uint_as_float(s_st.known_lo); }
     if (tid < NODES) s_edge[2 + tid] = __uint_as_float(node_threshold<LEVELS>(s_st, tid));
     __syncthreads();
-    float edge[NODES + 2];                                   // segment i: edge[i] <= |a| < edge[i + 1]; a threshold that is not needed repeats
-    edge[0] = s_edge[0]; edge[1] = s_edge[1];                // another one and leaves the order: made ascending here
+    // segment i: edge[i] <= |a| < edge[i + 1]; a threshold that is not needed repeats another one and leaves the order: made ascending here
+    float edge[NODES + 2];
+    edge[0] = s_edge[0]; edge[1] = s_edge[1];
 #pragma unroll
     for (int v = 0; v < NODES; ++v) edge[2 + v] = fmaxf(edge[1 + v], s_edge[2 + v]);
     const size_t t = blockIdx.x;
@@ -1059,14 +1060,15 @@ extern "C" clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_
     st = begin(ctx, layer, x_val, T, w, 1, 0.0f, stream);
     if (st != CLADA_OK) return st;
     // The large search pays where a dense probe costs more than a workgroup per token (0.1 us of a probe inside the bracket), and
-    // its bracket is only trusted where single neurons do not move the mean (ms, plain / large from 2^18 magnitudes of at least 1024 neurons on: 0.80 / 0.25 for 64
-    // tokens of 1024 x 4096, 1.43 / 0.33 of 4096 x 11008, 0.86 / 0.27 for 256 of 512 x 1999); fewer probes than the full 31 end somewhere on the
-    // way, which only the plain bisection passes through.  A bf16 projection of fewer than 2048 neurons costs less once the
-    // tokens fill the chip (ms, large / plain: 6.6 / 3.9 and 8.2 / 6.4 at 65536 tokens of 64 and 512 x 512, 7.9 / 7.1 of
-    // 256 x 1024, 1.9 / 1.7 at 16384 of 256 x 512; 0.79 / 1.04 at 4096 of 256 x 512, 8.2 / 11.1 at 65536 of 64 x 2048); an fp32
-    // one never does (2.1 / 2.7 at 16384 of 64 x 512).
-    const bool large = n_probes == 31 && bound > 0.0f && (size_t)T * layer->d_ff >= (layer->d_ff >= 1024 ? 1u << 18 : 1u << 20) && T >= 64 && layer->d_ff >= layer->d &&
-                       layer->d_ff >= 512 && large_fits(T, layer->d_ff) && (layer->dtype == CLADA_F32 || T <= 4096 || layer->d_ff >= 2048);
+    // its bracket is only trusted where single neurons do not move the mean (ms, plain / large from 2^18 magnitudes of at least 1024
+    // neurons on: 0.80 / 0.25 for 64 tokens of 1024 x 4096, 1.43 / 0.33 of 4096 x 11008, 0.86 / 0.27 for 256 of 512 x 1999); fewer probes
+    // than the full 31 end somewhere on the way, which only the plain bisection passes through.  A bf16 projection of fewer than 2048
+    // neurons costs less once the tokens fill the chip (ms, large / plain: 6.6 / 3.9 and 8.2 / 6.4 at 65536 tokens of 64 and 512 x 512,
+    // 7.9 / 7.1 of 256 x 1024, 1.9 / 1.7 at 16384 of 256 x 512; 0.79 / 1.04 at 4096 of 256 x 512, 8.2 / 11.1 at 65536 of 64 x 2048); an
+    // fp32 one never does (2.1 / 2.7 at 16384 of 64 x 512).
+    const int F = layer->d_ff;
+    const bool large = n_probes == 31 && bound > 0.0f && T >= 64 && (size_t)T * F >= (F >= 1024 ? 1u << 18 : 1u << 20) && F >= layer->d &&
+                       F >= 512 && large_fits(T, F) && (layer->dtype == CLADA_F32 || T <= 4096 || F >= 2048);
     if (large) {
         st = search_large(ctx, layer, T, w, bound, stream);
         if (st != CLADA_OK) return st;

@@ -7,13 +7,14 @@
 //     straight from LDS.  Epilogue on the accumulators: a = SiLU(C_g),
 //     h = a*C_u, per-neuron partial sums over the tile's tokens (|a|, a^2, h^2,
 //     max|a|), the |a| pool, and h stored in the layer dtype for kernel 2.
-//   kernel 2 (down): Y = H W_down, W_down tile transposed on its way into LDS.
-//   kernel 3: fixed-order reduction of the per-token-tile partials,
+//   kernel 2 (down): Y = H W_down.  W_down lies neuron-major, k by columns: the bf16 kernels keep it so in LDS and read the
+//     fragments transposed, the fp32 kernel transposes it on its way into LDS.  Short prefixes split d_ff.
+//   kernel 3: the parts of a split added up, and a fixed-order reduction of the per-token-tile partials,
 //     A_j = sqrt(sum_t h_tj^2) * ||W_down[j,:]||_2.
-// bf16 layers run on the pipelined tiles of prefix_tiles.h; fp32 layers, and bf16 ones whose rows are no
-// multiple of the k-tile, on plain tiles (gate/up 128 or 64 tokens x 64 neurons, down 128 x 128) of four
-// wavefronts, MFMA 32x32x16 (bf16) or 32x32x2 (fp32), fp32 accumulation.  Block ids are remapped so that the eight XCDs each walk their own range of tiles
-// (operand slices stay in that XCD's L2).
+// bf16 layers run on the pipelined tiles of prefix_tiles.h: the gate/up product for rows of whole k-tiles (d % 64 == 0), the down
+// projection for d % 256 == 0.  The rest, and fp32 layers, run on plain tiles (gate/up 128 or 64 tokens x 64 neurons, down 128 x 128) of
+// four wavefronts, MFMA 32x32x16 (bf16) or 32x32x2 (fp32), fp32 accumulation.  Block ids are remapped so that the eight XCDs each
+// walk their own range of tiles (operand slices stay in that XCD's L2).
 #include <math.h>
 
 #include "prefix_tiles.h"
@@ -120,9 +121,9 @@ struct GateUpParams {
 
 // Epilogue of the gate/up GEMM on the accumulators (shared by the fp32 and bf16 kernels):
 // a = SiLU(C_g), h = a*C_u, per-neuron partial sums over the tile's tokens, |a| pool, h store.
-template <int ES, int WMN, int MB, int NK, int NEU>
+template <int ES, int MB, int NK, int NEU>
 __device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[2][MB][NK], const GateUpParams &p, int tm, int tn,
-                                                int wm, int wn, int lane, int tid, float (&s_stat)[WMN][4][NEU])
+                                                int wm, int wn, int lane, int tid, float (&s_stat)[2][4][NEU])
 {
     // ------------------------------------------------------------------ epilogue
     const int n = lane & 31;
@@ -135,7 +136,7 @@ __device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[2][MB][NK], 
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int t = (tm * WMN + wm) * 32 * MB + mb * 32 + acc_row(r, lane);
+                const int t = (tm * 2 + wm) * 32 * MB + mb * 32 + acc_row(r, lane);
                 float a, h;
                 if (p.relu) {
                     const float g = acc[0][mb][nb][r] + ((p.b_in && j < p.F) ? p.b_in[j] : 0.0f);
@@ -177,11 +178,11 @@ __device__ __forceinline__ void gateup_epilogue(const f32x16 (&acc)[2][MB][NK], 
         const int j = tn * NEU + tid;
         if (j < p.F) {
             float *dst = p.part + (size_t)tm * 4 * p.F + j;
-            dst[0] = s_stat[0][0][tid] + (WMN > 1 ? s_stat[WMN - 1][0][tid] : 0.0f);
-            dst[(size_t)p.F] = s_stat[0][1][tid] + (WMN > 1 ? s_stat[WMN - 1][1][tid] : 0.0f);
-            const float m0 = s_stat[0][2][tid], m1 = s_stat[WMN - 1][2][tid];
+            dst[0] = s_stat[0][0][tid] + s_stat[1][0][tid];
+            dst[(size_t)p.F] = s_stat[0][1][tid] + s_stat[1][1][tid];
+            const float m0 = s_stat[0][2][tid], m1 = s_stat[1][2][tid];
             dst[2 * (size_t)p.F] = (m1 > m0 || m1 != m1) ? m1 : m0;
-            dst[3 * (size_t)p.F] = s_stat[0][3][tid] + (WMN > 1 ? s_stat[WMN - 1][3][tid] : 0.0f);
+            dst[3 * (size_t)p.F] = s_stat[0][3][tid] + s_stat[1][3][tid];
         }
     }
 }
@@ -195,19 +196,19 @@ __global__ void __launch_bounds__(256)
 k_prefix_gateup(const GateUpParams p)
 {
     constexpr int NEU = 64, ROW = Tile<ES>::ROW, CH = Tile<ES>::CHUNKS, PT = NEU * CH / 256, PX = TT * CH / 256;
-    constexpr int WMN = 2, MB = TT / 64, NK = 1;
+    constexpr int MB = TT / 64, NK = 1;
     static_assert(PX >= PT, "the token tile is the larger one");
     __shared__ __align__(16) char s_a[TT * ROW];
     __shared__ __align__(16) char s_g[NEU * ROW];
     __shared__ __align__(16) char s_u[NEU * ROW];
-    __shared__ float s_stat[WMN][4][NEU];
+    __shared__ float s_stat[2][4][NEU];
 
     const int total = p.n_tm * p.n_tn;
     const int tile = remap_block(blockIdx.x, total);
     if (tile >= total) return;
     const int tm = tile % p.n_tm, tn = tile / p.n_tm;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WMN, wn = wave / WMN;
+    const int wm = wave & 1, wn = wave >> 1;
     const size_t rowbytes = (size_t)p.d * ES;
 
     f32x16 acc[2][MB][NK];
@@ -251,7 +252,7 @@ k_prefix_gateup(const GateUpParams p)
         mma_tile<ES, 2, MB, NK>(s_a + wm * 32 * MB * ROW, sb, acc, lane);
     }
 
-    gateup_epilogue<ES, WMN, MB, NK, NEU>(acc, p, tm, tn, wm, wn, lane, tid, s_stat);
+    gateup_epilogue<ES, MB, NK, NEU>(acc, p, tm, tn, wm, wn, lane, tid, s_stat);
 }
 
 // Sum of squares of a row of W_down, by one wave: 16-byte chunks, lane l takes chunks l, l + 64, .. (eight loads in flight).
@@ -519,13 +520,13 @@ __device__ __forceinline__ void down_store32(const f32x16 (&acc)[2][2], const Do
 // PROBE (the three down kernels): the error-bounded search's form, with y32 and skip.  The others are built without: the
 // extra store loop alone raised k_prefix_down_bf16's registers (330 -> 401 us at 2368 x 4096 x 9728).
 // SOME: some parts of a split at a time, for a workspace that does not hold all of them; also with skip.
-template <int ES, bool PROBE, bool SOME = false>
+// fp32.
+template <bool PROBE, bool SOME = false>
 __global__ void __launch_bounds__(256)
 k_prefix_down(const DownParams p)
 {
     if (PROBE && p.skip && *p.skip) return;
-    constexpr int ROW = Tile<ES>::ROW, CH = Tile<ES>::CHUNKS, PT = Tile<ES>::PER_THREAD;
-    constexpr int VEC = 16 / ES;
+    constexpr int ES = 4, ROW = Tile<ES>::ROW, CH = Tile<ES>::CHUNKS, PT = Tile<ES>::PER_THREAD;
     __shared__ __align__(16) char s_a[BM * ROW];
     __shared__ __align__(16) char s_b[BN * ROW];      // [n][k]: W_down tile transposed
     __shared__ float s_rs[2][BM];
@@ -588,13 +589,8 @@ k_prefix_down(const DownParams p)
 #pragma unroll
             for (int i = 0; i < BPT; ++i) {
                 const int c = tid + i * 256, k = c / BCH, ch = c % BCH;
-                const unsigned int w[4] = {rb[i].x, rb[i].y, rb[i].z, rb[i].w};
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    const int nloc = ch * VEC + e;
-                    if (ES == 4) *reinterpret_cast<unsigned int *>(s_b + nloc * ROW + k * 4) = w[e];
-                    else *reinterpret_cast<unsigned short *>(s_b + nloc * ROW + k * 2) = (unsigned short)(w[e >> 1] >> (16 * (e & 1)));
-                }
+                for (int e = 0; e < 4; ++e) *reinterpret_cast<unsigned int *>(s_b + (ch * 4 + e) * ROW + k * 4) = rb[i][e];
             }
             __syncthreads();
             if (kt + 1 < nk) load_tile(kt + 1);
@@ -636,11 +632,8 @@ k_prefix_down(const DownParams p)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int t = tm * BM + wm * 64 + mb * 32 + acc_row(r, lane);
-                if (t < p.T && col < p.d) {
-                    const float v = acc[0][mb][nb][r] + (p.bias ? p.bias[col] : 0.0f);
-                    if (ES == 4) reinterpret_cast<float *>(p.y)[(size_t)t * p.d + col] = v;
-                    else reinterpret_cast<unsigned short *>(p.y)[(size_t)t * p.d + col] = (unsigned short)f32_to_bf16_bits(v);
-                }
+                if (t < p.T && col < p.d)
+                    reinterpret_cast<float *>(p.y)[(size_t)t * p.d + col] = acc[0][mb][nb][r] + (p.bias ? p.bias[col] : 0.0f);
             }
     }
 }
@@ -756,7 +749,8 @@ k_prefix_down_bf16(const DownParams p)
 }
 
 // bf16 down projection on the pipelined tiles (d % 256 == 0), 256 columns of W_down a tile as they lie in memory: S::TM tokens x 256
-// columns x one of the S ranges the neurons are split into.  (128 tokens: split only, for a wave then holds half a tile of the row norms.)
+// columns x one of the S ranges the neurons are split into.  (128 tokens: split only, for a wave then holds half a tile of the row
+// norms.)
 template <class S, bool PROBE, bool SOME = false>
 __global__ void __launch_bounds__(512, 2)
 k_prefix_down_tiles(const DownParams p)
@@ -773,7 +767,7 @@ k_prefix_down_tiles(const DownParams p)
             const int o = tile_order(tile, blocks, n_tm * n_tn * parts);
             if (o < 0) return false;
             id.pos = it - tile * (SOME ? chain : 1);
-            id.ks = o / (n_tm * n_tn);                      // the tiles of one range side by side: they share rows of W_down and columns of h
+            id.ks = o / (n_tm * n_tn);                      // a range's tiles side by side: they share rows of W_down and columns of h
             tile_coords(o - id.ks * n_tm * n_tn, n_tm, n_tn, id.tm, id.tn);
             return true;
         }
@@ -783,7 +777,7 @@ k_prefix_down_tiles(const DownParams p)
     const size_t hrow = (size_t)p.Fp * 2, wrow = (size_t)p.d * 2;
     int vw[S::PW];
 #pragma unroll
-    for (int i = 0; i < S::PW; ++i) {                       // two rows a transfer; piece s (32 bytes) of row r lies at s ^ ((r & 3) | (r >> 3 & 1) << 2)
+    for (int i = 0; i < S::PW; ++i) {                       // two rows a transfer; 32-byte piece s of row r at s ^ ((r & 3) | (r >> 3 & 1) << 2)
         const int row = 2 * wave + 16 * i + (lane >> 5), f = (row & 3) | ((row >> 3 & 1) << 2), at = lane & 31;
         vw[i] = row * (int)wrow + ((((at >> 1) ^ f) << 1) | (at & 1)) * 16;
     }
@@ -826,7 +820,8 @@ k_prefix_down_tiles(const DownParams p)
 #pragma unroll
                     for (int j = 0; j < 2 * S::NB; ++j) sum[i][j] = id.pos == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
                 if (id.pos + 1 < p.chain) return;
-                if (p.add && id.ks == 0) each([&](int i, int j, int r, float &at) { sum[i][j][r] += at; });      // (all loads before the first store)
+                // (all loads before the first store)
+                if (p.add && id.ks == 0) each([&](int i, int j, int r, float &at) { sum[i][j][r] += at; });
                 each([&](int i, int j, int r, float &at) { at = sum[i][j][r]; });
             } else {
                 each([&](int i, int j, int r, float &at) { at = acc[i][j][r]; });
@@ -925,8 +920,8 @@ __global__ void __launch_bounds__(256) k_prefix_reduce(const ReduceParams p) { r
 // Sum of the S split-K partial outputs [S][T][d] in ascending order, then what the direct epilogue does:
 // y in bf16 (+ bias) and / or the per-row sums of squares of every 128-column tile.  A workgroup takes
 // 8 rows x 128 columns: thread = (row tid >> 5, four columns 4 (tid & 31) ..).  The workgroups behind the first `blocks` do the
-// per-neuron reductions of the same call, which need nothing of this (bf16; 512 tokens of 4096 x 11008: 22.6 us in two launches and eight parts,
-// 16.8 so and with four).  y (fp32) or y32 may be the first part itself: a thread writes what only it has read.
+// per-neuron reductions of the same call, which need nothing of this (bf16; 512 tokens of 4096 x 11008: 22.6 us in two launches and
+// eight parts, 16.8 so and with four).  y (fp32) or y32 may be the first part itself: a thread writes what only it has read.
 template <int ES>
 __global__ void __launch_bounds__(256)
 k_prefix_down_combine(int blocks, const ReduceParams red, const float *part, int S, int T, int d, char *y,
@@ -1008,9 +1003,9 @@ static int down_splits(int d, int F, int T)
     return S < 2 ? 1 : S;
 }
 // The same for tiles of 128 tokens, up to 12 parts, if they are taken: where a part is short, the partial outputs weigh more than the
-// operands that a smaller tile reads again (whole calls, us, 256 / 128 tokens: 333 x 2560 x 10240 77.5 / 72.8, 512 x 4096 x 11008 136 / 130, 16 x
-// 4096 x 11008 81.9 / 71.3, 200 x 2048 x 8191 56 / 52; parts of more than 4096 neurons: 512 x 5120 x 13824 213 / 220, 333 x 8192 x
-// 20011 423 / 438, 777 x 4096 x 11008 218 / 211).  0: not taken.
+// operands that a smaller tile reads again (whole calls, us, 256 / 128 tokens: 333 x 2560 x 10240 77.5 / 72.8, 512 x 4096 x 11008
+// 136 / 130, 16 x 4096 x 11008 81.9 / 71.3, 200 x 2048 x 8191 56 / 52; parts of more than 4096 neurons: 512 x 5120 x 13824 213 / 220,
+// 333 x 8192 x 20011 423 / 438, 777 x 4096 x 11008 218 / 211).  0: not taken.
 static int down_splits_half(int d, int F, int T)
 {
     if (T <= 0 || d % 256 != 0) return 0;
@@ -1057,9 +1052,9 @@ size_t clada_ws_down_room(int d, int F, int T)
 }
 int clada_prefix_col_tiles(int d) { return (d + BN - 1) / BN; }
 
-// Gate/up GEMM with the fused activation epilogue: part [*n_part][4][F] per-neuron partial aggregates of the token tiles (always written, at
-// most clada_prefix_token_tiles(T) of them), pool [T][F] |a| or nullptr, hbuf [T][Fp] h in the layer dtype or nullptr (Fp = F rounded up
-// to 64, zero past F).
+// Gate/up GEMM with the fused activation epilogue: part [*n_part][4][F] per-neuron partial aggregates of the token tiles (always
+// written, at most clada_prefix_token_tiles(T) of them), pool [T][F] |a| or nullptr, hbuf [T][Fp] h in the layer dtype or nullptr
+// (Fp = F rounded up to 64, zero past F).
 hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, float *part, float *pool,
                                char *hbuf, int tile_mode, hipStream_t stream, int num_cu, int *n_part, float *wnorm2, int *norm_rows)
 {
@@ -1120,8 +1115,8 @@ hipError_t clada_prefix_gateup(const clada_layer *layer, const void *x, int T, f
             return launch(k_prefix_gateup_tiles<TileShape<4, 3, 2, false>, false>, t192, n_tmw, most_wide, 57, true);
         return launch(k_prefix_gateup_tiles<TileShape<4, 4, 2, false>, false>, t256, n_tmw, most_wide, 57);
     }
-    // one token tile and units left over: 64 neurons a tile (us, 128 / 64 neurons: 4096 x 11008 at 64 tokens 64.5 / 49.5, 2560 x 10240 38.5 /
-    // 32.6, 4096 x 14336 79.5 / 73.7; more than one round: 8192 x 20011 183 / 212)
+    // one token tile and units left over: 64 neurons a tile (us, 128 / 64 neurons: 4096 x 11008 at 64 tokens 64.5 / 49.5, 2560 x 10240
+    // 38.5 / 32.6, 4096 x 14336 79.5 / 73.7; more than one round: 8192 x 20011 183 / 212)
     if (T <= 128 && 2 * total <= num_cu)
         return launch(k_prefix_gateup_tiles<TileShape<2, 1, 4, false, true>, false>, g.n_tm * ((F + 63) / 64), g.n_tm, most_two, 50);
     return launch(k_prefix_gateup_tiles<TileShape<2, 2, 2, false>, false>, total, g.n_tm, most_two, 50);
@@ -1156,7 +1151,7 @@ static hipError_t prefix_down(const clada_layer *layer, const char *h, int T, ch
         q.parts = n;
         const bool some = n < q.S || q.chain > 1;
         if (es == 4) {
-            const auto kern = some ? k_prefix_down<4, true, true> : probe ? k_prefix_down<4, true> : k_prefix_down<4, false>;
+            const auto kern = some ? k_prefix_down<true, true> : probe ? k_prefix_down<true> : k_prefix_down<false>;
             hipLaunchKernelGGL(kern, dim3((q.n_tm * q.n_tn * n + 7) / 8 * 8), dim3(256), 0, stream, q);
         } else if (d % 256 != 0 || tile_mode == 1) {        // tile_mode 1 = 128 x 128 tiles of the plain kernel always
             hipLaunchKernelGGL((probe ? k_prefix_down_bf16<true> : k_prefix_down_bf16<false>), dim3((q.n_tm * q.n_tn + 7) / 8 * 8), dim3(256), 0,
@@ -1184,8 +1179,10 @@ static hipError_t prefix_down(const clada_layer *layer, const char *h, int T, ch
         return hipGetLastError();
     };
     if (q.S == 1) return product(1);
-    if (fit == 1) {                                         // all parts one after the other by the same workgroups (whole calls, us, a launch
-        q.chain = q.S;                                      // per part / so: 768 x 2111 at 300 tokens 96 / 60, 4096 x 9001 at 64 208 / 156)
+    if (fit == 1) {
+        // all parts one after the other by the same workgroups (whole calls, us, a launch per part / so: 768 x 2111 at 300 tokens 96 / 60,
+        // 4096 x 9001 at 64 208 / 156)
+        q.chain = q.S;
         const hipError_t e = product(1);
         return e != hipSuccess ? e : combine(1, true);
     }
