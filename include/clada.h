@@ -170,18 +170,18 @@ clada_status clada_threshold_calibrate(clada_ctx *ctx, const float *abs_act_pool
  * over the validation tokens x_val [T][d] (layer dtype), with a, h as in
  * clada_prefix_stats; the cut rule (strict '<' on |SiLU(gate)|, NaN never cut)
  * is the decode call's, so the result feeds clada_threshold directly.  A token
- * whose dense output is zero counts as CETT = 0.
+ * whose dense output is zero counts as CETT = 0, and so does one whose output is NaN.
  * The search bisects the bit pattern of eps between 0 (cuts nothing) and +inf
  * (cuts everything) with the bracket on the device, n_probes in [1,31] times: 31
  * resolve the float exactly, fewer return the lower, feasible end of the
  * remaining bracket.  Every probe is one masked down projection, save in the full
- * search (31) of a large layer (T >= 64, T d_ff >= 2^20, d_ff >= d and >= 512,
- * bound > 0; not bf16 layers of fewer than 2048 neurons over more than 4096
- * tokens).  There at most ten masked projections, placed by the order statistics
- * of a sample of the pool, close a bracket in on the threshold; the bisection
- * answers a probe outside the bracket from its ends, as on a monotone curve, and
- * one inside by adding the few neurons between the ends to the lower end's sums.
- * That takes 0.4 to 0.8 of the time (so 30 probes of such a layer are slower than
+ * search (31) of a larger layer: T >= 64, d_ff >= d and >= 512, bound > 0, and
+ * T d_ff >= 2^18 (2^20 below 1024 neurons), with 4 ceil(T/128) d_ff >= 12544 + T; not
+ * bf16 layers of fewer than 2048 neurons over more than 4096 tokens.  There at most five masked projections, placed by the
+ * order statistics of a sample of the pool, close a bracket in on the threshold; the
+ * bisection answers a probe outside the bracket from its ends, as on a monotone curve,
+ * and one inside by adding the neurons between the ends to the lower end's sums.  That
+ * takes 0.2 to 0.7 of the time (so 30 probes of such a layer are slower than
  * 31).  On a monotone curve all ways end at the same float.  Where the mean is not
  * monotone in eps at the scale of single neurons the result is a boundary of the
  * feasible set -- the mean at it is within the bound, at the next magnitude up it
