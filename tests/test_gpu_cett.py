@@ -286,8 +286,11 @@ def test_search_cost_grows_with_the_tokens_not_with_their_square(clada):
 # d, F, T, dtype: one, three and seven thresholds a launch of the last stage (by the row norms' room: 1, 2, 4, 6 and more of them), just above
 # the smallest search that is bracketed, d_ff below and above 2 d (the probes' sums kept or formed again), more magnitudes in
 # the bracket than threads.
-@pytest.mark.parametrize("d,F,T,dtype", [(64, 4099, 64, "bf16"), (256, 3300, 80, "bf16"), (512, 2100, 130, "bf16"), (512, 1028, 263, "f32"),
-                                         (1536, 2000, 140, "f32"), (1104, 4111, 64, "bf16"), (64, 140000, 64, "bf16")])
+PER_LAUNCH = [(64, 4099, 64, "bf16"), (256, 3300, 80, "bf16"), (512, 2100, 130, "bf16"), (512, 1100, 263, "f32"), (1536, 2000, 140, "f32"),
+              (1104, 4111, 64, "bf16"), (64, 140000, 64, "bf16")]
+
+
+@pytest.mark.parametrize("d,F,T,dtype", PER_LAUNCH)
 def test_search_thresholds_per_launch(clada, d, F, T, dtype):
     """Against the plain bisection of 30 probes.  The sums' order differs (rel. 1e-6 of a norm, so 1e-6 of a mean whose slope over the
     ranks is about one): the result may move by T F 1e-6 magnitudes and the one next to them, which lie up to 10 / (T F) apart."""

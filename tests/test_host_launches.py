@@ -4,6 +4,8 @@ import shutil
 
 import pytest
 
+import test_gpu_cett
+import test_gpu_prefix
 import test_gpu_stack
 from fake_hip import build_runtime, run_steps
 
@@ -164,6 +166,32 @@ def test_the_device_tests_of_the_lanes_take_them(fake, d, F, L, relu, B, dense, 
 def test_the_device_tests_of_captures_take_both_ways(fake, d, F, L):
     r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 1, 0, 0]}, {"do": "stack", "d": d, "F": F, "L": L, "B": 1}])
     assert (_stack_grid(r[1]) is None) == (d == 6144)
+
+
+def test_the_device_tests_of_bracketed_searches_bracket(fake):
+    """All of them, with one, three and seven thresholds a launch (the kernel's last template number is the steps: 1, 2, 3)."""
+    steps = set()
+    for d, F, T, dtype in test_gpu_cett.PER_LAUNCH:
+        r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 0, T, 0]}, {"do": "search", "d": d, "F": F, "T": T, "dtype": dtype}])
+        between = {n for n in _names(r[1]) if "k_cett_between" in n}
+        assert len(between) == 1, (d, F, T, dtype)
+        steps.add(between.pop().split("k_cett_betweenI")[1].split("Li")[3][0])
+    assert steps == {"1", "2", "3"}
+
+
+def test_the_device_tests_of_padded_columns_take_every_tile(fake):
+    """Which gate/up kernel each of them runs; the first ten are there for tiles of 96 neurons (three pairs of 16 for each of two waves)."""
+    seen = []
+    for d, F, T, kind, tile in test_gpu_prefix.PADDED:
+        step = {"do": "prefix", "d": d, "F": F, "T": T, "kind": "swiglu" if kind == "f32" else kind, "dtype": "f32" if kind == "f32" else "bf16"}
+        r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 0, T, 0]}, {"do": "option", "name": "prefix.tile", "value": tile}, step])
+        seen.append([n for n in _names(r[2]) if "k_prefix_gateup" in n][0])
+    is_ = lambda n, wm, nb, single: f"TileShapeILi{wm}ELi{nb}E" in n and f"ELb{single}EEEvNS_" in n
+    assert all(is_(n, 4, 3, 0) for n in seen[:10])
+    # 64, 128 and 256 neurons, gated and not; the plain kernel in both types
+    for want in ((2, 1, 0), (2, 2, 0), (2, 1, 1), (4, 4, 0), (4, 4, 1)):
+        assert any(is_(n, *want) for n in seen[10:]), (want, seen)
+    assert {n.split("k_prefix_gateupI")[1][:4] for n in seen if "k_prefix_gateupI" in n} == {"Li2E", "Li4E"}
 
 
 def _batched_layers(r):
