@@ -338,7 +338,8 @@ def test_what_the_workspace_held_does_not_reach_the_search(clada, d, F, T, dtype
         assert float(mean) == pytest.approx(exact(float(tau)).mean(), rel=TOL_CETT[dtype], abs=1e-6)
 
 
-# as above, in the calls of the error bound: plain and bracketed searches, kept sums in two buffers (d_ff >= 2 d) and formed again, biases
+# Splits of the down projection whose parts the smallest workspace does not hold, in the calls of the error bound: plain and bracketed
+# searches, kept sums in two buffers (d_ff >= 2 d) and formed again, biases
 @pytest.mark.parametrize("d,F,T,dtype,kind", [
     (1024, 4096, 64, "bf16", "swiglu"), (512, 3333, 100, "bf16", "swiglu"), (512, 3333, 100, "bf16", "relu"), (512, 900, 300, "bf16", "geglu"),
     (1024, 1984, 140, "bf16", "swiglu"), (256, 2085, 40, "bf16", "relu"), (260, 3001, 90, "f32", "swiglu"), (512, 1111, 140, "f32", "relu"),
