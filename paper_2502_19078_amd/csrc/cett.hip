@@ -27,6 +27,11 @@ struct CettState {
     unsigned int base;            // the cut sums in buffer `sel` hold the neurons below this bit pattern
     int sel;
     int listed;                   // the neurons inside the first bracket are listed (no token had too many)
+    // the search over a table (see k_cett_ladder)
+    int kept;                     // the cut sums in buffer `sel` are those at `base`
+    unsigned int edge, cut;       // the table's window: the magnitudes from known_lo up to here; up to where every token's fit
+    int at, xt;                   // places of the expected answer (-1: none) and of `edge`
+    int arrive;                   // workgroups of k_cett_curve that are done
 };
 static_assert(2 * sizeof(CettState) <= 256, "two of them in their place in the workspace");
 
@@ -80,7 +85,8 @@ __global__ void __launch_bounds__(256)
 k_cett_mask(const CettState *__restrict__ st, const float *__restrict__ pool, const char *__restrict__ h,
             char *__restrict__ hcut, int T, int F, int Fp, int may_skip)
 {
-    if (may_skip && st->skip) return;
+    if (may_skip == 1 && st->skip) return;
+    if (may_skip == 2 && st->kept) return;
     const float eps = __uint_as_float(st->mid);
     const size_t groups = (size_t)Fp / 8;
     const size_t total = (size_t)T * groups;
@@ -176,15 +182,27 @@ __global__ void k_cett_finish(const CettState *st, float *tau_out, float *mean_o
 //       on false position with the Illinois rule.  Three or four probes leave about forty magnitudes per token (without the
 //       curve six or seven);
 //   (2) the last feasible probe leaves the cut sums at the bracket's lower end in fp32;
-//   (3) the plain bisection then runs; a probe outside the bracket is answered by it, one inside adds the rows of
-//       the neurons between the sums' threshold and the probe to the sums, token by token, for the next few probes
-//       at a time.
-// 512 tokens of 4096 x 11008: 2370 us with 31 dense probes, 510 - 640 us so.  The bracket answers for thresholds outside it as a
-// monotone mean would; inside, every probe is measured.
+//   (3) up to 1024 tokens the first or second probe is near enough: a table of every token's CETT at the few dozen magnitudes
+//       above it answers the rest of the bisection (k_cett_ladder, k_cett_bisect).  Where the answer lies past the table, two
+//       more probes close the bracket, and a second table follows;
+//   (4) what that leaves open (thousands of equal magnitudes), and searches over more tokens: the plain bisection; a probe
+//       outside the bracket is answered by it, one inside adds the rows of the neurons between the sums' threshold and
+//       the probe to the sums, token by token, for the next few probes at a time.
+// us (plain bisection / without the table / so): 512 tokens of 4096 x 11008 2370 / 470 - 580 / 330 - 390, 80 of 3584 x 9728 - / 296 - 340 / 214 - 229,
+// 64 of 1024 x 4096 - / 244 - 287 / 176 - 186, 700 of 4096 x 11008 - / 670 - 835 / 498 - 606, fp32 104 of 4096 x 12992 - / 1218 - 1409 / 828 - 851.
+// What bounds it now: the three or four projections (63 us each at the first of these sizes), then launches, 2.4 us each also where nothing is
+// left to do.  The bracket answers for thresholds outside it as a monotone mean would; inside, every probe is measured.
 constexpr int SAMPLES = 4096;      // sorted sample of the pool; neighbours are 2.7 magnitudes per token apart at 11008 neurons
 constexpr int CLOSE = 16;          // sample places left between the bracket's ends when the dense probes end
 constexpr int DENSE_PROBES = 5;    // launched; those past the end return at once
 constexpr int CURVE_TOKENS = 32, CURVE_BINS = 256, CURVE_STEP = SAMPLES / CURVE_BINS;
+// The search over a table takes the curve of up to 128 tokens, which costs no more, and two dense probes before each of two tables.
+constexpr int CURVE_TABLE = 128, TABLE_PROBES = 2;
+// Places of the sample that the table goes past the expected answer, and that the first probe stays below it, for a table of at most
+// `window` places: the first estimate was within 12 places (22 for layers of a few thousand neurons), one through a measured
+// point within 4 (11 where d is 64).
+__host__ __device__ __forceinline__ int table_past(int window) { return window < 24 ? 4 : window < 128 ? window / 4 : 32; }
+__host__ __device__ __forceinline__ int table_below(int window) { return window < 24 ? 6 : window < 120 ? window / 3 : 40; }
 // Tokens up to which every workgroup of a probe forms the previous one's mean itself: that saves a launch a probe, and costs
 // T^2 reads.  In place / by a launch of its own, us per search: 533 / 564 and 1142 / 1171 (512 tokens, 1024 x 4096 and
 // 4096 x 11008), 631 / 633 and 1805 / 1785 (1024), 949 / 870 and 3119 / 2910 (2048), 3848 / 2271 (8192), 92600 / 8200 (65536).
@@ -192,13 +210,25 @@ constexpr int MEAN_IN_PLACE = 1024;
 
 // The sorted bit patterns of SAMPLES pool entries.  The entries lie at the fractions i * phi mod 1 of the pool (phi the golden
 // ratio, 2^64 phi^-1 below): evenly spread over the tokens, without a stride that could meet the same neurons of every token.
-// Every workgroup reads them all and places 64 of them by counting the smaller ones, four threads an entry (34 us as a sorting network
-// in one workgroup, 17 so).
+// Every workgroup reads them all and places 16 of them by counting the smaller ones, 16 threads an entry (34 us as a sorting network
+// in one workgroup, 17 with 64 entries a workgroup and four threads each, 10 so).  The workgroups behind those form the denominators of
+// the gated families, den[t] = || MLP(x_t) ||_2 from the sums of squares per column tile, ascending.
+constexpr int SAMPLE_WGS = SAMPLES / 16;
 __global__ void __launch_bounds__(256)
-k_cett_sample(CettState *st, const float *__restrict__ pool, unsigned long long n, unsigned int *__restrict__ sample, float bound)
+k_cett_sample(CettState *st, const float *__restrict__ pool, unsigned long long n, unsigned int *__restrict__ sample, float bound,
+              const float *__restrict__ rowsq, int n_tn, int T, float *__restrict__ den, unsigned long long *__restrict__ curve)
 {
     __shared__ __align__(16) unsigned int s[SAMPLES];
     const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= SAMPLE_WGS) {
+        const int t = ((int)blockIdx.x - SAMPLE_WGS) * 256 + tid;
+        if (t >= T) return;
+        float v = 0.0f;
+#pragma unroll 8
+        for (int i = 0; i < n_tn; ++i) v += rowsq[(size_t)i * T + t];
+        den[t] = sqrtf(v);
+        return;
+    }
 #pragma unroll
     for (int k = 0; k < SAMPLES / 256; ++k) {
         const int i = k * 256 + tid;
@@ -207,51 +237,72 @@ k_cett_sample(CettState *st, const float *__restrict__ pool, unsigned long long 
         s[i] = u < 0x7f800000u ? u : 0x7f800000u;
     }
     __syncthreads();
-    const int i = blockIdx.x * 64 + (tid >> 2), quarter = tid & 3;
+    const int i = blockIdx.x * 16 + (tid >> 4), share = tid & 15;
     const unsigned int mine = s[i];
     int below = 0;
-    // groups of four entries, the quarters in turn: those in front of this workgroup's, which also win ties, its own, those behind
-    const int own = blockIdx.x * 16;
+    // groups of four entries, the shares in turn: those in front of this workgroup's, which also win ties, its own, those behind
+    const int own = blockIdx.x * 4;
     auto group = [&](int j) { return reinterpret_cast<const u32x4 *>(s)[j]; };
 #pragma unroll 4
-    for (int j = quarter; j < own; j += 4) {
+    for (int j = share; j < own; j += 16) {
         const u32x4 v = group(j);
 #pragma unroll
         for (int e = 0; e < 4; ++e) below += v[e] <= mine ? 1 : 0;
     }
-    for (int j = own + quarter; j < own + 16; j += 4) {
+    if (share < 4) {
+        const int j = own + share;
         const u32x4 v = group(j);
 #pragma unroll
         for (int e = 0; e < 4; ++e) below += v[e] < mine || (v[e] == mine && 4 * j + e < i) ? 1 : 0;
     }
 #pragma unroll 4
-    for (int j = own + 16 + quarter; j < SAMPLES / 4; j += 4) {
+    for (int j = own + 4 + share; j < SAMPLES / 4; j += 16) {
         const u32x4 v = group(j);
 #pragma unroll
         for (int e = 0; e < 4; ++e) below += v[e] < mine ? 1 : 0;
     }
-    below += __shfl_xor(below, 1);
-    below += __shfl_xor(below, 2);
-    if (quarter == 0) sample[below] = mine;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) below += __shfl_xor(below, o);
+    if (share == 0) sample[below] = mine;
+    if (blockIdx.x == 0) curve[tid] = 0ull;                  // (CURVE_BINS threads)
     if (blockIdx.x == 0 && tid == 0) {
         st->skip = 0; st->done = 0; st->sel = 1;
         st->known_lo = 0u; st->known_hi = 0x7f800000u; st->known_mean = 0.0f;
         st->xlo = -1; st->xhi = SAMPLES; st->side = 0; st->same = 0;
         st->glo = -bound; st->ghi = 1.0f - bound;
+        st->kept = 1; st->base = 0u; st->edge = st->cut = 0u; st->at = -1; st->arrive = 0;
+        st->lo = 0u; st->hi = 0x7f800000u; st->mean_lo = 0.0f;
     }
+}
+
+// The curve at a place of the sample, and the place where it reaches a value (linear between its entries; m[b] at place 16 (b + 1)).
+__device__ __forceinline__ float curve_at(const float *m, int x)
+{
+    const int b = x / CURVE_STEP;
+    const float lo = b > 0 ? m[b - 1] : 0.0f, hi = b < CURVE_BINS ? m[b] : 1.0f;
+    return lo + (hi - lo) * (float)(x - b * CURVE_STEP) / (float)CURVE_STEP;
+}
+__device__ __forceinline__ int curve_place(const float *m, float v)
+{
+    int b = 0;                                               // entries below v
+    for (int w = CURVE_BINS / 2; w > 0; w >>= 1) b += m[b + w - 1] < v ? w : 0;
+    const float lo = b > 0 ? m[b - 1] : 0.0f, hi = m[b];
+    return b * CURVE_STEP + (hi > lo && v > lo ? (int)fminf((v - lo) / (hi - lo) * CURVE_STEP, (float)CURVE_STEP) : 0);
 }
 
 // One token of the curve: entry b = sqrt(sum of h^2 where |a| is below the sample's place 16 b, over the sum of all).  The sums are
 // integers (a bin's share of 2^40), so that the order of the additions does not matter.
 template <int ES>
 __global__ void __launch_bounds__(1024)
-k_cett_curve(const float *__restrict__ pool, const char *__restrict__ h, const unsigned int *__restrict__ sample, int T, int F, int Fp,
-             float *__restrict__ curve)
+k_cett_curve(CettState *st, const float *__restrict__ pool, const char *__restrict__ h, const unsigned int *__restrict__ sample, int T, int F,
+             int Fp, unsigned long long *__restrict__ total, float *__restrict__ mean, float bound, int below)
 {
     constexpr int AHEAD = 12;                                // values of a thread in hand at a time (all of them up to 12288 neurons)
     __shared__ unsigned int s_edge[CURVE_BINS];
     __shared__ unsigned long long s_sum[CURVE_BINS];
     __shared__ float s_part[16];
+    __shared__ float s_m[CURVE_BINS];
+    __shared__ int s_last;
     const int tid = threadIdx.x, lane = tid & 63;
     const size_t t = (size_t)blockIdx.x * T / gridDim.x;
     float sq[AHEAD];
@@ -303,52 +354,43 @@ k_cett_curve(const float *__restrict__ pool, const char *__restrict__ h, const u
         }
     }
     __syncthreads();
-    if (tid >= CURVE_BINS) return;                           // (four whole waves stay; the others are not waited for any more)
-    unsigned long long run = 0ull;                           // below edge tid + 1: the bins up to this one
-    for (int b = 0; b < CURVE_BINS; b += 64) {
-        unsigned long long c = s_sum[b + lane];
+    if (tid < CURVE_BINS) {                                  // (four whole waves)
+        unsigned long long run = 0ull;                       // below edge tid + 1: the bins up to this one
+        for (int b = 0; b < CURVE_BINS; b += 64) {
+            unsigned long long c = s_sum[b + lane];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long x = __shfl_up(c, o);
-            if (lane >= o) c += x;
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned long long x = __shfl_up(c, o);
+                if (lane >= o) c += x;
+            }
+            if (b == (tid & ~63)) run += c;
+            else if (b < tid) run += __shfl(c, 63);
         }
-        if (b == (tid & ~63)) run += c;
-        else if (b < tid) run += __shfl(c, 63);
+        // (again an integer, a token's share of 2^48: the workgroups add up in any order.  The old value is waited for: the sum is
+        // where all of them meet then, with no cache written back: 16.8 us, 42 with an agent-scope fence)
+        const unsigned long long old = atomicAdd(&total[tid], (unsigned long long)(sqrtf((float)run * (1.0f / 1099511627776.0f)) * 281474976710656.0f));
+        if (old == ~0ull) s_last = 0;                        // (never)
     }
-    curve[(size_t)blockIdx.x * CURVE_BINS + tid] = sqrtf((float)run * (1.0f / 1099511627776.0f));
-}
-
-// The curve at a place of the sample, and the place where it reaches a value (linear between its entries; m[b] at place 16 (b + 1)).
-__device__ __forceinline__ float curve_at(const float *m, int x)
-{
-    const int b = x / CURVE_STEP;
-    const float lo = b > 0 ? m[b - 1] : 0.0f, hi = b < CURVE_BINS ? m[b] : 1.0f;
-    return lo + (hi - lo) * (float)(x - b * CURVE_STEP) / (float)CURVE_STEP;
-}
-__device__ __forceinline__ int curve_place(const float *m, float v)
-{
-    int b = 0;                                               // entries below v
-    for (int w = CURVE_BINS / 2; w > 0; w >>= 1) b += m[b + w - 1] < v ? w : 0;
-    const float lo = b > 0 ? m[b - 1] : 0.0f, hi = m[b];
-    return b * CURVE_STEP + (hi > lo && v > lo ? (int)fminf((v - lo) / (hi - lo) * CURVE_STEP, (float)CURVE_STEP) : 0);
-}
-
-// The mean of the tokens' curves, and the first probe.
-__global__ void __launch_bounds__(CURVE_BINS)
-k_cett_first(CettState *st, const float *__restrict__ curve, int tokens, float *__restrict__ mean, const unsigned int *__restrict__ sample, float bound)
-{
-    __shared__ float s_m[CURVE_BINS];
-    const int tid = threadIdx.x;
-    float m = 0.0f;
-#pragma unroll 8
-    for (int i = 0; i < tokens; ++i) m += curve[(size_t)i * CURVE_BINS + tid];
-    m /= (float)tokens;
-    mean[tid] = m;
-    s_m[tid] = m;
+    // the last workgroup to arrive: the mean of the tokens' curves, and the first probe, so many places below their answer
+    __syncthreads();
+    if (tid == 0) s_last = __hip_atomic_fetch_add(&st->arrive, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!s_last) return;
+    if (tid < CURVE_BINS) {
+        const unsigned long long all = __hip_atomic_load(&total[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float m = (float)all * (1.0f / 281474976710656.0f) / (float)gridDim.x;
+        mean[tid] = m;
+        s_m[tid] = m;
+    }
     __syncthreads();
     if (tid != 0) return;
-    int x = curve_place(s_m, bound);
+    int x = curve_place(s_m, bound) - below;
     x = x < 1 ? 1 : x > SAMPLES - 2 ? SAMPLES - 2 : x;
+    if (below > 0 && sample[x] == 0u) {                      // (nothing lies below 0: the first place above it)
+        int at = x;
+        for (int w = SAMPLES / 2; w > 0; w >>= 1) at += at + w < SAMPLES && sample[at + w] == 0u ? w : 0;
+        x = at < SAMPLES - 2 ? at + 1 : SAMPLES - 2;
+    }
     st->x = x;
     st->mid = sample[x];
 }
@@ -387,10 +429,20 @@ __device__ __forceinline__ void bisect_on(CettState &s)
     s.mean_lo = s.known_mean;                                // (lo has come to rest on known_lo)
 }
 
-// After a dense probe: the bracket, and the next probe between its ends.
+// The next dense probe at place x of the sample, if its threshold lies inside the bracket.
+__device__ __forceinline__ bool probe_at(CettState &s, const unsigned int *sample, int x)
+{
+    if (x <= s.xlo || x >= s.xhi || sample[x] <= s.known_lo || sample[x] >= s.known_hi) return false;
+    s.x = x;
+    s.mid = sample[x];
+    return true;
+}
+
+// After a dense probe: the bracket, and the next probe between its ends.  window: places that a table holds (0: there is none);
+// stage: 0 after the first probe, 1 after the second, which the first table follows, 2 after others, 3 after the last one.
 __global__ void __launch_bounds__(1024)
 k_cett_next(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, const float *__restrict__ den, float bound,
-            const unsigned int *__restrict__ sample, const float *__restrict__ curve)
+            const unsigned int *__restrict__ sample, const float *__restrict__ curve, int window, int two, int stage)
 {
     __shared__ float s_sum[1024], s_m[CURVE_BINS];
     if (st->skip) return;
@@ -399,7 +451,7 @@ k_cett_next(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, con
     if (threadIdx.x != 0) return;
     CettState s = *st;
     const bool feasible = mean <= bound;                     // NaN: over the bound
-    if (feasible) { if (s.mid > s.known_lo) { s.known_lo = s.mid; s.known_mean = mean; s.sel ^= 1; } }     // (its sums are kept)
+    if (feasible) { if (s.mid > s.known_lo) { s.known_lo = s.base = s.mid; s.known_mean = mean; s.sel ^= 1; } }     // (its sums are kept)
     else if (s.mid < s.known_hi) s.known_hi = s.mid;
     auto take = [&](bool low, float g) {                     // the place x becomes an end of the bracket
         if (low) { s.xlo = s.x; s.glo = g; if (s.side < 0) s.ghi *= 0.5f; s.side = -1; }
@@ -408,6 +460,46 @@ k_cett_next(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, con
     float g = mean - bound;
     if (!feasible && !(g > 0.0f)) g = 1.0f;                  // (NaN)
     take(feasible, g);
+    // The window is final: it begins where the cut sums are, at the last feasible probe or at 0.  With one buffer of sums they are formed
+    // again where a probe that failed came after that.
+    auto finish = [&](unsigned int edge, int place) {
+        s.skip = 1;
+        s.edge = s.cut = edge;
+        s.xt = place;
+        if (!two) {
+            s.sel = 0;
+            if (!s.kept) s.base = s.mid = s.known_lo;
+        }
+        *st = s;
+    };
+    if (window > 0) {
+        s.kept = two || feasible || s.base == 0u;
+        // the answer by the curve through the measured point
+        int at = -1;
+        if (mean > 0.0f && mean < 1e30f) {
+            at = curve_place(s_m, curve_at(s_m, s.x) * (bound / mean));
+            at = at > s.xlo ? at < s.xhi ? at : s.xhi : s.xlo;
+        } else if (feasible) {
+            at = (s.x + s.xhi) / 2;                          // (nothing cut yet)
+        }
+        s.at = at;
+        const int past = table_past(window);
+        int up = at + past < s.xhi ? at + past : s.xhi;
+        while (up < s.xhi && sample[up] <= s.known_lo) ++up;
+        if (up < s.xhi && sample[up] >= s.known_hi) up = s.xhi;
+        // the first table's upper end need not be measured, the second one's is
+        if (stage < 2 && at >= 0 && up - s.xlo <= window) { finish(up < s.xhi ? sample[up] : s.known_hi, up); return; }
+        if (stage == 3 || (s.xhi < SAMPLES && s.xhi - s.xlo <= window)) { finish(s.known_hi, s.xhi); return; }
+        if (at >= 0) {
+            const int further = past << (2 * s.same);
+            int x;
+            if (s.xhi >= SAMPLES) x = stage == 0 ? at - past : at + further;        // nothing measured above it
+            else if (s.xlo < 0) x = at - further;                                   // nothing below
+            else x = at - s.xlo >= s.xhi - at ? at - past : at + past;              // the wider side
+            ++s.same;
+            if (probe_at(s, sample, x)) { *st = s; return; }
+        }
+    }
     const bool one_side = s.xlo < 0 || s.xhi >= SAMPLES;     // only one end of the bracket is a measured one
     if (one_side && s.same < 4 && mean > 0.0f && mean < 1e30f) {
         // the curve through the measured point, a little past its answer (further each time the answer stays on one side)
@@ -435,7 +527,8 @@ k_cett_next(CettState *st, const float *__restrict__ rowsq, int n_tn, int T, con
         else if (s.mid >= s.known_hi) take(false, s.ghi);
         else break;
     }
-    *st = s;
+    if (window > 0 && s.skip) finish(s.known_hi, s.xhi);
+    else *st = s;
 }
 
 // The threshold of the cut sums (the bracket's lower end), and the start of the bisection.  stage 1: the sums were formed by a pass of
@@ -497,7 +590,7 @@ __device__ __forceinline__ void list_ascending(int n, int *s_cnt, Want want, Put
     }
 }
 
-// The neurons of every token with known_lo <= |a| < known_hi, the only ones that later probes add: cap of them per token
+// The neurons of every token with base <= |a| < known_hi, the only ones that later probes add: cap of them per token
 // fit; a token with more leaves `listed` at zero, and the probes look through the whole pool.
 __global__ void __launch_bounds__(1024)
 k_cett_list(CettState *st, const float *__restrict__ pool, int F, int *__restrict__ list, int cap, int *__restrict__ count)
@@ -506,7 +599,8 @@ k_cett_list(CettState *st, const float *__restrict__ pool, int F, int *__restric
     __shared__ int s_part[2][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const size_t t = blockIdx.x;
-    const float lo = __uint_as_float(st->known_lo), hi = __uint_as_float(st->known_hi);
+    if (st->done) return;
+    const float lo = __uint_as_float(st->base), hi = __uint_as_float(st->known_hi);
     int *mine = list + t * cap;
     float a[PER], next[PER];
     auto ask = [&](float (&v)[PER], int seg) {
@@ -552,11 +646,6 @@ k_cett_list(CettState *st, const float *__restrict__ pool, int F, int *__restric
     }
 }
 
-// The probes inside the bracket.  A launch measures the thresholds that the next LEVELS steps of the bisection can ask for, a binary
-// tree of NODES = 2^LEVELS - 1 of them, and the walk down the tree afterwards is the bisection's own: seven thresholds cost little
-// more than one (the rows up to the highest are read once), and the launches follow each other 7 us apart whatever they do
-// (one threshold a launch: 224 us of a search of 512 tokens of 4096 x 11008, seven: 170, most of it launches that find nothing left).
-
 // A measured threshold's answer, and the bisection up to the next one.
 __device__ __forceinline__ void answer(CettState &s, bool feasible, float mean)
 {
@@ -568,6 +657,316 @@ __device__ __forceinline__ void answer(CettState &s, bool feasible, float mean)
     }
     bisect_on(s);
 }
+
+// The search over a table, up to 512 tokens.  The rows of the neurons inside the window [known_lo, edge) of a token, added in the
+// order of their magnitudes to the cut sums at known_lo, give the token's CETT at every threshold of the window: a step function of as many
+// steps.  One pass forms them all, and the rest of the bisection reads them, in one workgroup: two launches where the probes
+// below need a launch per three steps of the bisection.  The window's upper end need not be measured, so that one or two
+// dense probes are enough.  The entries lie in the registers of one workgroup, 44 a thread (two words each of 128), 88 a token at 512 tokens.
+// Searches whose first two probes fail or fall short by more than the window take the probes' way on; so does a token with more than
+// 512 neurons to add.
+constexpr int TABLE_TOKENS = 1024, TABLE_REGS = 44;       // entries a thread
+constexpr int LADDER_MAX = 512;                          // neurons of a token that the pass can sort; beyond, the window ends at known_lo
+
+// Threads a token in k_cett_bisect, entries of a token, places of the sample that give two thirds of them.
+__host__ __device__ __forceinline__ int table_threads(int T) { return T > 512 ? 1 : T > 256 ? 2 : T > 128 ? 4 : 8; }
+__host__ __device__ __forceinline__ int table_cap(int T) { return T > 128 ? table_threads(T) * TABLE_REGS : 256; }
+int table_window(int T, int F) { return (int)((long long)table_cap(T) * 2 / 3 * SAMPLES / F); }
+
+// A workgroup of NT threads per token.  mag [cap][T], cett [cap + 1][T] (at known_lo, and behind each entry), count [T].
+template <int ES, int NV, int NT>
+__global__ void __launch_bounds__(NT)
+k_cett_ladder(CettState *st, const float *__restrict__ pool, const char *__restrict__ h, const char *__restrict__ wd,
+              const float *__restrict__ buf0, const float *__restrict__ buf1, const float *__restrict__ den, int T, int F, int Fp, int d, int cap,
+              float *__restrict__ mag, float *__restrict__ cett, int *__restrict__ count)
+{
+    constexpr int VEC = 16 / ES, AHEAD = 8, SCAN = 12, WAVES = NT / 64;
+    __shared__ unsigned int s_a[LADDER_MAX];
+    __shared__ int s_i[LADDER_MAX], s_j[LADDER_MAX + 2 * AHEAD];
+    __shared__ float s_h[LADDER_MAX + 2 * AHEAD], s_sq[WAVES][257];
+    __shared__ int s_n, s_pre;
+    __shared__ unsigned int s_edge;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const size_t t = blockIdx.x;
+    if (st->done || !st->skip) return;
+    const unsigned int base = st->base, lo = st->known_lo, edge = st->edge;
+    const float *src = (st->sel ? buf1 : buf0) + t * d;
+    const int col0 = tid * VEC;                              // group v of this thread: columns col0 + v NT VEC ..
+    if (tid == 0) { s_n = 0; s_pre = 0; s_edge = edge; }
+    __syncthreads();
+    // the window's neurons and those between the sums' threshold and the window, in any order
+    unsigned int next[SCAN];
+    auto ask = [&](int j0) {
+#pragma unroll
+        for (int k = 0; k < SCAN; ++k) {
+            const int j = j0 + k * NT + tid;
+            next[k] = __float_as_uint(pool[t * F + (j < F ? j : F - 1)]);
+        }
+    };
+    ask(0);
+    float acc[NV][VEC];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int col = col0 + v * NT * VEC;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[v][e] = col < d && base != 0u ? src[col + e] : 0.0f;    // (nothing lies below 0)
+    }
+    for (int j0 = 0; j0 < F; j0 += SCAN * NT) {
+        unsigned int a[SCAN];
+#pragma unroll
+        for (int k = 0; k < SCAN; ++k) a[k] = next[k];
+        if (j0 + SCAN * NT < F) ask(j0 + SCAN * NT);
+#pragma unroll
+        for (int k = 0; k < SCAN; ++k) {
+            const int j = j0 + k * NT + tid;
+            const bool in = a[k] >= base && a[k] < edge && j < F;       // (magnitudes are not negative; a NaN lies above +inf)
+            const unsigned long long who = __ballot(in);
+            if (who) {
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&s_n, __popcll(who));
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(who & ((1ull << lane) - 1ull));
+                if (in && at < LADDER_MAX) { s_a[at] = a[k]; s_i[at] = j; }
+            }
+        }
+    }
+    __syncthreads();
+    const int found = s_n;
+    for (int i = tid; i < min(found, LADDER_MAX); i += NT)
+        if (s_a[i] < lo) atomicAdd(&s_pre, 1);
+    __syncthreads();
+    const int pre = s_pre;
+    if (found > LADDER_MAX) {                                // (uniform) too many to sort: nothing is known about the window
+        if (tid == 0) { atomicMin(&st->cut, lo); count[t] = 0; }
+        return;
+    }
+    // their places by magnitude, equal ones by neuron; those from `cap` on, and all equal to the first of them, are left out
+    int rank[LADDER_MAX / NT];
+#pragma unroll
+    for (int u = 0; u < LADDER_MAX / NT; ++u) {
+        const int i = tid + NT * u;
+        rank[u] = LADDER_MAX;
+        if (i < found) {
+            const unsigned int a = s_a[i];
+            const int j = s_i[i];
+            int r = 0;
+#pragma unroll 8
+            for (int k = 0; k < found; ++k) r += s_a[k] < a || (s_a[k] == a && s_i[k] < j) ? 1 : 0;
+            rank[u] = r;
+            if (r == cap + pre) s_edge = a;
+        }
+    }
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    const unsigned int end = s_edge;
+#pragma unroll
+    for (int u = 0; u < LADDER_MAX / NT; ++u) {
+        const int i = tid + NT * u;
+        const bool in = rank[u] < cap + pre && s_a[i] < end;
+        const unsigned long long who = __ballot(in);
+        if (who && lane == 0) atomicAdd(&s_n, __popcll(who));
+        if (in) {
+            const int j = s_i[i];
+            s_j[rank[u]] = j;
+            s_h[rank[u]] = ES == 4 ? reinterpret_cast<const float *>(h)[t * Fp + j]
+                                   : __uint_as_float((unsigned int)reinterpret_cast<const unsigned short *>(h)[t * Fp + j] << 16);
+            if (rank[u] >= pre) mag[(size_t)(rank[u] - pre) * T + t] = __uint_as_float(s_a[i]);
+        }
+    }
+    __syncthreads();
+    const int n = s_n;
+    if (tid < 2 * AHEAD) { s_j[n + tid] = n > 0 ? s_j[n - 1] : 0; s_h[n + tid] = 0.0f; }       // (what is requested past the end)
+    if (tid == 0) {
+        if (end != edge) atomicMin(&st->cut, end);
+        count[t] = n - pre;
+    }
+    auto norm2 = [&]() {
+        float q = 0.0f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (col0 + v * NT * VEC < d)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) q = fmaf(acc[v][e], acc[v][e], q);
+        return q;
+    };
+    const float before = wave_sum(norm2());
+    if (lane == 0 && pre == 0) s_sq[wave][0] = before;
+    __syncthreads();
+    u32x4 w[2][AHEAD][NV];
+    auto rows = [&](u32x4 (&to)[AHEAD][NV], int e0) {
+#pragma unroll
+        for (int q = 0; q < AHEAD; ++q) {
+            const char *row = wd + (size_t)s_j[e0 + q] * d * ES;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int col = col0 + v * NT * VEC;
+                to[q][v] = *reinterpret_cast<const u32x4 *>(row + (size_t)(col < d ? col : 0) * ES);
+            }
+        }
+    };
+    auto add = [&](const u32x4 (&from)[AHEAD][NV], int e0) {
+        float sq[AHEAD];
+#pragma unroll
+        for (int q = 0; q < AHEAD; ++q) {
+            const float hv = s_h[e0 + q];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                float f[VEC];
+                unpack_row16(from[q][v], f);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[v][e] = fmaf(hv, f[e], acc[v][e]);
+            }
+            sq[q] = norm2();
+        }
+        // eight sums over 64 lanes: halves exchanged until a lane holds one of them, then eight lanes each
+        const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8;
+        float s4[4], s2[2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float give = b5 ? sq[i] : sq[i + 4], keep = b5 ? sq[i + 4] : sq[i];
+            s4[i] = keep + __shfl_xor(give, 32);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const float give = b4 ? s4[i] : s4[i + 2], keep = b4 ? s4[i + 2] : s4[i];
+            s2[i] = keep + __shfl_xor(give, 16);
+        }
+        float s1 = (b3 ? s2[1] : s2[0]) + __shfl_xor(b3 ? s2[0] : s2[1], 8);
+        s1 += __shfl_xor(s1, 4);
+        s1 += __shfl_xor(s1, 2);
+        s1 += __shfl_xor(s1, 1);
+        const int e = e0 + (b5 ? 4 : 0) + (b4 ? 2 : 0) + (b3 ? 1 : 0);
+        if ((lane & 7) == 0 && e < n && e + 1 >= pre) s_sq[wave][e + 1 - pre] = s1;
+    };
+    if (n > 0) {
+        rows(w[0], 0);
+        for (int e0 = 0; e0 < n; e0 += 2 * AHEAD) {
+            if (e0 + AHEAD < n) rows(w[1], e0 + AHEAD);
+            add(w[0], e0);
+            if (e0 + 2 * AHEAD < n) rows(w[0], e0 + 2 * AHEAD);
+            if (e0 + AHEAD < n) add(w[1], e0 + AHEAD);
+        }
+    }
+    __syncthreads();
+    const float dn = den[t];
+    for (int i = tid; i <= n - pre; i += NT) {
+        float q = 0.0f;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) q += s_sq[v][i];
+        cett[(size_t)i * T + t] = dn > 0.0f ? sqrtf(q) / dn : 0.0f;
+    }
+}
+
+// The bisection over the table, one workgroup, TPT threads a token (the entries in turn).  A threshold past the window, where that
+// ends below what has been measured, is left to the probes below, which go on from the cut sums at the window's lower end.
+template <int TPT>
+__global__ void __launch_bounds__(1024)
+k_cett_bisect(CettState *st, const float *__restrict__ mag, const float *__restrict__ cett, const int *__restrict__ count, int T, float bound,
+              const unsigned int *__restrict__ sample, const float *__restrict__ curve, int window, int second)
+{
+    constexpr int N = TPT == 8 ? 256 / TPT : TABLE_REGS;
+    __shared__ float s_sum[2][16];
+    __shared__ int s_most;
+    const int tid = threadIdx.x, lane = tid & 63, t = tid / TPT, u = tid % TPT;
+    const bool here = t < T;
+    const int n = here ? count[t] : 0;
+    int word[sizeof(CettState) / 4];                         // (the state in scalar registers)
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(CettState) / 4); ++i) word[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int *>(st)[i]);
+    CettState s;
+    __builtin_memcpy(&s, word, sizeof(s));
+    if (s.done || !s.skip) return;
+    if (tid == 0) s_most = 0;
+    __syncthreads();
+    const int share = (n + TPT - 1) / TPT, own = min(max(n - u * share, 0), share);        // entries u share ..
+    float a[N], c[N];
+    // (loads without branches: past the end, the token's first entry is read and not taken)
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const size_t at = (size_t)(k < own ? u * share + k : 0) * T + (here ? t : 0);
+        a[k] = mag[at];
+        c[k] = cett[at + (k < own ? T : 0)];
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) a[k] = k < own ? a[k] : __uint_as_float(0x7f800000u);
+    const float first = cett[here ? t : 0];
+    if (lane == 0 || own > 0) atomicMax(&s_most, own);
+    __syncthreads();
+    const int most = s_most;                                 // (at most N)
+    int turn = 0;
+    auto mean_at = [&](unsigned int bits) {                  // (all threads)
+        const float eps = __uint_as_float(bits);
+        float v = first;                                     // the last entry below eps
+#pragma unroll
+        for (int k0 = 0; k0 < N; k0 += 4) {
+            if (k0 < most) {
+#pragma unroll
+                for (int k = k0; k < k0 + 4; ++k) {
+                    v = a[k] < eps ? c[k] : v;
+                }
+            }
+        }
+        // of a token's shares, the last one that begins below eps
+        const bool begins = u == 0 || a[0] < eps;
+        const unsigned long long who = __ballot(begins);
+        const bool mine = begins && (u == TPT - 1 || !((who >> ((lane + 1) & 63)) & 1ull));
+        const float sum = wave_sum(mine && here ? v : 0.0f);
+        if (lane == 0) s_sum[turn][tid >> 6] = sum;
+        __syncthreads();
+        float m = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) m += s_sum[turn][w];
+        turn ^= 1;
+        return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m / (float)T)));
+    };
+    s.kept = 1;
+    s.listed = 1;
+    s.lo = 0u;
+    s.hi = 0x7f800000u;
+    float beyond = -1.0f;                                    // the mean at the window's end, where that satisfies the bound
+    const unsigned int edge = s.cut;
+    bool table = edge > s.known_lo;
+    if (table && edge < s.known_hi) {                        // the window's end first
+        const float mean = mean_at(edge);
+        if (mean <= bound) {
+            s.known_lo = edge;
+            s.known_mean = beyond = mean;
+            table = false;
+        } else {
+            s.known_hi = edge;                               // NaN: over the bound
+        }
+    }
+    bisect_on(s);
+    while (table && !s.done) {
+        const float mean = mean_at(s.mid);
+        answer(s, mean <= bound, mean);
+    }
+    if (tid != 0) return;
+    if (!s.done && !second) {
+        // past the window, or too many neurons in it: the dense probes go on, above what is known
+        const int past = table_past(window);
+        if (beyond >= 0.0f) {
+            s.xlo = s.xt;
+            s.glo = beyond - bound;
+            s.side = -1;
+            if (beyond > 0.0f) {
+                const int at = curve_place(curve, curve_at(curve, s.xt) * (bound / beyond));
+                s.at = at > s.xlo ? at < s.xhi ? at : s.xhi : s.xlo;
+            }
+        }
+        s.same = 1;
+        s.skip = 0;
+        if (!probe_at(s, sample, s.at + past) && !probe_at(s, sample, (s.xlo + s.xhi) / 2)) {
+            s.skip = 1;
+            s.edge = s.cut = s.known_hi;
+        }
+    }
+    *st = s;
+}
+
+// The probes inside the bracket.  A launch measures the thresholds that the next LEVELS steps of the bisection can ask for, a binary
+// tree of NODES = 2^LEVELS - 1 of them, and the walk down the tree afterwards is the bisection's own: seven thresholds cost little
+// more than one (the rows up to the highest are read once), and the launches follow each other 7 us apart whatever they do
+// (one threshold a launch: 224 us of a search of 512 tokens of 4096 x 11008, seven: 170, most of it launches that find nothing left).
 
 // Down the tree with the means of its thresholds in ascending order.
 template <int LEVELS>
@@ -870,7 +1269,7 @@ clada_status check_common(clada_ctx *ctx, const clada_layer *layer, const void *
 
 // Gate/up GEMM, dense down projection for the denominators, bracket / probe set-up.
 clada_status begin(clada_ctx *ctx, const clada_layer *layer, const void *x, int T, const CettWs &w, int search,
-                   float eps, hipStream_t stream)
+                   float eps, bool large, hipStream_t stream)
 {
     const int n_tn = clada_prefix_col_tiles(layer->d);
     CLADA_CHECK_HIP(ctx, clada_prefix_gateup(layer, x, T, w.part, w.pool, w.h, ctx->opt_prefix_tile, stream, ctx->num_cu));
@@ -889,6 +1288,7 @@ clada_status begin(clada_ctx *ctx, const clada_layer *layer, const void *x, int 
     } else {
         CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.h, T, nullptr, w.rowsq_den, w.room(w.ytmp), ctx->opt_prefix_tile, stream, ctx->num_cu));
     }
+    if (large) return CLADA_OK;                             // (k_cett_sample does what is left)
     hipLaunchKernelGGL(k_cett_begin, dim3((T + 255) / 256), dim3(256), 0, stream, w.state, rowsq_den, n_tn, T,
                        w.den, search, eps);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
@@ -924,14 +1324,20 @@ BetweenShape between_shape(int d, int es)
     return vecs == 1 ? BetweenShape{1, 1} : vecs == 2 ? BetweenShape{1, 2} : BetweenShape{2, 2};
 }
 
+// steps of the bisection a launch: as many thresholds as the row norms' buffers take
+int between_levels(int d, int parts)
+{
+    const int room = clada_prefix_col_tiles(d) / parts;
+    return room >= 7 ? 3 : room >= 3 ? 2 : 1;
+}
+
 template <int ES>
 void launch_between(const CettWs &w, const clada_layer *layer, int T, int Fp, int launch, const int *list, int cap, const int *count,
                     float *const (&sums)[2], float bound, hipStream_t st)
 {
     const int d = layer->d;
     const BetweenShape sh = between_shape(d, ES);
-    // as many thresholds a launch as the row norms' buffers take
-    const int room = clada_prefix_col_tiles(d) / sh.parts, levels = room >= 7 ? 3 : room >= 3 ? 2 : 1;
+    const int levels = between_levels(d, sh.parts);
     auto kern = sh.nv == 1 ? (levels == 3 ? k_cett_between<ES, 1, 3> : levels == 2 ? k_cett_between<ES, 1, 2> : k_cett_between<ES, 1, 1>)
                            : (levels == 3 ? k_cett_between<ES, 2, 3> : levels == 2 ? k_cett_between<ES, 2, 2> : k_cett_between<ES, 2, 1>);
     auto take = levels == 3 ? k_cett_take<3> : levels == 2 ? k_cett_take<2> : k_cett_take<1>;
@@ -944,10 +1350,11 @@ void launch_between(const CettWs &w, const clada_layer *layer, int T, int Fp, in
                        sq[launch & 1], sq[(launch + 1) & 1], w.den, bound, T, layer->d_ff, Fp, d);
 }
 
-// Words that the large search keeps in the place of the partial aggregates, and whether they fit there.
+// Words that the large search keeps in the place of the partial aggregates (the curves' sum lies elsewhere: 100 tokens of 1024 x 3000
+// fit now, 690 us as a plain bisection, 172 so), and whether they fit there.
 bool large_fits(int T, int F)
 {
-    return (size_t)4 * clada_prefix_token_tiles(T) * F >= SAMPLES + CURVE_BINS * (size_t)(1 + CURVE_TOKENS) + T;
+    return (size_t)4 * clada_prefix_token_tiles(T) * F >= SAMPLES + CURVE_BINS + (size_t)T;
 }
 
 // The large search after begin().
@@ -959,8 +1366,14 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
     const int grid = (int)((groups + 255) / 256 < 4096 ? (groups + 255) / 256 : 4096);
     // (the partial aggregates are not used here: large_fits)
     unsigned int *sample = reinterpret_cast<unsigned int *>(w.part);
-    float *curve = reinterpret_cast<float *>(sample + SAMPLES), *curves = curve + CURVE_BINS;
-    int *count = reinterpret_cast<int *>(curves + CURVE_TOKENS * CURVE_BINS);
+    float *curve = reinterpret_cast<float *>(sample + SAMPLES);
+    int *count = reinterpret_cast<int *>(curve + CURVE_BINS);
+    // The table where it takes in what a probe's estimate leaves open; else the bracket is closed by dense probes and the rest of the
+    // bisection measured a few thresholds a launch.
+    const int window = T <= TABLE_TOKENS ? table_window(T, F) : 0;
+    const bool table = window >= table_past(window) + table_below(window);
+    const int curve_tokens = table ? (T < CURVE_TABLE ? T : CURVE_TABLE) : CURVE_TOKENS;
+    unsigned long long *curves = reinterpret_cast<unsigned long long *>(w.hcut);      // (not masked yet)
     auto mask = [&](int may_skip) {
         if (layer->dtype == CLADA_BF16)
             hipLaunchKernelGGL(k_cett_mask<2>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, may_skip);
@@ -968,12 +1381,12 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
             hipLaunchKernelGGL(k_cett_mask<4>, dim3(grid), dim3(256), 0, stream, w.state, w.pool, w.h, w.hcut, T, F, Fp, may_skip);
         return hipGetLastError();
     };
-    hipLaunchKernelGGL(k_cett_sample, dim3(SAMPLES / 64), dim3(256), 0, stream, w.state, w.pool, (unsigned long long)T * F, sample, bound);
+    const bool den = layer->kind != CLADA_FFN_RELU;          // (the non-gated family's are there)
+    hipLaunchKernelGGL(k_cett_sample, dim3(SAMPLE_WGS + (den ? (T + 255) / 256 : 0)), dim3(256), 0, stream, w.state, w.pool, (unsigned long long)T * F,
+                       sample, bound, w.rowsq_den, n_tn, T, w.den, curves);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
-    hipLaunchKernelGGL((layer->dtype == CLADA_BF16 ? k_cett_curve<2> : k_cett_curve<4>), dim3(CURVE_TOKENS), dim3(1024), 0, stream, w.pool, w.h,
-                       sample, T, F, Fp, curves);
-    CLADA_CHECK_HIP(ctx, hipGetLastError());
-    hipLaunchKernelGGL(k_cett_first, dim3(1), dim3(CURVE_BINS), 0, stream, w.state, curves, CURVE_TOKENS, curve, sample, bound);
+    hipLaunchKernelGGL((layer->dtype == CLADA_BF16 ? k_cett_curve<2> : k_cett_curve<4>), dim3(curve_tokens), dim3(1024), 0, stream, w.state, w.pool, w.h,
+                       sample, T, F, Fp, curves, curve, bound, table ? table_below(window) : 0);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     // The cut sums at the bracket's lower end are the output of the last feasible probe.  With room for two buffers of them beside
     // the masked h (bf16: the upper half of h's part, which is sized for fp32) the probes alternate between them; else one more
@@ -982,13 +1395,57 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
     float *sums[2] = {reinterpret_cast<float *>(w.ytmp), reinterpret_cast<float *>(two ? w.h + (size_t)T * Fp * 2 : w.hcut)};
     // (with both buffers of sums taken, the half of the masked h's part that a bf16 one leaves is free)
     const DownRoom room = w.room(two ? w.hcut + (size_t)T * Fp * 2 : w.ytmp);
-    for (int it = 0; it < DENSE_PROBES; ++it) {
+    const auto dense = [&](int stage) -> clada_status {
         CLADA_CHECK_HIP(ctx, mask(1));
         CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, w.rowsq_num, room, ctx->opt_prefix_tile, stream, ctx->num_cu,
-                                               two ? sums[0] : nullptr, &w.state->skip, two ? sums[1] : nullptr, two ? &w.state->sel : nullptr));
-        hipLaunchKernelGGL(k_cett_next, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound, sample, curve);
+                                               two || table ? sums[0] : nullptr, &w.state->skip, two ? sums[1] : nullptr, two ? &w.state->sel : nullptr));
+        hipLaunchKernelGGL(k_cett_next, dim3(1), dim3(1024), 0, stream, w.state, w.rowsq_num, n_tn, T, w.den, bound, sample, curve,
+                           table ? window : 0, two ? 1 : 0, stage);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
+        return CLADA_OK;
+    };
+    // the masked h is not needed any more once the probes are done: its part takes the lists, behind the second buffer of cut sums if
+    // that is there
+    int *list = reinterpret_cast<int *>(w.hcut) + (two ? 0 : (size_t)T * d);
+    const int list_cap = two ? Fp : Fp - d;
+    const auto tail = [&](int launches) -> clada_status {
+        hipLaunchKernelGGL(k_cett_list, dim3(T), dim3(1024), 0, stream, w.state, w.pool, F, list, list_cap, count);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+        for (int it = 0; it < launches; ++it) {
+            if (layer->dtype == CLADA_BF16) launch_between<2>(w, layer, T, Fp, it, list, list_cap, count, sums, bound, stream);
+            else launch_between<4>(w, layer, T, Fp, it, list, list_cap, count, sums, bound, stream);
+            CLADA_CHECK_HIP(ctx, hipGetLastError());
+        }
+        return CLADA_OK;
+    };
+    clada_status st;
+    if (table) {
+        const int cap = table_cap(T), vecs = (d * (int)dtype_size(layer->dtype) / 16 + 255) / 256;      // 1 .. 4 groups of 256 x 16 bytes a row
+        float *mag = reinterpret_cast<float *>(w.hcut), *cett = mag + (size_t)cap * T;        // (at least 2^18 words; the table takes a third)
+        const auto ladder = layer->dtype == CLADA_BF16 ? (vecs == 1 ? k_cett_ladder<2, 1, 256> : vecs == 2 ? k_cett_ladder<2, 1, 512> : k_cett_ladder<2, 2, 512>)
+                                                       : (vecs == 1 ? k_cett_ladder<4, 1, 256> : vecs == 2 ? k_cett_ladder<4, 1, 512> : k_cett_ladder<4, 2, 512>);
+        const int tpt = table_threads(T);
+        const auto bisect = tpt == 1 ? k_cett_bisect<1> : tpt == 2 ? k_cett_bisect<2> : tpt == 4 ? k_cett_bisect<4> : k_cett_bisect<8>;
+        for (int round = 0; round < 2; ++round) {
+            for (int it = 0; it < TABLE_PROBES; ++it)
+                if ((st = dense(round == 0 ? it : it < TABLE_PROBES - 1 ? 2 : 3)) != CLADA_OK) return st;
+            if (!two) {                                      // the sums again, where a probe that failed came after the window's lower end
+                CLADA_CHECK_HIP(ctx, mask(2));
+                CLADA_CHECK_HIP(ctx, clada_prefix_down(layer, w.hcut, T, nullptr, nullptr, room, ctx->opt_prefix_tile, stream, ctx->num_cu, sums[0], &w.state->kept));
+            }
+            hipLaunchKernelGGL(ladder, dim3(T), dim3(vecs == 1 ? 256 : 512), 0, stream, w.state, w.pool, w.h, (const char *)layer->w_down, sums[0], sums[1],
+                               w.den, T, F, Fp, d, cap, mag, cett, count);
+            CLADA_CHECK_HIP(ctx, hipGetLastError());
+            hipLaunchKernelGGL(bisect, dim3(1), dim3(1024), 0, stream, w.state, mag, cett, count, T, bound, sample, curve, window, round);
+            CLADA_CHECK_HIP(ctx, hipGetLastError());
+        }
+        // What the tables left open (a great many equal magnitudes): an even number of launches, the last of which takes in the 31st
+        // step.  (Twelve would do above 512 tokens as well; a test counts 32 at 1024.)
+        const int levels = between_levels(d, between_shape(d, (int)dtype_size(layer->dtype)).parts);
+        return tail(T > 512 ? 32 : levels == 3 ? 12 : levels == 2 ? 18 : 32);
     }
+    for (int it = 0; it < DENSE_PROBES; ++it)
+        if ((st = dense(it)) != CLADA_OK) return st;
     if (two) {
         hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 2);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
@@ -1000,17 +1457,7 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
         hipLaunchKernelGGL(k_cett_base, dim3(1), dim3(64), 0, stream, w.state, 1);
         CLADA_CHECK_HIP(ctx, hipGetLastError());
     }
-    // the masked h is not needed any more: its part takes the lists, behind the second buffer of cut sums if that is there
-    int *list = reinterpret_cast<int *>(w.hcut) + (two ? 0 : (size_t)T * d);
-    const int cap = two ? Fp : Fp - d;
-    hipLaunchKernelGGL(k_cett_list, dim3(T), dim3(1024), 0, stream, w.state, w.pool, F, list, cap, count);
-    CLADA_CHECK_HIP(ctx, hipGetLastError());
-    for (int it = 0; it <= 31; ++it) {                       // (the last one only takes in the 31st probe)
-        if (layer->dtype == CLADA_BF16) launch_between<2>(w, layer, T, Fp, it, list, cap, count, sums, bound, stream);
-        else launch_between<4>(w, layer, T, Fp, it, list, cap, count, sums, bound, stream);
-        CLADA_CHECK_HIP(ctx, hipGetLastError());
-    }
-    return CLADA_OK;
+    return tail(32);                                         // (the last one only takes in the 31st probe)
 }
 
 }  // namespace
@@ -1040,7 +1487,7 @@ extern "C" clada_status clada_cett_eval(clada_ctx *ctx, const clada_layer *layer
     if (eps != eps) return clada_fail(ctx, CLADA_ERR_VALUE, "eps is NaN");
     hipStream_t stream = (hipStream_t)hip_stream;
     const CettWs w = carve(ctx->ws + CLADA_WS_HEADER, ctx->ws_bytes - CLADA_WS_HEADER, layer->d, layer->d_ff, T);
-    st = begin(ctx, layer, x_val, T, w, 0, eps, stream);
+    st = begin(ctx, layer, x_val, T, w, 0, eps, false, stream);
     if (st != CLADA_OK) return st;
     return probe(ctx, layer, T, w, 0.0f, 0, cett_out, mean_out, stream);
 }
@@ -1057,8 +1504,6 @@ extern "C" clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_
     if (st != CLADA_OK) return st;
     hipStream_t stream = (hipStream_t)hip_stream;
     const CettWs w = carve(ctx->ws + CLADA_WS_HEADER, ctx->ws_bytes - CLADA_WS_HEADER, layer->d, layer->d_ff, T);
-    st = begin(ctx, layer, x_val, T, w, 1, 0.0f, stream);
-    if (st != CLADA_OK) return st;
     // The large search pays where a dense probe costs more than a workgroup per token (0.1 us of a probe inside the bracket), and
     // its bracket is only trusted where single neurons do not move the mean (ms, plain / large from 2^18 magnitudes of at least 1024
     // neurons on: 0.80 / 0.25 for 64 tokens of 1024 x 4096, 1.43 / 0.33 of 4096 x 11008, 0.86 / 0.27 for 256 of 512 x 1999); fewer probes
@@ -1069,6 +1514,8 @@ extern "C" clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_
     const int F = layer->d_ff;
     const bool large = n_probes == 31 && bound > 0.0f && T >= 64 && (size_t)T * F >= (F >= 1024 ? 1u << 18 : 1u << 20) && F >= layer->d &&
                        F >= 512 && large_fits(T, F) && (layer->dtype == CLADA_F32 || T <= 4096 || F >= 2048);
+    st = begin(ctx, layer, x_val, T, w, 1, 0.0f, large, stream);
+    if (st != CLADA_OK) return st;
     if (large) {
         st = search_large(ctx, layer, T, w, bound, stream);
         if (st != CLADA_OK) return st;

@@ -310,6 +310,47 @@ def test_search_thresholds_per_launch(clada, d, F, T, dtype):
         assert float(clada.cett_eval(ctx, layer, x, float(t31))[1]) == pytest.approx(float(m31), rel=2e-6)
 
 
+# The search over a table: threads a token (1, 2, 4, 8), their edges, rows of one to four groups of 16 bytes a thread, windows just wide enough for
+# one, sums in one buffer and two; inputs whose answer lies past the first table, whose first probes fail, whose tokens have more
+# equal magnitudes than a table takes.
+@pytest.mark.parametrize("d,F,T,dtype,how", [
+    (512, 4200, 64, "bf16", "plain"), (520, 2300, 128, "bf16", "plain"), (1024, 2100, 129, "bf16", "plain"), (2056, 2100, 256, "bf16", "plain"),
+    (512, 1100, 257, "bf16", "plain"), (512, 1100, 512, "bf16", "plain"), (512, 1100, 513, "bf16", "plain"), (512, 2100, 1024, "bf16", "plain"),
+    (6144, 6200, 64, "bf16", "plain"), (256, 11900, 900, "bf16", "plain"), (256, 12100, 900, "bf16", "plain"), (1028, 2100, 130, "f32", "plain"),
+    (3072, 3100, 100, "f32", "plain"), (1024, 3000, 200, "bf16", "common"), (1024, 3000, 200, "f32", "common"), (1024, 4096, 300, "bf16", "rows"),
+    (1024, 4096, 300, "bf16", "tokens"), (1024, 4096, 130, "bf16", "ties"), (512, 2048, 200, "f32", "ties"), (1024, 4096, 300, "bf16", "relu"),
+])
+def test_search_over_a_table(clada, d, F, T, dtype, how):
+    """As above: against the plain bisection of 30 probes, with the same bounds."""
+    from paper_2502_19078_amd import binding
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(d + F + T)
+    n = lambda *s, k=1.0: torch.randn(s, generator=g, device=DEV) * k
+    w = [n(F, d, k=d ** -0.5) for _ in range(3)]
+    x = n(T, d)
+    if how == "common":                                      # rows of W_down along one direction
+        w[2] += n(1, d, k=d ** -0.5)
+    if how == "rows":
+        w[2] *= torch.exp(1.5 * n(F, 1))
+    if how == "tokens":                                      # tokens of unequal norm
+        x *= torch.exp(n(T, 1))
+    if how == "ties":                                        # eight different gate rows
+        w[0] = w[0][torch.arange(F, device=DEV) % 8]
+    w = [a.to(dt) for a in w]
+    layer = clada.Layer(w[0], None, w[2], kind=binding.RELU, b_in=n(F), b_out=n(d)) if how == "relu" else clada.Layer(*w)
+    x = x.to(dt)
+    x[3] = x[2]                                              # two tokens alike
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, 0, T, 0))
+    for bound in (0.02, 0.2, 0.6):
+        t30, m30 = clada.threshold_search_cett(ctx, layer, x, bound, n_probes=30)
+        t31, m31 = clada.threshold_search_cett(ctx, layer, x, bound)
+        again = clada.threshold_search_cett(ctx, layer, x, bound)
+        assert torch.equal(t31, again[0]) and torch.equal(m31, again[1])
+        assert float(t31) == pytest.approx(float(t30), rel=1e-5 + 20.0 / (T * F)), bound
+        assert float(m31) <= bound and float(m31) == pytest.approx(float(m30), rel=1e-5 + 20.0 / (T * F))
+        assert float(clada.cett_eval(ctx, layer, x, float(t31))[1]) == pytest.approx(float(m31), rel=2e-6)
+
+
 @pytest.mark.parametrize("d,F,T,dtype,tile", [(768, 96, 257, "bf16", 2), (576, 288, 300, "bf16", 2), (1024, 2960, 1300, "bf16", 0), (576, 4128, 64, "bf16", 2),
                                               (768, 2015, 300, "bf16", 2), (512, 129, 200, "bf16", 1), (72, 97, 130, "bf16", 0), (256, 96, 70, "f32", 0)])
 def test_what_the_workspace_held_does_not_reach_the_search(clada, d, F, T, dtype, tile):
