@@ -1504,15 +1504,18 @@ extern "C" clada_status clada_threshold_search_cett(clada_ctx *ctx, const clada_
     if (st != CLADA_OK) return st;
     hipStream_t stream = (hipStream_t)hip_stream;
     const CettWs w = carve(ctx->ws + CLADA_WS_HEADER, ctx->ws_bytes - CLADA_WS_HEADER, layer->d, layer->d_ff, T);
-    // The large search pays where a dense probe costs more than a workgroup per token (0.1 us of a probe inside the bracket), and
-    // its bracket is only trusted where single neurons do not move the mean (ms, plain / large from 2^18 magnitudes of at least 1024
-    // neurons on: 0.80 / 0.25 for 64 tokens of 1024 x 4096, 1.43 / 0.33 of 4096 x 11008, 0.86 / 0.27 for 256 of 512 x 1999); fewer probes
+    // The large search pays where 31 dense probes, four launches each, cost more than a pass over the tokens and a table: up to 1024
+    // tokens from 64 tokens and 1024 neurons on, as far as its words fit (us, plain / large: 613 / 180 for 197 tokens of 512 x 1185,
+    // 571 / 557 for 78 of 512 x 1024, where they do not; 1096 / 189 for 72 of 1024 x 1398; fp32 1562 / 305 for 71 of 768 x 1746; 60 such
+    // searches ended at the same threshold either way: a bracket of a few hundred magnitudes is several times as wide as the stretch where single
+    // neurons turn the mean).  Beyond, a probe inside the bracket is a workgroup per token, and the bracket is only trusted from 2^18 magnitudes
+    // on (ms, 1.43 / 0.33 for 64 tokens of 4096 x 11008, 0.86 / 0.27 for 256 of 512 x 1999), 2^20 below 1024 neurons; fewer probes
     // than the full 31 end somewhere on the way, which only the plain bisection passes through.  A bf16 projection of fewer than 2048
     // neurons costs less once the tokens fill the chip (ms, large / plain: 6.6 / 3.9 and 8.2 / 6.4 at 65536 tokens of 64 and 512 x 512,
     // 7.9 / 7.1 of 256 x 1024, 1.9 / 1.7 at 16384 of 256 x 512; 0.79 / 1.04 at 4096 of 256 x 512, 8.2 / 11.1 at 65536 of 64 x 2048); an
     // fp32 one never does (2.1 / 2.7 at 16384 of 64 x 512).
     const int F = layer->d_ff;
-    const bool large = n_probes == 31 && bound > 0.0f && T >= 64 && (size_t)T * F >= (F >= 1024 ? 1u << 18 : 1u << 20) && F >= layer->d &&
+    const bool large = n_probes == 31 && bound > 0.0f && T >= 64 && (size_t)T * F >= (F < 1024 ? 1u << 20 : T > TABLE_TOKENS ? 1u << 18 : 0u) && F >= layer->d &&
                        F >= 512 && large_fits(T, F) && (layer->dtype == CLADA_F32 || T <= 4096 || F >= 2048);
     st = begin(ctx, layer, x_val, T, w, 1, 0.0f, large, stream);
     if (st != CLADA_OK) return st;

@@ -314,7 +314,7 @@ def test_search_thresholds_per_launch(clada, d, F, T, dtype):
 # one, sums in one buffer and two; inputs whose answer lies past the first table, whose first probes fail, whose tokens have more
 # equal magnitudes than a table takes.
 @pytest.mark.parametrize("d,F,T,dtype,how", [
-    (512, 4200, 64, "bf16", "plain"), (520, 2300, 128, "bf16", "plain"), (1024, 2100, 129, "bf16", "plain"), (2056, 2100, 256, "bf16", "plain"),
+    (512, 1200, 70, "f32", "plain"), (768, 1500, 64, "bf16", "plain"), (512, 4200, 64, "bf16", "plain"), (520, 2300, 128, "bf16", "plain"), (1024, 2100, 129, "bf16", "plain"), (2056, 2100, 256, "bf16", "plain"),
     (512, 1100, 257, "bf16", "plain"), (512, 1100, 512, "bf16", "plain"), (512, 1100, 513, "bf16", "plain"), (512, 2100, 1024, "bf16", "plain"),
     (6144, 6200, 64, "bf16", "plain"), (256, 11900, 900, "bf16", "plain"), (256, 12100, 900, "bf16", "plain"), (1028, 2100, 130, "f32", "plain"),
     (3072, 3100, 100, "f32", "plain"), (1024, 3000, 200, "bf16", "common"), (1024, 3000, 200, "f32", "common"), (1024, 4096, 300, "bf16", "rows"),
