@@ -78,13 +78,17 @@ clada_status clada_require_swiglu(clada_ctx *ctx, const clada_layer *layer, cons
 // list / list_n (device; nullptr for all neurons): run over the listed neurons only, all kept (dense must be set).
 clada_status clada_decode_batched(clada_ctx *ctx, const clada_layer *layer, const void *x, int32_t B,
                                   const float *tau, void *y, unsigned char *keep, float *partial,
-                                  char *scratch, bool dense, hipStream_t stream, bool *ran,
+                                  char *scratch, bool dense, hipStream_t stream, bool *ran, int tiles,
                                   const int32_t *list = nullptr, const int32_t *list_n = nullptr);
+int clada_batched_passes(const clada_layer *layer, int32_t B);      // passes of a batch: more than 16 tokens a pass are taken in two tiles
+// Partial outputs of a pass in two tiles (floats per column of y: 64 groups x 32 tokens); its scratch follows them, both in the partial outputs'
+// part of the workspace, which holds 512 rows a token.
+#define CLADA_BAT_WIDE (64 * 32)
 clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int32_t L, const void *x, int32_t B,
                                  const float *tau, void *y, bool dense, char *scratch, size_t bytes, hipStream_t stream, bool *ran);
 size_t clada_ws_decode_batched(int32_t d_ff);
 size_t clada_ws_decode_batched_partial(int32_t d);
-bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *layer, int32_t B);
+bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *layer, int32_t B, int tiles);
 // Batch-1 decode over a neuron list with the streaming kernel, when the shape fits it (*ran).
 hipError_t clada_decode_list_b1(clada_ctx *ctx, const clada_layer *layer, const void *x, const int32_t *idx,
                                 const int32_t *n_active, float *partial, int *P_out, hipStream_t stream, bool *ran);

@@ -35,6 +35,9 @@ size_t ws_partial_bytes(int B, int d)
     return align_up(sizeof(float) * rows * d, 256);
 }
 
+// (three of them and their scratch, 33 d_ff floats and 2 KiB each, fit ws_partial_bytes from 17 tokens on: 8704 d floats; d_ff <= 16 d, d >= 1024)
+size_t bat_wide_partial(int d) { return sizeof(float) * CLADA_BAT_WIDE * (size_t)d; }
+
 struct DecodeParams {
     const char *wg, *wu, *wd;   // [F][d] neuron-major
     const char *x;              // [B][d]
@@ -1445,21 +1448,22 @@ clada_status run_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
             return CLADA_OK;
         }
     }
-    // ---- batched MFMA path (bf16, supported widths): up to 16 tokens per pass; larger batches run
-    // as ceil(B/16) passes of near-equal size, each re-reading the weights of its own union
+    // ---- batched MFMA path (bf16, supported widths): up to 16 or 32 tokens per pass; larger batches run
+    // as passes of near-equal size, each re-reading the weights of its own union
     if (B >= 2 && ctx->opt_decode_batched) {
         unsigned char *keep_region = reinterpret_cast<unsigned char *>(ws + ws_partial_bytes(B, d));
-        char *scratch = reinterpret_cast<char *>(keep_region) + align_up((size_t)B * F, 256);
-        const int n_groups = (B + 15) / 16, per_group = (B + n_groups - 1) / n_groups;     // per_group >= 2 whenever B >= 2
+        const int n_groups = clada_batched_passes(layer, B), per_group = (B + n_groups - 1) / n_groups;     // per_group >= 2 whenever B >= 2
+        const int tiles = per_group > 16 ? 2 : 1;
+        char *scratch = tiles == 2 ? ws + bat_wide_partial(d) : reinterpret_cast<char *>(keep_region) + align_up((size_t)B * F, 256);
         bool ran_all = false;
         if (ctx->opt_diag_events) CLADA_CHECK_HIP(ctx, hipEventRecord(ctx->ev[0], stream));
         for (int g0 = 0; g0 < B; g0 += per_group) {
             const int Bg = (B - g0 < per_group) ? B - g0 : per_group;
             bool ran = false;
-            if (Bg >= 2)
+            if (Bg >= 2 || tiles == 2)
                 st = clada_decode_batched(ctx, layer, (const char *)x + (size_t)g0 * d * es, Bg, tau ? tau + g0 : nullptr,
                                           (char *)y + (size_t)g0 * d * es, p.keep ? p.keep + (size_t)g0 * F : nullptr,
-                                          p.partial, scratch, dense, stream, &ran);
+                                          p.partial, scratch, dense, stream, &ran, tiles);
             if (st != CLADA_OK) return st;
             if (!ran) {
                 // not eligible (decided by dtype and shape before anything is launched, so by the first
@@ -1555,16 +1559,16 @@ clada_status run_list_decode(clada_ctx *ctx, const clada_layer *layer, const voi
     // ---- matrix-core path (bf16, supported widths), up to 16 tokens per pass, as in the thresholded call
     if (B >= 2 && ctx->opt_decode_batched) {
         char *ws = ctx->ws + CLADA_WS_HEADER;
-        char *scratch = ws + ws_partial_bytes(B, d) + align_up((size_t)B * F, 256);
-        const int n_groups = (B + 15) / 16, per_group = (B + n_groups - 1) / n_groups;
+        const int n_groups = clada_batched_passes(layer, B), per_group = (B + n_groups - 1) / n_groups, tiles = per_group > 16 ? 2 : 1;
+        char *scratch = tiles == 2 ? ws + bat_wide_partial(d) : ws + ws_partial_bytes(B, d) + align_up((size_t)B * F, 256);
         bool ran_all = false;
         for (int g0 = 0; g0 < B; g0 += per_group) {
             const int Bg = (B - g0 < per_group) ? B - g0 : per_group;
             bool ran = false;
-            if (Bg >= 2) {
+            if (Bg >= 2 || tiles == 2) {
                 st = clada_decode_batched(ctx, layer, (const char *)x + (size_t)g0 * d * es, Bg, nullptr,
                                           (char *)y + (size_t)g0 * d * es, nullptr, p.partial, scratch, true, stream, &ran,
-                                          idx, n_active);
+                                          tiles, idx, n_active);
                 if (st != CLADA_OK) return st;
             }
             ran_all = ran;
@@ -1839,7 +1843,7 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
     // ---- batches on the matrix-core path: one launch per kernel over all units (layer, pass of up to 16 tokens), or,
     // where clada_stack_batched leaves them, the units go round three lanes, each with its own partial outputs and
     // scratch.  The path's three launches per unit and its thin ends weigh more than at batch 1 (c3 layer shape, B = 8: 69.5 -> 60.2 -> 58.5 us per layer with one, two, three lanes).
-    const int n_groups = (B + 15) / 16, per_group = (B + n_groups - 1) / n_groups;
+    const int n_groups = clada_batched_passes(&layers[0], B), per_group = (B + n_groups - 1) / n_groups, tiles = per_group > 16 ? 2 : 1;
     if (B >= 2 && smode == 3 && !n_active && ctx->opt_decode_batched) {
         bool ran = false;
         const clada_status st = clada_stack_batched(ctx, layers, L, x, B, tau, y, dense, ctx->ws + CLADA_WS_HEADER,
@@ -1848,8 +1852,8 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
         if (ran) return CLADA_OK;
     }
     if (B >= 2 && smode == 3 && !n_active && ctx->opt_decode_batched && L * n_groups >= 3 &&
-        clada_decode_batched_eligible(ctx, &layers[0], per_group) &&
-        clada_decode_batched_eligible(ctx, &layers[0], B - (n_groups - 1) * per_group)) {
+        clada_decode_batched_eligible(ctx, &layers[0], per_group, tiles) &&
+        clada_decode_batched_eligible(ctx, &layers[0], B - (n_groups - 1) * per_group, tiles)) {
         const int n_lanes = 3;
         char *ws = ctx->ws + CLADA_WS_HEADER;
         char *lane_base[3];
@@ -1865,11 +1869,16 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
                 float *partial = lane ? reinterpret_cast<float *>(lane_base[lane]) : reinterpret_cast<float *>(ws);
                 char *scratch = lane ? lane_base[lane] + clada_ws_decode_batched_partial(d)
                                      : ws + ws_partial_bytes(B, d) + align_up((size_t)B * F, 256);
+                if (tiles == 2) {                            // the lanes side by side in the partial outputs' part
+                    char *base = ws + lane * (bat_wide_partial(d) + align_up(sizeof(float) * 33 * (size_t)F, 256) + 2048);
+                    partial = reinterpret_cast<float *>(base);
+                    scratch = base + bat_wide_partial(d);
+                }
                 const size_t row = (size_t)l * B + g0;
                 bool ran = false;
                 clada_status st = clada_decode_batched(ctx, &layers[l], (const char *)x + row * d * es, Bg, tau ? tau + row : nullptr,
                                                        (char *)y + row * d * es, nullptr, partial, scratch, dense,
-                                                       lane ? ctx->lane_stream[lane - 1] : stream, &ran);
+                                                       lane ? ctx->lane_stream[lane - 1] : stream, &ran, tiles);
                 if (st != CLADA_OK || !ran) {
                     (void)lanes_join(ctx, n_lanes, stream);      // leave no lane forked (a capture would not end)
                     return st != CLADA_OK ? st : clada_fail(ctx, CLADA_ERR_SHAPE, "batched path refused a unit it had accepted");

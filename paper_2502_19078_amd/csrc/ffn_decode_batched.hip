@@ -1,4 +1,4 @@
-// Batched (2 <= B <= 16) thresholded sparse SwiGLU FFN at decode time on the matrix cores
+// Batched (2 <= B <= 16 a pass, 32 in two tiles) thresholded sparse SwiGLU FFN at decode time on the matrix cores
 // (algorithm "CLADA Inference", generation phase; bf16 layers).  With B tokens every weight
 // element feeds B multiply-adds, which the vector ALUs cannot sustain at HBM speed, so the
 // three projections run as MFMA 16x16x32 (bf16 in, fp32 accumulate) with the tokens as the
@@ -15,8 +15,8 @@
 //     partial 16x16 tiles of the waves are summed through LDS in fixed order; sigma, the per-token
 //     fp32 compare and the per-neuron 16-bit keep masks follow.  The neurons of gate tile i that at
 //     least one token keeps (the union) are compacted by ballot and form up tile i: the same MFMA
-//     loop over their W_up rows gives u, and h = keep ? a*u : 0 goes to a [d_ff][16] fp32 buffer
-//     (the 16 tokens of a neuron = one 64-byte line).  Gate and up tiles alternate (G0 G1 U0 G2 U1
+//     loop over their W_up rows gives u, and h = keep ? a*u : 0, split into two bf16, goes to a [d_ff][16]
+//     buffer (the 16 tokens of a neuron = one 64-byte line).  Gate and up tiles alternate (G0 G1 U0 G2 U1
 //     ...), so the stream of row loads does not drain between the two projections.  The workgroup
 //     also leaves the list of its union-kept neurons, ascending, and their count for kernel B.
 //   kernel B (down): 2-D split -- column groups of 256 x row groups (a fixed range of neuron
@@ -24,7 +24,7 @@
 //     R partial y's exist instead of one per workgroup.  Work is dealt to the waves in units of 32
 //     neurons x 128 columns (wave w: column half w & 1, neuron blocks w >> 1, + 4, ...).  W_down
 //     rows arrive as 256-byte segments, are staged per wave in LDS and read
-//     back K-major with ds_read_b64_tr_b16 as MFMA B-fragments; h is split into bf16 hi + lo
+//     back K-major with ds_read_b64_tr_b16 as MFMA B-fragments; h comes as bf16 hi + lo
 //     A-fragments (two MFMAs), so the down projection keeps ~fp32 accuracy of h.
 //   kernel C: k_ffn_finalize adds the R partials in fixed order.
 #include <atomic>
@@ -41,7 +41,7 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 struct BatParams {
     const char *wg, *wu, *wd, *x;
     const float *tau;           // [B]
-    float *hbuf;                // [F][16] fp32 (neuron-major: one 64-byte line per neuron), written for union-kept neurons only
+    unsigned int *hbuf;         // [F][16 or 32] h, split (neuron-major: a 64-byte line or two per neuron), written for union-kept neurons only
     int *ulist;                 // [F] union-kept neurons: gate/up workgroup q writes its own, ascending, from
                                 //     the first neuron it owns (q * F / P) on
     int *ucnt;                  // [P] how many each wrote
@@ -53,6 +53,7 @@ struct BatParams {
     const int *list, *list_n;   // prefix-static run (with DENSE): the neurons are the list_n[0] entries of list
                                 // (device), every one kept by every token; nullptr: all F neurons
     int row0, rows;             // this unit's first row of the launch's tokens, and their number (stride of the partials)
+    int mt;                     // tiles of 16 tokens a pass
 };
 
 // A launch of the whole-stack call runs n units, pass blockIdx.y of the tokens of layer blockIdx.z, as many layers as the workspace
@@ -79,11 +80,19 @@ __device__ __forceinline__ BatParams bat_unit(const BatArgs &)
     p.b_in = a->b_in[layer];
     p.x += (size_t)p.row0 * p.d * 2;
     if (p.tau) p.tau += p.row0;
-    p.hbuf += (size_t)unit * p.F * 16;
+    p.hbuf += (size_t)unit * p.F * (16 * p.mt);
     p.ulist += (size_t)unit * p.F;
     p.ucnt += (size_t)unit * COOP_MAX_WGS;
     p.B = min(a->per_pass, p.B - t0);
     return p;
+}
+
+// An fp32 h as the sum of two bf16: the rounded value below, the rounded rest above.  Split once here and not by every column group of the down
+// kernel.
+__device__ __forceinline__ unsigned int split_bf16(float h)
+{
+    const __bf16 hi = (__bf16)h, lo = (__bf16)(h - (float)hi);       // (one instruction each; nearest even)
+    return (unsigned int)__builtin_bit_cast(unsigned short, hi) | ((unsigned int)__builtin_bit_cast(unsigned short, lo) << 16);
 }
 
 __device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, const f32x4 c)
@@ -105,15 +114,20 @@ constexpr int MAX_TILES = 4;    // 16-neuron tiles per workgroup in kernel A (on
 // indices are plain arithmetic on the run's start (fewer registers: the 10 and 16 KiB rows need that).
 // RELU: the non-gated family (gate tiles only).  A template flag: as a run-time one it cost the
 // 10 and 16 KiB rows ~25 registers and pushed them into scratch (52 -> 68 us at the 13B shape).
-template <int KSTEPS, int NW, bool DENSE, bool LIST, bool RELU, class Args>
+// MT: tiles of 16 tokens; two share every fragment of the weights, so that 17 to 32 tokens read them once.  x takes 8 KSTEPS registers
+// then, which rows of up to 8 KiB leave room for (16 k-steps a wave; 5 to 8 thousand values would be 24 or 32).  us, passes of 16 / so: one layer
+// 117 / 69 at 24 tokens of 4096 x 11008, 61.5 / 38.5 of 2048 x 8192, 35 / 22 of 1024 x 3000, 173 / 132 at 33 (three passes / two); six layers at 24 of
+// these 578 / 354, 240 / 159, 86 / 67.
+template <int KSTEPS, int NW, bool DENSE, bool LIST, bool RELU, int MT, class Args>
 __global__ void __launch_bounds__(NW * 64)
 k_bat_gateup(const Args args)
 {
     const BatParams p = bat_unit(args);
     static_assert(!LIST || DENSE, "a list run keeps every listed neuron");
     static_assert(NW >= 4 && NW <= 8, "the tile reductions run on waves 0..3");
-    __shared__ float s_part[2][NW][256];
-    __shared__ float s_a[MAX_TILES][16][16];
+    constexpr int NBUF = MT == 1 ? 2 : 1, NT = NW * 64, ELEMS = 256 * MT, TURNS = (ELEMS + NT - 1) / NT, HS = 16 * MT;
+    __shared__ float s_part[NBUF][NW][ELEMS];               // (two of them for two token tiles would not fit beside the rows)
+    __shared__ float s_a[MAX_TILES][HS][16];
     __shared__ int s_km[MAX_TILES * 16];
     __shared__ int s_ul[MAX_TILES * 16];
     __shared__ int s_ku[MAX_TILES];
@@ -160,13 +174,16 @@ k_bat_gateup(const Args args)
     const int j_hi_all = bat_run_lo(blk + 1, Fn, P);
 
     // this wave's slice of x as A-fragments: lane = (token n, k-group q)
-    u32x4 xa[KSTEPS];
+    u32x4 xa[MT][KSTEPS];
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (n < B) v = *reinterpret_cast<const u32x4 *>(p.x + (size_t)n * rowb + koff + (ks / SP) * PB + (q * SP + ks % SP) * 16);
-        xa[ks] = v;
-    }
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            const int m = 16 * mt + n;
+            if (m < B) v = *reinterpret_cast<const u32x4 *>(p.x + (size_t)m * rowb + koff + (ks / SP) * PB + (q * SP + ks % SP) * 16);
+            xa[mt][ks] = v;
+        }
     __syncthreads();
 
     auto stage_write = [&](const u32x4 (&wr)[NL], int half) {
@@ -180,19 +197,21 @@ k_bat_gateup(const Args args)
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    auto part_mma = [&](int part, f32x4 acc) {
+    auto part_mma = [&](int part, f32x4 (&acc)[MT]) {
 #pragma unroll
         for (int ks = 0; ks < SP; ++ks) {
             const u32x4 frag = *reinterpret_cast<const u32x4 *>(stage + n * PITCH + (q * SP + ks) * 16);
-            acc = mfma16(xa[part * SP + ks], frag, acc);
-        }
-        return acc;
-    };
-    auto part_store = [&](const f32x4 acc, int buf) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s_part[buf][wave][r * 64 + lane] = acc[r];
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma16(xa[mt][part * SP + ks], frag, acc[mt]);
+        }
     };
-    // element (r, ln) of the 16x16 tile: token m = 4*(ln/16) + r, neuron ln%16; waves summed in order
+    auto part_store = [&](const f32x4 (&acc)[MT], int buf) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s_part[buf][wave][256 * mt + r * 64 + lane] = acc[mt][r];
+    };
+    // element (mt, r, ln) of the 16x16 tiles: token m = 16 mt + 4*(ln/16) + r, neuron ln%16; waves summed in order
     auto tile_sum = [&](int buf, int e) {
         float s = 0.0f;
 #pragma unroll
@@ -201,8 +220,13 @@ k_bat_gateup(const Args args)
     };
     int nlist = 0;                                          // entries of this workgroup's union list so far (uniform)
     // the token this thread compares for in the gate reduction, and its threshold (kept out of the tile loop)
-    const int red_m = 4 * ((tid & 63) >> 4) + (tid >> 6);
-    const float red_tau = (!DENSE && tid < 256 && red_m < B) ? p.tau[red_m] : 0.0f;
+    auto token_of = [&](int e) { return 16 * (e >> 8) + 4 * ((e & 63) >> 4) + ((e & 255) >> 6); };
+    float red_tau[TURNS];
+#pragma unroll
+    for (int k = 0; k < TURNS; ++k) {
+        const int e = tid + k * NT;
+        red_tau[k] = (!DENSE && e < ELEMS && token_of(e) < B) ? p.tau[token_of(e)] : 0.0f;
+    }
     for (int j_lo = j_lo_all; j_lo < j_hi_all; j_lo += 16 * MAX_TILES) {
     const int nown = min(16 * MAX_TILES, j_hi_all - j_lo);  // <= 64
     const int ni = (nown + 15) / 16;                        // <= MAX_TILES
@@ -253,22 +277,25 @@ k_bat_gateup(const Args args)
         }
     };
     auto gate_reduce = [&](int i, int buf) {
-        if (tid < 256) {
-            const int r = tid >> 6, ln = tid & 63;
-            const int m = 4 * (ln >> 4) + r, nn = ln & 15, j = LIST ? s_nl[16 * i + nn] : j_lo + 16 * i + nn;
-            const bool here = 16 * i + nn < nown, valid = m < B && here;
-            float a = tile_sum(buf, tid);
-            if (RELU) {
-                if (p.b_in && valid) a += p.b_in[j];
-                a = a > 0.0f ? a : (a != a ? a : 0.0f);
-            } else {
-                a = gate_sigma_f32(a, p.gelu);
+#pragma unroll
+        for (int k = 0; k < TURNS; ++k) {
+            const int e = tid + k * NT;
+            if (e < ELEMS) {
+                const int m = token_of(e), nn = e & 15, j = LIST ? s_nl[16 * i + nn] : j_lo + 16 * i + nn;
+                const bool here = 16 * i + nn < nown, valid = m < B && here;
+                float a = tile_sum(buf, e);
+                if (RELU) {
+                    if (p.b_in && valid) a += p.b_in[j];
+                    a = a > 0.0f ? a : (a != a ? a : 0.0f);
+                } else {
+                    a = gate_sigma_f32(a, p.gelu);
+                }
+                const bool keep = valid && (DENSE ? true : (fabsf(a) >= red_tau[k]));
+                s_a[i][m][nn] = a;
+                if (keep) atomicOr(&s_km[i * 16 + nn], 1 << m);
+                if (p.keep && valid) p.keep[(size_t)m * F + j] = keep ? 1 : 0;
+                if (RELU && here) p.hbuf[(size_t)j * HS + m] = keep ? split_bf16(a) : 0u;     // read back for union-kept neurons only
             }
-            const bool keep = valid && (DENSE ? true : (fabsf(a) >= red_tau));
-            s_a[i][m][nn] = a;
-            if (keep) atomicOr(&s_km[i * 16 + nn], 1 << m);
-            if (p.keep && valid) p.keep[(size_t)m * F + j] = keep ? 1 : 0;
-            if (RELU && here) p.hbuf[(size_t)j * 16 + m] = keep ? a : 0.0f;     // read back for union-kept neurons only
         }
     };
     // Union-kept neurons of gate tile i, compacted by ballot.  Every wave does it for itself (same
@@ -285,15 +312,15 @@ k_bat_gateup(const Args args)
         wave_sync();
     };
     auto up_reduce = [&](int i, int buf) {
-        if (tid < 256) {
-            const int r = tid >> 6, ln = tid & 63;
-            const int m = 4 * (ln >> 4) + r, nn = ln & 15;
-            if (nn < s_ku[i]) {
+#pragma unroll
+        for (int k = 0; k < TURNS; ++k) {
+            const int e = tid + k * NT, m = token_of(e), nn = e & 15;
+            if (e < ELEMS && nn < s_ku[i]) {
                 const int l2 = s_ul[16 * i + nn];
                 const int j = LIST ? s_nl[16 * i + l2] : j_lo + 16 * i + l2;
-                const float usum = tile_sum(buf, tid);
+                const float usum = tile_sum(buf, e);
                 const bool keep = (s_km[16 * i + l2] >> m) & 1;
-                p.hbuf[(size_t)j * 16 + m] = keep ? s_a[i][m][l2] * usum : 0.0f;
+                p.hbuf[(size_t)j * HS + m] = keep ? split_bf16(s_a[i][m][l2] * usum) : 0u;
             }
         }
     };
@@ -310,7 +337,9 @@ k_bat_gateup(const Args args)
             seq_tile(sq + 1, nup, nti);
             nready = !nup || nti < ncomp;
         }
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        f32x4 acc[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int part = 0; part < NPART; ++part) {            // unrolled: x fragments stay in registers
             if (!have) {
@@ -332,17 +361,19 @@ k_bat_gateup(const Args args)
             }
             have = nxt;
             wave_sync();
-            acc = part_mma(part, acc);
+            part_mma(part, acc);
         }
-        part_store(acc, sq & 1);
+        const int buf = NBUF == 2 ? sq & 1 : 0;
+        part_store(acc, buf);
         __syncthreads();
         if (!up) {
-            gate_reduce(ti, sq & 1);
+            gate_reduce(ti, buf);
             __syncthreads();                                  // the tile's keep masks are complete
             compact(ti);
             ++ncomp;
         } else {
-            up_reduce(ti, sq & 1);
+            up_reduce(ti, buf);
+            if (NBUF == 1) __syncthreads();                  // the sums are read before the next tile's are written
         }
     }
     }   // rounds
@@ -356,8 +387,8 @@ constexpr int DN_TILE_BYTES = 32 * DN_PITCH;    // one wave's staging tile: 32 n
 constexpr int DN_MAX_ROWS = 2048;               // union neurons per row group
 constexpr int DN_MAX_WGS = 64;                  // gate/up workgroups per row group
 
-template <class Args>
-__global__ void __launch_bounds__(512, 4)
+template <int MT, class Args>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_bat_down(const Args args)
 {
     const BatParams p = bat_unit(args);
@@ -418,42 +449,51 @@ k_bat_down(const Args args)
     // blocks rw, rw + 4, ... (rw = w >> 1): units of 32 rows x 128 columns dealt round-robin, so the
     // eight waves differ by at most one unit.
     const int sub = wave & 1, rw = wave >> 1;
-    f32x4 acc[DN_SUB / 16];
+    f32x4 acc[MT][DN_SUB / 16];
 #pragma unroll
-    for (int t = 0; t < DN_SUB / 16; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int t = 0; t < DN_SUB / 16; ++t) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int n = lane & 15, q = lane >> 4;
     unsigned char *tile = s_tile + wave * DN_TILE_BYTES;
     const int nkb = (nrows + 31) / 32;
     static_assert(DN_COLS == 2 * DN_SUB, "two staging passes per block of neurons");
 
-    // h[token n][8 consecutive list entries] of block kb (raw fp32, converted when used)
-    auto h_load = [&](float (&hv)[8], int kb) {
+    // eight consecutive list entries; past the list the last one again, whose row is on its way already
+    const int last_row = nrows > 0 ? s_rows[nrows - 1] : 0;
+    auto rows8 = [&](int (&row)[8], int e0) {
+        const u32x4 a = *reinterpret_cast<const u32x4 *>(s_rows + e0), b = *reinterpret_cast<const u32x4 *>(s_rows + e0 + 4);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int e = 32 * kb + 8 * q + i;
-            hv[i] = (e < nrows && n < B) ? p.hbuf[(size_t)s_rows[e] * 16 + n] : 0.0f;
-        }
+        for (int i = 0; i < 8; ++i) row[i] = e0 + i < nrows ? (int)(i < 4 ? a[i & 3] : b[i & 3]) : last_row;
     };
-    // W_down[32 list entries][128 columns]: half-waves read 256-byte row pieces
+    // h[token n][list entries 8 q ..] of block kb (a token that does not exist: the last one again, or one that keeps nothing; its sums are
+    // not stored).  No branch around any load: eight of
+    // them, one after the other behind a look into the list, held every unit up (one layer of 5120 x 13824 at 16 tokens 87.1 / 86.3 us,
+    // six of 2048 x 8192 136 / 135).
+    auto h_load = [&](unsigned int (&hv)[MT][8], int kb) {
+        int row[8];
+        rows8(row, 32 * kb + 8 * q);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) hv[mt][i] = p.hbuf[(size_t)row[i] * (16 * MT) + (MT == 1 ? min(n, B - 1) : 16 * mt + n)];
+    };
+    // W_down[32 list entries][128 columns]: quarter-waves read 256-byte row pieces, lane group q the entries 8 q ..; columns past d cannot
+    // occur for the supported widths (d is a multiple of 256)
+    const char *wcol = p.wd + (size_t)(col0 + sub * DN_SUB + 8 * n) * 2;
     auto w_load = [&](u32x4 (&wv)[8], int kb) {
+        int row[8];
 #pragma unroll
-        for (int ii = 0; ii < 8; ++ii) {
-            const int c = lane + 64 * ii, row = c >> 4, cc = c & 15;
-            const int e = 32 * kb + row;
-            const int col = col0 + sub * DN_SUB + 8 * cc;
-            // rows past the list repeat the last row (their h is zero); columns past d cannot
-            // occur for the supported widths (d is a multiple of 256)
-            const int er = e < nrows ? e : nrows - 1;
-            wv[ii] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p.wd + (size_t)s_rows[er] * rowb + (size_t)col * 2));
-        }
+        for (int ii = 0; ii < 8; ++ii) row[ii] = s_rows[min(32 * kb + 4 * ii + q, nrows - 1)];
+#pragma unroll
+        for (int ii = 0; ii < 8; ++ii) wv[ii] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wcol + (size_t)row[ii] * rowb));
     };
-    auto process = [&](const u32x4 (&wv)[8], const u32x4 ahi, const u32x4 alo) {
+    auto stage = [&](const u32x4 (&wv)[8]) {
 #pragma unroll
-        for (int ii = 0; ii < 8; ++ii) {
-            const int c = lane + 64 * ii, row = c >> 4, cc = c & 15;
-            *reinterpret_cast<u32x4 *>(tile + row * DN_PITCH + cc * 16) = wv[ii];
-        }
+        for (int ii = 0; ii < 8; ++ii) *reinterpret_cast<u32x4 *>(tile + (4 * ii + q) * DN_PITCH + n * 16) = wv[ii];
+    };
+    auto process = [&](const u32x4 (&ahi)[MT], const u32x4 (&alo)[MT]) {
         // K-major B-fragments by transpose reads: in each 16-lane group lane t = 4r + c4 supplies
         // row 8q + r, columns 4*c4 .. 4*c4+3 and receives column t of rows 8q .. 8q+3
         const int r = (lane & 15) >> 2, c4 = lane & 3;
@@ -464,67 +504,85 @@ k_bat_down(const Args args)
             const s16x4 b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(src + 4 * DN_PITCH));
             const uint2 u0 = __builtin_bit_cast(uint2, b0), u1 = __builtin_bit_cast(uint2, b1);
             const u32x4 bf = {u0.x, u0.y, u1.x, u1.y};
-            acc[t] = mfma16(ahi, bf, acc[t]);
-            acc[t] = mfma16(alo, bf, acc[t]);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                acc[mt][t] = mfma16(ahi[mt], bf, acc[mt][t]);
+                acc[mt][t] = mfma16(alo[mt], bf, acc[mt][t]);
+            }
         }
     };
-    auto split_h = [&](const float (&hv)[8], u32x4 &ahi, u32x4 &alo) {
-        unsigned int hi16[8], lo16[8];
+    auto split_h = [&](unsigned int (&hv)[8], u32x4 &ahi, u32x4 &alo, int kb) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            hi16[i] = f32_to_bf16_bits(hv[i]);
-            lo16[i] = f32_to_bf16_bits(hv[i] - __uint_as_float(hi16[i] << 16));
+        for (int i = 0; i < 8; ++i) hv[i] = 32 * kb + 8 * q + i < nrows ? hv[i] : 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ahi[i] = (hv[2 * i] & 0xffffu) | (hv[2 * i + 1] << 16);
+            alo[i] = (hv[2 * i] >> 16) | (hv[2 * i + 1] & 0xffff0000u);
         }
-        ahi = u32x4{hi16[0] | (hi16[1] << 16), hi16[2] | (hi16[3] << 16), hi16[4] | (hi16[5] << 16), hi16[6] | (hi16[7] << 16)};
-        alo = u32x4{lo16[0] | (lo16[1] << 16), lo16[2] | (lo16[3] << 16), lo16[4] | (lo16[5] << 16), lo16[6] | (lo16[7] << 16)};
     };
 
     // A unit is requested and consumed in turn; the waves of two workgroups share a compute unit (at most 128
-    // registers per lane, 80 KiB of LDS each), and it is their loads that cover this wave's consumption.
+    // registers per lane, 80 KiB of LDS each; four waves a SIMD and no more: left to itself the compiler aims at six and waits for each load
+    // in turn, 13 % slower per call), and it is their loads that cover this wave's consumption.
     // (Requesting the next unit before consuming the current one needed 182 registers, one workgroup per
     // compute unit, and was 1.5 - 4 % slower per step, most with a sparse union.)
     u32x4 wA[8];
-    float hA[8];
+    unsigned int hA[MT][8];
     for (int kb = rw; kb < nkb; kb += 4) {
-        u32x4 ahi, alo;
-        h_load(hA, kb);
+        u32x4 ahi[MT], alo[MT];
+        if (MT == 1) h_load(hA, kb);
         w_load(wA, kb);
-        split_h(hA, ahi, alo);
-        process(wA, ahi, alo);
+        if (MT == 2) {                                       // (the order that 128 registers hold without spills)
+            __builtin_amdgcn_sched_barrier(0);
+            h_load(hA, kb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stage(wA);
+        if (MT == 2) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) split_h(hA[mt], ahi[mt], alo[mt], kb);
+        process(ahi, alo);
     }
 
     // ---- fixed-order fold of the four row-waves of each column half through LDS, then the partial
     // y of this row group
     __syncthreads();
     float *s_red = reinterpret_cast<float *>(s_tile);                   // [2 halves][2][8 tiles][4][64]
-    constexpr int ACC_FLOATS = (DN_SUB / 16) * 4 * 64;
+    constexpr int ACC_FLOATS = MT * (DN_SUB / 16) * 4 * 64;
+    static_assert(4 * ACC_FLOATS * sizeof(float) <= 8 * DN_TILE_BYTES, "the folds take the place of the tiles");
 #pragma unroll
     for (int s2 = 2; s2 >= 1; s2 >>= 1) {
         if (rw >= s2 && rw < 2 * s2) {
             float *dst = s_red + (size_t)(sub * 2 + (rw - s2)) * ACC_FLOATS;
 #pragma unroll
-            for (int t = 0; t < DN_SUB / 16; ++t)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) dst[(t * 4 + r) * 64 + lane] = acc[t][r];
+                for (int t = 0; t < DN_SUB / 16; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) dst[((mt * (DN_SUB / 16) + t) * 4 + r) * 64 + lane] = acc[mt][t][r];
         }
         __syncthreads();
         if (rw < s2) {
             const float *src = s_red + (size_t)(sub * 2 + rw) * ACC_FLOATS;
 #pragma unroll
-            for (int t = 0; t < DN_SUB / 16; ++t)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[t][r] += src[(t * 4 + r) * 64 + lane];
+                for (int t = 0; t < DN_SUB / 16; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[mt][t][r] += src[((mt * (DN_SUB / 16) + t) * 4 + r) * 64 + lane];
         }
         __syncthreads();
     }
     if (rw == 0) {
 #pragma unroll
-        for (int t = 0; t < DN_SUB / 16; ++t)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = 4 * q + r, col = col0 + sub * DN_SUB + t * 16 + n;
-                if (m < B && col < d) p.partial[((size_t)rg * p.rows + p.row0 + m) * d + col] = acc[t][r];
-            }
+            for (int t = 0; t < DN_SUB / 16; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int m = 16 * mt + 4 * q + r, col = col0 + sub * DN_SUB + t * 16 + n;
+                    if (m < B && col < d) p.partial[((size_t)rg * p.rows + p.row0 + m) * d + col] = acc[mt][t][r];
+                }
     }
 }
 
@@ -584,12 +642,20 @@ size_t clada_ws_decode_batched(int32_t d_ff)
            align_up(sizeof(int) * COOP_MAX_WGS, 256);
 }
 
-// Launch shape of the batched path for a layer and a pass of B tokens; false when the shape is not eligible
+// Passes over the weights of a batch, of nearly equal size: 16 tokens each, or 32 in two tiles where their x fits the registers and their h the
+// room that a call of more than 16 tokens has beside its partial outputs (CLADA_BAT_WIDE floats).
+int clada_batched_passes(const clada_layer *layer, int32_t B)
+{
+    const int most = B > 16 && layer->d <= 4096 && layer->d_ff <= 16 * (int64_t)layer->d ? 32 : 16;
+    return (B + most - 1) / most;
+}
+
+// Launch shape of the batched path for a layer and a pass of B tokens in tiles of 16; false when the shape is not eligible
 // (decided by dtype and sizes alone, before anything is launched).
-static bool bat_plan(const clada_ctx *ctx, const clada_layer *layer, int B, int *P_out, int *CG_out, int *RG_out)
+static bool bat_plan(const clada_ctx *ctx, const clada_layer *layer, int B, int tiles, int *P_out, int *CG_out, int *RG_out)
 {
     const int d = layer->d, F = layer->d_ff;
-    if (layer->dtype != CLADA_BF16 || B < 2 || B > 16) return false;
+    if (layer->dtype != CLADA_BF16 || B < 1 || (B < 2 && tiles < 2) || B > 16 * tiles) return false;
     const int ksteps = d / 256;                                  // 8 waves x ksteps x 32 = d (5 waves x 16 or 32 x 32 for ksteps 10, 20)
     if (d % 256 != 0 || !(ksteps == 4 || ksteps == 8 || ksteps == 10 || ksteps == 12 || ksteps == 16 || ksteps == 20 ||
                           ksteps == 24 || ksteps == 32))
@@ -615,13 +681,13 @@ static bool bat_plan(const clada_ctx *ctx, const clada_layer *layer, int B, int 
     return true;
 }
 
-bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *layer, int32_t B)
+bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *layer, int32_t B, int tiles)
 {
     int P, CG, RG;
-    return bat_plan(ctx, layer, B, &P, &CG, &RG);
+    return bat_plan(ctx, layer, B, tiles, &P, &CG, &RG);
 }
 
-// Bytes of partial outputs one pass of the batched path writes at most: [RG <= 64][B <= 16][d] fp32.
+// Bytes of partial outputs one pass of up to 16 tokens writes at most: [RG <= 64][B <= 16][d] fp32.
 size_t clada_ws_decode_batched_partial(int32_t d)
 {
     return align_up(sizeof(float) * 64 * 16 * (size_t)d, 256);
@@ -637,30 +703,32 @@ static clada_status bat_launch(clada_ctx *ctx, const Args &args, const BatParams
     const int d = p.d;
     const bool list = p.list != nullptr;
     const dim3 grid(p.P, n_pass, n_layers);
-#define CLADA_BAT_LAUNCH(KS, NW, RELU)                                                                                                \
-    {                                                                                                                                  \
-        if (list)       hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, LONE, RELU, Args>), grid, dim3(NW * 64), 0, stream, args);   \
-        else if (dense) hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, false, RELU, Args>), grid, dim3(NW * 64), 0, stream, args);  \
-        else            hipLaunchKernelGGL((k_bat_gateup<KS, NW, false, false, RELU, Args>), grid, dim3(NW * 64), 0, stream, args); \
+#define CLADA_BAT_LAUNCH(KS, NW, RELU, MT)                                                                                                \
+    {                                                                                                                                      \
+        if (list)       hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, LONE, RELU, MT, Args>), grid, dim3(NW * 64), 0, stream, args);   \
+        else if (dense) hipLaunchKernelGGL((k_bat_gateup<KS, NW, true, false, RELU, MT, Args>), grid, dim3(NW * 64), 0, stream, args);  \
+        else            hipLaunchKernelGGL((k_bat_gateup<KS, NW, false, false, RELU, MT, Args>), grid, dim3(NW * 64), 0, stream, args); \
     }
-#define CLADA_BAT_CASE(D, KS, NW)                                                                            \
-    if (d == D) {                                                                                             \
+#define CLADA_BAT_CASE(D, KS, NW, MT)                                                                        \
+    if (d == D && p.mt == MT) {                                                                               \
         static_assert(D == NW * 32 * KS, "waves x k-steps x 32 = d");                                         \
-        if (relu) CLADA_BAT_LAUNCH(KS, NW, true) else CLADA_BAT_LAUNCH(KS, NW, false)                         \
+        if (relu) CLADA_BAT_LAUNCH(KS, NW, true, MT) else CLADA_BAT_LAUNCH(KS, NW, false, MT)                 \
     }
-    CLADA_BAT_CASE(1024, 4, 8) CLADA_BAT_CASE(2048, 8, 8) CLADA_BAT_CASE(2560, 16, 5) CLADA_BAT_CASE(3072, 12, 8)
-    CLADA_BAT_CASE(4096, 16, 8) CLADA_BAT_CASE(5120, 32, 5) CLADA_BAT_CASE(6144, 24, 8) CLADA_BAT_CASE(8192, 32, 8)
+    CLADA_BAT_CASE(1024, 4, 8, 1) CLADA_BAT_CASE(2048, 8, 8, 1) CLADA_BAT_CASE(2560, 16, 5, 1) CLADA_BAT_CASE(3072, 12, 8, 1)
+    CLADA_BAT_CASE(4096, 16, 8, 1) CLADA_BAT_CASE(5120, 32, 5, 1) CLADA_BAT_CASE(6144, 24, 8, 1) CLADA_BAT_CASE(8192, 32, 8, 1)
+    CLADA_BAT_CASE(1024, 4, 8, 2) CLADA_BAT_CASE(2048, 8, 8, 2) CLADA_BAT_CASE(2560, 16, 5, 2) CLADA_BAT_CASE(3072, 12, 8, 2)
+    CLADA_BAT_CASE(4096, 16, 8, 2)
 #undef CLADA_BAT_LAUNCH
 #undef CLADA_BAT_CASE
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     const size_t lds = 8 * (size_t)DN_TILE_BYTES + sizeof(int) * DN_MAX_ROWS;
-    static std::atomic<bool> attr_set{false};                           // set once per process and kernel (two first callers may both set it)
-    if (!attr_set.load(std::memory_order_relaxed)) {
-        CLADA_CHECK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_bat_down<Args>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        attr_set.store(true, std::memory_order_relaxed);
+    static std::atomic<bool> attr_set[2];                               // set once per process and kernel (two first callers may both set it)
+    const auto down = p.mt == 2 ? k_bat_down<2, Args> : k_bat_down<1, Args>;
+    if (!attr_set[p.mt - 1].load(std::memory_order_relaxed)) {
+        CLADA_CHECK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(down), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        attr_set[p.mt - 1].store(true, std::memory_order_relaxed);
     }
-    hipLaunchKernelGGL(k_bat_down<Args>, dim3(p.CG * p.RG, n_pass, n_layers), dim3(512), lds, stream, args);
+    hipLaunchKernelGGL(down, dim3(p.CG * p.RG, n_pass, n_layers), dim3(512), lds, stream, args);
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     return CLADA_OK;
 }
@@ -679,13 +747,14 @@ clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int3
 {
     *ran = false;
     const int d = layers[0].d, F = layers[0].d_ff;
-    const int n_pass = (B + 15) / 16, per = (B + n_pass - 1) / n_pass;
+    const int n_pass = clada_batched_passes(&layers[0], B), per = (B + n_pass - 1) / n_pass, mt = per > 16 ? 2 : 1;
+    const int n16 = (B + 15) / 16;                           // (the rule below is by passes of 16)
     const double layer_bytes = (layers[0].kind == CLADA_FFN_RELU ? 2.0 : 3.0) * F * d * 2;
-    if (L < 2 || (per > 4 && layer_bytes > 340e6 && layer_bytes * L * n_pass > 12e9)) return CLADA_OK;
+    if (L < 2 || ((B + n16 - 1) / n16 > 4 && layer_bytes > 340e6 && layer_bytes * L * n16 > 12e9)) return CLADA_OK;
     int P, CG, RG;
-    if (!bat_plan(ctx, &layers[0], B - (n_pass - 1) * per, &P, &CG, &RG) || !bat_plan(ctx, &layers[0], per, &P, &CG, &RG)) return CLADA_OK;
+    if (!bat_plan(ctx, &layers[0], B - (n_pass - 1) * per, mt, &P, &CG, &RG) || !bat_plan(ctx, &layers[0], per, mt, &P, &CG, &RG)) return CLADA_OK;
     const size_t part = sizeof(float) * (size_t)RG * B * d;
-    const size_t per_layer = part + n_pass * (sizeof(float) * 16 * (size_t)F + sizeof(int) * ((size_t)F + COOP_MAX_WGS));
+    const size_t per_layer = part + n_pass * (sizeof(float) * 16 * mt * (size_t)F + sizeof(int) * ((size_t)F + COOP_MAX_WGS));
     int nl = bytes < 768 ? 0 : (int)((bytes - 768) / per_layer < (size_t)L ? (bytes - 768) / per_layer : (size_t)L);
     if (nl > BAT_UNITS / n_pass) nl = BAT_UNITS / n_pass;
     if (nl < 2) return CLADA_OK;
@@ -693,7 +762,7 @@ clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int3
     nl = (L + n_launch - 1) / n_launch;
     const bool relu = layers[0].kind == CLADA_FFN_RELU;
     char *hb = scratch + align_up(part * nl, 256);
-    char *ul = hb + align_up(sizeof(float) * 16 * (size_t)F * n_pass * nl, 256);
+    char *ul = hb + align_up(sizeof(float) * 16 * mt * (size_t)F * n_pass * nl, 256);
     char *uc = ul + align_up(sizeof(int) * (size_t)F * n_pass * nl, 256);
     for (int l0 = 0; l0 < L; l0 += nl) {
         const int n = L - l0 < nl ? L - l0 : nl;
@@ -702,9 +771,9 @@ clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int3
         memset(&a, 0, sizeof(a));
         BatParams &p = a.p;
         p.x = (const char *)x + row * d * 2; p.tau = tau ? tau + row : nullptr;
-        p.hbuf = reinterpret_cast<float *>(hb); p.ulist = reinterpret_cast<int *>(ul); p.ucnt = reinterpret_cast<int *>(uc);
+        p.hbuf = reinterpret_cast<unsigned int *>(hb); p.ulist = reinterpret_cast<int *>(ul); p.ucnt = reinterpret_cast<int *>(uc);
         p.partial = reinterpret_cast<float *>(scratch);
-        p.d = d; p.F = F; p.B = B; p.P = P; p.RG = RG; p.CG = CG; p.rows = n * B;
+        p.d = d; p.F = F; p.B = B; p.P = P; p.RG = RG; p.CG = CG; p.rows = n * B; p.mt = mt;
         p.gelu = layers[0].kind == CLADA_FFN_GEGLU ? 1 : 0;
         a.n_pass = n_pass; a.per_pass = per;
         bool bias = false;
@@ -732,25 +801,27 @@ clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int3
     return CLADA_OK;
 }
 
-// Runs the batched MFMA path when the shape is eligible (*ran; an ineligible shape launches nothing and the
-// caller uses the generic kernels).
+// Runs the batched MFMA path for a pass of B tokens in tiles of 16 when the shape is eligible (*ran; an ineligible shape launches nothing
+// and the caller uses the generic kernels).
 clada_status clada_decode_batched(clada_ctx *ctx, const clada_layer *layer, const void *x, int32_t B,
                                   const float *tau, void *y, unsigned char *keep, float *partial,
-                                  char *scratch, bool dense, hipStream_t stream, bool *ran,
+                                  char *scratch, bool dense, hipStream_t stream, bool *ran, int tiles,
                                   const int32_t *list, const int32_t *list_n)
 {
     *ran = false;
     const int d = layer->d, F = layer->d_ff;
     int P, CG, RG;
-    if (!bat_plan(ctx, layer, B, &P, &CG, &RG)) return CLADA_OK;
+    if (!bat_plan(ctx, layer, B, tiles, &P, &CG, &RG)) return CLADA_OK;
 
     BatParams p;
     p.wg = (const char *)layer->w_gate; p.wu = (const char *)layer->w_up; p.wd = (const char *)layer->w_down;
     p.b_in = layer->b_in;
     p.x = (const char *)x; p.tau = tau;
-    p.hbuf = reinterpret_cast<float *>(scratch);
-    p.ulist = reinterpret_cast<int *>(scratch + align_up(sizeof(float) * 16 * (size_t)F, 256));
-    p.ucnt = reinterpret_cast<int *>(scratch + align_up(sizeof(float) * 16 * (size_t)F, 256) + align_up(sizeof(int) * (size_t)F, 256));
+    p.hbuf = reinterpret_cast<unsigned int *>(scratch);
+    const size_t h_bytes = align_up(sizeof(float) * 16 * tiles * (size_t)F, 256);
+    p.ulist = reinterpret_cast<int *>(scratch + h_bytes);
+    p.ucnt = reinterpret_cast<int *>(scratch + h_bytes + align_up(sizeof(int) * (size_t)F, 256));
+    p.mt = tiles;
     p.keep = keep; p.partial = partial;
     p.d = d; p.F = F; p.B = B; p.P = P; p.RG = RG; p.CG = CG; p.row0 = 0; p.rows = B;
     p.gelu = layer->kind == CLADA_FFN_GEGLU ? 1 : 0;

@@ -354,6 +354,27 @@ def test_several_tokens_per_pass_on_the_vector_units(clada, cfg_name, d, F, B):
     assert_close_y(to_np(ys), oracle.decode_given_mask(*w, x, np.broadcast_to(keep, (B, F))), TOL_Y[cfg.dtype], "list run")
 
 
+# Passes of 17 to 32 tokens in two tiles: every width that has them, the edges of a tile and of a pass, one pass and two (the second one a
+# single tile or short), more than 64 neurons a workgroup, the widest layer for its rows and one past it (passes of 16)
+@pytest.mark.parametrize("cfg_name,d,F,B", [
+    ("c2", 1024, 777, 17), ("c2", 1024, 16384, 31), ("c2", 1024, 16385, 20), ("c2", 2048, 700, 32), ("c2", 2048, 300, 33), ("c2", 2560, 640, 18),
+    ("c2", 2560, 900, 49), ("c2", 3072, 500, 32), ("c2", 4096, 3000, 17), ("c2", 4096, 255, 48),
+])
+def test_two_tiles_of_tokens_a_pass(clada, cfg_name, d, F, B):
+    """Thresholds spread over the tokens (one keeps nothing); the dense twin and a list run go through the same kernels."""
+    cfg, w, x = _case(cfg_name, 31, d, F, B)
+    tau = _tau_for(w, x, 0.45) * np.resize(np.array([1.0, 1.8, 1e9, 0.08, 1.3], np.float32), B)
+    ctx, layer, xd, y, idx, cnt, mask = _run_sparse(clada, cfg, w, x, tau)
+    _check_against_oracle(cfg, w, x, tau, y, idx, cnt, mask, f"{cfg_name} d={d} F={F} B={B}")
+    yd = clada.dense_ffn_decode(ctx, layer, xd)
+    assert_close_y(to_np(yd), oracle.dense_decode(*w, x), TOL_Y[cfg.dtype], "dense twin")
+    lst = torch.arange(0, F, 3, dtype=torch.int32, device=DEV)
+    ys = clada.static_ffn_decode(ctx, layer, xd, lst, torch.tensor([lst.numel()], dtype=torch.int32, device=DEV))
+    keep = np.zeros(F, bool)
+    keep[::3] = True
+    assert_close_y(to_np(ys), oracle.decode_given_mask(*w, x, np.broadcast_to(keep, (B, F))), TOL_Y[cfg.dtype], "list run")
+
+
 def test_infinite_weight_of_a_neuron_a_token_cuts_stays_out_of_its_output(clada):
     """Token 0 keeps neuron 5, whose output row holds an infinity; token 1 cuts it and stays finite."""
     cfg, w, x = _case("c1", 22, 2048, 500, 2)

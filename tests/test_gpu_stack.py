@@ -339,6 +339,16 @@ def test_batched_launches_over_all_units_are_the_per_layer_calls_bit_for_bit(cla
             assert torch.equal(yd[l], clada.dense_ffn_decode(ctx, layers[l], x[l])), f"dense, layer {l}"
 
 
+# Passes of 17 to 32 tokens in two tiles: one pass, two (the second one a single tile), biases, and round the lanes
+@pytest.mark.parametrize("d,F,L,B,relu", [(1024, 700, 5, 20, True), (3072, 900, 7, 33, False), (2560, 600, 5, 64, True), (4096, 900, 7, 32, False),
+                                          (4096, 14400, 18, 32, False)])
+def test_stacks_in_two_tiles_a_pass_are_the_per_layer_calls_bit_for_bit(clada, d, F, L, B, relu):
+    if F > 14000:
+        test_lanes_are_the_per_layer_calls_bit_for_bit(clada, d, F, L, relu, B, False, 1)
+    else:
+        test_batched_launches_over_all_units_are_the_per_layer_calls_bit_for_bit(clada, d, F, L, B, relu)
+
+
 # d, F, L, relu, B, dense, option lane_occ2: stacks that go round the lanes.  Batch 1: rows of 12 and 16 KiB, a few 10 KiB rows
 # of large layers, dense stacks of 4 and 8 KiB rows with both kernel instances; batches: long stacks of large layers, one and
 # two passes of tokens.  Two layers' weights are listed in turn; every output row has its own input row and threshold.
