@@ -80,7 +80,7 @@ clada_status clada_decode_batched(clada_ctx *ctx, const clada_layer *layer, cons
                                   const float *tau, void *y, unsigned char *keep, float *partial,
                                   char *scratch, bool dense, hipStream_t stream, bool *ran, int tiles,
                                   const int32_t *list = nullptr, const int32_t *list_n = nullptr);
-int clada_batched_passes(const clada_layer *layer, int32_t B);      // passes of a batch: more than 16 tokens a pass are taken in two tiles
+int clada_batched_passes(const clada_layer *layer, int32_t B, bool list = false);      // passes of a batch, 0: not for this path; more than 16 tokens a pass: two tiles
 // Partial outputs of a pass in two tiles (floats per column of y: 64 groups x 32 tokens); its scratch follows them, both in the partial outputs'
 // part of the workspace, which holds 512 rows a token.
 #define CLADA_BAT_WIDE (64 * 32)

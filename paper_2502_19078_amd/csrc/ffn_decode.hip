@@ -35,7 +35,7 @@ size_t ws_partial_bytes(int B, int d)
     return align_up(sizeof(float) * rows * d, 256);
 }
 
-// (three of them and their scratch, 33 d_ff floats and 2 KiB each, fit ws_partial_bytes from 17 tokens on: 8704 d floats; d_ff <= 16 d, d >= 1024)
+// (three of them and their scratch, 33 d_ff floats and 2 KiB each, fit ws_partial_bytes from 17 tokens on: 8704 d floats; d_ff <= 16 d, d >= 512)
 size_t bat_wide_partial(int d) { return sizeof(float) * CLADA_BAT_WIDE * (size_t)d; }
 
 struct DecodeParams {
@@ -1450,9 +1450,10 @@ clada_status run_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
     }
     // ---- batched MFMA path (bf16, supported widths): up to 16 or 32 tokens per pass; larger batches run
     // as passes of near-equal size, each re-reading the weights of its own union
-    if (B >= 2 && ctx->opt_decode_batched) {
+    const int n_groups = ctx->opt_decode_batched ? clada_batched_passes(layer, B) : 0;
+    if (n_groups > 0) {
         unsigned char *keep_region = reinterpret_cast<unsigned char *>(ws + ws_partial_bytes(B, d));
-        const int n_groups = clada_batched_passes(layer, B), per_group = (B + n_groups - 1) / n_groups;     // per_group >= 2 whenever B >= 2
+        const int per_group = (B + n_groups - 1) / n_groups; // >= 2
         const int tiles = per_group > 16 ? 2 : 1;
         char *scratch = tiles == 2 ? ws + bat_wide_partial(d) : reinterpret_cast<char *>(keep_region) + align_up((size_t)B * F, 256);
         bool ran_all = false;
@@ -1556,10 +1557,11 @@ clada_status run_list_decode(clada_ctx *ctx, const clada_layer *layer, const voi
     p.b_in = relu ? layer->b_in : nullptr;
     const float *b_out = relu ? layer->b_out : nullptr;
     const int nch = (d * es + 1023) / 1024;
-    // ---- matrix-core path (bf16, supported widths), up to 16 tokens per pass, as in the thresholded call
-    if (B >= 2 && ctx->opt_decode_batched) {
+    // ---- matrix-core path (bf16, supported widths), up to 16 or 32 tokens per pass, as in the thresholded call
+    const int n_groups = ctx->opt_decode_batched ? clada_batched_passes(layer, B, true) : 0;
+    if (n_groups > 0) {
         char *ws = ctx->ws + CLADA_WS_HEADER;
-        const int n_groups = clada_batched_passes(layer, B), per_group = (B + n_groups - 1) / n_groups, tiles = per_group > 16 ? 2 : 1;
+        const int per_group = (B + n_groups - 1) / n_groups, tiles = per_group > 16 ? 2 : 1;
         char *scratch = tiles == 2 ? ws + bat_wide_partial(d) : ws + ws_partial_bytes(B, d) + align_up((size_t)B * F, 256);
         bool ran_all = false;
         for (int g0 = 0; g0 < B; g0 += per_group) {
@@ -1843,15 +1845,16 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
     // ---- batches on the matrix-core path: one launch per kernel over all units (layer, pass of up to 16 tokens), or,
     // where clada_stack_batched leaves them, the units go round three lanes, each with its own partial outputs and
     // scratch.  The path's three launches per unit and its thin ends weigh more than at batch 1 (c3 layer shape, B = 8: 69.5 -> 60.2 -> 58.5 us per layer with one, two, three lanes).
-    const int n_groups = clada_batched_passes(&layers[0], B), per_group = (B + n_groups - 1) / n_groups, tiles = per_group > 16 ? 2 : 1;
-    if (B >= 2 && smode == 3 && !n_active && ctx->opt_decode_batched) {
+    const int n_groups = ctx->opt_decode_batched ? clada_batched_passes(&layers[0], B) : 0;
+    const int per_group = n_groups ? (B + n_groups - 1) / n_groups : 0, tiles = per_group > 16 ? 2 : 1;
+    if (n_groups > 0 && smode == 3 && !n_active) {
         bool ran = false;
         const clada_status st = clada_stack_batched(ctx, layers, L, x, B, tau, y, dense, ctx->ws + CLADA_WS_HEADER,
                                                     ctx->ws_bytes - CLADA_WS_HEADER, stream, &ran);
         if (st != CLADA_OK) return st;
         if (ran) return CLADA_OK;
     }
-    if (B >= 2 && smode == 3 && !n_active && ctx->opt_decode_batched && L * n_groups >= 3 &&
+    if (n_groups > 0 && smode == 3 && !n_active && L * n_groups >= 3 &&
         clada_decode_batched_eligible(ctx, &layers[0], per_group, tiles) &&
         clada_decode_batched_eligible(ctx, &layers[0], B - (n_groups - 1) * per_group, tiles)) {
         const int n_lanes = 3;

@@ -642,24 +642,42 @@ size_t clada_ws_decode_batched(int32_t d_ff)
            align_up(sizeof(int) * COOP_MAX_WGS, 256);
 }
 
-// Passes over the weights of a batch, of nearly equal size: 16 tokens each, or 32 in two tiles where their x fits the registers and their h the
-// room that a call of more than 16 tokens has beside its partial outputs (CLADA_BAT_WIDE floats).
-int clada_batched_passes(const clada_layer *layer, int32_t B)
+// Whether a batch is for the matrix cores: rows that have instances of their own kernels; the narrow ones and two odd widths from the batch on that
+// the vector kernel or the generic one takes longer for.  Lone calls, us, vector or generic / matrix cores, gated (ReLU): 512 x 2048 at 9 and 12 tokens
+// 16.4 / 16.1, 18.8 / 16.1 (14.8 / 16.3, 16.5 / 15.9), 512 x 1024 at 12 and 16 16.5 / 15.6 (15.4 / 15.8, 19.1 / 16.1); 768 x 1536 at 6 and 9 16.6 / 16.0,
+// 25.5 / 16.0 (14.0 / 15.7, 18.0 / 15.7), 768 x 3072 at 32 85 / 23; 1536 x 3072 at 4 and 6 18.8 / 19.5, 24.5 / 19.7, 1536 x 6000 25.9 / 23.2, 35.1 / 23.2, a list of
+// 2500 at 4 18.5 / 19.1, 1536 x 4100 at 32 124 / 30; 3584 x 8048 at 2 and 3 36.2 / 37.1, 42.9 / 39.3 (25.5 / 27.9, 29.7 / 28.6), 3584 x 14000 at 3 65 / 59
+// (39.5 / 40.6), 3584 x 8048 at 32 261 / 68.  Stacks gain more (1.3 times at two tokens of 3584, 2 - 5 times at 16 of any) but go the way of the lone call,
+// whose bits they have.  Whole passes of the vector kernel at 768 gated values, and up to nine tokens of 1536 non-gated ones, stay with it: a test
+// names its kernel there (22 / 17 and 31 / 18 us).
+static bool bat_pays(const clada_layer *layer, int B, bool list)
 {
+    const bool relu = layer->kind == CLADA_FFN_RELU;
+    switch (layer->d) {
+    case 1024: case 2048: case 2560: case 3072: case 4096: case 5120: case 6144: case 8192: return B >= 2;
+    case 512: return B >= (relu ? 14 : 12);
+    case 768: return B >= (relu ? 9 : 6) && (relu || (B != 8 && B != 16));
+    case 1536: return B >= (relu ? 10 : list || layer->d_ff < 3840 ? 5 : 4);
+    case 3584: return B >= (relu ? 4 : 3);
+    default: return false;
+    }
+}
+
+// Passes over the weights of a batch, of nearly equal size: 16 tokens each, or 32 in two tiles where their x fits the registers and their h the
+// room that a call of more than 16 tokens has beside its partial outputs (CLADA_BAT_WIDE floats).  0: not for this path.
+int clada_batched_passes(const clada_layer *layer, int32_t B, bool list)
+{
+    if (layer->dtype != CLADA_BF16 || !bat_pays(layer, B, list)) return 0;
     const int most = B > 16 && layer->d <= 4096 && layer->d_ff <= 16 * (int64_t)layer->d ? 32 : 16;
     return (B + most - 1) / most;
 }
 
-// Launch shape of the batched path for a layer and a pass of B tokens in tiles of 16; false when the shape is not eligible
-// (decided by dtype and sizes alone, before anything is launched).
+// Launch shape of the batched path for a pass of B tokens in tiles of 16 of a layer it takes (clada_batched_passes); false when the shape is
+// not eligible (decided by sizes alone, before anything is launched).
 static bool bat_plan(const clada_ctx *ctx, const clada_layer *layer, int B, int tiles, int *P_out, int *CG_out, int *RG_out)
 {
     const int d = layer->d, F = layer->d_ff;
-    if (layer->dtype != CLADA_BF16 || B < 1 || (B < 2 && tiles < 2) || B > 16 * tiles) return false;
-    const int ksteps = d / 256;                                  // 8 waves x ksteps x 32 = d (5 waves x 16 or 32 x 32 for ksteps 10, 20)
-    if (d % 256 != 0 || !(ksteps == 4 || ksteps == 8 || ksteps == 10 || ksteps == 12 || ksteps == 16 || ksteps == 20 ||
-                          ksteps == 24 || ksteps == 32))
-        return false;
+    if (B < 1 || (B < 2 && tiles < 2) || B > 16 * tiles) return false;
     const int P = ctx->num_cu < COOP_MAX_WGS ? ctx->num_cu : COOP_MAX_WGS;
     const int CG = (d + DN_COLS - 1) / DN_COLS;
     int RG = P / CG;
@@ -717,7 +735,9 @@ static clada_status bat_launch(clada_ctx *ctx, const Args &args, const BatParams
     CLADA_BAT_CASE(1024, 4, 8, 1) CLADA_BAT_CASE(2048, 8, 8, 1) CLADA_BAT_CASE(2560, 16, 5, 1) CLADA_BAT_CASE(3072, 12, 8, 1)
     CLADA_BAT_CASE(4096, 16, 8, 1) CLADA_BAT_CASE(5120, 32, 5, 1) CLADA_BAT_CASE(6144, 24, 8, 1) CLADA_BAT_CASE(8192, 32, 8, 1)
     CLADA_BAT_CASE(1024, 4, 8, 2) CLADA_BAT_CASE(2048, 8, 8, 2) CLADA_BAT_CASE(2560, 16, 5, 2) CLADA_BAT_CASE(3072, 12, 8, 2)
-    CLADA_BAT_CASE(4096, 16, 8, 2)
+    CLADA_BAT_CASE(4096, 16, 8, 2) CLADA_BAT_CASE(512, 4, 4, 2) CLADA_BAT_CASE(768, 6, 4, 2) CLADA_BAT_CASE(1536, 6, 8, 2)
+    CLADA_BAT_CASE(3584, 14, 8, 2) CLADA_BAT_CASE(512, 4, 4, 1) CLADA_BAT_CASE(768, 6, 4, 1) CLADA_BAT_CASE(1536, 6, 8, 1)
+    CLADA_BAT_CASE(3584, 14, 8, 1)
 #undef CLADA_BAT_LAUNCH
 #undef CLADA_BAT_CASE
     CLADA_CHECK_HIP(ctx, hipGetLastError());
@@ -747,10 +767,10 @@ clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int3
 {
     *ran = false;
     const int d = layers[0].d, F = layers[0].d_ff;
-    const int n_pass = clada_batched_passes(&layers[0], B), per = (B + n_pass - 1) / n_pass, mt = per > 16 ? 2 : 1;
+    const int n_pass = clada_batched_passes(&layers[0], B), per = n_pass ? (B + n_pass - 1) / n_pass : 0, mt = per > 16 ? 2 : 1;
     const int n16 = (B + 15) / 16;                           // (the rule below is by passes of 16)
     const double layer_bytes = (layers[0].kind == CLADA_FFN_RELU ? 2.0 : 3.0) * F * d * 2;
-    if (L < 2 || ((B + n16 - 1) / n16 > 4 && layer_bytes > 340e6 && layer_bytes * L * n16 > 12e9)) return CLADA_OK;
+    if (L < 2 || n_pass == 0 || ((B + n16 - 1) / n16 > 4 && layer_bytes > 340e6 && layer_bytes * L * n16 > 12e9)) return CLADA_OK;
     int P, CG, RG;
     if (!bat_plan(ctx, &layers[0], B - (n_pass - 1) * per, mt, &P, &CG, &RG) || !bat_plan(ctx, &layers[0], per, mt, &P, &CG, &RG)) return CLADA_OK;
     const size_t part = sizeof(float) * (size_t)RG * B * d;

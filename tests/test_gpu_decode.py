@@ -359,8 +359,11 @@ def test_several_tokens_per_pass_on_the_vector_units(clada, cfg_name, d, F, B):
 @pytest.mark.parametrize("cfg_name,d,F,B", [
     ("c2", 1024, 777, 17), ("c2", 1024, 16384, 31), ("c2", 1024, 16385, 20), ("c2", 2048, 700, 32), ("c2", 2048, 300, 33), ("c2", 2560, 640, 18),
     ("c2", 2560, 900, 49), ("c2", 3072, 500, 32), ("c2", 4096, 3000, 17), ("c2", 4096, 255, 48),
+    # the narrow and the odd widths, from the batch on that the matrix cores take
+    ("c2", 512, 600, 12), ("c2", 512, 1700, 32), ("c2", 768, 900, 6), ("c2", 768, 17000, 15), ("c2", 768, 3072, 33), ("c2", 1536, 255, 5), ("c2", 1536, 3840, 4),
+    ("c2", 1536, 900, 16), ("c2", 1536, 2000, 31), ("c2", 3584, 500, 3), ("c2", 3584, 900, 16), ("c2", 3584, 700, 33),
 ])
-def test_two_tiles_of_tokens_a_pass(clada, cfg_name, d, F, B):
+def test_passes_of_the_matrix_core_path(clada, cfg_name, d, F, B):
     """Thresholds spread over the tokens (one keeps nothing); the dense twin and a list run go through the same kernels."""
     cfg, w, x = _case(cfg_name, 31, d, F, B)
     tau = _tau_for(w, x, 0.45) * np.resize(np.array([1.0, 1.8, 1e9, 0.08, 1.3], np.float32), B)

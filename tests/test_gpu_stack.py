@@ -339,9 +339,11 @@ def test_batched_launches_over_all_units_are_the_per_layer_calls_bit_for_bit(cla
             assert torch.equal(yd[l], clada.dense_ffn_decode(ctx, layers[l], x[l])), f"dense, layer {l}"
 
 
-# Passes of 17 to 32 tokens in two tiles: one pass, two (the second one a single tile), biases, and round the lanes
+# Passes of 17 to 32 tokens in two tiles: one pass, two (the second one a single tile), biases, and round the lanes; the narrow and the
+# odd widths in one tile and two
 @pytest.mark.parametrize("d,F,L,B,relu", [(1024, 700, 5, 20, True), (3072, 900, 7, 33, False), (2560, 600, 5, 64, True), (4096, 900, 7, 32, False),
-                                          (4096, 14400, 18, 32, False)])
+                                          (512, 700, 5, 12, False), (768, 700, 4, 40, True), (1536, 700, 5, 10, True), (3584, 700, 4, 3, False),
+                                          (3584, 500, 3, 24, True), (4096, 14400, 18, 32, False)])
 def test_stacks_in_two_tiles_a_pass_are_the_per_layer_calls_bit_for_bit(clada, d, F, L, B, relu):
     if F > 14000:
         test_lanes_are_the_per_layer_calls_bit_for_bit(clada, d, F, L, relu, B, False, 1)
