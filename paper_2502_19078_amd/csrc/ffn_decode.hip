@@ -1448,6 +1448,20 @@ clada_status run_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
             return CLADA_OK;
         }
     }
+    // ---- other whole-KiB rows at batch 1: the kernel of the whole-stack calls over one layer
+    if (ctx->opt_decode_b1 >= 1 && B == 1 && clada_stack_b1_only(layer) && ctx->num_cu >= COOP_MAX_WGS && F >= COOP_MAX_WGS &&
+        F <= 1024 * COOP_MAX_WGS) {
+        if (ctx->opt_diag_events) CLADA_CHECK_HIP(ctx, hipEventRecord(ctx->ev[0], stream));
+        CLADA_CHECK_HIP(ctx, clada_stack_b1_lone(layer, x, tau, dense, p.partial, p.keep, stream));
+        if (ctx->opt_diag_events) CLADA_CHECK_HIP(ctx, hipEventRecord(ctx->ev[1], stream));
+        launch_finalize(es, p.partial, COOP_MAX_WGS, 1, d, (char *)y, nullptr, stream, ctx->opt_diag_events ? ctx->ev[2] : nullptr, ctx->ev[3], b_out);
+        CLADA_CHECK_HIP(ctx, hipGetLastError());
+        if (lists) {
+            hipLaunchKernelGGL(k_ffn_lists, dim3(1), dim3(1024), 0, stream, p.keep, B, F, active_idx, n_active, mask_bits);
+            CLADA_CHECK_HIP(ctx, hipGetLastError());
+        }
+        return CLADA_OK;
+    }
     // ---- batched MFMA path (bf16, supported widths): up to 16 or 32 tokens per pass; larger batches run
     // as passes of near-equal size, each re-reading the weights of its own union
     const int n_groups = ctx->opt_decode_batched ? clada_batched_passes(layer, B) : 0;
@@ -1785,9 +1799,10 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
     // for them runs the per-layer calls below.
     const int smode = ctx->opt_decode_stack;
     if (smode == 3) CLADA_CHECK_HIP(ctx, lanes_first_call(ctx, stream));
-    const bool own_launches = B == 1 && smode >= 2 && ctx->opt_decode_b1 >= 1 && !n_active && (d * es) % 1024 == 0 &&
-                              b1_shape_ok(es, nch, relu) && Pb == COOP_MAX_WGS && F >= Pb && ni_b <= 1024 && L >= 2;
-    if (own_launches && smode == 3 && clada_stack_b1_fits(&layers[0], L, dense)) {
+    const bool b1_stack = B == 1 && smode >= 2 && ctx->opt_decode_b1 >= 1 && !n_active && (d * es) % 1024 == 0 &&
+                          Pb == COOP_MAX_WGS && F >= Pb && ni_b <= 1024 && L >= 2;
+    const bool own_launches = b1_stack && b1_shape_ok(es, nch, relu);
+    if (b1_stack && smode == 3 && clada_stack_b1_fits(&layers[0], L, dense)) {
         CLADA_CHECK_HIP(ctx, clada_stack_b1(layers, L, x, tau, y, dense, reinterpret_cast<float *>(ctx->ws + CLADA_WS_HEADER),
                                             ctx->ws_bytes - CLADA_WS_HEADER, stream));
         return CLADA_OK;

@@ -14,28 +14,33 @@
 namespace {
 
 constexpr int CLASSES = 256, SLICES = 32, CHAIN = CLASSES / SLICES;
+constexpr int KEEP_ROUNDS = 16;             // rounds of 64 neurons of a class whose keep flags can be asked for
 
-struct StackLaunch {                        // kernel argument; the tables are read by scalar loads at the layer's index
-    const char *wg[CLADA_STACK_LAUNCH_LAYERS], *wu[CLADA_STACK_LAUNCH_LAYERS], *wd[CLADA_STACK_LAUNCH_LAYERS];
-    const float *b_in[CLADA_STACK_LAUNCH_LAYERS];
+template <int N> struct StackTables {        // kernel argument; the tables are read by scalar loads at the layer's index
+    const char *wg[N], *wu[N], *wd[N];
+    const float *b_in[N];
     const char *x;                          // [n][d]
     const float *tau;                       // [n] (unused when dense)
     float *partial;                         // [n][256 / chain][d]
+    unsigned char *keep;                    // a single layer's [F] keep flags, or nullptr
     int F, d, chain, dense, gelu;
 };
-typedef const __attribute__((address_space(4))) StackLaunch *StackLaunchArgs;
+typedef StackTables<CLADA_STACK_LAUNCH_LAYERS> StackLaunch;
 
 // Per row length (NCH chunks of 1 KiB): the workgroup's waves and a wave's ring in LDS, two units of UC loads of 1 KiB.  A
 // unit is half a row, a row or two short rows; for the down projection UC * EPL kept rows of the wave's columns (one or half
 // a KiB).  The waves of a compute unit keep about 100 KiB of weight rows in flight; 7 TB/s take 55 KiB at 2 us of loaded
-// latency.  (Four waves for 2 KiB rows: 62 us per step of 24 layers of 8 MB against 67 us with eight.)
-template <int NCH> struct RowShape {
-    static constexpr int NW = NCH == 2 ? 4 : NCH;
-    static constexpr int UC = NCH % 5 == 0 ? 5 : 4;
+// latency.  (Four waves for 2 KiB rows: 62 us per step of 24 layers of 8 MB against 67 us with eight.)  Rows of 1 and 3 KiB have
+// two waves for every KiB as well; units of three loads serve the rows of 3 and 6 KiB, rows of 7 KiB go whole.
+// LONE: a single layer, one workgroup on a unit: more waves, the further ones for whole rows only.
+template <int NCH, bool LONE = false> struct RowShape {
+    static constexpr int NWC = NCH < 4 ? 2 * NCH : NCH;      // waves with columns of the kept rows
+    static constexpr int NW = !LONE || NCH > 7 ? NWC : NCH == 1 ? 4 : NCH == 7 ? 10 : 16;
+    static constexpr int UC = NCH % 5 == 0 ? 5 : NCH == 3 || NCH == 6 ? 3 : NCH == 7 ? 7 : 4;
     static constexpr int RD = 2;                             // units of a ring
     static constexpr int R = UC > NCH ? UC / NCH : 1;        // rows per gate / up unit
     static constexpr int PARTS = NCH > UC ? NCH / UC : 1;    // units per row
-    static constexpr int CWB = NCH * 1024 / NW;              // bytes of a row's columns per wave
+    static constexpr int CWB = NCH * 1024 / NWC;             // bytes of a row's columns per wave
     static constexpr int EPL = 1024 / CWB;                   // kept rows per down-projection load
     static_assert((R * NCH == UC || PARTS * UC == NCH) && (EPL == 1 || EPL == 2), "whole rows or whole parts");
 };
@@ -48,9 +53,19 @@ __device__ __forceinline__ unsigned int lds_offset(const void *p)
 // and would wait for every load in flight before any LDS access.  A load has no register result; its slot is read only
 // after the wait for the vector-memory counter below, and is refilled only after that read has returned.  The slot's address
 // reaches m0 through its constraint, so the compiler knows what m0 holds.
+template <bool VBASE = false>
 __device__ __forceinline__ void ring_load(const char *base, unsigned int voff, unsigned int slot)
 {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "{m0}"(slot) : "memory");
+    if constexpr (!VBASE) {
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "{m0}"(slot) : "memory");
+    } else {
+        // The base is the same in every lane, but the instances of 6 KiB rows compute it in vector registers.  A scalar register
+        // that a vector instruction has written may be a load's base five wait states later at the earliest, which the assembler
+        // does not see to.
+        const unsigned long long b = (unsigned long long)base;
+        const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)b), hi = __builtin_amdgcn_readfirstlane((unsigned int)(b >> 32));
+        asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(((unsigned long long)hi << 32) | lo), "{m0}"(slot) : "memory");
+    }
 }
 __device__ __forceinline__ void ring_load_lanes(const char *p, unsigned int slot)
 {
@@ -125,17 +140,83 @@ template <> __device__ __forceinline__ void ring_read<5, 4>(unsigned int a, Ring
                  : "v"(a) : "memory");
 }
 
+template <> __device__ __forceinline__ void ring_read_x<3>(unsigned int a, unsigned int b, u32x4 (&w)[3], u32x4 (&x)[3])
+{
+    asm volatile("ds_read_b128 %0, %6 offset:0\n\t"
+                 "ds_read_b128 %3, %7 offset:0\n\t"
+                 "ds_read_b128 %1, %6 offset:1024\n\t"
+                 "ds_read_b128 %4, %7 offset:1024\n\t"
+                 "ds_read_b128 %2, %6 offset:2048\n\t"
+                 "ds_read_b128 %5, %7 offset:2048\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2])
+                 : "v"(a), "v"(b) : "memory");
+}
+template <> __device__ __forceinline__ void ring_read_x<7>(unsigned int a, unsigned int b, u32x4 (&w)[7], u32x4 (&x)[7])
+{
+    asm volatile("ds_read_b128 %0, %14 offset:0\n\t"
+                 "ds_read_b128 %7, %15 offset:0\n\t"
+                 "ds_read_b128 %1, %14 offset:1024\n\t"
+                 "ds_read_b128 %8, %15 offset:1024\n\t"
+                 "ds_read_b128 %2, %14 offset:2048\n\t"
+                 "ds_read_b128 %9, %15 offset:2048\n\t"
+                 "ds_read_b128 %3, %14 offset:3072\n\t"
+                 "ds_read_b128 %10, %15 offset:3072\n\t"
+                 "ds_read_b128 %4, %14 offset:4096\n\t"
+                 "ds_read_b128 %11, %15 offset:4096\n\t"
+                 "ds_read_b128 %5, %14 offset:5120\n\t"
+                 "ds_read_b128 %12, %15 offset:5120\n\t"
+                 "ds_read_b128 %6, %14 offset:6144\n\t"
+                 "ds_read_b128 %13, %15 offset:6144\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6])
+                 : "v"(a), "v"(b) : "memory");
+}
+template <> __device__ __forceinline__ void ring_read<3, 2>(unsigned int a, RingWords<2>::type (&w)[3])
+{
+    asm volatile("ds_read_b64 %0, %3 offset:0\n\t"
+                 "ds_read_b64 %1, %3 offset:1024\n\t"
+                 "ds_read_b64 %2, %3 offset:2048\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2])
+                 : "v"(a) : "memory");
+}
+template <> __device__ __forceinline__ void ring_read<3, 4>(unsigned int a, RingWords<4>::type (&w)[3])
+{
+    asm volatile("ds_read_b128 %0, %3 offset:0\n\t"
+                 "ds_read_b128 %1, %3 offset:1024\n\t"
+                 "ds_read_b128 %2, %3 offset:2048\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2])
+                 : "v"(a) : "memory");
+}
+template <> __device__ __forceinline__ void ring_read<7, 4>(unsigned int a, RingWords<4>::type (&w)[7])
+{
+    asm volatile("ds_read_b128 %0, %7 offset:0\n\t"
+                 "ds_read_b128 %1, %7 offset:1024\n\t"
+                 "ds_read_b128 %2, %7 offset:2048\n\t"
+                 "ds_read_b128 %3, %7 offset:3072\n\t"
+                 "ds_read_b128 %4, %7 offset:4096\n\t"
+                 "ds_read_b128 %5, %7 offset:5120\n\t"
+                 "ds_read_b128 %6, %7 offset:6144\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6])
+                 : "v"(a) : "memory");
+}
+
 // One workgroup streams the rows of its neurons through per-wave rings in LDS.  Round r = 64 neurons: G(r) their gate rows
 // (whole rows, dealt to the waves), U(r) the W_up rows of those kept (likewise), D(r) the kept W_down rows, of which every
 // wave takes its own columns.  A wave loads and consumes in the order G0 G1 U0 D0 G2 U1 D1 ..: the list of round r is known
 // (barrier) while the rows of G(r + 1) are in flight, and the exchange of h (barrier) happens while D(r) is, so the stream
 // of loads never waits for either.
-template <int ES, int NCH, bool RELU>
-__global__ void __launch_bounds__(RowShape<NCH>::NW * 64)
-k_ffn_stack(const StackLaunch)
+template <int ES, int NCH, bool RELU, bool LONE = false>
+__global__ void __launch_bounds__((RowShape<NCH, LONE>::NW * 64))
+k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
 {
-    typedef RowShape<NCH> S;
-    constexpr int NW = S::NW, RD = S::RD, UC = S::UC, R = S::R, PARTS = S::PARTS, CWB = S::CWB, EPL = S::EPL;
+    typedef RowShape<NCH, LONE> S;
+    typedef const __attribute__((address_space(4))) StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS> *StackLaunchArgs;
+    constexpr bool VBASE = NCH == 6;
+    constexpr int NW = S::NW, NWC = S::NWC, RD = S::RD, UC = S::UC, R = S::R, PARTS = S::PARTS, CWB = S::CWB, EPL = S::EPL;
     constexpr int ROWB = NCH * 1024, UNIT = UC * 1024;
     constexpr int DW = CWB / 256, VEC = 4 * DW / ES;          // words / values of a kept row per lane
     constexpr int EPU = UC * EPL;                             // kept rows per down-projection unit
@@ -145,11 +226,12 @@ k_ffn_stack(const StackLaunch)
     __shared__ int s_keep[2][64];
     __shared__ int s_lrow[2][64], s_lcls[2][64];
     __shared__ float s_la[2][64], s_h[2][64];
+    __shared__ unsigned long long s_kept[LONE ? KEEP_ROUNDS : 1];
 
     const StackLaunchArgs ka = (StackLaunchArgs)__builtin_amdgcn_kernarg_segment_ptr();
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int layer = blockIdx.y, group = blockIdx.x, chain = ka->chain;
+    const int layer = LONE ? 0 : blockIdx.y, group = blockIdx.x, chain = ka->chain;
     const int F = ka->F, dense = ka->dense, gelu = ka->gelu;
     const char *wg = ka->wg[layer], *wu = ka->wu[layer], *wd = ka->wd[layer];
     const __attribute__((address_space(4))) float *b_in = (const __attribute__((address_space(4))) float *)(RELU ? ka->b_in[layer] : nullptr);
@@ -157,7 +239,7 @@ k_ffn_stack(const StackLaunch)
     const unsigned int loff = lane * 16;
     const unsigned int ring0 = lds_offset(&s_ring[0][0][0]) + wave * (RD * UNIT), x0 = lds_offset(s_x);
 
-    for (int c = wave; c < NCH; c += NW) ring_load(xg + c * 1024, loff, x0 + c * 1024);
+    for (int c = wave; c < NCH; c += NW) ring_load<VBASE>(xg + c * 1024, loff, x0 + c * 1024);
 
     // local neuron i = (class i / per, position i % per) of this workgroup: neuron group + 32 class + 256 position
     // when it takes a whole slice, group + 256 i when it takes one class
@@ -180,7 +262,7 @@ k_ffn_stack(const StackLaunch)
                 if (lr >= n_list) return false;              // not known yet: come back later
                 lim = kp2[lr & 1];
             }
-            if (li < lim) break;
+            if (li < (NWC < NW && ph == 2 && wave >= NWC ? 0 : lim)) break;
             if (ph == 0) {                                   // after G(lr): U(lr - 1); after G(0) the next round's rows
                 if (lr == 0 && n_round > 1) {
                     lr = 1; li = wave; jv_load = neuron_of(64 + lane); lim = min(64, n_local - 64);
@@ -214,7 +296,7 @@ k_ffn_stack(const StackLaunch)
                     row = wu + (size_t)__builtin_amdgcn_readfirstlane(s_lrow[lr & 1][i]) * ROWB;
                 }
 #pragma unroll
-                for (int c = 0; c < UC / R; ++c) ring_load(row + lp * UNIT + c * 1024, loff, slot + (q * (UC / R) + c) * 1024);
+                for (int c = 0; c < UC / R; ++c) ring_load<VBASE>(row + lp * UNIT + c * 1024, loff, slot + (q * (UC / R) + c) * 1024);
             }
             if (++lp == PARTS) { lp = 0; li += NW * R; }
         } else {
@@ -223,7 +305,7 @@ k_ffn_stack(const StackLaunch)
 #pragma unroll
                 for (int q = 0; q < UC; ++q) {
                     const int e = min(li + q, kp - 1);
-                    ring_load(wd + (size_t)__builtin_amdgcn_readfirstlane(s_lrow[lr & 1][e]) * ROWB + wave * CWB, loff, slot + q * 1024);
+                    ring_load<VBASE>(wd + (size_t)__builtin_amdgcn_readfirstlane(s_lrow[lr & 1][e]) * ROWB + wave * CWB, loff, slot + q * 1024);
                 }
             } else {                                         // EPL rows per load, the lanes shared out
                 constexpr int LPR = 64 / EPL;
@@ -331,6 +413,7 @@ k_ffn_stack(const StackLaunch)
             opens2[p] = __ballot(lane < kp && lcls != lprev);
             if (kp > 0) cur_cls = __builtin_amdgcn_readlane(lcls, kp - 1);
             kp2[p] = kp;
+            if (LONE && tid == 0) s_kept[r & (KEEP_ROUNDS - 1)] = mask;
             n_list = r + 1;
             fill();                                          // the ring may have run dry waiting for this list
         }
@@ -351,7 +434,7 @@ k_ffn_stack(const StackLaunch)
                 __syncthreads();
                 hs = s_h[p];
             }
-            for (int e0 = 0; e0 < kp; e0 += EPU) {
+            for (int e0 = 0; e0 < (wave < NWC ? kp : 0); e0 += EPU) {
                 const unsigned int slot = wait_oldest();
                 typename RingWords<DW>::type v[EPL][UC];
 #pragma unroll
@@ -381,8 +464,16 @@ k_ffn_stack(const StackLaunch)
     }
     close_class();
     float *dst = ka->partial + ((size_t)layer * gridDim.x + group) * ka->d + wave * (CWB / ES) + lane * VEC;
+    if (wave < NWC) {
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) dst[k] = sum[k];
+        for (int k = 0; k < VEC; ++k) dst[k] = sum[k];
+    }
+    if (LONE && ka->keep && wave == 0) {                             // written and read by this wave; stores during the stream would count as its loads
+        for (int r = 0; r < n_round && r < KEEP_ROUNDS; ++r) {
+            const int j = neuron_of(64 * r + lane);
+            if (j >= 0) ka->keep[j] = (unsigned char)((s_kept[r] >> lane) & 1ull);
+        }
+    }
 }
 
 struct StackReduceArgs {
@@ -443,25 +534,87 @@ k_ffn_stack_reduce(const StackReduceArgs a)
     }
 }
 
-// (The non-gated family has bf16 rows of 2, 5, 8 and 10 KiB only.)
 template <int ES, int NCH>
 hipError_t launch_rows(const StackLaunch &p, dim3 grid, bool relu, hipStream_t st)
 {
     constexpr int threads = RowShape<NCH>::NW * 64;
-    if (!relu) {
-        hipLaunchKernelGGL((k_ffn_stack<ES, NCH, false>), grid, dim3(threads), 0, st, p);
-        return hipGetLastError();
+    if constexpr (NCH != 12 && !(ES == 2 && NCH == 3)) {     // (gated rows of 12 KiB: lanes; of 3 KiB: per-layer calls)
+        if (!relu) {
+            hipLaunchKernelGGL((k_ffn_stack<ES, NCH, false>), grid, dim3(threads), 0, st, p);
+            return hipGetLastError();
+        }
     }
-    if constexpr (ES == 2 && NCH != 4) {
-        hipLaunchKernelGGL((k_ffn_stack<ES, NCH, true>), grid, dim3(threads), 0, st, p);
-        return hipGetLastError();
+    if constexpr (ES == 2) {
+        if (relu) {
+            hipLaunchKernelGGL((k_ffn_stack<ES, NCH, true>), grid, dim3(threads), 0, st, p);
+            return hipGetLastError();
+        }
+    }
+    return hipErrorNotSupported;
+}
+
+template <int ES, int NCH>
+hipError_t launch_lone(const StackTables<1> &p, bool relu, hipStream_t st)
+{
+    constexpr int threads = RowShape<NCH, true>::NW * 64;
+    if constexpr (ES == 2) {
+        if (relu) {
+            hipLaunchKernelGGL((k_ffn_stack<2, NCH, true, true>), dim3(CLASSES), dim3(threads), 0, st, p);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (NCH != 4 && NCH != 12 && !(ES == 2 && NCH == 3)) {      // (these gated rows do not come here)
+        if (!relu) {
+            hipLaunchKernelGGL((k_ffn_stack<ES, NCH, false, true>), dim3(CLASSES), dim3(threads), 0, st, p);
+            return hipGetLastError();
+        }
     }
     return hipErrorNotSupported;
 }
 
 }  // namespace
 
+// Single layers of clada_stack_b1_only.  us, lone calls, the generic kernel / this one, within a spread of
+// 0.5: 11.0 / 10.7 at 512 x 1376, 11.7 / 11.9 at 1536 x 6000 ReLU, 14.2 / 14.3 at 2048 x 8192 ReLU, 23.3 / 23.4 at 3072 x 8192, 26.3 / 26.7
+// at 3584 x 8496, ReLU 21.1 / 19.0, 42.7 / 38.2 at 6144 x 13000 ReLU.
+hipError_t clada_stack_b1_lone(const clada_layer *layer, const void *x, const float *tau, bool dense, float *partial,
+                               unsigned char *keep, hipStream_t stream)
+{
+    const int es = (int)dtype_size(layer->dtype), nch = layer->d * es / 1024;
+    const bool relu = layer->kind == CLADA_FFN_RELU;
+    StackTables<1> p;
+    p.wg[0] = (const char *)layer->w_gate; p.wu[0] = (const char *)layer->w_up; p.wd[0] = (const char *)layer->w_down;
+    p.b_in[0] = relu ? layer->b_in : nullptr;
+    p.x = (const char *)x; p.tau = tau; p.partial = partial; p.keep = keep;
+    p.F = layer->d_ff; p.d = layer->d; p.chain = 1; p.dense = dense ? 1 : 0;
+    p.gelu = layer->kind == CLADA_FFN_GEGLU ? 1 : 0;
+    switch (es == 2 ? nch : 100 + nch) {
+    case 1: return launch_lone<2, 1>(p, relu, stream);
+    case 3: return launch_lone<2, 3>(p, relu, stream);
+    case 4: return launch_lone<2, 4>(p, relu, stream);
+    case 6: return launch_lone<2, 6>(p, relu, stream);
+    case 7: return launch_lone<2, 7>(p, relu, stream);
+    case 12: return launch_lone<2, 12>(p, relu, stream);
+    case 103: return launch_lone<4, 3>(p, relu, stream);
+    default: return hipErrorNotSupported;
+    }
+}
+
 size_t clada_ws_stack(int32_t d) { return sizeof(float) * (size_t)CLADA_STACK_LAUNCH_LAYERS * SLICES * d; }
+
+// Rows that have no batch-1 kernel of their own: every layer of them, alone or in a stack, runs here (us per step, generic kernel /
+// this one: 189 / 36 at 24 layers of 512 x 1376, 282 / 86 at 24 of 1536 x 4096 ReLU, 343 / 112 at 24 of 2048 x 4632 ReLU, 610 / 442 at
+// 24 of 3072 x 8192, 686 / 480 at 24 of 3584 x 8496, 368 / 262 at 8 of 6144 x 13000 ReLU, 83 / 36 at 8 of 768 x 2048 fp32; two layers
+// 1.03 - 1.3 times as fast).  A stack has the bits of its layers' lone calls, so only rows whose lone call is not slower here: gated bf16 rows
+// of 3 KiB (11.7 / 12.7 at 1536 x 4096), fp32 rows of 4 and 6 KiB (10.8 / 12.3, 15.7 / 17.4) stay on the generic kernel.
+bool clada_stack_b1_only(const clada_layer *layer)
+{
+    const int row = layer->d * (int)dtype_size(layer->dtype), nch = row / 1024;
+    if (row % 1024 != 0) return false;
+    if (layer->kind == CLADA_FFN_RELU)
+        return layer->dtype == CLADA_BF16 && (nch == 1 || nch == 3 || nch == 4 || nch == 6 || nch == 7 || nch == 12);
+    return layer->dtype == CLADA_BF16 ? nch == 1 || nch == 6 || nch == 7 : nch == 3;
+}
 
 // Where the launches over all layers are the faster way (us per step of L layers against lanes of per-layer launches, sparsity
 // 0.45).  Nearly everywhere: 2 KiB rows 91 / 197 (L = 24, 1024 x 4096), 4 KiB 521 / 557 (24, 2048 x 16384), 5 KiB ReLU 92 / 110
@@ -476,6 +629,7 @@ bool clada_stack_b1_fits(const clada_layer *layer, int32_t L, bool dense)
     const int es = (int)dtype_size(layer->dtype), nch = layer->d * es / 1024, F = layer->d_ff;
     const bool gated = layer->kind != CLADA_FFN_RELU;
     if (layer->d * es % 1024 != 0 || L < 2) return false;
+    if (clada_stack_b1_only(layer)) return true;
     if (es == 4) return nch == 2 || nch == 8;
     if (nch == 4) return !(dense && gated && F > 12288 && L < 32);
     if (nch == 8) return !(dense && gated && F > 8192 && L > 8);
@@ -495,7 +649,7 @@ hipError_t clada_stack_b1(const clada_layer *layers, int32_t L, const void *x, c
     // them (us, whole slices / single classes: 162 / 176 at 5 layers of 4096 x 11008, 155 / 141 at 4; 5 KiB rows 1.08 / 0.98 of
     // the lanes at 5 of 2560 x 10240, 0.88 / 0.94 at 6; 4 KiB rows 1.04 / 0.95 at 7 of 2048 x 14336, 0.91 / 0.93 at 8; 2 KiB
     // rows 40 / 39 at 8 of 1024 x 4096, 40 / 35 at 6: their workgroups have four waves).
-    const int whole = nch == 2 || nch == 4 ? 8 : nch == 5 ? 6 : 5;
+    const int whole = nch <= 4 ? 8 : nch == 5 ? 6 : 5;
     int most = room / SLICES < CLADA_STACK_LAUNCH_LAYERS ? room / SLICES : CLADA_STACK_LAUNCH_LAYERS;
     if (most > 8) most -= most % 8;
     for (int l0 = 0, n; l0 < L; l0 += n) {
@@ -505,7 +659,7 @@ hipError_t clada_stack_b1(const clada_layer *layers, int32_t L, const void *x, c
         // 4096 x 11008: 352 us in one launch, 275 in two, 303 in lanes; 17: 584, 510, 537; at four more the two are even, but for
         // 5 KiB rows: 1.10 at 12 dense layers of 2560 x 10240).  Rows of 4 KiB, whose workgroups are half as wide, notice from the
         // third round on, rows of 2 KiB not at all.
-        const int more = n % 8, thin = nch == 2 ? 0 : nch == 5 ? 4 : 3;
+        const int more = n % 8, thin = nch <= 3 ? 0 : nch == 5 ? 4 : 3;
         if (n > (nch == 4 ? 16 : 8) && more <= thin) n -= more;
         const int chain = n >= whole ? CHAIN : 1, P = CLASSES / chain;
         if (n > room / P) {                                  // (single classes: launches of like size)
@@ -530,12 +684,18 @@ hipError_t clada_stack_b1(const clada_layer *layers, int32_t L, const void *x, c
         const dim3 grid(P, n);
         hipError_t e;
         switch (es == 2 ? nch : 100 + nch) {
+        case 1: e = launch_rows<2, 1>(p, grid, relu, stream); break;
         case 2: e = launch_rows<2, 2>(p, grid, relu, stream); break;
+        case 3: e = launch_rows<2, 3>(p, grid, relu, stream); break;
         case 4: e = launch_rows<2, 4>(p, grid, relu, stream); break;
         case 5: e = launch_rows<2, 5>(p, grid, relu, stream); break;
+        case 6: e = launch_rows<2, 6>(p, grid, relu, stream); break;
+        case 7: e = launch_rows<2, 7>(p, grid, relu, stream); break;
         case 8: e = launch_rows<2, 8>(p, grid, relu, stream); break;
         case 10: e = launch_rows<2, 10>(p, grid, relu, stream); break;
+        case 12: e = launch_rows<2, 12>(p, grid, relu, stream); break;
         case 102: e = launch_rows<4, 2>(p, grid, relu, stream); break;
+        case 103: e = launch_rows<4, 3>(p, grid, relu, stream); break;
         case 108: e = launch_rows<4, 8>(p, grid, relu, stream); break;
         default: e = hipErrorNotSupported;
         }
