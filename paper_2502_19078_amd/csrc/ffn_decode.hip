@@ -1802,7 +1802,7 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
     const bool b1_stack = B == 1 && smode >= 2 && ctx->opt_decode_b1 >= 1 && !n_active && (d * es) % 1024 == 0 &&
                           Pb == COOP_MAX_WGS && F >= Pb && ni_b <= 1024 && L >= 2;
     const bool own_launches = b1_stack && b1_shape_ok(es, nch, relu);
-    if (b1_stack && smode == 3 && clada_stack_b1_fits(&layers[0], L, dense)) {
+    if (b1_stack && smode == 3 && (own_launches || clada_stack_b1_only(&layers[0])) && clada_stack_b1_fits(&layers[0], L, dense)) {
         CLADA_CHECK_HIP(ctx, clada_stack_b1(layers, L, x, tau, y, dense, reinterpret_cast<float *>(ctx->ws + CLADA_WS_HEADER),
                                             ctx->ws_bytes - CLADA_WS_HEADER, stream));
         return CLADA_OK;

@@ -630,7 +630,7 @@ bool clada_stack_b1_fits(const clada_layer *layer, int32_t L, bool dense)
     const bool gated = layer->kind != CLADA_FFN_RELU;
     if (layer->d * es % 1024 != 0 || L < 2) return false;
     if (clada_stack_b1_only(layer)) return true;
-    if (es == 4) return nch == 2 || nch == 8;
+    if (es == 4) return gated && (nch == 2 || nch == 8);
     if (nch == 4) return !(dense && gated && F > 12288 && L < 32);
     if (nch == 8) return !(dense && gated && F > 8192 && L > 8);
     if (nch == 10) return L >= 6 || (!dense && (gated ? 3.0 : 2.0) * F * layer->d * es < 400e6);

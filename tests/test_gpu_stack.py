@@ -268,6 +268,12 @@ def test_one_launch_over_the_layers_is_the_per_layer_calls_bit_for_bit(clada, d,
     assert (cl - cg).abs().max() <= 2 and (yl - yg).double().norm() <= (2 ** -8 if dtype == "bf16" else 2e-4) * yg.double().norm() + 1e-30
 
 
+@pytest.mark.parametrize("d,F,L", [(512, 256, 2), (512, 1376, 9), (2048, 700, 3)])
+def test_fp32_relu_stacks_run_as_the_per_layer_calls(clada, d, F, L):
+    """Row lengths that the gated family has launches over many layers for; the non-gated one has none."""
+    test_one_launch_over_the_layers_is_the_per_layer_calls_bit_for_bit(clada, d, F, L, True, "f32")
+
+
 def _batch_stack(clada, cfg_name, d, F, L, B, seed, shared_frac=0.5):
     cfg = synth.CONFIGS[cfg_name]
     ws = [synth.layer_weights(cfg, seed, l, d=d, d_ff=F) for l in range(L)]

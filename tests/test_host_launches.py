@@ -122,6 +122,23 @@ def test_batch_1_stacks_fill_their_rounds(fake, d, F, L, kw, want):
     assert _stack_grid(r[1]) == want
 
 
+@pytest.mark.parametrize("dtype,widths", [("bf16", (64, 512, 768, 1024, 1536, 2048, 2560, 3072, 3584, 4096, 5120, 6144, 7168, 8192)),
+                                          ("f32", (32, 256, 512, 768, 1024, 1536, 2048, 2560, 3072, 4096))])
+@pytest.mark.parametrize("kind", ["swiglu", "relu", "geglu"])
+def test_no_stack_or_call_is_refused(fake, dtype, widths, kind):
+    """Every row length there is a kernel for, in every mode: a rule that admits a shape has an instance for it in both families."""
+    steps = []
+    for d in widths:
+        for F in (200, 300, 20000):
+            steps += [{"do": "ctx", "sizes": [d, F, 16, 0, 0]}]
+            for mode in (3, 2, 1, 0):
+                steps += [{"do": "option", "name": "decode.stack", "value": mode}]
+                steps += [{"do": "stack", "d": d, "F": F, "L": L, "B": B, "kind": kind, "dtype": dtype, "dense": dense}
+                          for L in (1, 2, 9) for B in (1, 2, 16) for dense in (False, True)]
+            steps += [{"do": "decode", "d": d, "F": F, "B": B, "kind": kind, "dtype": dtype} for B in (1, 5, 12)]
+    assert [(s, r["status"]) for s, r in zip(steps, run_steps(fake, steps)) if r["status"] != 0] == []
+
+
 @pytest.mark.parametrize("first", [{"d": 4096, "F": 11008, "L": 8, "B": 1}, {"d": 4096, "F": 11008, "L": 8, "B": 4}, {"d": 1024, "F": 300, "L": 1, "B": 1}])
 def test_first_stack_call_makes_the_lanes_whichever_way_it_takes(fake, first):
     """A capture must not have to create streams: not one that needs the lanes after a first call that did not."""
