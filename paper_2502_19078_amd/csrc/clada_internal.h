@@ -88,7 +88,7 @@ clada_status clada_stack_batched(clada_ctx *ctx, const clada_layer *layers, int3
                                  const float *tau, void *y, bool dense, char *scratch, size_t bytes, hipStream_t stream, bool *ran);
 size_t clada_ws_decode_batched(int32_t d_ff);
 size_t clada_ws_decode_batched_partial(int32_t d);
-bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *layer, int32_t B, int tiles);
+bool clada_decode_batched_fits_lane(const clada_ctx *ctx, const clada_layer *layer, int32_t B, int tiles);
 // Batch-1 decode over a neuron list with the streaming kernel, when the shape fits it (*ran).
 hipError_t clada_decode_list_b1(clada_ctx *ctx, const clada_layer *layer, const void *x, const int32_t *idx,
                                 const int32_t *n_active, float *partial, int *P_out, hipStream_t stream, bool *ran);

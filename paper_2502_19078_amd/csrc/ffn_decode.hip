@@ -1870,8 +1870,8 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
         if (ran) return CLADA_OK;
     }
     if (n_groups > 0 && smode == 3 && !n_active && L * n_groups >= 3 &&
-        clada_decode_batched_eligible(ctx, &layers[0], per_group, tiles) &&
-        clada_decode_batched_eligible(ctx, &layers[0], B - (n_groups - 1) * per_group, tiles)) {
+        clada_decode_batched_fits_lane(ctx, &layers[0], per_group, tiles) &&
+        clada_decode_batched_fits_lane(ctx, &layers[0], B - (n_groups - 1) * per_group, tiles)) {
         const int n_lanes = 3;
         char *ws = ctx->ws + CLADA_WS_HEADER;
         char *lane_base[3];

@@ -699,16 +699,19 @@ static bool bat_plan(const clada_ctx *ctx, const clada_layer *layer, int B, int 
     return true;
 }
 
-bool clada_decode_batched_eligible(const clada_ctx *ctx, const clada_layer *layer, int32_t B, int tiles)
-{
-    int P, CG, RG;
-    return bat_plan(ctx, layer, B, tiles, &P, &CG, &RG);
-}
-
-// Bytes of partial outputs one pass of up to 16 tokens writes at most: [RG <= 64][B <= 16][d] fp32.
+// Bytes of partial outputs that a lane of the whole-stack calls has room for in front of a pass's scratch: 64 x 16 rows of fp32
+// (CLADA_BAT_WIDE floats a column in two tiles).
 size_t clada_ws_decode_batched_partial(int32_t d)
 {
     return align_up(sizeof(float) * 64 * 16 * (size_t)d, 256);
+}
+
+// Whether a pass can go round the lanes.  A lone pass has room for 512 rows a token; very wide layers whose row groups were doubled past 64
+// (72 of 3584 x 66000, 84 of 1536 x 76000, 96 of 5120 x 99000) write more than a lane holds once the pass has tokens enough.
+bool clada_decode_batched_fits_lane(const clada_ctx *ctx, const clada_layer *layer, int32_t B, int tiles)
+{
+    int P, CG, RG;
+    return bat_plan(ctx, layer, B, tiles, &P, &CG, &RG) && RG * B <= (tiles == 2 ? CLADA_BAT_WIDE : 64 * 16);
 }
 
 // Launches the two kernels for n_layers layers in n_pass passes of tokens: args are BatArgs, or BatParams p for a single unit

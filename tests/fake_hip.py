@@ -9,7 +9,7 @@ torch): `python fake_hip.py FAKE LIB`, with a JSON list of steps on stdin, and a
   {"do": "prefix", "d", "F", "T", "kind"} / {"do": "calibrate", "n": ..} / {"do": "search", "d", "F", "T", "bound", "n_probes"}
   {"do": "fail", "in": n} / {"do": "capturing", "on": 0 | 1}
 
-A result is {"status": .., "launches": [[kernel, gx, gy, gz, bx], ..], "created": streams and events}."""
+A result is {"status": .., "launches": [[kernel, gx, gy, gz, bx, on a lane's stream], ..], "created": streams and events}."""
 import ctypes as C
 import json
 import os

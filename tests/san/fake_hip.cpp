@@ -1,6 +1,6 @@
 // A HIP runtime without a device, for tests of the library's host side on the CPU: loaded with RTLD_GLOBAL before
 // libclada.so it takes every runtime call the library makes.  Kernels are not run; their launches are written down, in
-// order, as "name gridx gridy gridz blockx" (one per line), and the n-th launch from now can be made to fail.
+// order, as "name gridx gridy gridz blockx lane" (one per line; lane: 1 on a stream that the library made), and the n-th launch from now can be made to fail.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -20,11 +20,11 @@ static hipError_t g_last = hipSuccess;
 static struct { dim3 grid, block; size_t lds; hipStream_t st; } g_cfg;
 
 static hipError_t refuse(hipError_t e) { g_last = e; return e; }
-static hipError_t launch(const void *fn, dim3 g, dim3 b)
+static hipError_t launch(const void *fn, dim3 g, dim3 b, hipStream_t st)
 {
     if (g_fail_in >= 0 && g_fail_in-- == 0) return refuse(hipErrorLaunchFailure);
     char line[512];
-    std::snprintf(line, sizeof(line), "%s %u %u %u %u\n", names()[fn].c_str(), g.x, g.y, g.z, b.x);
+    std::snprintf(line, sizeof(line), "%s %u %u %u %u %d\n", names()[fn].c_str(), g.x, g.y, g.z, b.x, st != nullptr);
     g_log += line;
     return hipSuccess;
 }
@@ -45,8 +45,8 @@ void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t st) { g_cfg = {g, b, lds, st}; return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t *st) { *g = g_cfg.grid; *b = g_cfg.block; *lds = g_cfg.lds; *st = g_cfg.st; return hipSuccess; }
 
-hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **, size_t, hipStream_t) { return launch(fn, g, b); }
-hipError_t hipExtLaunchKernel(const void *fn, dim3 g, dim3 b, void **, size_t, hipStream_t, hipEvent_t, hipEvent_t, int) { return launch(fn, g, b); }
+hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **, size_t, hipStream_t st) { return launch(fn, g, b, st); }
+hipError_t hipExtLaunchKernel(const void *fn, dim3 g, dim3 b, void **, size_t, hipStream_t st, hipEvent_t, hipEvent_t, int) { return launch(fn, g, b, st); }
 hipError_t hipGetLastError(void) { const hipError_t e = g_last; g_last = hipSuccess; return e; }
 const char *hipGetErrorString(hipError_t e) { return e == hipSuccess ? "no error" : "refused by the test"; }
 

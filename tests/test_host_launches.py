@@ -230,6 +230,23 @@ def test_batched_stacks_are_launched_over_many_layers(fake, d, F, L, B, kw, want
     assert _batched_layers(r[1]) == want
 
 
+@pytest.mark.parametrize("d,F,L,B,lanes", [
+    # row groups of a lone pass (CG: column groups of 256): 42 doubled, 18 doubled, 24, 20, 12 and 10 doubled twice or three times, at 16 tokens a pass and fewer
+    (1536, 76000, 20, 13, False), (1536, 76000, 20, 12, True), (1536, 84000, 18, 16, False), (3584, 66000, 12, 15, False), (3584, 66000, 12, 14, True), (3584, 73000, 20, 32, False),
+    (2560, 100000, 9, 16, False), (3072, 82000, 9, 16, False), (5120, 99000, 5, 16, False), (5120, 80000, 6, 16, True), (5120, 99000, 8, 10, True),
+    (6144, 90000, 5, 16, False), (8192, 70000, 5, 16, True), (4096, 130000, 5, 16, True),
+])
+def test_a_lane_holds_the_partial_outputs_of_its_units(fake, d, F, L, B, lanes):
+    """64 x 16 rows of partial outputs lie in front of a lane's h; a unit that has more of them does not go round the lanes."""
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, B, 0, 0]}, {"do": "stack", "d": d, "F": F, "L": L, "B": B}])
+    per_pass = -(-B // -(-B // 16))
+    for x in r[1]["launches"]:
+        if x[5] and "k_bat_down" in x[0]:
+            assert x[1] // -(-d // 256) * per_pass <= 64 * 16, x
+    assert any(x[5] for x in r[1]["launches"]) == lanes and _batched_layers(r[1]) is None
+    assert len([n for n in _names(r[1]) if "k_bat_gateup" in n]) == L * -(-B // 16)
+
+
 def test_a_single_unit_has_kernels_of_its_own(fake):
     """Lone batched calls, and the units that go round the lanes, take their parameters directly; launches over several units
     take the arrays of their layers' weights."""
