@@ -87,10 +87,11 @@ __device__ __forceinline__ BatParams bat_unit(const BatArgs &)
     return p;
 }
 
-// An fp32 h as the sum of two bf16: the rounded value below, the rounded rest above.  Split once here and not by every column group of the down
-// kernel.
+// An fp32 h as the sum of two bf16: the rounded value below, the rounded rest above (16 to 17 of its 24 bits).  Split once here and not by every
+// column group of the down kernel.  The rest is that of the rounded h, not of the product inside an fma.
 __device__ __forceinline__ unsigned int split_bf16(float h)
 {
+#pragma clang fp contract(off)
     const __bf16 hi = (__bf16)h, lo = (__bf16)(h - (float)hi);       // (one instruction each; nearest even)
     return (unsigned int)__builtin_bit_cast(unsigned short, hi) | ((unsigned int)__builtin_bit_cast(unsigned short, lo) << 16);
 }

@@ -378,6 +378,36 @@ def test_passes_of_the_matrix_core_path(clada, cfg_name, d, F, B):
     assert_close_y(to_np(ys), oracle.decode_given_mask(*w, x, np.broadcast_to(keep, (B, F))), TOL_Y[cfg.dtype], "list run")
 
 
+def _parts(v):
+    """fp32 values as three bf16 each, exactly (cut, not rounded)."""
+    hi = (v.view(torch.int32) & -65536).view(torch.float32)
+    mid = ((v - hi).view(torch.int32) & -65536).view(torch.float32)
+    return torch.stack([hi, mid, v - hi - mid], 1)
+
+
+@pytest.mark.parametrize("d,B", [(768, 7), (1024, 2), (2048, 20), (4096, 16)])
+def test_equal_h_of_neurons_with_opposite_rows_cancel_exactly(clada, d, B):
+    """Neuron 2k has h = fl32(a u), neuron 2k + 1 the same float with nothing rounded (32 times h / 32), and their W_down rows are +1 and -1 in one
+    column: whatever h becomes on its way, it is a function of that float.  (A rest taken from the unrounded product differs for one in 500.)"""
+    F = 8192
+    g = torch.Generator(device=DEV).manual_seed(d)
+    a = 32.0 + 32.0 * torch.rand(F // 2, generator=g, device=DEV)        # SiLU(a) = a
+    u = 1.0 + torch.rand(F // 2, generator=g, device=DEV)
+    h = a * u
+    w = [torch.zeros(F, d, device=DEV) for _ in range(3)]
+    w[0][0::2, :3], w[1][0::2, :3] = _parts(a), _parts(u)
+    w[0][1::2, 0], w[1][1::2, :3] = 32.0, _parts(h / 32.0)
+    k = torch.arange(F // 2, device=DEV)
+    w[2][2 * k, k % d], w[2][2 * k + 1, k % d] = 1.0, -1.0
+    assert all(torch.equal(v.bfloat16().float(), v) for v in w)
+    x = torch.zeros(B, d, device=DEV)
+    x[:, :3] = 1.0
+    layer = clada.Layer(*[v.bfloat16() for v in w])
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, B, 0, 0))
+    y, _, cnt, _ = clada.sparse_ffn_decode(ctx, layer, x.bfloat16(), torch.full((B,), 1.0, device=DEV), want_lists=True)
+    assert int(cnt[0]) == F and not y.any()
+
+
 def test_infinite_weight_of_a_neuron_a_token_cuts_stays_out_of_its_output(clada):
     """Token 0 keeps neuron 5, whose output row holds an infinity; token 1 cuts it and stays finite."""
     cfg, w, x = _case("c1", 22, 2048, 500, 2)
