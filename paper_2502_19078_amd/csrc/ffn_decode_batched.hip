@@ -88,13 +88,21 @@ __device__ __forceinline__ BatParams bat_unit(const BatArgs &)
 }
 
 // An fp32 h as the sum of two bf16: the rounded value below, the rounded rest above (16 to 17 of its 24 bits).  Split once here and not by every
-// column group of the down kernel.  The rest is that of the rounded h, not of the product inside an fma.
+// column group of the down kernel.  The rest is taken from the rounded product, not from the product inside an fma.  An infinite h has no rest, and
+// one that would round up to infinity is cut instead, so that neither turns into infinity minus infinity.
 __device__ __forceinline__ unsigned int split_bf16(float h)
 {
 #pragma clang fp contract(off)
-    const __bf16 hi = (__bf16)h, lo = (__bf16)(h - (float)hi);       // (one instruction each; nearest even)
-    return (unsigned int)__builtin_bit_cast(unsigned short, hi) | ((unsigned int)__builtin_bit_cast(unsigned short, lo) << 16);
+    float hi = (float)(__bf16)h, lo = h - hi;                        // (nearest even)
+    if (!(fabsf(lo) < INFINITY)) {
+        const bool finite = fabsf(h) < INFINITY;
+        if (finite) hi = copysignf(0x1.fep127f, h);
+        lo = finite ? h - hi : 0.0f;
+    }
+    return (unsigned int)__builtin_bit_cast(unsigned short, (__bf16)hi) | ((unsigned int)__builtin_bit_cast(unsigned short, (__bf16)lo) << 16);
 }
+// h of a neuron that the token cuts: a zero, and no value of the above (its rest has the sign of h, or is +0).
+constexpr unsigned int H_CUT = 0x80000000u;
 
 __device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, const f32x4 c)
 {
@@ -295,7 +303,7 @@ k_bat_gateup(const Args args)
                 s_a[i][m][nn] = a;
                 if (keep) atomicOr(&s_km[i * 16 + nn], 1 << m);
                 if (p.keep && valid) p.keep[(size_t)m * F + j] = keep ? 1 : 0;
-                if (RELU && here) p.hbuf[(size_t)j * HS + m] = keep ? split_bf16(a) : 0u;     // read back for union-kept neurons only
+                if (RELU && here) p.hbuf[(size_t)j * HS + m] = keep ? split_bf16(a) : H_CUT;     // read back for union-kept neurons only
             }
         }
     };
@@ -321,7 +329,7 @@ k_bat_gateup(const Args args)
                 const int j = LIST ? s_nl[16 * i + l2] : j_lo + 16 * i + l2;
                 const float usum = tile_sum(buf, e);
                 const bool keep = (s_km[16 * i + l2] >> m) & 1;
-                p.hbuf[(size_t)j * HS + m] = keep ? split_bf16(s_a[i][m][l2] * usum) : 0u;
+                p.hbuf[(size_t)j * HS + m] = keep ? split_bf16(s_a[i][m][l2] * usum) : H_CUT;
             }
         }
     };
@@ -482,8 +490,8 @@ k_bat_down(const Args args)
     };
     // W_down[32 list entries][128 columns]: quarter-waves read 256-byte row pieces, lane group q the entries 8 q ..; columns past d cannot
     // occur for the supported widths (d is a multiple of 256)
-    const char *wcol = p.wd + (size_t)(col0 + sub * DN_SUB + 8 * n) * 2;
     auto w_load = [&](u32x4 (&wv)[8], int kb) {
+        const char *wcol = p.wd + (size_t)(col0 + sub * DN_SUB + 8 * n) * 2;
         int row[8];
 #pragma unroll
         for (int ii = 0; ii < 8; ++ii) row[ii] = s_rows[min(32 * kb + 4 * ii + q, nrows - 1)];
@@ -497,7 +505,7 @@ k_bat_down(const Args args)
     auto process = [&](const u32x4 (&ahi)[MT], const u32x4 (&alo)[MT]) {
         // K-major B-fragments by transpose reads: in each 16-lane group lane t = 4r + c4 supplies
         // row 8q + r, columns 4*c4 .. 4*c4+3 and receives column t of rows 8q .. 8q+3
-        const int r = (lane & 15) >> 2, c4 = lane & 3;
+        const int r = n >> 2, c4 = n & 3;
 #pragma unroll
         for (int t = 0; t < DN_SUB / 16; ++t) {
             const unsigned char *src = tile + (8 * q + r) * DN_PITCH + (t * 16 + 4 * c4) * 2;
@@ -543,6 +551,54 @@ k_bat_down(const Args args)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) split_h(hA[mt], ahi[mt], alo[mt], kb);
         process(ahi, alo);
+    }
+
+    // ---- A cut neuron counts as h = 0 above, and 0 times an infinite weight is NaN.  Finite sums prove that no such weight was in the way, so that
+    // the loop looks at none.  Where a sum is not, this wave looks for one in its units, and if there is one forms its sums again,
+    // neuron by neuron, for the tokens that keep it.
+    float finite = 0.0f;                                                // NaN unless every sum is
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int t = 0; t < DN_SUB / 16; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) finite = fmaf(acc[mt][t][r], 0.0f, finite);
+    if (__ballot(finite != 0.0f)) {
+        bool bad = false;
+#pragma unroll 1
+        for (int kb = rw; kb < nkb; kb += 4) {
+            w_load(wA, kb);
+#pragma unroll
+            for (int ii = 0; ii < 8; ++ii)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) bad = bad || (wA[ii][k] & 0x7f80u) == 0x7f80u || (wA[ii][k] & 0x7f800000u) == 0x7f800000u;
+        }
+        if (__ballot(bad)) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int t = 0; t < DN_SUB / 16; ++t) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int e0 = 32 * rw; e0 < nrows; e0 += 128)
+#pragma unroll 1
+                for (int e = e0; e < min(e0 + 32, nrows); ++e) {
+                    const int row = s_rows[e];
+                    const unsigned short *w = reinterpret_cast<const unsigned short *>(p.wd + (size_t)row * rowb) + col0 + sub * DN_SUB + n;
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const u32x4 h = *reinterpret_cast<const u32x4 *>(p.hbuf + (size_t)row * (16 * MT) + 16 * mt + 4 * q);
+#pragma unroll
+                        for (int t = 0; t < DN_SUB / 16; ++t) {
+                            const float wv = __uint_as_float((unsigned int)w[16 * t] << 16);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const float sum = fmaf(__uint_as_float(h[r] << 16) + __uint_as_float(h[r] & 0xffff0000u), wv, acc[mt][t][r]);
+                                acc[mt][t][r] = h[r] != H_CUT ? sum : acc[mt][t][r];
+                            }
+                        }
+                    }
+                }
+        }
     }
 
     // ---- fixed-order fold of the four row-waves of each column half through LDS, then the partial

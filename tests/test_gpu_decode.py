@@ -420,6 +420,71 @@ def test_infinite_weight_of_a_neuron_a_token_cuts_stays_out_of_its_output(clada)
     assert not np.isfinite(to_np(y)[0, 7]) and np.isfinite(to_np(y)[1]).all()
 
 
+# The matrix-core path at every width and both tilings: one, two and many units of rows a wave; the bad neuron inside the list or
+# its last entry, which the padding of the last unit repeats
+@pytest.mark.parametrize("j", [5, -1])
+@pytest.mark.parametrize("d,F,B,relu", [(512, 300, 13, False), (768, 900, 7, False), (768, 3072, 33, False), (1024, 700, 2, True), (1536, 600, 16, True),
+                                        (2048, 4000, 20, False), (3584, 500, 3, False), (3584, 700, 24, True), (4096, 900, 5, False), (5120, 300, 16, False)])
+def test_values_that_are_not_finite_stay_with_the_tokens_that_keep_the_neuron(clada, d, F, B, relu, j):
+    """y_b sums over the neurons that b keeps.  An infinite and a NaN entry of W_down, and an infinite u (a: non-gated), reach the tokens that keep
+    theirs, as an infinity where the terms say so, and no other; an h above the largest bf16 stays finite."""
+    from paper_2502_19078_amd import binding
+    g = torch.Generator(device=DEV).manual_seed(d + F + B)
+    n = lambda *s, k=1.0: torch.randn(s, generator=g, device=DEV) * k
+    j, ju, jh = j % F, F // 2, F // 3
+    w = [n(F, d, k=d ** -0.5).bfloat16() for _ in range(2 if relu else 3)]
+    b_in = n(F, k=0.1) if relu else None
+    wd = w[-1]
+    wd[j, 7], wd[j, d - 1] = float("inf"), float("nan")
+    wd[ju] = wd[ju].abs() + 0.01
+    wd[jh] = 1e-30
+    x = n(B, d).bfloat16()
+    # neurons j and ju: kept by the even and by the odd tokens alone; jh by every one
+    keep_even = torch.arange(B, device=DEV) % 2 == 0
+    x[:, 0] = torch.where(keep_even, 30.0, -30.0).bfloat16()
+    for k, s in ((j, 1.0), (ju, -1.0)):
+        w[0][k] = 0
+        w[0][k, 0] = s * 4.0                                 # a = 120 or (a sigma of) -120
+    if relu:
+        b_in[jh] = 3.4e38                                    # rounds up to infinity in bf16
+        b_in[j] = 0.0
+        b_in[ju] = 0.0
+        w[0][ju, 0] = float("-inf")                          # (a = +inf for the odd tokens, 0 for the even)
+    else:
+        w[0][jh] = 0
+        w[0][jh, 1] = 1e20
+        x[:, 1] = x[:, 1].abs() + 1.0
+        w[1][jh] = 0
+        w[1][jh, 1] = 1e10
+        w[1][ju, 0] = float("-inf")                          # u = +inf for the odd tokens
+    layer = clada.Layer(w[0], None, w[1], kind=binding.RELU, b_in=b_in, b_out=n(d)) if relu else clada.Layer(*w)
+    tau = torch.full((B,), 0.2, device=DEV)
+    ctx = clada.Context(0, clada.workspace_bytes(d, F, B, 0, 0))
+    y, _, _, bits = clada.sparse_ffn_decode(ctx, layer, x, tau, want_lists=True)
+    mask = torch.from_numpy(unpack_bits(bits, F)).to(DEV)
+    assert torch.equal(mask[:, j], keep_even) and torch.equal(mask[:, ju], ~keep_even) and mask[:, jh].all()
+    a = x.double() @ w[0].double().t()
+    a = (a + b_in.double()).clamp_min(0) if relu else a * torch.sigmoid(a)
+    h = a if relu else a * (x.double() @ w[1].double().t())
+    want = torch.where(mask, h, 0.0)
+    special = torch.zeros(F, dtype=torch.bool, device=DEV)
+    special[[j, ju]] = True
+    y64 = (want * ~special).nan_to_num(0.0) @ wd.double().nan_to_num(0.0, 0.0, 0.0)
+    if relu:
+        y64 += layer.b_out.double()
+    for b in range(B):
+        cols = torch.ones(d, dtype=torch.bool, device=DEV)
+        if keep_even[b]:                                     # (the neuron j's own terms)
+            assert y[b, 7] == torch.sign(h[b, j]) * float("inf") and torch.isnan(y[b, d - 1]), b
+            cols[7] = cols[d - 1] = False
+            r = y64[b] + h[b, j] * wd[j].double()
+            assert (y[b].double() - r)[cols].norm() <= 2 ** -8 * r[cols].norm(), b
+        else:
+            assert (y[b] == float("inf")).all(), b
+    ref = clada.sparse_ffn_stack_decode(ctx, [layer, layer, layer], torch.stack([x] * 3), tau.repeat(3, 1))
+    assert all(torch.equal(r.nan_to_num(7.0), y.nan_to_num(7.0)) for r in ref)
+
+
 def test_sizes_beyond_the_limits_are_rejected(clada):
     from paper_2502_19078_amd.binding import CladaError
     cfg, w, x = _case("c2", 12, 256, 64, 1)
