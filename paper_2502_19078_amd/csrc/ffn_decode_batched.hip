@@ -103,6 +103,15 @@ __device__ __forceinline__ unsigned int split_bf16(float h)
 }
 // h of a neuron that the token cuts: a zero, and no value of the above (its rest has the sign of h, or is +0).
 constexpr unsigned int H_CUT = 0x80000000u;
+// What gate/up leaves of h.  Rows of 512, 768, 1536 and 3584 values, whose batches of few tokens and whose other types run on the vector units with
+// all of fp32, keep it: the down kernel takes it apart into three bf16, exactly (WHOLE).
+constexpr bool whole_h(int d) { return d == 512 || d == 768 || d == 1536 || d == 3584; }
+template <bool WHOLE>
+__device__ __forceinline__ unsigned int kept_h(float h)
+{
+    if (!WHOLE) return split_bf16(h);
+    return h == 0.0f ? 0u : __float_as_uint(h);                      // (-0 is a cut neuron's)
+}
 
 __device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, const f32x4 c)
 {
@@ -134,6 +143,7 @@ k_bat_gateup(const Args args)
     const BatParams p = bat_unit(args);
     static_assert(!LIST || DENSE, "a list run keeps every listed neuron");
     static_assert(NW >= 4 && NW <= 8, "the tile reductions run on waves 0..3");
+    constexpr bool WHOLE = whole_h(NW * 32 * KSTEPS);
     constexpr int NBUF = MT == 1 ? 2 : 1, NT = NW * 64, ELEMS = 256 * MT, TURNS = (ELEMS + NT - 1) / NT, HS = 16 * MT;
     __shared__ float s_part[NBUF][NW][ELEMS];               // (two of them for two token tiles would not fit beside the rows)
     __shared__ float s_a[MAX_TILES][HS][16];
@@ -303,7 +313,7 @@ k_bat_gateup(const Args args)
                 s_a[i][m][nn] = a;
                 if (keep) atomicOr(&s_km[i * 16 + nn], 1 << m);
                 if (p.keep && valid) p.keep[(size_t)m * F + j] = keep ? 1 : 0;
-                if (RELU && here) p.hbuf[(size_t)j * HS + m] = keep ? split_bf16(a) : H_CUT;     // read back for union-kept neurons only
+                if (RELU && here) p.hbuf[(size_t)j * HS + m] = keep ? kept_h<WHOLE>(a) : H_CUT;     // read back for union-kept neurons only
             }
         }
     };
@@ -329,7 +339,7 @@ k_bat_gateup(const Args args)
                 const int j = LIST ? s_nl[16 * i + l2] : j_lo + 16 * i + l2;
                 const float usum = tile_sum(buf, e);
                 const bool keep = (s_km[16 * i + l2] >> m) & 1;
-                p.hbuf[(size_t)j * HS + m] = keep ? split_bf16(s_a[i][m][l2] * usum) : H_CUT;
+                p.hbuf[(size_t)j * HS + m] = keep ? kept_h<WHOLE>(s_a[i][m][l2] * usum) : H_CUT;
             }
         }
     };
@@ -396,7 +406,7 @@ constexpr int DN_TILE_BYTES = 32 * DN_PITCH;    // one wave's staging tile: 32 n
 constexpr int DN_MAX_ROWS = 2048;               // union neurons per row group
 constexpr int DN_MAX_WGS = 64;                  // gate/up workgroups per row group
 
-template <int MT, class Args>
+template <int MT, bool WHOLE, class Args>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_bat_down(const Args args)
 {
@@ -502,7 +512,8 @@ k_bat_down(const Args args)
 #pragma unroll
         for (int ii = 0; ii < 8; ++ii) *reinterpret_cast<u32x4 *>(tile + (4 * ii + q) * DN_PITCH + n * 16) = wv[ii];
     };
-    auto process = [&](const u32x4 (&ahi)[MT], const u32x4 (&alo)[MT]) {
+    constexpr int PARTS = WHOLE ? 3 : 2;                                // of h, the largest first
+    auto process = [&](const u32x4 (&a)[MT][PARTS]) {
         // K-major B-fragments by transpose reads: in each 16-lane group lane t = 4r + c4 supplies
         // row 8q + r, columns 4*c4 .. 4*c4+3 and receives column t of rows 8q .. 8q+3
         const int r = n >> 2, c4 = n & 3;
@@ -514,21 +525,33 @@ k_bat_down(const Args args)
             const uint2 u0 = __builtin_bit_cast(uint2, b0), u1 = __builtin_bit_cast(uint2, b1);
             const u32x4 bf = {u0.x, u0.y, u1.x, u1.y};
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                acc[mt][t] = mfma16(ahi[mt], bf, acc[mt][t]);
-                acc[mt][t] = mfma16(alo[mt], bf, acc[mt][t]);
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int k = 0; k < PARTS; ++k) acc[mt][t] = mfma16(a[mt][k], bf, acc[mt][t]);
+        }
+    };
+    auto split_h = [&](unsigned int (&hv)[8], u32x4 (&a)[PARTS], int kb) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) hv[i] = 32 * kb + 8 * q + i < nrows ? hv[i] : 0u;
+        if constexpr (WHOLE) {                               // eight bits at a time, cut, not rounded: nothing is left behind the third
+#pragma unroll
+            for (int k = 0; k < PARTS; ++k)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const unsigned int top = hv[i] & 0xffff0000u;
+                    if (i & 1) a[k][i / 2] |= top;
+                    else a[k][i / 2] = top >> 16;
+                    hv[i] = __float_as_uint(__uint_as_float(hv[i]) - __uint_as_float(top));
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[0][i] = (hv[2 * i] & 0xffffu) | (hv[2 * i + 1] << 16);
+                a[1][i] = (hv[2 * i] >> 16) | (hv[2 * i + 1] & 0xffff0000u);
             }
         }
     };
-    auto split_h = [&](unsigned int (&hv)[8], u32x4 &ahi, u32x4 &alo, int kb) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) hv[i] = 32 * kb + 8 * q + i < nrows ? hv[i] : 0u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            ahi[i] = (hv[2 * i] & 0xffffu) | (hv[2 * i + 1] << 16);
-            alo[i] = (hv[2 * i] >> 16) | (hv[2 * i + 1] & 0xffff0000u);
-        }
-    };
+    auto h_value = [](unsigned int v) { return WHOLE ? __uint_as_float(v) : __uint_as_float(v << 16) + __uint_as_float(v & 0xffff0000u); };
 
     // A unit is requested and consumed in turn; the waves of two workgroups share a compute unit (at most 128
     // registers per lane, 80 KiB of LDS each; four waves a SIMD and no more: left to itself the compiler aims at six and waits for each load
@@ -538,7 +561,7 @@ k_bat_down(const Args args)
     u32x4 wA[8];
     unsigned int hA[MT][8];
     for (int kb = rw; kb < nkb; kb += 4) {
-        u32x4 ahi[MT], alo[MT];
+        u32x4 a[MT][PARTS];
         if (MT == 1) h_load(hA, kb);
         w_load(wA, kb);
         if (MT == 2) {                                       // (the order that 128 registers hold without spills)
@@ -549,13 +572,13 @@ k_bat_down(const Args args)
         stage(wA);
         if (MT == 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) split_h(hA[mt], ahi[mt], alo[mt], kb);
-        process(ahi, alo);
+        for (int mt = 0; mt < MT; ++mt) split_h(hA[mt], a[mt], kb);
+        process(a);
     }
 
     // ---- A cut neuron counts as h = 0 above, and 0 times an infinite weight is NaN.  Finite sums prove that no such weight was in the way, so that
-    // the loop looks at none.  Where a sum is not, this wave looks for one in its units, and if there is one forms its sums again,
-    // neuron by neuron, for the tokens that keep it.
+    // the loop looks at none.  Where a sum is not, this wave looks for one in its units (or for an infinite h that was taken apart), and if there is one
+    // forms its sums again, neuron by neuron, for the tokens that keep it.
     float finite = 0.0f;                                                // NaN unless every sum is
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -572,6 +595,13 @@ k_bat_down(const Args args)
             for (int ii = 0; ii < 8; ++ii)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) bad = bad || (wA[ii][k] & 0x7f80u) == 0x7f80u || (wA[ii][k] & 0x7f800000u) == 0x7f800000u;
+            if constexpr (WHOLE) {
+                h_load(hA, kb);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) bad = bad || (hA[mt][i] & 0x7fffffffu) == 0x7f800000u;
+            }
         }
         if (__ballot(bad)) {
 #pragma unroll
@@ -592,7 +622,7 @@ k_bat_down(const Args args)
                             const float wv = __uint_as_float((unsigned int)w[16 * t] << 16);
 #pragma unroll
                             for (int r = 0; r < 4; ++r) {
-                                const float sum = fmaf(__uint_as_float(h[r] << 16) + __uint_as_float(h[r] & 0xffff0000u), wv, acc[mt][t][r]);
+                                const float sum = fmaf(h_value(h[r]), wv, acc[mt][t][r]);
                                 acc[mt][t][r] = h[r] != H_CUT ? sum : acc[mt][t][r];
                             }
                         }
@@ -802,11 +832,14 @@ static clada_status bat_launch(clada_ctx *ctx, const Args &args, const BatParams
 #undef CLADA_BAT_CASE
     CLADA_CHECK_HIP(ctx, hipGetLastError());
     const size_t lds = 8 * (size_t)DN_TILE_BYTES + sizeof(int) * DN_MAX_ROWS;
-    static std::atomic<bool> attr_set[2];                               // set once per process and kernel (two first callers may both set it)
-    const auto down = p.mt == 2 ? k_bat_down<2, Args> : k_bat_down<1, Args>;
-    if (!attr_set[p.mt - 1].load(std::memory_order_relaxed)) {
+    static std::atomic<bool> attr_set[4];                               // set once per process and kernel (two first callers may both set it)
+    const bool whole = whole_h(d);
+    const auto down = p.mt == 2 ? (whole ? k_bat_down<2, true, Args> : k_bat_down<2, false, Args>)
+                                : (whole ? k_bat_down<1, true, Args> : k_bat_down<1, false, Args>);
+    std::atomic<bool> &set = attr_set[2 * (p.mt - 1) + whole];
+    if (!set.load(std::memory_order_relaxed)) {
         CLADA_CHECK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(down), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        attr_set[p.mt - 1].store(true, std::memory_order_relaxed);
+        set.store(true, std::memory_order_relaxed);
     }
     hipLaunchKernelGGL(down, dim3(p.CG * p.RG, n_pass, n_layers), dim3(512), lds, stream, args);
     CLADA_CHECK_HIP(ctx, hipGetLastError());

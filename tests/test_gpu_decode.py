@@ -408,6 +408,36 @@ def test_equal_h_of_neurons_with_opposite_rows_cancel_exactly(clada, d, B):
     assert int(cnt[0]) == F and not y.any()
 
 
+@pytest.mark.parametrize("d,B,relu", [(512, 12, False), (512, 40, True), (768, 7, False), (768, 32, True), (1536, 5, False), (1536, 16, True), (1536, 17, False),
+                                      (3584, 3, False), (3584, 4, True), (3584, 31, False)])
+def test_h_has_all_its_bits_where_the_vector_kernel_has_them(clada, d, B, relu):
+    """Neuron 2k has a random h of 24 bits, neuron 2k + 1 its first 16 bits, and their W_down rows are +1 and -1 in column k: what is left is the other
+    eight bits, exactly.  Batches of these widths run on the vector units or on the matrix cores by their size."""
+    from paper_2502_19078_amd import binding
+    F = 1000
+    g = torch.Generator(device=DEV).manual_seed(d + B)
+    p = _parts(1.0 + torch.rand(F // 2, generator=g, device=DEV))
+    w = [torch.zeros(F, d, device=DEV) for _ in range(3)]
+    w[0][:, 0] = 32.0                                        # SiLU(32) = 32
+    up = w[0] if relu else w[1]
+    up[0::2, :3] = p
+    up[1::2, :3] = p * torch.tensor([1.0, 1.0, 0.0], device=DEV)
+    k = torch.arange(F // 2, device=DEV)
+    w[2][2 * k, k], w[2][2 * k + 1, k] = 1.0, -1.0
+    assert all(torch.equal(v.bfloat16().float(), v) for v in w)
+    x = torch.zeros(B, d, device=DEV)
+    x[:, :3] = 1.0
+    w = [v.bfloat16() for v in w]
+    layer = clada.Layer(w[0], None, w[2], kind=binding.RELU) if relu else clada.Layer(*w)
+    want = torch.zeros(B, d, device=DEV)
+    want[:, :F // 2] = p[:, 2] * (1.0 if relu else 32.0)
+    for batched in (1, 0):
+        ctx = clada.Context(0, clada.workspace_bytes(d, F, B, 0, 0))
+        ctx.set_option("decode.batched", batched)
+        y = clada.sparse_ffn_decode(ctx, layer, x.bfloat16(), torch.full((B,), 0.5, device=DEV))
+        assert p[:, 2].count_nonzero() > F // 3 and torch.equal(y.float(), want), batched
+
+
 def test_infinite_weight_of_a_neuron_a_token_cuts_stays_out_of_its_output(clada):
     """Token 0 keeps neuron 5, whose output row holds an infinity; token 1 cuts it and stays finite."""
     cfg, w, x = _case("c1", 22, 2048, 500, 2)
