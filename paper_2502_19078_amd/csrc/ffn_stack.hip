@@ -53,19 +53,15 @@ __device__ __forceinline__ unsigned int lds_offset(const void *p)
 // and would wait for every load in flight before any LDS access.  A load has no register result; its slot is read only
 // after the wait for the vector-memory counter below, and is refilled only after that read has returned.  The slot's address
 // reaches m0 through its constraint, so the compiler knows what m0 holds.
-template <bool VBASE = false>
+// The base is the same in every lane, but the compiler is free to compute it in vector registers (it does for some row lengths), and a scalar register
+// that a vector instruction has written may be a load's base five wait states later at the earliest, which the assembler does not see to.
+// So the load reads a copy that a scalar instruction makes right before it, which the hardware waits for; that is also the wait state behind m0.
 __device__ __forceinline__ void ring_load(const char *base, unsigned int voff, unsigned int slot)
 {
-    if constexpr (!VBASE) {
-        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "{m0}"(slot) : "memory");
-    } else {
-        // The base is the same in every lane, but the instances of 6 KiB rows compute it in vector registers.  A scalar register
-        // that a vector instruction has written may be a load's base five wait states later at the earliest, which the assembler
-        // does not see to.
-        const unsigned long long b = (unsigned long long)base;
-        const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)b), hi = __builtin_amdgcn_readfirstlane((unsigned int)(b >> 32));
-        asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(((unsigned long long)hi << 32) | lo), "{m0}"(slot) : "memory");
-    }
+    const unsigned long long b = (unsigned long long)base;
+    const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)b), hi = __builtin_amdgcn_readfirstlane((unsigned int)(b >> 32));
+    unsigned long long copy;
+    asm volatile("s_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0 nt" : "=&s"(copy) : "v"(voff), "s"(((unsigned long long)hi << 32) | lo), "{m0}"(slot) : "memory");
 }
 __device__ __forceinline__ void ring_load_lanes(const char *p, unsigned int slot)
 {
@@ -215,7 +211,6 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
 {
     typedef RowShape<NCH, LONE> S;
     typedef const __attribute__((address_space(4))) StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS> *StackLaunchArgs;
-    constexpr bool VBASE = NCH == 6;
     constexpr int NW = S::NW, NWC = S::NWC, RD = S::RD, UC = S::UC, R = S::R, PARTS = S::PARTS, CWB = S::CWB, EPL = S::EPL;
     constexpr int ROWB = NCH * 1024, UNIT = UC * 1024;
     constexpr int DW = CWB / 256, VEC = 4 * DW / ES;          // words / values of a kept row per lane
@@ -239,7 +234,7 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
     const unsigned int loff = lane * 16;
     const unsigned int ring0 = lds_offset(&s_ring[0][0][0]) + wave * (RD * UNIT), x0 = lds_offset(s_x);
 
-    for (int c = wave; c < NCH; c += NW) ring_load<VBASE>(xg + c * 1024, loff, x0 + c * 1024);
+    for (int c = wave; c < NCH; c += NW) ring_load(xg + c * 1024, loff, x0 + c * 1024);
 
     // local neuron i = (class i / per, position i % per) of this workgroup: neuron group + 32 class + 256 position
     // when it takes a whole slice, group + 256 i when it takes one class
@@ -296,7 +291,7 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
                     row = wu + (size_t)__builtin_amdgcn_readfirstlane(s_lrow[lr & 1][i]) * ROWB;
                 }
 #pragma unroll
-                for (int c = 0; c < UC / R; ++c) ring_load<VBASE>(row + lp * UNIT + c * 1024, loff, slot + (q * (UC / R) + c) * 1024);
+                for (int c = 0; c < UC / R; ++c) ring_load(row + lp * UNIT + c * 1024, loff, slot + (q * (UC / R) + c) * 1024);
             }
             if (++lp == PARTS) { lp = 0; li += NW * R; }
         } else {
@@ -305,7 +300,7 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
 #pragma unroll
                 for (int q = 0; q < UC; ++q) {
                     const int e = min(li + q, kp - 1);
-                    ring_load<VBASE>(wd + (size_t)__builtin_amdgcn_readfirstlane(s_lrow[lr & 1][e]) * ROWB + wave * CWB, loff, slot + q * 1024);
+                    ring_load(wd + (size_t)__builtin_amdgcn_readfirstlane(s_lrow[lr & 1][e]) * ROWB + wave * CWB, loff, slot + q * 1024);
                 }
             } else {                                         // EPL rows per load, the lanes shared out
                 constexpr int LPR = 64 / EPL;
