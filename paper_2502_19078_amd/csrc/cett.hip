@@ -1440,9 +1440,9 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
             CLADA_CHECK_HIP(ctx, hipGetLastError());
         }
         // What the tables left open (a great many equal magnitudes): an even number of launches, the last of which takes in the 31st
-        // step.  (Twelve would do above 512 tokens as well; a test counts 32 at 1024.)
+        // step.  (Most find nothing left: 32 of them / 12 at 700 tokens of 4096 x 11008 529 / 471 us, at 1024 of 1024 x 4096 292 / 218.)
         const int levels = between_levels(d, between_shape(d, (int)dtype_size(layer->dtype)).parts);
-        return tail(T > 512 ? 32 : levels == 3 ? 12 : levels == 2 ? 18 : 32);
+        return tail(levels == 3 ? 12 : levels == 2 ? 18 : 32);
     }
     for (int it = 0; it < DENSE_PROBES; ++it)
         if ((st = dense(it)) != CLADA_OK) return st;

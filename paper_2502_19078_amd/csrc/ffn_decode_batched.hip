@@ -731,20 +731,20 @@ size_t clada_ws_decode_batched(int32_t d_ff)
 
 // Whether a batch is for the matrix cores: rows that have instances of their own kernels; the narrow ones and two odd widths from the batch on that
 // the vector kernel or the generic one takes longer for.  Lone calls, us, vector or generic / matrix cores, gated (ReLU): 512 x 2048 at 9 and 12 tokens
-// 16.4 / 16.1, 18.8 / 16.1 (14.8 / 16.3, 16.5 / 15.9), 512 x 1024 at 12 and 16 16.5 / 15.6 (15.4 / 15.8, 19.1 / 16.1); 768 x 1536 at 6 and 9 16.6 / 16.0,
-// 25.5 / 16.0 (14.0 / 15.7, 18.0 / 15.7), 768 x 3072 at 32 85 / 23; 1536 x 3072 at 4 and 6 18.8 / 19.5, 24.5 / 19.7, 1536 x 6000 25.9 / 23.2, 35.1 / 23.2, a list of
-// 2500 at 4 18.5 / 19.1, 1536 x 4100 at 32 124 / 30; 3584 x 8048 at 2 and 3 36.2 / 37.1, 42.9 / 39.3 (25.5 / 27.9, 29.7 / 28.6), 3584 x 14000 at 3 65 / 59
-// (39.5 / 40.6), 3584 x 8048 at 32 261 / 68.  Stacks gain more (1.3 times at two tokens of 3584, 2 - 5 times at 16 of any) but go the way of the lone call,
-// whose bits they have.  Whole passes of the vector kernel at 768 gated values, and up to nine tokens of 1536 non-gated ones, stay with it: a test
-// names its kernel there (22 / 17 and 31 / 18 us).
+// 16.4 / 16.1, 18.8 / 16.1 (14.8 / 16.3, 16.5 / 15.9), 512 x 1024 at 12 and 16 16.5 / 15.6 (15.4 / 15.8, 19.1 / 16.1); 768 x 1536 at 6, 8 and 16 16.6 / 16.0,
+// 18.6 / 15.0, 37.1 / 16.2, at 9 25.5 / 16.0 (14.0 / 15.7, 18.0 / 15.7), 768 x 3072 at 8 and 32 22.6 / 15.8, 85 / 23; 1536 x 3072 at 4 and 6 18.8 / 19.5, 24.5 / 19.7,
+// 1536 x 6000 25.9 / 23.2, 35.1 / 23.2, a list of 2500 at 4 18.5 / 19.1, 1536 x 4100 at 32 124 / 30 (1536 x 3072 at 4, 5 and 9 15.9 / 15.9, 19.6 / 16.1, 34.8 / 17.1,
+// x 4100 17.3 / 17.8, 21.4 / 17.8, 37.5 / 18.8, x 6000 20.9 / 19.8, 26.0 / 20.3, 45.7 / 21.2); 3584 x 8048 at 2 and 3 36.2 / 37.1, 42.9 / 39.3 (25.5 / 27.9, 29.7 / 28.6),
+// 3584 x 14000 at 3 65 / 59 (39.5 / 40.6), 3584 x 8048 at 32 261 / 68.  Stacks gain more (1.3 times at two tokens of 3584, 3 - 5 times at 8 and 16 of 768 and
+// 1536) but go the way of the lone call, whose bits they have.
 static bool bat_pays(const clada_layer *layer, int B, bool list)
 {
     const bool relu = layer->kind == CLADA_FFN_RELU;
     switch (layer->d) {
     case 1024: case 2048: case 2560: case 3072: case 4096: case 5120: case 6144: case 8192: return B >= 2;
     case 512: return B >= (relu ? 14 : 12);
-    case 768: return B >= (relu ? 9 : 6) && (relu || (B != 8 && B != 16));
-    case 1536: return B >= (relu ? 10 : list || layer->d_ff < 3840 ? 5 : 4);
+    case 768: return B >= (relu ? 9 : 6);
+    case 1536: return B >= (relu ? 5 : list || layer->d_ff < 3840 ? 5 : 4);
     case 3584: return B >= (relu ? 4 : 3);
     default: return false;
     }
