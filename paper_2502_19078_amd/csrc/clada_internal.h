@@ -102,9 +102,7 @@ hipError_t clada_decode_multi(const clada_layer *layer, const void *x, int32_t B
 #define CLADA_STACK_LAUNCH_LAYERS 48
 size_t clada_ws_stack(int32_t d);
 bool clada_stack_b1_fits(const clada_layer *layer, int32_t L, bool dense);      // shapes it is faster for than lanes
-bool clada_stack_b1_only(const clada_layer *layer);      // rows without a batch-1 kernel of their own: single layers too
-hipError_t clada_stack_b1_lone(const clada_layer *layer, const void *x, const float *tau, bool dense, float *partial /* [256][d] */,
-                               unsigned char *keep /* [d_ff] flags or nullptr */, hipStream_t stream);
+bool clada_stack_b1_only(const clada_layer *layer);      // rows of no other kind of stack; lone layers of them are never balanced
 hipError_t clada_stack_b1(const clada_layer *layers, int32_t L, const void *x, const float *tau, void *y, bool dense,
                           float *partial, size_t partial_bytes, hipStream_t stream);
 // Fixed-order sum of P partial y's [P][B][d] (fp32) into y (element size es).

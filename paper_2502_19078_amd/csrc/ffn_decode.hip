@@ -1348,6 +1348,27 @@ hipError_t launch_b1_shape(clada_ctx *ctx, const B1Params &b, int Pb, int es, in
     return eb;
 }
 
+// Single layers of the rows that clada_stack_b1_only names; never balanced, so that a stack of them has the bits of these calls whatever "decode.b1".
+// us, chains of lone calls, generic kernel / the stack's kernel over one layer / this one (a spread of 0.1): 7.5 / 9.3 / 7.5 at 512 x 1376,
+// 25.9 / 26.3 / 24.6 at 3072 x 8192, 28.8 / 29.5 / 27.7 and 40.2 / 41.6 / 39.8 at 3584 x 8496 and 14000, 9.1 / 10.3 / 8.3 at 768 x 2048 fp32; ReLU 10.6 / 10.8 / 9.2
+// at 1536 x 3200, 14.4 / 14.6 / 12.4 at 2048 x 6000, 21.4 / 19.6 / 18.5 at 3072 x 8192, 23.4 / 21.7 / 20.2 at 3584 x 8496, 44.4 / 40.5 / 40.3 at 6144 x 13000.
+hipError_t launch_b1_lone(clada_ctx *ctx, const B1Params &b, int Pb, int es, int nch, bool relu, bool dense, hipStream_t stream)
+{
+    auto run = [&](auto es_c, auto nch_c, auto relu_c) {
+        constexpr int ES = decltype(es_c)::value, NCH = decltype(nch_c)::value, DCH = NCH > 8 ? 8 : 16;
+        constexpr bool RELU = decltype(relu_c)::value;
+        return dense ? launch_b1_variant<ES, NCH, DCH, true, false, RELU>(ctx, b, Pb, stream)
+                     : launch_b1_variant<ES, NCH, DCH, false, false, RELU>(ctx, b, Pb, stream);
+    };
+#define CLADA_LONE_CASE(ES, NCH, RELU) \
+    if (es == ES && nch == NCH && relu == RELU) return run(std::integral_constant<int, ES>{}, std::integral_constant<int, NCH>{}, std::integral_constant<bool, RELU>{});
+    CLADA_LONE_CASE(2, 1, false) CLADA_LONE_CASE(2, 6, false) CLADA_LONE_CASE(2, 7, false) CLADA_LONE_CASE(4, 3, false)
+    CLADA_LONE_CASE(2, 1, true) CLADA_LONE_CASE(2, 3, true) CLADA_LONE_CASE(2, 4, true) CLADA_LONE_CASE(2, 6, true) CLADA_LONE_CASE(2, 7, true)
+    CLADA_LONE_CASE(2, 12, true)
+#undef CLADA_LONE_CASE
+    return hipErrorNotSupported;
+}
+
 // Balancing pays when the kept-row phase is long enough to hide the mask exchange behind the
 // workgroup's own first chunk: measured faster on the 7B/8B shapes (90-117 MB per matrix), slower
 // on 52 MB ReLU layers (17.0 vs 14.1 us) and on 8 MB ones (10.0 vs 6.4 us).  With 10 KiB gated rows
@@ -1418,7 +1439,9 @@ clada_status run_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
     // ---- split-d path (decode batch 1, whole-KiB rows, <= 64 neurons per workgroup)
     // (exactly the instantiations launched below: a shape admitted here without one would fail the call)
     const bool b1_shape = b1_shape_ok(es, nch, relu);
-    if (ctx->opt_decode_b1 >= 1 && B == 1 && (d * es) % 1024 == 0 && b1_shape) {
+    // rows whose stacks have no other kernel: with the 256 workgroups whose order of summation those have
+    const bool b1_only = clada_stack_b1_only(layer) && ctx->num_cu >= COOP_MAX_WGS;
+    if (ctx->opt_decode_b1 >= 1 && B == 1 && (d * es) % 1024 == 0 && (b1_shape || b1_only)) {
         const int Pb = ctx->num_cu < COOP_MAX_WGS ? ctx->num_cu : COOP_MAX_WGS;
         const int ni_b = (F + Pb - 1) / Pb;
         if (F >= Pb && ni_b <= 1024) {
@@ -1434,9 +1457,10 @@ clada_status run_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
             b.d = d; b.F = F;
             b.K0 = ctx->opt_decode_own_first > 0 ? ctx->opt_decode_own_first : 14;
             b.gelu = p.gelu;
-            bool balance = b1_wants_balance(ctx, dense, relu, ni_b, d, F, es);
+            bool balance = b1_shape && b1_wants_balance(ctx, dense, relu, ni_b, d, F, es);
             b.prev_partial = nullptr; b.prev_y = nullptr; b.prev_bias = nullptr; b.epoch_out = nullptr;
-            hipError_t eb = launch_b1_shape(ctx, b, Pb, es, nch, relu, dense, &balance, stream);
+            hipError_t eb = b1_shape ? launch_b1_shape(ctx, b, Pb, es, nch, relu, dense, &balance, stream)
+                                     : launch_b1_lone(ctx, b, Pb, es, nch, relu, dense, stream);
             CLADA_CHECK_HIP(ctx, eb);
             launch_finalize(es, p.partial, Pb, 1, d, (char *)y, balance ? epoch : nullptr, stream,
                             ctx->opt_diag_events ? ctx->ev[2] : nullptr, ctx->ev[3], b_out, balance ? b.fault : nullptr);
@@ -1447,20 +1471,6 @@ clada_status run_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
             }
             return CLADA_OK;
         }
-    }
-    // ---- other whole-KiB rows at batch 1: the kernel of the whole-stack calls over one layer
-    if (ctx->opt_decode_b1 >= 1 && B == 1 && clada_stack_b1_only(layer) && ctx->num_cu >= COOP_MAX_WGS && F >= COOP_MAX_WGS &&
-        F <= 1024 * COOP_MAX_WGS) {
-        if (ctx->opt_diag_events) CLADA_CHECK_HIP(ctx, hipEventRecord(ctx->ev[0], stream));
-        CLADA_CHECK_HIP(ctx, clada_stack_b1_lone(layer, x, tau, dense, p.partial, p.keep, stream));
-        if (ctx->opt_diag_events) CLADA_CHECK_HIP(ctx, hipEventRecord(ctx->ev[1], stream));
-        launch_finalize(es, p.partial, COOP_MAX_WGS, 1, d, (char *)y, nullptr, stream, ctx->opt_diag_events ? ctx->ev[2] : nullptr, ctx->ev[3], b_out);
-        CLADA_CHECK_HIP(ctx, hipGetLastError());
-        if (lists) {
-            hipLaunchKernelGGL(k_ffn_lists, dim3(1), dim3(1024), 0, stream, p.keep, B, F, active_idx, n_active, mask_bits);
-            CLADA_CHECK_HIP(ctx, hipGetLastError());
-        }
-        return CLADA_OK;
     }
     // ---- batched MFMA path (bf16, supported widths): up to 16 or 32 tokens per pass; larger batches run
     // as passes of near-equal size, each re-reading the weights of its own union

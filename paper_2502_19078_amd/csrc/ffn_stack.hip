@@ -14,33 +14,29 @@
 namespace {
 
 constexpr int CLASSES = 256, SLICES = 32, CHAIN = CLASSES / SLICES;
-constexpr int KEEP_ROUNDS = 16;             // rounds of 64 neurons of a class whose keep flags can be asked for
 
-template <int N> struct StackTables {        // kernel argument; the tables are read by scalar loads at the layer's index
-    const char *wg[N], *wu[N], *wd[N];
-    const float *b_in[N];
+struct StackLaunch {                        // kernel argument; the tables are read by scalar loads at the layer's index
+    const char *wg[CLADA_STACK_LAUNCH_LAYERS], *wu[CLADA_STACK_LAUNCH_LAYERS], *wd[CLADA_STACK_LAUNCH_LAYERS];
+    const float *b_in[CLADA_STACK_LAUNCH_LAYERS];
     const char *x;                          // [n][d]
     const float *tau;                       // [n] (unused when dense)
     float *partial;                         // [n][256 / chain][d]
-    unsigned char *keep;                    // a single layer's [F] keep flags, or nullptr
     int F, d, chain, dense, gelu;
 };
-typedef StackTables<CLADA_STACK_LAUNCH_LAYERS> StackLaunch;
+typedef const __attribute__((address_space(4))) StackLaunch *StackLaunchArgs;
 
 // Per row length (NCH chunks of 1 KiB): the workgroup's waves and a wave's ring in LDS, two units of UC loads of 1 KiB.  A
 // unit is half a row, a row or two short rows; for the down projection UC * EPL kept rows of the wave's columns (one or half
 // a KiB).  The waves of a compute unit keep about 100 KiB of weight rows in flight; 7 TB/s take 55 KiB at 2 us of loaded
 // latency.  (Four waves for 2 KiB rows: 62 us per step of 24 layers of 8 MB against 67 us with eight.)  Rows of 1 and 3 KiB have
 // two waves for every KiB as well; units of three loads serve the rows of 3 and 6 KiB, rows of 7 KiB go whole.
-// LONE: a single layer, one workgroup on a unit: more waves, the further ones for whole rows only.
-template <int NCH, bool LONE = false> struct RowShape {
-    static constexpr int NWC = NCH < 4 ? 2 * NCH : NCH;      // waves with columns of the kept rows
-    static constexpr int NW = !LONE || NCH > 7 ? NWC : NCH == 1 ? 4 : NCH == 7 ? 10 : 16;
+template <int NCH> struct RowShape {
+    static constexpr int NW = NCH < 4 ? 2 * NCH : NCH;
     static constexpr int UC = NCH % 5 == 0 ? 5 : NCH == 3 || NCH == 6 ? 3 : NCH == 7 ? 7 : 4;
     static constexpr int RD = 2;                             // units of a ring
     static constexpr int R = UC > NCH ? UC / NCH : 1;        // rows per gate / up unit
     static constexpr int PARTS = NCH > UC ? NCH / UC : 1;    // units per row
-    static constexpr int CWB = NCH * 1024 / NWC;             // bytes of a row's columns per wave
+    static constexpr int CWB = NCH * 1024 / NW;              // bytes of a row's columns per wave
     static constexpr int EPL = 1024 / CWB;                   // kept rows per down-projection load
     static_assert((R * NCH == UC || PARTS * UC == NCH) && (EPL == 1 || EPL == 2), "whole rows or whole parts");
 };
@@ -205,13 +201,12 @@ template <> __device__ __forceinline__ void ring_read<7, 4>(unsigned int a, Ring
 // wave takes its own columns.  A wave loads and consumes in the order G0 G1 U0 D0 G2 U1 D1 ..: the list of round r is known
 // (barrier) while the rows of G(r + 1) are in flight, and the exchange of h (barrier) happens while D(r) is, so the stream
 // of loads never waits for either.
-template <int ES, int NCH, bool RELU, bool LONE = false>
-__global__ void __launch_bounds__((RowShape<NCH, LONE>::NW * 64))
-k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
+template <int ES, int NCH, bool RELU>
+__global__ void __launch_bounds__(RowShape<NCH>::NW * 64)
+k_ffn_stack(const StackLaunch)
 {
-    typedef RowShape<NCH, LONE> S;
-    typedef const __attribute__((address_space(4))) StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS> *StackLaunchArgs;
-    constexpr int NW = S::NW, NWC = S::NWC, RD = S::RD, UC = S::UC, R = S::R, PARTS = S::PARTS, CWB = S::CWB, EPL = S::EPL;
+    typedef RowShape<NCH> S;
+    constexpr int NW = S::NW, RD = S::RD, UC = S::UC, R = S::R, PARTS = S::PARTS, CWB = S::CWB, EPL = S::EPL;
     constexpr int ROWB = NCH * 1024, UNIT = UC * 1024;
     constexpr int DW = CWB / 256, VEC = 4 * DW / ES;          // words / values of a kept row per lane
     constexpr int EPU = UC * EPL;                             // kept rows per down-projection unit
@@ -221,12 +216,11 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
     __shared__ int s_keep[2][64];
     __shared__ int s_lrow[2][64], s_lcls[2][64];
     __shared__ float s_la[2][64], s_h[2][64];
-    __shared__ unsigned long long s_kept[LONE ? KEEP_ROUNDS : 1];
 
     const StackLaunchArgs ka = (StackLaunchArgs)__builtin_amdgcn_kernarg_segment_ptr();
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int layer = LONE ? 0 : blockIdx.y, group = blockIdx.x, chain = ka->chain;
+    const int layer = blockIdx.y, group = blockIdx.x, chain = ka->chain;
     const int F = ka->F, dense = ka->dense, gelu = ka->gelu;
     const char *wg = ka->wg[layer], *wu = ka->wu[layer], *wd = ka->wd[layer];
     const __attribute__((address_space(4))) float *b_in = (const __attribute__((address_space(4))) float *)(RELU ? ka->b_in[layer] : nullptr);
@@ -257,7 +251,7 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
                 if (lr >= n_list) return false;              // not known yet: come back later
                 lim = kp2[lr & 1];
             }
-            if (li < (NWC < NW && ph == 2 && wave >= NWC ? 0 : lim)) break;
+            if (li < lim) break;
             if (ph == 0) {                                   // after G(lr): U(lr - 1); after G(0) the next round's rows
                 if (lr == 0 && n_round > 1) {
                     lr = 1; li = wave; jv_load = neuron_of(64 + lane); lim = min(64, n_local - 64);
@@ -408,7 +402,6 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
             opens2[p] = __ballot(lane < kp && lcls != lprev);
             if (kp > 0) cur_cls = __builtin_amdgcn_readlane(lcls, kp - 1);
             kp2[p] = kp;
-            if (LONE && tid == 0) s_kept[r & (KEEP_ROUNDS - 1)] = mask;
             n_list = r + 1;
             fill();                                          // the ring may have run dry waiting for this list
         }
@@ -429,7 +422,7 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
                 __syncthreads();
                 hs = s_h[p];
             }
-            for (int e0 = 0; e0 < (wave < NWC ? kp : 0); e0 += EPU) {
+            for (int e0 = 0; e0 < kp; e0 += EPU) {
                 const unsigned int slot = wait_oldest();
                 typename RingWords<DW>::type v[EPL][UC];
 #pragma unroll
@@ -459,16 +452,8 @@ k_ffn_stack(const StackTables<LONE ? 1 : CLADA_STACK_LAUNCH_LAYERS>)
     }
     close_class();
     float *dst = ka->partial + ((size_t)layer * gridDim.x + group) * ka->d + wave * (CWB / ES) + lane * VEC;
-    if (wave < NWC) {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) dst[k] = sum[k];
-    }
-    if (LONE && ka->keep && wave == 0) {                             // written and read by this wave; stores during the stream would count as its loads
-        for (int r = 0; r < n_round && r < KEEP_ROUNDS; ++r) {
-            const int j = neuron_of(64 * r + lane);
-            if (j >= 0) ka->keep[j] = (unsigned char)((s_kept[r] >> lane) & 1ull);
-        }
-    }
+    for (int k = 0; k < VEC; ++k) dst[k] = sum[k];
 }
 
 struct StackReduceArgs {
@@ -548,60 +533,14 @@ hipError_t launch_rows(const StackLaunch &p, dim3 grid, bool relu, hipStream_t s
     return hipErrorNotSupported;
 }
 
-template <int ES, int NCH>
-hipError_t launch_lone(const StackTables<1> &p, bool relu, hipStream_t st)
-{
-    constexpr int threads = RowShape<NCH, true>::NW * 64;
-    if constexpr (ES == 2) {
-        if (relu) {
-            hipLaunchKernelGGL((k_ffn_stack<2, NCH, true, true>), dim3(CLASSES), dim3(threads), 0, st, p);
-            return hipGetLastError();
-        }
-    }
-    if constexpr (NCH != 4 && NCH != 12 && !(ES == 2 && NCH == 3)) {      // (these gated rows do not come here)
-        if (!relu) {
-            hipLaunchKernelGGL((k_ffn_stack<ES, NCH, false, true>), dim3(CLASSES), dim3(threads), 0, st, p);
-            return hipGetLastError();
-        }
-    }
-    return hipErrorNotSupported;
-}
-
 }  // namespace
-
-// Single layers of clada_stack_b1_only.  us, lone calls, the generic kernel / this one, within a spread of
-// 0.5: 11.0 / 10.7 at 512 x 1376, 11.7 / 11.9 at 1536 x 6000 ReLU, 14.2 / 14.3 at 2048 x 8192 ReLU, 23.3 / 23.4 at 3072 x 8192, 26.3 / 26.7
-// at 3584 x 8496, ReLU 21.1 / 19.0, 42.7 / 38.2 at 6144 x 13000 ReLU.
-hipError_t clada_stack_b1_lone(const clada_layer *layer, const void *x, const float *tau, bool dense, float *partial,
-                               unsigned char *keep, hipStream_t stream)
-{
-    const int es = (int)dtype_size(layer->dtype), nch = layer->d * es / 1024;
-    const bool relu = layer->kind == CLADA_FFN_RELU;
-    StackTables<1> p;
-    p.wg[0] = (const char *)layer->w_gate; p.wu[0] = (const char *)layer->w_up; p.wd[0] = (const char *)layer->w_down;
-    p.b_in[0] = relu ? layer->b_in : nullptr;
-    p.x = (const char *)x; p.tau = tau; p.partial = partial; p.keep = keep;
-    p.F = layer->d_ff; p.d = layer->d; p.chain = 1; p.dense = dense ? 1 : 0;
-    p.gelu = layer->kind == CLADA_FFN_GEGLU ? 1 : 0;
-    switch (es == 2 ? nch : 100 + nch) {
-    case 1: return launch_lone<2, 1>(p, relu, stream);
-    case 3: return launch_lone<2, 3>(p, relu, stream);
-    case 4: return launch_lone<2, 4>(p, relu, stream);
-    case 6: return launch_lone<2, 6>(p, relu, stream);
-    case 7: return launch_lone<2, 7>(p, relu, stream);
-    case 12: return launch_lone<2, 12>(p, relu, stream);
-    case 103: return launch_lone<4, 3>(p, relu, stream);
-    default: return hipErrorNotSupported;
-    }
-}
 
 size_t clada_ws_stack(int32_t d) { return sizeof(float) * (size_t)CLADA_STACK_LAUNCH_LAYERS * SLICES * d; }
 
-// Rows that have no batch-1 kernel of their own: every layer of them, alone or in a stack, runs here (us per step, generic kernel /
+// Rows that only run here in a stack and, layer by layer, on the batch-1 kernel without balancing (us per step, per-layer calls of the generic kernel /
 // this one: 189 / 36 at 24 layers of 512 x 1376, 282 / 86 at 24 of 1536 x 4096 ReLU, 343 / 112 at 24 of 2048 x 4632 ReLU, 610 / 442 at
 // 24 of 3072 x 8192, 686 / 480 at 24 of 3584 x 8496, 368 / 262 at 8 of 6144 x 13000 ReLU, 83 / 36 at 8 of 768 x 2048 fp32; two layers
-// 1.03 - 1.3 times as fast).  A stack has the bits of its layers' lone calls, so only rows whose lone call is not slower here: gated bf16 rows
-// of 3 KiB (11.7 / 12.7 at 1536 x 4096), fp32 rows of 4 and 6 KiB (10.8 / 12.3, 15.7 / 17.4) stay on the generic kernel.
+// 1.03 - 1.3 times as fast).  Gated bf16 rows of 3 KiB and fp32 rows of 4 and 6 KiB stay on the generic kernel, alone and in stacks.
 bool clada_stack_b1_only(const clada_layer *layer)
 {
     const int row = layer->d * (int)dtype_size(layer->dtype), nch = row / 1024;

@@ -230,7 +230,7 @@ ONE_LAUNCH = [
     # a thin last round in a launch of its own, of single classes; single classes in two launches
     (4096, 1030, 9, False, "bf16"), (2560, 2600, 12, True, "bf16"), (2048, 1100, 18, False, "bf16"), (1024, 1000, 7, False, "bf16"),
     (5120, 700, 51, False, "bf16"), (2048, 900, 11, False, "f32"),
-    # rows that no other batch-1 kernel takes: their lone layers are single classes of the same kernel
+    # rows that run here only as stacks: their lone layers are the batch-1 kernel without balancing
     (512, 1283, 9, False, "bf16"), (512, 300, 3, True, "bf16"), (512, 17000, 2, True, "bf16"), (1536, 3001, 8, True, "bf16"), (1536, 700, 5, True, "bf16"),
     (2048, 2300, 17, True, "bf16"), (3072, 2111, 9, False, "bf16"), (3072, 900, 3, True, "bf16"), (3584, 1700, 6, False, "bf16"),
     (3584, 16500, 2, False, "bf16"), (3584, 257, 9, True, "bf16"), (6144, 1100, 5, True, "bf16"), (6144, 600, 2, True, "bf16"),
@@ -260,12 +260,14 @@ def test_one_launch_over_the_layers_is_the_per_layer_calls_bit_for_bit(clada, d,
         for l in range(L):
             assert torch.equal(y[l], clada.sparse_ffn_decode(ctx, layers[l], x[l:l + 1], tau[l:l + 1])[0]), f"layer {l}"
             assert torch.equal(yd[l], clada.dense_ffn_decode(ctx, layers[l], x[l:l + 1])[0]), f"dense, layer {l}"
-    # the generic kernel, another order of fp32 sums: one output rounding (2^-8 of a value for bf16, spread over the row) apart at most
+    # the generic kernel, another order of the same products' sum: one output rounding (2^-8 of a value for bf16, spread over the row) apart at most;
+    # fp32: 2^-24 of the running sum an addition, independent of each other, chains and trees of fewer than 256 of them on either side:
+    # sqrt(512) 2^-24 = 1.3e-6
     yl, _, cl, _ = clada.sparse_ffn_decode(ctx, layers[1], x[1:2], tau[1:2], want_lists=True)
     assert torch.equal(yl[0], y[1])
     ctx.set_option("decode.b1", 0)
     yg, _, cg, _ = clada.sparse_ffn_decode(ctx, layers[1], x[1:2], tau[1:2], want_lists=True)
-    assert (cl - cg).abs().max() <= 2 and (yl - yg).double().norm() <= (2 ** -8 if dtype == "bf16" else 2e-4) * yg.double().norm() + 1e-30
+    assert (cl - cg).abs().max() <= 2 and (yl - yg).double().norm() <= (2 ** -8 if dtype == "bf16" else 1.3e-6) * yg.double().norm() + 1e-30
 
 
 @pytest.mark.parametrize("d,F,L", [(512, 256, 2), (512, 1376, 9), (2048, 700, 3)])

@@ -280,6 +280,22 @@ def test_decode_of_several_tokens_takes_the_faster_kernel(fake, d, F, B, dtype, 
         assert any("k_bat_gateup" in n for n in _names(r[1])) != multi
 
 
+@pytest.mark.parametrize("d,dtype,kind,stack", [
+    # every row length that only the launches over many layers take in a stack, and neighbours of theirs that the generic kernel runs either way
+    (512, "bf16", "swiglu", True), (512, "bf16", "relu", True), (1536, "bf16", "relu", True), (2048, "bf16", "relu", True), (3072, "bf16", "geglu", True),
+    (3072, "bf16", "relu", True), (3584, "bf16", "swiglu", True), (3584, "bf16", "relu", True), (6144, "bf16", "relu", True), (768, "f32", "swiglu", True),
+    (1536, "bf16", "swiglu", False), (768, "f32", "relu", False), (1024, "f32", "geglu", False), (1536, "f32", "swiglu", False),
+])
+def test_a_lone_layer_is_the_batch_1_kernel_where_its_stack_is_one_launch(fake, d, dtype, kind, stack):
+    """A stack has the bits of its layers' lone calls: single classes of 256 workgroups, never balanced, up to 1024 neurons a workgroup."""
+    for F, dense in ((256, False), (16000, False), (60000, False), (60000, True), (255, False)):
+        step = {"d": d, "F": F, "B": 1, "dtype": dtype, "kind": kind, "dense": dense}
+        r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 1, 0, 0]}, dict(step, do="decode"), dict(step, do="stack", L=3)])
+        assert any("k_ffn_decode_b1" in n for n in _names(r[1])) == (stack and F >= 256)
+        assert [x[1] for x in r[1]["launches"] if "k_ffn_decode_b1" in x[0]] == [256] * (stack and F >= 256)
+        assert (_stack_grid(r[2]) is not None) == (stack and F >= 256)
+
+
 @pytest.mark.parametrize("d,F,T,kind,tiles,spare", [
     # gated, 128-token tiles (2 x neurons / 128), the units that are left take the norms of at most 16 + d / 64 rows a wave
     (4096, 11008, 129, "swiglu", 176, 80), (4096, 12288, 256, "swiglu", 192, 64), (4096, 14336, 129, "swiglu", 224, 0),
