@@ -88,18 +88,13 @@ __device__ __forceinline__ BatParams bat_unit(const BatArgs &)
 }
 
 // An fp32 h as the sum of two bf16: the rounded value below, the rounded rest above (16 to 17 of its 24 bits).  Split once here and not by every
-// column group of the down kernel.  The rest is taken from the rounded product, not from the product inside an fma.  An infinite h has no rest, and
-// one that would round up to infinity is cut instead, so that neither turns into infinity minus infinity.
+// column group of the down kernel.  The rest is taken from the rounded product, not from the product inside an fma.  What would round up to infinity
+// is cut to the largest bf16 first; an infinite h is that and an infinite rest, so that nothing turns into infinity minus infinity.
 __device__ __forceinline__ unsigned int split_bf16(float h)
 {
 #pragma clang fp contract(off)
-    float hi = (float)(__bf16)h, lo = h - hi;                        // (nearest even)
-    if (!(fabsf(lo) < INFINITY)) {
-        const bool finite = fabsf(h) < INFINITY;
-        if (finite) hi = copysignf(0x1.fep127f, h);
-        lo = finite ? h - hi : 0.0f;
-    }
-    return (unsigned int)__builtin_bit_cast(unsigned short, (__bf16)hi) | ((unsigned int)__builtin_bit_cast(unsigned short, (__bf16)lo) << 16);
+    const __bf16 hi = (__bf16)__builtin_amdgcn_fmed3f(h, -0x1.fep127f, 0x1.fep127f), lo = (__bf16)(h - (float)hi);       // (nearest even)
+    return (unsigned int)__builtin_bit_cast(unsigned short, hi) | ((unsigned int)__builtin_bit_cast(unsigned short, lo) << 16);
 }
 // h of a neuron that the token cuts: a zero, and no value of the above (its rest has the sign of h, or is +0).
 constexpr unsigned int H_CUT = 0x80000000u;
@@ -486,17 +481,25 @@ k_bat_down(const Args args)
 #pragma unroll
         for (int i = 0; i < 8; ++i) row[i] = e0 + i < nrows ? (int)(i < 4 ? a[i & 3] : b[i & 3]) : last_row;
     };
-    // h[token n][list entries 8 q ..] of block kb (a token that does not exist: the last one again, or one that keeps nothing; its sums are
-    // not stored).  No branch around any load: eight of
-    // them, one after the other behind a look into the list, held every unit up (one layer of 5120 x 13824 at 16 tokens 87.1 / 86.3 us,
-    // six of 2048 x 8192 136 / 135).
+    // h[token n][list entries 8 q ..] of block kb (a token that does not exist: 0, or in two tiles one that keeps nothing; its sums are not stored).
+    // One branch around all the loads, not one each: eight of them, one after the other behind a look into the list, held every unit up (one layer of
+    // 5120 x 13824 at 16 tokens 87.1 / 86.3 us, six of 2048 x 8192 136 / 135).  Tokens past the batch that read the last one's again cost 24 ReLU
+    // layers of 2560 x 10240 at eight tokens 563 us for 560.
     auto h_load = [&](unsigned int (&hv)[MT][8], int kb) {
         int row[8];
         rows8(row, 32 * kb + 8 * q);
+        if (MT == 1) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) hv[0][i] = 0u;
+            if (n < B)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) hv[0][i] = p.hbuf[(size_t)row[i] * 16 + n];
+            return;
+        }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) hv[mt][i] = p.hbuf[(size_t)row[i] * (16 * MT) + (MT == 1 ? min(n, B - 1) : 16 * mt + n)];
+            for (int i = 0; i < 8; ++i) hv[mt][i] = p.hbuf[(size_t)row[i] * (16 * MT) + 16 * mt + n];
     };
     // W_down[32 list entries][128 columns]: quarter-waves read 256-byte row pieces, lane group q the entries 8 q ..; columns past d cannot
     // occur for the supported widths (d is a multiple of 256)
