@@ -1,5 +1,6 @@
 """Which kernels a call launches, and what a refused launch leaves behind: the library's host side on the CPU, over a runtime
 that only writes the launches down (fake_hip.py)."""
+import re
 import shutil
 
 import pytest
@@ -256,6 +257,41 @@ def test_a_single_unit_has_kernels_of_its_own(fake):
     for res, args in ((r[1], "BatParams"), (r[2], "BatParams"), (r[3], "BatArgs")):
         bat = [n for n in _names(res) if "k_bat_gateup" in n or "k_bat_down" in n]
         assert bat and all(args in n for n in bat), bat[:2]
+
+
+@pytest.mark.parametrize("d,F,B,tiles", [
+    # 16 tokens a pass, or 32 in two tiles: from 17 tokens on, up to 4096 values and 16 d neurons; passes of nearly equal size
+    (1024, 777, 16, [1]), (1024, 777, 17, [2]), (1024, 16384, 31, [2]), (1024, 16385, 20, [1, 1]), (2048, 300, 33, [2, 2]), (2560, 900, 49, [2, 2]),
+    (3072, 500, 32, [2]), (4096, 255, 48, [2, 2]), (4096, 65536, 17, [2]), (5120, 900, 17, [1, 1]), (4096, 900, 64, [2, 2]), (4096, 900, 65, None),
+    # the narrow and the odd widths, from the batch on that the matrix cores take
+    (512, 600, 11, []), (512, 600, 12, [1]), (512, 1700, 32, [2]), (768, 900, 5, []), (768, 900, 6, [1]), (768, 3072, 33, [2, 2]), (1536, 3839, 4, []),
+    (1536, 3840, 4, [1]), (1536, 2000, 31, [2]), (3584, 500, 2, []), (3584, 500, 3, [1]), (3584, 700, 33, [2, 2]),
+])
+def test_passes_and_tiles_of_the_matrix_core_path(fake, d, F, B, tiles):
+    """The instances by the mangled tail of their parameters: k_bat_gateup<.., tiles, Args>, k_bat_down<tiles, ..>."""
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, min(B, 64), 0, 0]}, {"do": "decode", "d": d, "F": F, "B": B}])[1]
+    if tiles is None:
+        assert r["status"] != 0 and r["launches"] == []
+        return
+    up = [int(re.search(r"ELi([12])EN", n)[1]) for n in _names(r) if "k_bat_gateup" in n]
+    down = [int(re.search(r"k_bat_downILi([12])E", n)[1]) for n in _names(r) if "k_bat_down" in n]
+    assert r["status"] == 0 and up == down == tiles
+
+
+@pytest.mark.parametrize("d,F,T,dtype,ladder,bisect", [
+    # rows of one, two and up to four groups of 256 x 16 bytes; eight, four, two threads and one a token
+    (512, 1200, 70, "f32", (4, 1, 256), 8), (768, 1500, 64, "bf16", (2, 1, 256), 8), (520, 2300, 128, "bf16", (2, 1, 256), 8), (1024, 2100, 129, "bf16", (2, 1, 256), 4),
+    (2056, 2100, 256, "bf16", (2, 1, 512), 4), (512, 1100, 257, "bf16", (2, 1, 256), 2), (512, 1100, 512, "bf16", (2, 1, 256), 2), (512, 1100, 513, "bf16", (2, 1, 256), 1),
+    (6144, 6200, 64, "bf16", (2, 2, 512), 8), (1028, 2100, 130, "f32", (4, 1, 512), 4), (3072, 3100, 100, "f32", (4, 2, 512), 8), (4096, 11008, 512, "bf16", (2, 1, 512), 2),
+    # the narrowest window that is one (10 places of the sample: 29 entries of 44, 58 of 88, 117 of 176, 170 of 256), and past it; more tokens than a table has
+    (256, 11878, 900, "bf16", (2, 1, 256), 1), (256, 11879, 900, "bf16", None, None), (4096, 23756, 300, "bf16", (2, 1, 512), 2), (4096, 23757, 300, "bf16", None, None),
+    (512, 2100, 1024, "bf16", (2, 1, 256), 1), (512, 2100, 1025, "bf16", None, None),
+])
+def test_a_search_over_a_table_where_it_is_wide_enough(fake, d, F, T, dtype, ladder, bisect):
+    r = run_steps(fake, [{"do": "ctx", "sizes": [d, F, 0, T, 0]}, {"do": "search", "d": d, "F": F, "T": T, "dtype": dtype}])[1]
+    assert r["status"] == 0 and any("k_cett_curve" in n for n in _names(r))
+    assert [tuple(map(int, re.search(r"k_cett_ladderILi(\d)ELi(\d)ELi(\d+)E", n).groups())) for n in _names(r) if "k_cett_ladder" in n] == [ladder] * 2 * (ladder is not None)
+    assert [int(re.search(r"k_cett_bisectILi(\d)E", n)[1]) for n in _names(r) if "k_cett_bisect" in n] == [bisect] * 2 * (bisect is not None)
 
 
 @pytest.mark.parametrize("d,F,B,dtype,kind,multi", [
