@@ -77,9 +77,8 @@ const char *clada_last_error(const clada_ctx *ctx);
  * per-layer calls; see clada_sparse_ffn_stack_decode), "decode.lane_occ2" (1 = where the lanes of
  * a batch-1 stack have a kernel instance of which two workgroups fit a compute unit, they use
  * it [default], 0 = the instance of the per-layer call),
- * "decode.batched" (1 = matrix-core kernels for bf16 batches of 2 and more, 16 tokens
- * per pass [default], 0 = the
- * generic kernels), "decode.spin_limit" (how often a balanced batch-1 kernel polls
+ * "decode.batched" (1 = the kernels that take several tokens a pass: matrix cores for bf16,
+ * vector units [default]; 0 = the generic kernels), "decode.spin_limit" (how often a balanced batch-1 kernel polls
  * for the other workgroups' masks before it gives up; default 4096, a few
  * milliseconds against the microseconds a healthy exchange takes;
  * 0 = give up without polling; see clada_device_fault), "prefix.tile" (workgroup
@@ -175,14 +174,17 @@ clada_status clada_threshold_calibrate(clada_ctx *ctx, const float *abs_act_pool
  * (cuts everything) with the bracket on the device, n_probes in [1,31] times: 31
  * resolve the float exactly, fewer return the lower, feasible end of the
  * remaining bracket.  Every probe is one masked down projection, save in the full
- * search (31) of a larger layer: T >= 64, d_ff >= d and >= 512, bound > 0, and
- * T d_ff >= 2^18 (2^20 below 1024 neurons), with 4 ceil(T/128) d_ff >= 12544 + T; not
- * bf16 layers of fewer than 2048 neurons over more than 4096 tokens.  There at most five masked projections, placed by the
- * order statistics of a sample of the pool, close a bracket in on the threshold; the
- * bisection answers a probe outside the bracket from its ends, as on a monotone curve,
- * and one inside by adding the neurons between the ends to the lower end's sums.  That
- * takes 0.2 to 0.7 of the time (so 30 probes of such a layer are slower than
- * 31).  On a monotone curve all ways end at the same float.  Where the mean is not
+ * search (31) with bound > 0 of T >= 64 tokens and d_ff >= d neurons, where there are
+ *   - at least 1024 neurons and either T <= 1024 or T d_ff >= 2^18, or
+ *   - 512 to 1023 neurons and T d_ff >= 2^20,
+ * with 4 ceil(T/128) d_ff >= 4352 + T; not bf16 layers of fewer than 2048 neurons over more
+ * than 4096 tokens.  There a few masked projections (at most six), placed by the order statistics of a
+ * sample of the pool, close in on the threshold.  Up to 1024 tokens a table of every
+ * token's CETT at the magnitudes around it answers what is left of the bisection; with
+ * more tokens, or where the table does not reach, the bisection answers a probe outside the bracket
+ * from its ends, as on a monotone curve, and one inside by adding the neurons between the
+ * ends to the lower end's sums.  That takes 0.15 to 0.7 of the time (so 30 probes of such a
+ * layer are slower than 31).  On a monotone curve all ways end at the same float.  Where the mean is not
  * monotone in eps at the scale of single neurons the result is a boundary of the
  * feasible set -- the mean at it is within the bound, at the next magnitude up it
  * is not -- but not necessarily the last one, nor the one that the plain bisection
@@ -261,12 +263,18 @@ clada_status clada_cognitive_signals_static(clada_ctx *ctx, const void *logits, 
  * n_active [1+B] = {union count, per-token counts}; mask_bits
  * [B][ceil(d_ff/32)] bit j%32 of word j/32 set iff keep_bj.
  * The result is bit-reproducible from run to run (fixed summation order).
- * Paths: B = 1 with rows of whole KiB runs the row-streaming kernel (vector ALUs); bf16
- * batches of 2 and more run on the matrix cores, 16 tokens per pass, every weight row read
- * once per pass.  Other batches (fp32, other widths) of rows longer than 1024 values, shorter
+ * Paths: B = 1 runs the row-streaming kernel (vector ALUs) for bf16 rows of 1, 2 and 4 to 8 KiB, 10, 12
+ * and 16 KiB (non-gated: 1 to 8, 10 and 12 KiB) and gated fp32 rows of 2, 3 and 8 KiB.  bf16 batches of 1024,
+ * 2048, 2560, 3072, 4096, 5120, 6144 and 8192 values run on the matrix cores from two tokens
+ * on, those of 512, 768, 1536 and 3584 values from the batch on where that is faster (3 to 14
+ * tokens), every weight row read once per pass of 16 tokens; batches of more than 16 tokens take up to 32 a pass
+ * up to 4096 values and 16 d neurons.  h enters the down projection there as two bf16 (16
+ * to 17 bits), at 512, 768, 1536 and 3584 values as three, which hold all of it.
+ * Other batches (fp32, other widths) of rows longer than 1024 values, shorter
  * ones down to 512 where the passes are full enough, and gated fp32 rows above 8 KiB at B = 1,
  * run a vector kernel that reads every row once per pass of up to eight tokens (256 neurons and
- * more); the rest runs a generic kernel that works through the tokens one by one. */
+ * more); the rest runs a generic kernel that works through the tokens one by one.  Whatever the path,
+ * a weight or an h that is not finite reaches the tokens that keep its neuron alone. */
 clada_status clada_sparse_ffn_decode(clada_ctx *ctx, const clada_layer *layer, const void *x,
                                      int32_t B, const float *tau_final, void *y,
                                      int32_t *active_idx, int32_t *n_active,
@@ -285,11 +293,11 @@ clada_status clada_dense_ffn_decode(clada_ctx *ctx, const clada_layer *layer, co
  * future-work paragraphs leave open; this is the second.  Knowing the whole stack, the
  * library can hide what every per-layer call pays: the start-up of a kernel, its ragged
  * end, and the launch of the final reduction.  Option "decode.stack" chooses how:
- *   3 (default)  at batch 1, for rows of 2, 4, 5, 8 and 10 KiB and fp32 rows of 2 and 8
- *                KiB: launches over many layers on hip_stream (all of them, up to 48), whose
+ *   3 (default)  at batch 1, for bf16 rows of 1, 2, 4 to 8 and 10 KiB (non-gated: 3 and 12 too)
+ *                and gated fp32 rows of 2, 3 and 8 KiB: launches over many layers on hip_stream (all of them, up to 48), whose
  *                workgroups follow each other without a gap, each with a reduction launch;
  *                layers beyond a multiple of eight may go in a launch of their own.
- *                Lanes for the rest (rows of 12 and 16 KiB; fewer than six layers of 10 KiB
+ *                Lanes for the rest (gated rows of 12 and 16 KiB; fewer than six layers of 10 KiB
  *                rows, dense or above 400 MB a layer; dense gated stacks of large 4 and
  *                8 KiB layers): the layers go round two streams -- hip_stream and one
  *                that the context owns (default priority), forked and joined by events
@@ -313,7 +321,7 @@ clada_status clada_dense_ffn_decode(clada_ctx *ctx, const clada_layer *layer, co
  * kernels' order of summation.  For B = 1, modes 2 and 3 need the batch-1 kernel's shapes
  * (rows of whole KiB), 256 compute units or more and n_active = NULL.  For B >= 2 there is
  * mode 3 only, where the matrix-core path applies (bf16, its widths) and n_active = NULL: its
- * kernels run over up to 48 units (layer, pass of up to 16 tokens) in one launch each, or as
+ * kernels run over up to 48 units (layer, pass of up to 16 or 32 tokens) in one launch each, or as
  * many layers as the context's workspace has room for; long stacks of large layers (above
  * 340 MB each and 12 GB a step, more than four tokens per pass) go round three lanes unit by
  * unit.  Every mode falls back to mode 0 where it does not apply.  The remarks on clada_device_fault apply to modes 0 - 2
