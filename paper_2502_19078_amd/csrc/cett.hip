@@ -658,19 +658,22 @@ __device__ __forceinline__ void answer(CettState &s, bool feasible, float mean)
     bisect_on(s);
 }
 
-// The search over a table, up to 512 tokens.  The rows of the neurons inside the window [known_lo, edge) of a token, added in the
+// The search over a table, up to 1024 tokens.  The rows of the neurons inside the window [known_lo, edge) of a token, added in the
 // order of their magnitudes to the cut sums at known_lo, give the token's CETT at every threshold of the window: a step function of as many
 // steps.  One pass forms them all, and the rest of the bisection reads them, in one workgroup: two launches where the probes
 // below need a launch per three steps of the bisection.  The window's upper end need not be measured, so that one or two
-// dense probes are enough.  The entries lie in the registers of one workgroup, 44 a thread (two words each of 128), 88 a token at 512 tokens.
+// dense probes are enough.  The entries lie in the registers of one workgroup, 44 a thread (two words each of 128): 256 a
+// token up to 128 tokens, 176 up to 256, 88 up to 512, 44 beyond.
 // Searches whose first two probes fail or fall short by more than the window take the probes' way on; so does a token with more than
 // 512 neurons to add.
 constexpr int TABLE_TOKENS = 1024, TABLE_REGS = 44;       // entries a thread
 constexpr int LADDER_MAX = 512;                          // neurons of a token that the pass can sort; beyond, the window ends at known_lo
 
 // Threads a token in k_cett_bisect, entries of a token, places of the sample that give two thirds of them.
-__host__ __device__ __forceinline__ int table_threads(int T) { return T > 512 ? 1 : T > 256 ? 2 : T > 128 ? 4 : 8; }
-__host__ __device__ __forceinline__ int table_cap(int T) { return T > 128 ? table_threads(T) * TABLE_REGS : 256; }
+__host__ __device__ constexpr int table_threads(int T) { return T > 512 ? 1 : T > 256 ? 2 : T > 128 ? 4 : 8; }
+__host__ __device__ constexpr int table_cap(int T) { return T > 128 ? table_threads(T) * TABLE_REGS : 256; }
+// (a token whose cut sums lie below the window lists the neurons in between too; those that the sort has no room for leave the window empty)
+static_assert(2 * table_cap(1) <= LADDER_MAX && table_cap(129) <= table_cap(1), "a full window and as many neurons below it can be sorted");
 int table_window(int T, int F) { return (int)((long long)table_cap(T) * 2 / 3 * SAMPLES / F); }
 
 // A workgroup of NT threads per token.  mag [cap][T], cett [cap + 1][T] (at known_lo, and behind each entry), count [T].
@@ -761,7 +764,7 @@ k_cett_ladder(CettState *st, const float *__restrict__ pool, const char *__restr
 #pragma unroll
     for (int u = 0; u < LADDER_MAX / NT; ++u) {
         const int i = tid + NT * u;
-        const bool in = rank[u] < cap + pre && s_a[i] < end;
+        const bool in = i < found && rank[u] < cap + pre && s_a[i] < end;
         const unsigned long long who = __ballot(in);
         if (who && lane == 0) atomicAdd(&s_n, __popcll(who));
         if (in) {
@@ -1371,7 +1374,7 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
     // The table where it takes in what a probe's estimate leaves open; else the bracket is closed by dense probes and the rest of the
     // bisection measured a few thresholds a launch.
     const int window = T <= TABLE_TOKENS ? table_window(T, F) : 0;
-    const bool table = window >= table_past(window) + table_below(window);
+    const bool table = window >= table_past(window) + table_below(window) && 2 * table_cap(T) < Fp;      // (and fits the masked h's part)
     const int curve_tokens = table ? (T < CURVE_TABLE ? T : CURVE_TABLE) : CURVE_TOKENS;
     unsigned long long *curves = reinterpret_cast<unsigned long long *>(w.hcut);      // (not masked yet)
     auto mask = [&](int may_skip) {
@@ -1421,7 +1424,7 @@ clada_status search_large(clada_ctx *ctx, const clada_layer *layer, int T, const
     clada_status st;
     if (table) {
         const int cap = table_cap(T), vecs = (d * (int)dtype_size(layer->dtype) / 16 + 255) / 256;      // 1 .. 4 groups of 256 x 16 bytes a row
-        float *mag = reinterpret_cast<float *>(w.hcut), *cett = mag + (size_t)cap * T;        // (at least 2^18 words; the table takes a third)
+        float *mag = reinterpret_cast<float *>(w.hcut), *cett = mag + (size_t)cap * T;        // (2 cap + 1 <= Fp words a token)
         const auto ladder = layer->dtype == CLADA_BF16 ? (vecs == 1 ? k_cett_ladder<2, 1, 256> : vecs == 2 ? k_cett_ladder<2, 1, 512> : k_cett_ladder<2, 2, 512>)
                                                        : (vecs == 1 ? k_cett_ladder<4, 1, 256> : vecs == 2 ? k_cett_ladder<4, 1, 512> : k_cett_ladder<4, 2, 512>);
         const int tpt = table_threads(T);

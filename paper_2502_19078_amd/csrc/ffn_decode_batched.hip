@@ -128,7 +128,8 @@ constexpr int MAX_TILES = 4;    // 16-neuron tiles per workgroup in kernel A (on
 // RELU: the non-gated family (gate tiles only).  A template flag: as a run-time one it cost the
 // 10 and 16 KiB rows ~25 registers and pushed them into scratch (52 -> 68 us at the 13B shape).
 // MT: tiles of 16 tokens; two share every fragment of the weights, so that 17 to 32 tokens read them once.  x takes 8 KSTEPS registers
-// then, which rows of up to 8 KiB leave room for (16 k-steps a wave; 5 to 8 thousand values would be 24 or 32).  us, passes of 16 / so: one layer
+// then, which rows of up to 8 KiB leave room for (16 k-steps a wave; 5 to 8 thousand values would be 24 or 32); the instances of 3584 values
+// spill 14 - 24 registers, 60 - 100 bytes a lane, and take 68 us for the vector kernel's 253 at 32 tokens of 3584 x 8048 all the same.  us, passes of 16 / so: one layer
 // 117 / 69 at 24 tokens of 4096 x 11008, 61.5 / 38.5 of 2048 x 8192, 35 / 22 of 1024 x 3000, 173 / 132 at 33 (three passes / two); six layers at 24 of
 // these 578 / 354, 240 / 159, 86 / 67.
 template <int KSTEPS, int NW, bool DENSE, bool LIST, bool RELU, int MT, class Args>
@@ -567,7 +568,7 @@ k_bat_down(const Args args)
         u32x4 a[MT][PARTS];
         if (MT == 1) h_load(hA, kb);
         w_load(wA, kb);
-        if (MT == 2) {                                       // (the order that 128 registers hold without spills)
+        if (MT == 2) {                                       // (the order that takes the fewest of the 128 registers: three are spilled, one of them read back in the loop)
             __builtin_amdgcn_sched_barrier(0);
             h_load(hA, kb);
             __builtin_amdgcn_sched_barrier(0);
