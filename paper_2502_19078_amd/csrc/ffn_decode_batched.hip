@@ -482,25 +482,17 @@ k_bat_down(const Args args)
 #pragma unroll
         for (int i = 0; i < 8; ++i) row[i] = e0 + i < nrows ? (int)(i < 4 ? a[i & 3] : b[i & 3]) : last_row;
     };
-    // h[token n][list entries 8 q ..] of block kb (a token that does not exist: 0, or in two tiles one that keeps nothing; its sums are not stored).
-    // One branch around all the loads, not one each: eight of them, one after the other behind a look into the list, held every unit up (one layer of
-    // 5120 x 13824 at 16 tokens 87.1 / 86.3 us, six of 2048 x 8192 136 / 135).  Tokens past the batch that read the last one's again cost 24 ReLU
-    // layers of 2560 x 10240 at eight tokens 563 us for 560.
+    // h[token n][list entries 8 q ..] of block kb (a token that does not exist: the last one again, or in two tiles one that keeps nothing; its sums are
+    // not stored).  No branch around any load: eight of them, one after the other behind a look into the list, held every unit up (one layer of
+    // 5120 x 13824 at 16 tokens 87.1 / 86.3 us, six of 2048 x 8192 136 / 135); one branch around all eight for the tokens past the batch: lone calls of
+    // 1024 x 4096 and 2560 x 8000 at 4 to 16 tokens 0.5 - 1 % slower, 24 ReLU layers of 2560 x 10240 at eight 0.5 % faster.
     auto h_load = [&](unsigned int (&hv)[MT][8], int kb) {
         int row[8];
         rows8(row, 32 * kb + 8 * q);
-        if (MT == 1) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) hv[0][i] = 0u;
-            if (n < B)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) hv[0][i] = p.hbuf[(size_t)row[i] * 16 + n];
-            return;
-        }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) hv[mt][i] = p.hbuf[(size_t)row[i] * (16 * MT) + 16 * mt + n];
+            for (int i = 0; i < 8; ++i) hv[mt][i] = p.hbuf[(size_t)row[i] * (16 * MT) + (MT == 1 ? min(n, B - 1) : 16 * mt + n)];
     };
     // W_down[32 list entries][128 columns]: quarter-waves read 256-byte row pieces, lane group q the entries 8 q ..; columns past d cannot
     // occur for the supported widths (d is a multiple of 256)
