@@ -189,7 +189,7 @@ __global__ void k_cett_finish(const CettState *st, float *tau_out, float *mean_o
 //       outside the bracket is answered by it, one inside adds the rows of the neurons between the sums' threshold and
 //       the probe to the sums, token by token, for the next few probes at a time.
 // us (plain bisection / without the table / so): 512 tokens of 4096 x 11008 2370 / 470 - 580 / 330 - 390, 80 of 3584 x 9728 - / 296 - 340 / 214 - 229,
-// 64 of 1024 x 4096 - / 244 - 287 / 176 - 186, 700 of 4096 x 11008 - / 670 - 835 / 498 - 606, fp32 104 of 4096 x 12992 - / 1218 - 1409 / 828 - 851.
+// 64 of 1024 x 4096 - / 244 - 287 / 176 - 186, 700 of 4096 x 11008 - / 670 - 835 / 449 - 556, fp32 104 of 4096 x 12992 - / 1218 - 1409 / 828 - 851.
 // What bounds it now: the three or four projections (63 us each at the first of these sizes), then launches, 2.4 us each also where nothing is
 // left to do.  The bracket answers for thresholds outside it as a monotone mean would; inside, every probe is measured.
 constexpr int SAMPLES = 4096;      // sorted sample of the pool; neighbours are 2.7 magnitudes per token apart at 11008 neurons

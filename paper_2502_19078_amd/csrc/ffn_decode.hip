@@ -1867,7 +1867,7 @@ clada_status run_stack_decode(clada_ctx *ctx, const clada_layer *layers, int32_t
         CLADA_CHECK_HIP(ctx, lanes_join(ctx, n_lanes, stream));
         return CLADA_OK;
     }
-    // ---- batches on the matrix-core path: one launch per kernel over all units (layer, pass of up to 16 tokens), or,
+    // ---- batches on the matrix-core path: one launch per kernel over all units (layer, pass of up to 16 or 32 tokens), or,
     // where clada_stack_batched leaves them, the units go round three lanes, each with its own partial outputs and
     // scratch.  The path's three launches per unit and its thin ends weigh more than at batch 1 (c3 layer shape, B = 8: 69.5 -> 60.2 -> 58.5 us per layer with one, two, three lanes).
     const int n_groups = ctx->opt_decode_batched ? clada_batched_passes(&layers[0], B) : 0;
