@@ -266,6 +266,9 @@ def test_a_single_unit_has_kernels_of_its_own(fake):
     # the narrow and the odd widths, from the batch on that the matrix cores take
     (512, 600, 11, []), (512, 600, 12, [1]), (512, 1700, 32, [2]), (768, 900, 5, []), (768, 900, 6, [1]), (768, 3072, 33, [2, 2]), (1536, 3839, 4, []),
     (1536, 3840, 4, [1]), (1536, 2000, 31, [2]), (3584, 500, 2, []), (3584, 500, 3, [1]), (3584, 700, 33, [2, 2]),
+    # the widest layers in two tiles, and one neuron past them
+    (512, 8192, 32, [2]), (512, 8193, 32, [1, 1]), (768, 12288, 32, [2]), (1024, 16384, 32, [2]), (1536, 24576, 32, [2]), (2048, 32768, 32, [2]), (2560, 40960, 32, [2]),
+    (3072, 49152, 32, [2]), (3584, 57344, 32, [2]), (3584, 57345, 32, [1, 1]), (4096, 65536, 32, [2]),
 ])
 def test_passes_and_tiles_of_the_matrix_core_path(fake, d, F, B, tiles):
     """The instances by the mangled tail of their parameters: k_bat_gateup<.., tiles, Args>, k_bat_down<tiles, ..>."""
@@ -276,6 +279,9 @@ def test_passes_and_tiles_of_the_matrix_core_path(fake, d, F, B, tiles):
     up = [int(re.search(r"ELi([12])EN", n)[1]) for n in _names(r) if "k_bat_gateup" in n]
     down = [int(re.search(r"k_bat_downILi([12])E", n)[1]) for n in _names(r) if "k_bat_down" in n]
     assert r["status"] == 0 and up == down == tiles
+    # two tiles: a pass's partial outputs, row groups x tokens, have 64 x 32 rows in front of its h
+    for x in r["launches"]:
+        assert "k_bat_downILi2E" not in x[0] or x[1] // -(-d // 256) * -(-B // len(tiles)) <= 64 * 32, x
 
 
 @pytest.mark.parametrize("d,F,T,dtype,ladder,bisect", [
